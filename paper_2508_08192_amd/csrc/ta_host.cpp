@@ -45,7 +45,11 @@ int mfma_rows_group(int rows)
 // tiles' time there (two for the register-staged kernel, nothing for the scalar one).  With few lists cut over the
 // whole chip (batch size one) the merge becomes a latency problem and one workgroup per output row is faster from
 // 13 partials per list on, while the batch has at most 1024 output rows.
+// A single list counts no fixed work: the units it would add only keep workgroups idle (a list of 129 tiles was cut
+// into 65 shares of two instead of 129 of one; KV pass + merge: 8192 tokens and 64 rows 19.7 -> 18.8 us, 2048 tokens and
+// 60 rows 15.8 -> 14.7, 16384 to 65536 tokens unchanged).
 const TADispatchRow kTable[] = {
+    {TA_KERNEL_MFMA, 64, 1, 4, 1, 1, 13, 1024},
     {TA_KERNEL_MFMA, 64, INT32_MAX, 4, 1, 9, 13, 1024},
     {TA_KERNEL_MFMA, 128, INT32_MAX, 4, 2, 9, 13, 1024},
     {TA_KERNEL_MFMA, 256, INT32_MAX, 4, 4, 9, 13, 1024},
