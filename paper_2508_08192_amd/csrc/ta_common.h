@@ -458,6 +458,7 @@ __device__ __forceinline__ void ta_scatter_store(const TAParams &p, int b, int g
 // (`dev`: index of the current device, which the caller already knows)
 hipError_t ta_launch_generic(const TAParams &p, hipStream_t stream, int dev);
 hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev);
+hipError_t ta_launch_mfma_ks(const TAParams &p, hipStream_t stream, int dev);
 hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream);
 hipError_t ta_launch_append(const TAAppend &a, hipStream_t stream);
 hipError_t ta_launch_compact(const TACompact &c, hipStream_t stream, int dev);

@@ -42,7 +42,9 @@ int mfma_rows_group(int rows)
 // The pipelined matrix-core kernel runs one workgroup per compute unit (its tile rings fill the LDS).  A partial
 // result costs rows * D * 4 bytes written and read again against TA_TILE * D * 4 bytes per tile of keys and values,
 // hence the longer smallest shares of the larger row groups; the fixed work of entering a list is worth about eight
-// tiles' time there (two for the register-staged kernel, nothing for the scalar one).  With few lists cut over the
+// tiles' time there, and seven in the key-split kernel (its family is MFMA_BASIC; head_dim 64, L 730..12152 with 40 lists:
+// 21.8 us with a cost of 3, 19.8 with 8; one list of 14265 tokens 14.6 and 12.3), which keeps row groups of 32 or 64
+// rows; nothing for the scalar one.  With few lists cut over the
 // whole chip (batch size one) the merge becomes a latency problem and one workgroup per output row is faster from
 // 13 partials per list on, while the batch has at most 1024 output rows.
 // A single list counts no fixed work: the units it would add only keep workgroups idle (a list of 129 tiles was cut
@@ -53,9 +55,8 @@ const TADispatchRow kTable[] = {
     {TA_KERNEL_MFMA, 64, INT32_MAX, 4, 1, 9, 13, 1024},
     {TA_KERNEL_MFMA, 128, INT32_MAX, 4, 2, 9, 13, 1024},
     {TA_KERNEL_MFMA, 256, INT32_MAX, 4, 4, 9, 13, 1024},
-    {TA_KERNEL_MFMA_BASIC, 64, INT32_MAX, 4, 1, 3, 13, 1024},
-    {TA_KERNEL_MFMA_BASIC, 128, INT32_MAX, 4, 2, 3, 13, 1024},
-    {TA_KERNEL_MFMA_BASIC, 256, INT32_MAX, 4, 4, 3, 13, 1024},
+    {TA_KERNEL_MFMA_BASIC, 32, INT32_MAX, 4, 1, 8, 13, 1024},
+    {TA_KERNEL_MFMA_BASIC, 256, INT32_MAX, 4, 1, 8, 13, 1024},
     {TA_KERNEL_GENERIC, 256, INT32_MAX, 16, 1, 1, 13, 1024},
 };
 constexpr int kTableRows = (int)(sizeof(kTable) / sizeof(kTable[0]));
@@ -215,8 +216,8 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         return TA_ERR_OPTS;
     if (kernel == TA_KERNEL_AUTO)
         kernel = mfma_ok ? TA_KERNEL_MFMA : TA_KERNEL_GENERIC;
-    if (kernel == TA_KERNEL_MFMA && D != 128)
-        basic = 1;                               // the pipelined kernel is written for head_dim 128 only
+    if (kernel == TA_KERNEL_MFMA && (D != 128 || B > TA_SP_MAX_BATCH))
+        basic = 1;                               // what the pipelined kernel does not take: head_dim 64, very large batches
 
     TAParams &p = pr->p;
     memset(&p, 0, sizeof p);
@@ -265,8 +266,8 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     pl.kernel = kernel;
     const int family = kernel == TA_KERNEL_MFMA ? (basic ? TA_KERNEL_MFMA_BASIC : TA_KERNEL_MFMA) : TA_KERNEL_GENERIC;
     if (kernel == TA_KERNEL_MFMA) {
-        pl.rows_grp = mfma_rows_group(p.rows);
-        pl.threads = 512;                                   // always eight waves
+        pl.rows_grp = basic ? (p.rows <= 32 ? 32 : 64) : mfma_rows_group(p.rows);
+        pl.threads = basic && D == 128 && pl.rows_grp == 64 ? 256 : 512;
     } else {
         pl.rows_grp = p.rows < TA_ROW_GROUP ? p.rows : TA_ROW_GROUP;
         pl.threads = 256;

@@ -8,9 +8,8 @@
 // one workgroup are merged on the fly by the running softmax, which is the same log-sum-exp merge the
 // merge pass applies across workgroups.
 //
-// Two kernels share this scheme: ta_mfma_sp_kernel (the one that normally runs: per-tile instruction streams
-// written in assembly, tiles loaded straight into LDS) and ta_mfma_kv_kernel (plain, compiler-scheduled,
-// register-staged tiles; the fallback).
+// ta_mfma_sp_kernel: per-tile instruction streams written in assembly, tiles loaded straight into LDS.  (Its sibling in
+// ta_mfma_ks.hip splits the keys of a share over the waves and serves head_dim 64.)
 //
 // Each wave owns a block of 32 rows.  Both contractions are issued in transposed form so that
 // a lane owns one query row per block throughout (row statistics never leave the lane):
@@ -18,120 +17,13 @@
 //     O^T[d, row]    += V^T[d, token] . P^T[token, row]   A = V^T fragment (LDS), B = P (registers)
 // with v_mfma_f32_32x32x16_bf16.  The accumulator layout of S^T (lane = row, registers = tokens) is,
 // up to a fixed permutation of the 16 contraction slots, the B-operand layout the second product
-// needs; V is stored in LDS with the same slot permutation, token-minor, so its A fragments are
-// single 16-byte reads.
-#include <stdlib.h>
-
+// needs; the V fragments come out of the row-major tile with the same slot permutation.
 #include "ta_common.h"
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define MF_D 128
 #define MF_TILE_BYTES (TA_TILE * MF_D * 2)       // one K or V tile in LDS: 16 KB
-#define MF_STAGES 2
-#define MF_UNITS 512                             // staging units per tile: 256 for K, 256 for V
 
 static_assert(TA_TILE == 64, "the fragment maps below assume 64-token tiles");
-
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v)
-{
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    f32x2 f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
-}
-
-// Staging unit u of a tile: 4 consecutive tokens (quad) x 8 consecutive head-dim elements (chunk),
-// i.e. four 16-byte global loads.  Units 0..255 carry K, 256..511 carry V.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-struct Unit {
-    uint4 r[4];
-};
-
-// Loads one unit.  tbase already points at (KV head, 8-element chunk) of the cache; pos0 = logical
-// position of the unit's first token; of its four tokens those with index n_skip .. n_valid-1 exist for
-// this call (tokens before a window start and past the end are staged as zeros and never loaded, so stale
-// cache contents -- NaN included -- never reach a product and released pages are never touched).  Page and slot
-// strides fit 32 bits (checked on the host), which keeps the address arithmetic to a few instructions.
-__device__ __forceinline__ void load_unit(const TAParams &p, Unit &u, const uint16_t *tbase, uint32_t sp, uint32_t ss,
-                                          int b, int pos0, int n_valid, bool contiguous, int n_skip = 0)
-{
-    const uint16_t *ptr[4];
-    if (n_valid > n_skip) {
-        if (contiguous) {
-            const uint16_t *p0 = tbase + (uint64_t)(uint32_t)b * sp + (uint64_t)(uint32_t)pos0 * ss;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                ptr[k] = p0 + (uint32_t)k * ss;
-        } else if (p.ps_shift >= 2 && (pos0 & 3) == 0) {
-            // (one page holds all four tokens, and at least one of them exists: the page id is a checked one)
-            const uint32_t page = (uint32_t)p.page_table[(int64_t)b * p.pt_sb + (pos0 >> p.ps_shift)];
-            const uint16_t *p0 = tbase + (uint64_t)page * sp + (uint32_t)(pos0 & (p.ps - 1)) * ss;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                ptr[k] = p0 + (uint32_t)k * ss;
-        } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int pos = pos0 + (k < n_valid && k >= n_skip ? k : n_skip);
-                const uint32_t page = (uint32_t)p.page_table[(int64_t)b * p.pt_sb + (pos >> p.ps_shift)];
-                ptr[k] = tbase + (uint64_t)page * sp + (uint32_t)(pos & (p.ps - 1)) * ss;
-            }
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (k < n_valid && k >= n_skip)
-            // keys and values are read once: the non-temporal hint keeps them from displacing the partial results
-            u.r[k] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4 *)ptr[k]));
-        else
-            u.r[k] = make_uint4(0, 0, 0, 0);
-    }
-}
-
-// K tile in LDS: [token 0..63][DH / 8 chunks of 16 B], chunk index XOR-swizzled with the token's low bits so that
-// the 16-byte fragment reads of different tokens at one chunk hit distinct banks.
-template <int DH>
-__device__ __forceinline__ void store_k_unit(char *ktile, const Unit &u, int quad, int chunk)
-{
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int row = quad * 4 + k;
-        *(uint4 *)(ktile + row * (DH * 2) + ((chunk ^ (row & (DH / 8 - 1))) << 4)) = u.r[k];
-    }
-}
-
-// V tile in LDS, token-minor: [kb 0..3][half 0..1][DH head-dim slots][8 tokens] of bf16, where the 8
-// tokens of (kb, half) are 16kb + 4half + {0,1,2,3} and 16kb + 8 + 4half + {0,1,2,3}: exactly the
-// contraction slots a lane of that half feeds to the second MFMA.  The head-dim slot of column d is
-// d ^ ((d >> 4) & 7), which spreads the eight 8-byte writes of a staging thread over the banks.
-template <int DH>
-__device__ __forceinline__ void store_v_unit(char *vtile, const Unit &u, int quad, int chunk)
-{
-    const int kb = quad >> 2, half = quad & 1, sec = (quad >> 1) & 1;
-    char *base = vtile + ((kb * 2 + half) * DH) * 16 + sec * 8;
-    const uint32_t *r0 = (const uint32_t *)&u.r[0], *r1 = (const uint32_t *)&u.r[1];
-    const uint32_t *r2 = (const uint32_t *)&u.r[2], *r3 = (const uint32_t *)&u.r[3];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        // dword w of every token holds columns 8*chunk + 2w (low half) and 2w+1 (high half)
-        uint2 lo, hi;
-        lo.x = (r0[w] & 0xffffu) | (r1[w] << 16);
-        lo.y = (r2[w] & 0xffffu) | (r3[w] << 16);
-        hi.x = (r0[w] >> 16) | (r1[w] & 0xffff0000u);
-        hi.y = (r2[w] >> 16) | (r3[w] & 0xffff0000u);
-        const int d_lo = chunk * 8 + 2 * w, d_hi = d_lo + 1;
-        *(uint2 *)(base + ((d_lo ^ ((d_lo >> 4) & 7)) << 4)) = lo;
-        *(uint2 *)(base + ((d_hi ^ ((d_hi >> 4) & 7)) << 4)) = hi;
-    }
-}
-
 
 __device__ __forceinline__ void lds_barrier()
 {
@@ -139,404 +31,8 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-__device__ __forceinline__ float max3(float a, float b, float c)
-{
-    // one instruction; the generic fmaxf would first quiet every operand
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-__device__ __forceinline__ float half_swap_max(float x)
-{
-    // max over the two lanes that share a query row (lane and lane ^ 32)
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// Scores of tokens that do not exist for this lane's row become -inf.  Bit k of vm covers the register
-// with token offset k = 32tb + 8(i/4) + (i%4) (the lane's half offset 4hf is already shifted out).
-__device__ __forceinline__ void mask_scores(f32x16 (&acc_s)[2], unsigned long long vm)
-{
-    const uint32_t lo = (uint32_t)vm, hi = (uint32_t)(vm >> 32);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int bit = 8 * (i / 4) + (i % 4);
-        if (!((lo >> bit) & 1u))
-            acc_s[0][i] = -INFINITY;
-        if (!((hi >> bit) & 1u))
-            acc_s[1][i] = -INFINITY;
-    }
-}
-
-// Running-softmax bookkeeping of one 64-token tile for one 32-row block: s holds the lane's 32 raw
-// (unscaled) scores, c = softmax scale * log2(e).  Produces P as four bf16 B-operands and updates the
-// running max (raw units), the lane's shares of the running sums -- l of the probabilities (for the log-sum-exp)
-// and l2 of their bf16 roundings, the weights the second product really applies (O is normalised by l2, which makes
-// the output an exact weighted mean of V rows) -- and (rarely) rescales O.
-template <int NDB>
-__device__ __forceinline__ void softmax_tile(const f32x16 (&s)[2], float c, float &m_run, float &l_run, float &l2_run,
-                                             f32x16 (&acc_o)[NDB], uint4 (&pb)[4])
-{
-    float tmax = fmaxf(s[0][0], s[1][0]);
-#pragma unroll
-    for (int i = 1; i < 16; ++i)
-        tmax = max3(tmax, s[0][i], s[1][i]);
-    tmax = half_swap_max(tmax);
-    const float m_new = fmaxf(m_run, tmax);
-    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
-    const float neg_mc = -m_new * c;
-    m_run = m_new;
-    float psum = 0.f, psum2 = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-        float e[8];
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            e[jj] = __builtin_amdgcn_exp2f(fmaf(s[kb >> 1][8 * (kb & 1) + jj], c, neg_mc));
-            psum += e[jj];
-        }
-        pb[kb].x = pack_bf16(e[0], e[1]);
-        pb[kb].y = pack_bf16(e[2], e[3]);
-        pb[kb].z = pack_bf16(e[4], e[5]);
-        pb[kb].w = pack_bf16(e[6], e[7]);
-        const uint32_t w4[4] = {pb[kb].x, pb[kb].y, pb[kb].z, pb[kb].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            psum2 += __uint_as_float(w4[k] << 16) + __uint_as_float(w4[k] & 0xffff0000u);
-    }
-    l_run = l_run * alpha + psum;
-    l2_run = l2_run * alpha + psum2;
-    if (__any(alpha != 1.0f)) {
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                acc_o[db][i] *= alpha;
-    }
-}
-
-// NCW compute waves of RB 32-row blocks each (rows per workgroup = 32*RB*NCW), NT threads in all
-// (NT/64 - NCW waves only help with staging).  DH: head dimension, 64 or 128.
-template <int NCW, int RB, int NT, int DH>
-__global__ __launch_bounds__(NT) void ta_mfma_kv_kernel(TAParams p)
-{
-    constexpr int CH = DH / 8;                    // 16-byte chunks of a row
-    constexpr int UNITS_K = 16 * CH;              // staging units of the K tile (as many again for V)
-    constexpr int UPT = (2 * UNITS_K + NT - 1) / NT;   // staging units per thread
-    constexpr int TILE_BYTES = TA_TILE * DH * 2;
-    constexpr int NKK = DH / 16, NDB = DH / 32;   // contraction steps of the first product, head-dim blocks of the second
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    char *tiles = smem;                                                   // [MF_STAGES][K tile | V tile]
-    unsigned long long *masks = (unsigned long long *)(smem + MF_STAGES * 2 * TILE_BYTES);   // [64]
-    int *flag = (int *)(masks + TA_MAX_TREE);
-    int *par_s = flag + 4;                                                // [TA_MAX_TREE]
-    int *cum = par_s + TA_MAX_TREE;                                       // [B + 1]
-
-    ta_build_schedule(p, cum);
-    const int total = __builtin_amdgcn_readfirstlane(p.Hkv * cum[p.B]);
-    const int w = blockIdx.x, rg = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // wave-uniform, lives in SGPRs
-    const int r32 = lane & 31, hf = lane >> 5;
-    const bool compute_wave = wave < NCW;
-    int t, t_end;
-    ta_wg_range(p, total, w, t, t_end);
-    t = __builtin_amdgcn_readfirstlane(t);
-    t_end = __builtin_amdgcn_readfirstlane(t_end);
-    const int rows_here = min(p.rows_grp, p.rows - rg * p.rows_grp);
-    const float c = p.scale_log2e;
-    // LDS byte offsets of this lane's fragments inside a tile
-    const int sw = r32 & (CH - 1);
-    const int krow_off = r32 * (DH * 2);                                  // + tb*32 rows + (((2kk+hf)^sw) << 4)
-    int vcol_off[NDB];                                                    // + kb * 2 * DH * 16
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-        const int d = db * 32 + r32;
-        vcol_off[db] = (hf * DH + (d ^ ((d >> 4) & 7))) << 4;
-    }
-
-    while (t < t_end) {
-        // the schedule comes out of LDS, which the compiler treats as lane-varying: pin it to SGPRs
-        const int b = __builtin_amdgcn_readfirstlane(ta_find_request(p, cum, t));
-        const int n_u = __builtin_amdgcn_readfirstlane(cum[b + 1] - cum[b]);   // schedule units of one list
-        const int cum_b = __builtin_amdgcn_readfirstlane(cum[b]);
-        const int g = (t - p.Hkv * cum_b) / n_u;
-        const int seg_start = p.Hkv * cum_b + g * n_u;                         // unit of the list's tile 0
-        const int n_b = n_u - p.pad;
-        const int j0 = t - seg_start;
-        const int j1 = min(n_b, t_end - seg_start);
-        if (j1 <= j0) {
-            t = seg_start + n_u;                              // t lies in the list's trailing padding
-            continue;
-        }
-        const int slot = w + b * p.Hkv + g;
-        ta_note_owner(p, b, g, w, j0, j1, n_b);
-        const int L = __builtin_amdgcn_readfirstlane(p.seq_lens[(int64_t)b * p.sl_s]);
-        const int S = __builtin_amdgcn_readfirstlane(ta_kv_start(p, b));
-        bool poison = !ta_request_ok(p, L, S);
-        const int tile0 = poison ? 0 : S / TA_TILE;                // absolute index of the list's first prefix tile
-        if (poison && tid == 0)
-            ta_raise(p, TA_STATUS_BAD_SEQLEN);
-        const bool has_tree_tile = (j1 == n_b);
-        if (!poison) {
-            int pos_lo, pos_hi;
-            ta_item_positions(p, j0, j1, n_b, tile0, L, S, pos_lo, pos_hi);
-            if (!ta_pages_ok(p, b, pos_lo, pos_hi, flag)) {
-                poison = true;
-                if (tid == 0)
-                    ta_raise(p, TA_STATUS_BAD_PAGE);
-            }
-        }
-        if (has_tree_tile && !poison && p.masks_in) {
-            if (tid == 0)
-                *flag = 0;
-            __syncthreads();
-            if ((int)threadIdx.x < p.T) {
-                const unsigned long long m = ta_given_mask(p, b, threadIdx.x);
-                masks[threadIdx.x] = m;
-                if (!ta_given_mask_ok(m, threadIdx.x))
-                    atomicOr(flag, 1);
-            }
-            __syncthreads();
-            if (*flag != 0) {
-                poison = true;
-                if (tid == 0)
-                    ta_raise(p, TA_STATUS_BAD_PARENT);
-            }
-        } else if (has_tree_tile && !poison) {
-            if (!ta_encode_tree(p.parent + (int64_t)b * p.par_sb, p.T, masks, flag, par_s)) {
-                poison = true;
-                if (tid == 0)
-                    ta_raise(p, TA_STATUS_BAD_PARENT);
-            }
-        }
-
-        if (poison) {
-            if (compute_wave) {
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    const int row = (wave * RB + rb) * 32 + r32;
-                    if (row < rows_here) {
-                        const int64_t wrow = ta_ws_row(p, slot, rg, row);
-                        for (int o = hf * DH; o < (hf + 1) * DH; o += 16)          // DH 16-bit values per row
-                            *(float4 *)(ta_part_row(p, wrow) + o) = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (hf == 0)
-                            p.ws_lse[2 * wrow] = __uint_as_float(0x7fc00000u);
-                    }
-                }
-            }
-            __syncthreads();
-            t = seg_start + (j1 == n_b ? n_u : j1);
-            continue;
-        }
-
-        // Q fragments (B operand of the first product): row r32 of each block, head-dim 16kk + 8hf .. +8.
-        uint4 qf[RB][NKK];
-        unsigned long long tree_mask[RB];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            const int row = (wave * RB + rb) * 32 + r32;
-            const int R = rg * p.rows_grp + row;
-            const bool row_ok = compute_wave && row < rows_here;
-            const int node = row_ok ? R / p.G : 0;
-            if (row_ok) {
-                const uint16_t *qp = (const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
-                                     (int64_t)(g * p.G + R % p.G) * p.q_sh + hf * 8;
-#pragma unroll
-                for (int kk = 0; kk < NKK; ++kk)
-                    qf[rb][kk] = *(const uint4 *)(qp + kk * 16);
-            } else {
-#pragma unroll
-                for (int kk = 0; kk < NKK; ++kk)
-                    qf[rb][kk] = make_uint4(0, 0, 0, 0);
-            }
-            // Rows of padding keep an all-ones mask so that their (discarded) softmax stays finite.
-            tree_mask[rb] = (has_tree_tile && row_ok) ? masks[p.q_off + node] : ~0ull;
-        }
-
-        f32x16 acc_o[RB][NDB];
-        float m_run[RB], l_run[RB], l2_run[RB];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            m_run[rb] = -INFINITY;
-            l_run[rb] = 0.f;
-            l2_run[rb] = 0.f;
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    acc_o[rb][db][i] = 0.f;
-        }
-
-        // ---- staging: which units this thread carries, and loading tile j into registers
-        Unit stage[UPT];
-        auto load_tile = [&](int j) {
-            const bool tree_tile = (j == n_b - 1);
-            const int tile_pos0 = tree_tile ? L : (tile0 + j) * TA_TILE;
-            const int limit = tree_tile ? L + p.T : L;
-#pragma unroll
-            for (int s = 0; s < UPT; ++s) {
-                const int u = tid + s * NT;
-                if (u >= 2 * UNITS_K)
-                    continue;
-                const int uu = u < UNITS_K ? u : u - UNITS_K, quad = uu / CH, chunk = uu % CH;
-                const int pos0 = tile_pos0 + quad * 4;
-                const int n_valid = max(0, min(4, limit - pos0));
-                const int n_skip = tree_tile ? 0 : max(0, min(4, S - pos0));      // tokens before the window start
-                if (tree_tile && p.kn) {
-                    // write-back folded into the call: the tree tokens sit in the dense tensors of this step, which
-                    // are addressed like a contiguous cache -- request stride for the page, token stride for the slot
-                    if (u < UNITS_K)
-                        load_unit(p, stage[s], (const uint16_t *)p.kn + (int64_t)g * p.kn_sh + chunk * 8,
-                                  (uint32_t)p.kn_sb, (uint32_t)p.kn_st, b, pos0 - L, n_valid, true);
-                    else
-                        load_unit(p, stage[s], (const uint16_t *)p.vn + (int64_t)g * p.vn_sh + chunk * 8,
-                                  (uint32_t)p.vn_sb, (uint32_t)p.vn_st, b, pos0 - L, n_valid, true);
-                } else if (u < UNITS_K) {
-                    load_unit(p, stage[s], (const uint16_t *)p.k + (int64_t)g * p.k_sh + chunk * 8, (uint32_t)p.k_sp,
-                              (uint32_t)p.k_ss, b, pos0, n_valid, !p.page_table, n_skip);
-                } else {
-                    load_unit(p, stage[s], (const uint16_t *)p.v + (int64_t)g * p.v_sh + chunk * 8, (uint32_t)p.v_sp,
-                              (uint32_t)p.v_ss, b, pos0, n_valid, !p.page_table, n_skip);
-                }
-            }
-        };
-        auto store_tile = [&](int buf) {
-            char *kt = tiles + buf * 2 * TILE_BYTES, *vt = kt + TILE_BYTES;
-#pragma unroll
-            for (int s = 0; s < UPT; ++s) {
-                const int u = tid + s * NT;
-                if (u >= 2 * UNITS_K)
-                    continue;
-                const int uu = u < UNITS_K ? u : u - UNITS_K, quad = uu / CH, chunk = uu % CH;
-                if (u < UNITS_K)
-                    store_k_unit<DH>(kt, stage[s], quad, chunk);
-                else
-                    store_v_unit<DH>(vt, stage[s], quad, chunk);
-            }
-        };
-
-        load_tile(j0);
-        store_tile(0);
-        lds_barrier();
-
-        for (int j = j0; j < j1; ++j) {
-            const int buf = (j - j0) & 1;
-            if (j + 1 < j1)
-                load_tile(j + 1);                              // in flight while this tile is computed
-
-            if (compute_wave) {
-                const char *kt = tiles + buf * 2 * TILE_BYTES, *vt = kt + TILE_BYTES;
-                constexpr int TB_OFF = 32 * DH * 2;            // second block of 32 tokens in the K tile
-                // ---- S^T = K . Q^T for the two 32-token blocks of the tile, each K fragment feeding RB blocks
-                f32x16 acc_s[RB][2];
-                const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                uint4 kf[3][2];
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk) {
-                    const int co = ((2 * kk + hf) ^ sw) << 4;
-                    kf[kk][0] = *(const uint4 *)(kt + krow_off + co);
-                    kf[kk][1] = *(const uint4 *)(kt + TB_OFF + krow_off + co);
-                }
-#pragma unroll
-                for (int kk = 0; kk < NKK; ++kk) {
-                    if (kk + 2 < NKK) {
-                        const int co = ((2 * (kk + 2) + hf) ^ sw) << 4;
-                        kf[(kk + 2) % 3][0] = *(const uint4 *)(kt + krow_off + co);
-                        kf[(kk + 2) % 3][1] = *(const uint4 *)(kt + TB_OFF + krow_off + co);
-                    }
-#pragma unroll
-                    for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                        for (int rb = 0; rb < RB; ++rb)
-                            acc_s[rb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                as_bf16x8(kf[kk % 3][tb]), as_bf16x8(qf[rb][kk]), kk == 0 ? zero16 : acc_s[rb][tb],
-                                0, 0, 0);
-                }
-                // ---- which of this lane's 32 tokens count, then the running softmax per row block
-                const bool tree_tile = (j == n_b - 1);
-                const int pos0 = (tile0 + j) * TA_TILE;            // a prefix tile holds positions pos0 .. pos0+63,
-                const bool partial = L - pos0 < TA_TILE || pos0 < S;   // of which those in [S, L) count
-                uint4 pb[RB][4];
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    if (tree_tile || partial)
-                        mask_scores(acc_s[rb], (tree_tile ? tree_mask[rb] : ta_prefix_tile_mask(pos0, L, S)) >> (4 * hf));
-                    softmax_tile<NDB>(acc_s[rb], c, m_run[rb], l_run[rb], l2_run[rb], acc_o[rb], pb[rb]);
-                }
-                // ---- O^T += V^T . P^T, each V fragment feeding RB blocks
-                constexpr int KB_OFF = 2 * DH * 16;            // token slab kb of the V tile; step s = kb * NDB + db
-                uint4 vf[4];
-#pragma unroll
-                for (int s = 0; s < 3; ++s)
-                    vf[s] = *(const uint4 *)(vt + (s / NDB) * KB_OFF + vcol_off[s % NDB]);
-#pragma unroll
-                for (int s = 0; s < 4 * NDB; ++s) {
-                    if (s + 3 < 4 * NDB)
-                        vf[(s + 3) & 3] = *(const uint4 *)(vt + ((s + 3) / NDB) * KB_OFF + vcol_off[(s + 3) % NDB]);
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb)
-                        acc_o[rb][s % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            as_bf16x8(vf[s & 3]), as_bf16x8(pb[rb][s / NDB]), acc_o[rb][s % NDB], 0, 0, 0);
-                }
-            }
-
-            if (j + 1 < j1)
-                store_tile(buf ^ 1);
-            lds_barrier();
-        }
-
-        // ---- partial result of this (workgroup, list) overlap: normalised O and base-2 log-sum-exp
-        if (compute_wave) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                const int row = (wave * RB + rb) * 32 + r32;
-                if (row < rows_here) {
-                    const int64_t wrow = ta_ws_row(p, slot, rg, row);
-                    const float l_tot = l_run[rb] + __shfl_xor(l_run[rb], 32, TA_WAVE);
-                    const float inv = 1.f / (l2_run[rb] + __shfl_xor(l2_run[rb], 32, TA_WAVE));
-                    // 16-bit fixed point with the row's own scale: the two lanes of a row find its largest magnitude
-                    float amax = 0.f;
-                    bool has_nan = false;
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const float x = acc_o[rb][db][i] * inv;
-                            amax = fmaxf(amax, fabsf(x));
-                            has_nan |= x != x;
-                        }
-                    amax = fmaxf(amax, __shfl_xor(amax, 32, TA_WAVE));
-                    has_nan |= __shfl_xor((int)has_nan, 32, TA_WAVE) != 0;
-                    float scale, to_q;
-                    ta_q15_scale(amax, has_nan, scale, to_q);
-                    to_q *= inv;
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db) {
-#pragma unroll
-                        for (int i4 = 0; i4 < 4; ++i4) {
-                            uint2 o;
-                            o.x = ta_q15_pack(acc_o[rb][db][4 * i4 + 0], acc_o[rb][db][4 * i4 + 1], to_q);
-                            o.y = ta_q15_pack(acc_o[rb][db][4 * i4 + 2], acc_o[rb][db][4 * i4 + 3], to_q);
-                            *(uint2 *)(ta_part_row(p, wrow) + 2 * (db * 32 + 8 * i4 + 4 * hf)) = o;
-                        }
-                    }
-                    if (hf == 0)
-                        *(float2 *)&p.ws_lse[2 * wrow] = make_float2(m_run[rb] * c + log2f(l_tot), scale);
-                }
-            }
-        }
-        __syncthreads();                                       // masks and tiles are reused by the next item
-        t = seg_start + (j1 == n_b ? n_u : j1);
-    }
-}
-
 #define PP_PAGES 2048                             // page ids cached in LDS per span of tiles
 #define SP_OWN_FIRST 32                           // see issue_first in ta_mfma_sp_kernel
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // every lane moves 16 bytes from its own global address to LDS offset lds_wave_base + 16*lane
 __device__ __forceinline__ void dma16(const void *gptr, uint32_t lds_wave_base)
@@ -1094,38 +590,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
     }
 }
 
-template <int NCW, int RB, int NT, int DH>
-static hipError_t launch_variant(const TAParams &p, hipStream_t stream, int dev)
-{
-    const size_t smem = MF_STAGES * 2 * (TA_TILE * DH * 2) + sizeof(unsigned long long) * TA_MAX_TREE + 16 +
-                        sizeof(int) * TA_MAX_TREE + sizeof(int) * (p.B + 2);
-    static bool attr_set[64] = {};      // per device and variant; setting it twice is harmless
-    if (dev < 0 || dev >= 64)
-        return hipErrorInvalidDevice;
-    if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void *)ta_mfma_kv_kernel<NCW, RB, NT, DH>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512);
-        if (e != hipSuccess)
-            return e;
-        attr_set[dev] = true;
-    }
-    hipLaunchKernelGGL((ta_mfma_kv_kernel<NCW, RB, NT, DH>), dim3(p.n_wg, p.n_rg), dim3(NT), smem, stream, p);
-    return hipGetLastError();
-}
-
 hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
 {
+    if (p.D == 64 || p.basic)
+        return ta_launch_mfma_ks(p, stream, dev);
     if (p.rows_grp != 32 && p.rows_grp != 64 && p.rows_grp != 128 && p.rows_grp != 256)
         return hipErrorInvalidValue;
     if (!p.part_q15 || p.ls != 2)                          // the one partial format these kernels write
         return hipErrorInvalidValue;
-    if (p.D == 64)                                         // the register-staged kernel is the only one for this head dim
-        return launch_variant<8, 1, 512, 64>(p, stream, dev);
     // One kernel for every row group: with fewer than 256 rows some of its eight waves only move tiles.
     const size_t smem = SP_AUX_OFF + sizeof(unsigned long long) * TA_MAX_TREE + 16 + sizeof(int) * TA_MAX_TREE +
                         sizeof(int) * PP_PAGES + sizeof(int) * (3 * p.B + 2);
-    if (p.basic || smem > 160 * 1024 - 512)
-        return launch_variant<8, 1, 512, 128>(p, stream, dev);   // register-staged kernel: very large batches, or on request
+    if (smem > 160 * 1024 - 512)
+        return hipErrorInvalidValue;                       // the plan takes the key-split kernel for such batches
     static bool attr_set[64] = {};
     if (dev < 0 || dev >= 64)
         return hipErrorInvalidDevice;
