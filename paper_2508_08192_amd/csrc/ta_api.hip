@@ -272,12 +272,11 @@ int tree_attn_compact(ta_tensor *k_cache, ta_tensor *v_cache, const ta_tensor *p
     if (rc != TA_OK || c.B == 0)
         return rc;
     DeviceState *s = nullptr;
-    int dev = 0;
-    rc = device_state(&s, &dev);
+    rc = device_state(&s);
     if (rc != TA_OK)
         return rc;
     c.status = s->status;
-    return ta_launch_compact(c, (hipStream_t)stream, dev) == hipSuccess ? TA_OK : TA_ERR_HIP;
+    return ta_launch_compact(c, (hipStream_t)stream) == hipSuccess ? TA_OK : TA_ERR_HIP;
 }
 
 int tree_attn_last_status(int32_t *host_status, void *stream)

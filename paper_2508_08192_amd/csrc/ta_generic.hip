@@ -860,40 +860,52 @@ __global__ __launch_bounds__(256) void ta_append_kernel(TAAppend a)
 }
 
 // Bookkeeping after acceptance (section 3, stage 6): the accepted path's K/V rows move behind the prefix.  One
-// workgroup per request.  The rows of one phase -- as many (KV head, K or V) units of n rows as fit the staging
-// buffer -- are all read into LDS before any of them is written back, and no two phases touch the same bytes, so
-// sources that are also destinations are safe.
-constexpr int CP_STAGE_BYTES = 64 * 1024;
+// workgroup per request (the lengths may be updated in place, so no second workgroup may still have to read one).  A
+// request's work is n rows times the columns of its 2 * Hkv rows per token, a column being one piece of type P; only
+// pieces of the same column can be each other's source and destination.  Columns are therefore taken in phases of as many
+// as the registers of the workgroup hold all n rows of: a phase reads every piece before it writes any, and no two
+// phases touch the same bytes, so sources that are also destinations are safe.
+// What bounds it: three dependent round trips (lengths; page ids; rows) of few bytes.  B 8, Hkv 8, head_dim 128, paths of
+// up to eight nodes: 26.1 us (the kernel alone) when single elements went through LDS in a loop with the page looked up
+// for each, 5.0 now.
+constexpr int CP_THREADS = 512, CP_REGS = 8;
 
-template <typename E>
-__global__ __launch_bounds__(256) void ta_compact_kernel(TACompact c)
+template <typename P>
+__global__ __launch_bounds__(CP_THREADS) void ta_compact_kernel(TACompact c)
 {
-    extern __shared__ __attribute__((aligned(16))) char cp_stage[];
     __shared__ int ids[TA_MAX_TREE];
+    __shared__ int64_t k_at[TA_MAX_TREE], v_at[TA_MAX_TREE];       // element offsets of tree token i's rows of KV head 0
     __shared__ int bad;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int L = c.seq_lens[(int64_t)b * c.sl_s];
     const int n = c.n_accepted[(int64_t)b * c.na_s];
+    const int id = tid < c.A ? c.accepted[(int64_t)b * c.acc_sb + tid] : 0;
+    const bool len_ok = L >= 0 && (int64_t)L + c.T <= (int64_t)c.capacity;
+    const bool n_ok = n >= 0 && n <= c.A;
     if (tid == 0)
         bad = 0;
     __syncthreads();
-    const bool len_ok = L >= 0 && (int64_t)L + c.T <= (int64_t)c.capacity;
-    const bool n_ok = n >= 0 && n <= c.A;
     if (n_ok && tid < n) {
-        const int id = c.accepted[(int64_t)b * c.acc_sb + tid];
         ids[tid] = id;
         if (id < 0 || id >= c.T)
             atomicOr(&bad, 1);
     }
-    __syncthreads();
-    const bool path_ok = n_ok && (bad & 1) == 0;
     // every page a row may come from or go to (positions L .. L+T-1) must be a page of the cache
-    if (len_ok && c.page_table && tid < c.T) {
-        const int id = c.page_table[(int64_t)b * c.pt_sb + (L + tid) / c.ps];
-        if (id < 0 || id >= c.n_pages)
-            atomicOr(&bad, 2);
+    if (len_ok && tid < c.T) {
+        int64_t page = b, slot = L + tid;
+        if (c.page_table) {
+            page = c.page_table[(int64_t)b * c.pt_sb + (L + tid) / c.ps];
+            slot = (L + tid) % c.ps;
+            if (page < 0 || page >= c.n_pages) {
+                atomicOr(&bad, 2);
+                page = 0;
+            }
+        }
+        k_at[tid] = page * c.k_sp + slot * c.k_ss;
+        v_at[tid] = page * c.v_sp + slot * c.v_ss;
     }
     __syncthreads();
+    const bool path_ok = n_ok && (bad & 1) == 0;
     const bool pages_ok = (bad & 2) == 0;
     if (!len_ok || !path_ok || !pages_ok) {
         if (tid == 0) {
@@ -903,59 +915,45 @@ __global__ __launch_bounds__(256) void ta_compact_kernel(TACompact c)
         }
         return;
     }
-    E *stage = (E *)cp_stage;
-    const int unit = n * c.D;                                      // elements of one (KV head, K or V) unit
-    const int units = 2 * c.Hkv;
-    const int per_phase = unit > 0 ? max(1, (int)(CP_STAGE_BYTES / sizeof(E)) / unit) : units;
-    for (int u0 = 0; u0 < units && unit > 0; u0 += per_phase) {
-        const int nu = min(per_phase, units - u0);
-        for (int pass = 0; pass < 2; ++pass) {                     // 0: cache -> LDS (sources), 1: LDS -> cache
-            for (int x = tid; x < nu * unit; x += blockDim.x) {
-                const int u = u0 + x / unit, r = x % unit;
-                const int j = r / c.D, d = r % c.D;
-                const int g = u >> 1;
-                const int pos = L + (pass == 0 ? ids[j] : j);
-                int64_t page = b, slot = pos;
-                if (c.page_table) {
-                    page = c.page_table[(int64_t)b * c.pt_sb + pos / c.ps];
-                    slot = pos % c.ps;
-                }
-                E *row = (u & 1) ? (E *)c.v + page * c.v_sp + g * c.v_sh + slot * c.v_ss
-                                 : (E *)c.k + page * c.k_sp + g * c.k_sh + slot * c.k_ss;
-                if (pass == 0)
-                    stage[x] = row[d];
-                else
-                    row[d] = stage[x];
-            }
-            __syncthreads();
+    const int es = c.elem_bytes;
+    const int per_row = c.D * es / (int)sizeof(P);                 // pieces of a row
+    const int cols = 2 * c.Hkv * per_row;                          // columns: KV head, K or V, piece
+    const int per_phase = n > 0 ? CP_THREADS * CP_REGS / n : 0;    // n <= TA_MAX_TREE: at least 64
+    auto piece = [&](int col, int tok) {
+        const int u = col / per_row, g = u >> 1;
+        char *base = (u & 1) ? (char *)c.v + (v_at[tok] + g * c.v_sh) * es : (char *)c.k + (k_at[tok] + g * c.k_sh) * es;
+        return (P *)base + (col - u * per_row);
+    };
+    for (int c0 = 0; c0 < cols && n > 0; c0 += per_phase) {
+        const int nc = min(per_phase, cols - c0);
+        P r[CP_REGS];
+#pragma unroll
+        for (int k = 0; k < CP_REGS; ++k) {
+            const int x = tid + k * CP_THREADS;
+            if (x < nc * n)
+                r[k] = *piece(c0 + x % nc, ids[x / nc]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < CP_REGS; ++k) {
+            const int x = tid + k * CP_THREADS;
+            if (x < nc * n)
+                *piece(c0 + x % nc, x / nc) = r[k];
         }
     }
     if (tid == 0 && c.seq_lens_out)
         c.seq_lens_out[(int64_t)b * c.slo_s] = L + n;
 }
 
-hipError_t ta_launch_compact(const TACompact &c, hipStream_t stream, int dev)
+hipError_t ta_launch_compact(const TACompact &c, hipStream_t stream)
 {
-    // staging: one phase holds at most CP_STAGE_BYTES; a single unit (A rows of D elements) never exceeds that
-    const size_t unit_bytes = (size_t)c.A * c.D * c.elem_bytes;
-    if (unit_bytes > (size_t)CP_STAGE_BYTES)
-        return hipErrorInvalidValue;
-    const size_t smem = CP_STAGE_BYTES;                            // with the static part just above the 64 KB default
-    static bool attr_set[64] = {};
-    if (dev < 0 || dev >= 64)
-        return hipErrorInvalidDevice;
-    if (!attr_set[dev]) {
-        for (const void *fn : {(const void *)ta_compact_kernel<uint16_t>, (const void *)ta_compact_kernel<uint32_t>}) {
-            hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess)
-                return e;
-        }
-        attr_set[dev] = true;
-    }
-    if (c.elem_bytes == 2)
-        hipLaunchKernelGGL(ta_compact_kernel<uint16_t>, dim3(c.B), dim3(256), smem, stream, c);
+    const dim3 grid(c.B), block(CP_THREADS);
+    if (c.vec)                          // rows in 16-byte pieces
+        hipLaunchKernelGGL(ta_compact_kernel<uint4>, grid, block, 0, stream, c);
+    else if (c.elem_bytes == 2)
+        hipLaunchKernelGGL(ta_compact_kernel<uint16_t>, grid, block, 0, stream, c);
     else
-        hipLaunchKernelGGL(ta_compact_kernel<uint32_t>, dim3(c.B), dim3(256), smem, stream, c);
+        hipLaunchKernelGGL(ta_compact_kernel<uint32_t>, grid, block, 0, stream, c);
     return hipGetLastError();
 }
 

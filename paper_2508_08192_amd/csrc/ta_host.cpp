@@ -28,6 +28,19 @@ bool new_rows_aligned(const ta_tensor *n)
            n->stride[0] < INT32_MAX && n->stride[1] < INT32_MAX;
 }
 
+// Do all rows (D elements, the last dimension) start on 16 bytes and end there?
+// A dimension of extent 1 has no stride that counts.
+bool rows_of_16_bytes(const ta_tensor *t, int64_t D)
+{
+    const int64_t per16 = t->dtype == TA_BF16 ? 8 : 4;
+    if ((uintptr_t)t->data % 16 != 0 || D % per16 != 0)
+        return false;
+    for (int i = 0; i < t->ndim - 1; ++i)
+        if (t->shape[i] > 1 && t->stride[i] % per16 != 0)
+            return false;
+    return true;
+}
+
 int mfma_rows_group(int rows)
 {
     // 32 rows per wave; workgroups of 1, 2, 4 or 8 such waves, at most TA_ROW_GROUP rows.
@@ -512,6 +525,7 @@ int ta_host_check_compact(const ta_tensor *k, const ta_tensor *v, const ta_tenso
     c.B = (int)B; c.T = (int)T; c.A = (int)A; c.Hkv = (int)Hkv; c.D = (int)D; c.ps = (int)ps; c.capacity = (int)capacity;
     c.n_pages = (int)k->shape[0];
     c.elem_bytes = k->dtype == TA_BF16 ? 2 : 4;
+    c.vec = rows_of_16_bytes(k, D) && rows_of_16_bytes(v, D);
     return TA_OK;
 }
 

@@ -79,6 +79,7 @@ struct TACompact {
     int32_t *seq_lens_out;             // or nullptr
     int64_t k_sp, k_sh, k_ss, v_sp, v_sh, v_ss, pt_sb, sl_s, acc_sb, na_s, slo_s;
     int32_t B, T, A, Hkv, D, ps, capacity, n_pages, elem_bytes;
+    int32_t vec;                       // rows can be moved in 16-byte pieces
     int32_t *status;
 };
 
