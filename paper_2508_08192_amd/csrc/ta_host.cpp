@@ -459,6 +459,7 @@ int ta_host_check_append(const ta_tensor *kn, const ta_tensor *vn, const ta_tens
     a.B = (int)B; a.T = (int)T; a.Hkv = (int)Hkv; a.D = (int)D; a.ps = (int)ps; a.capacity = (int)capacity;
     a.n_pages = (int)k->shape[0];
     a.elem_bytes = kn->dtype == TA_BF16 ? 2 : 4;
+    a.vec = rows_of_16_bytes(kn, D) && rows_of_16_bytes(vn, D) && rows_of_16_bytes(k, D) && rows_of_16_bytes(v, D);
     return TA_OK;
 }
 

@@ -70,6 +70,7 @@ struct TAAppend {
     int64_t kn_sb, kn_st, kn_sh, vn_sb, vn_st, vn_sh;
     int64_t k_sp, k_sh, k_ss, v_sp, v_sh, v_ss, pt_sb, sl_s;
     int32_t B, T, Hkv, D, ps, capacity, n_pages, elem_bytes;
+    int32_t vec;                       // rows can be moved in 16-byte pieces
     int32_t *status;
 };
 
