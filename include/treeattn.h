@@ -106,7 +106,10 @@ typedef struct {
 
 /* Kernel families (ta_opts.kernel).  AUTO picks MFMA when the shape allows it. */
 #define TA_KERNEL_AUTO 0
-#define TA_KERNEL_GENERIC 1   /* scalar fp32-accumulating kernel: any dtype, head_dim, page size */
+#define TA_KERNEL_GENERIC 1   /* scalar fp32-accumulating kernel: any dtype, head_dim, page size.  A plan names this
+                                 family also for the fp32 calls that AUTO gives to a matrix-core kernel of their own
+                                 (head_dim 64 or 128, power-of-two pages or contiguous, 16-byte aligned rows, at most 256
+                                 query heads per KV head; all products and sums stay fp32) */
 #define TA_KERNEL_MFMA 2      /* bf16 matrix-core kernel: head_dim 128 or 64, power-of-two page size (or contiguous),
                                  16-byte aligned q/k/v rows, at most 256 query heads per KV head */
 #define TA_KERNEL_MFMA_BASIC 3 /* as MFMA, but with the key-split matrix-core kernel instead of the pipelined one (the
@@ -262,7 +265,7 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * rows per group, plan[6] = partial slots, plan[7] = workgroups of the merge pass, plan[8] = smallest share of
  * tiles per workgroup, plan[9] = schedule units a list counts (item_cost), plan[10] = merge kernel (0 general,
  * 1 head_dim 128, 2 head_dim 128 with one workgroup per row), plan[11] = row of the dispatch table that was
- * taken (-1: the options fixed everything), plan[12] = workspace bytes the call needs, plan[13] = format
+ * taken (-1: none, fp32 on the matrix cores), plan[12] = workspace bytes the call needs, plan[13] = format
  * of the partial results (0: fp32; 1: 16-bit fixed point with one fp32 scale per row), plan[14..15] = 0.
  * HOST pointers.
  */

@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtreeattn.so")
-SOURCES = ["ta_api.hip", "ta_generic.hip", "ta_mfma.hip", "ta_mfma_ks.hip", "ta_host.cpp"]
+SOURCES = ["ta_api.hip", "ta_generic.hip", "ta_mfma.hip", "ta_mfma_ks.hip", "ta_f32.hip", "ta_host.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # hipcc must not form packed-fp32 instructions on these machines

@@ -98,7 +98,8 @@ int launch_call(const TAProblem &pr, hipStream_t st, int dev, void *const *ev)
 {
     if (ev && ev[0] && hipEventRecord((hipEvent_t)ev[0], st) != hipSuccess)
         return TA_ERR_HIP;
-    hipError_t e = pr.plan.kernel == TA_KERNEL_MFMA ? ta_launch_mfma(pr.p, st, dev) : ta_launch_generic(pr.p, st, dev);
+    hipError_t e = pr.plan.kernel == TA_KERNEL_MFMA ? ta_launch_mfma(pr.p, st, dev)
+                   : pr.p.f32_mfma ? ta_launch_f32(pr.p, st, dev) : ta_launch_generic(pr.p, st, dev);
     if (e != hipSuccess)
         return TA_ERR_HIP;
     if (ev && ev[1] && hipEventRecord((hipEvent_t)ev[1], st) != hipSuccess)

@@ -91,6 +91,18 @@ __device__ __forceinline__ void ta_build_schedule(const TAParams &p, int *cum, i
     __syncthreads();
 }
 
+// Inclusive prefix sum over the lanes of a wave.
+__device__ __forceinline__ int ta_wave_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);       // row_shr:1, 2, 4, 8: sums within 16 lanes
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);       // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);       // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
 __device__ __forceinline__ int ta_share(const TAParams &p, int total)
 {
     int share = (total + p.n_wg - 1) / p.n_wg;
@@ -457,6 +469,7 @@ __device__ __forceinline__ void ta_scatter_store(const TAParams &p, int b, int g
 // Launchers implemented next to their kernels.
 // (`dev`: index of the current device, which the caller already knows)
 hipError_t ta_launch_generic(const TAParams &p, hipStream_t stream, int dev);
+hipError_t ta_launch_f32(const TAParams &p, hipStream_t stream, int dev);
 hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev);
 hipError_t ta_launch_mfma_ks(const TAParams &p, hipStream_t stream, int dev);
 hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream);

@@ -72,6 +72,13 @@ const TADispatchRow kTable[] = {
     {TA_KERNEL_MFMA_BASIC, 256, INT32_MAX, 4, 1, 8, 13, 1024},
     {TA_KERNEL_GENERIC, 256, INT32_MAX, 16, 1, 1, 13, 1024},
 };
+// fp32 on the matrix cores (ta_f32.hip) stands outside the table (a plan names row -1): one workgroup per compute unit and
+// row group -- two fit, but what fp32 calls hold is at most a few tiles per unit, and twice as many shares only cost more
+// partial results (36 MB: 22.5 us a call against 24.6) -- and a list's fixed work counts one tile (36 MB in 16 lists: 22.5
+// against 25.6 us with none and 22.1 with two; 128 lists of up to three tiles 12.7, two: 13.8); a single list counts none
+// (three tiles: 11.8 against 13.3 us).
+const TADispatchRow kF32Rows[2] = {{TA_KERNEL_GENERIC, TA_F32_ROWS, 1, 4, 1, 1, 13, 1024},
+                                   {TA_KERNEL_GENERIC, TA_F32_ROWS, INT32_MAX, 4, 1, 2, 13, 1024}};
 constexpr int kTableRows = (int)(sizeof(kTable) / sizeof(kTable[0]));
 
 int find_row(int family, int rows_grp, int64_t lists)
@@ -225,6 +232,13 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     int basic = kernel == TA_KERNEL_MFMA_BASIC ? 1 : 0;
     if (basic)
         kernel = TA_KERNEL_MFMA;
+    // fp32 goes to the matrix cores where rows can be loaded in 16-byte pieces (a call that names the scalar kernel gets it)
+    auto rows16 = [](const ta_tensor *n) {
+        return (uintptr_t)n->data % 16 == 0 && n->stride[0] % 4 == 0 && n->stride[1] % 4 == 0 && n->stride[2] % 4 == 0 &&
+               n->stride[3] == 1;
+    };
+    const bool f32_mfma = kernel == TA_KERNEL_AUTO && q->dtype == TA_F32 && (D == 128 || D == 64) && Hq / Hkv <= 256 &&
+                          (!pt || ps_shift >= 0) && rows16(q) && rows16(k) && rows16(v) && (!kn || (rows16(kn) && rows16(vn)));
     if (kernel == TA_KERNEL_MFMA && !mfma_ok)
         return TA_ERR_OPTS;
     if (kernel == TA_KERNEL_AUTO)
@@ -235,6 +249,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     TAParams &p = pr->p;
     memset(&p, 0, sizeof p);
     p.basic = basic;
+    p.f32_mfma = f32_mfma;
     p.q = q->data; p.k = k->data; p.v = v->data; p.out = out->data;
     p.lse = lse ? (float *)lse->data : nullptr;
     p.page_table = pt ? (const int32_t *)pt->data : nullptr;
@@ -281,16 +296,21 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     if (kernel == TA_KERNEL_MFMA) {
         pl.rows_grp = basic ? (p.rows <= 32 ? 32 : 64) : mfma_rows_group(p.rows);
         pl.threads = basic && D == 128 && pl.rows_grp == 64 ? 256 : 512;
+    } else if (f32_mfma) {
+        // as few groups of up to 32 rows as hold them, of equal size, so that the scratch holds no more rows than needed
+        const int groups = (p.rows + TA_F32_ROWS - 1) / TA_F32_ROWS;
+        pl.rows_grp = (p.rows + groups - 1) / groups;
+        pl.threads = 256;
     } else {
         pl.rows_grp = p.rows < TA_ROW_GROUP ? p.rows : TA_ROW_GROUP;
         pl.threads = 256;
     }
     pl.n_rg = (p.rows + pl.rows_grp - 1) / pl.rows_grp;
     const int64_t lists = B * Hkv;
-    const int row = find_row(family, pl.rows_grp, lists);
-    if (row < 0)
+    const int row = f32_mfma ? -1 : find_row(family, pl.rows_grp, lists);
+    if (row < 0 && !f32_mfma)
         return TA_ERR_OPTS;                                 // cannot happen: every family ends in a catch-all row
-    const TADispatchRow &dr = kTable[row];
+    const TADispatchRow &dr = f32_mfma ? kF32Rows[lists > kF32Rows[0].lists_max] : kTable[row];
     pl.table_row = row;
     pl.item_cost = item_cost > 0 ? item_cost : dr.item_cost;
     p.pad = pl.item_cost - 1;
@@ -298,7 +318,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     if (tiles_cap + lists * p.pad > INT32_MAX)              // schedule units are counted in 32 bits
         return TA_ERR_SHAPE;
     int64_t want = (int64_t)num_cus * dr.wg_per_cu_x4 / 4;
-    if (kernel == TA_KERNEL_MFMA)
+    if (kernel == TA_KERNEL_MFMA || f32_mfma)
         want /= pl.n_rg;                                    // the row groups of a list run side by side
     if (want < 1)
         want = 1;

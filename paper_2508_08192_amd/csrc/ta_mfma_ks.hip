@@ -82,18 +82,6 @@ __device__ __forceinline__ void ks_dma_4k(const void *base, uint32_t o0, uint32_
                  : "memory");
 }
 
-// Inclusive prefix sum over the lanes of a wave.
-__device__ __forceinline__ int ks_wave_scan(int x)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);       // row_shr:1, 2, 4, 8: sums within 16 lanes
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);       // row_bcast:15 into rows 1 and 3
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);       // row_bcast:31 into rows 2 and 3
-    return x;
-}
-
 // Sizes of one instance.  RB: 32-row blocks a wave keeps; NW: waves of a workgroup; OCC: workgroups per compute unit,
 // which share its LDS.  A wave's ring holds NS runs of 32 tokens of K and as many of V, and is at least as large as its
 // RB * 32 x DH block of fp32 results, which it stages there at the end.
@@ -145,7 +133,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             s_start = ta_kv_start(p, lane);
             s_units = ta_list_tiles(p, s_len, s_start) + p.pad;
         }
-        s_cum = ks_wave_scan(s_units);
+        s_cum = ta_wave_scan(s_units);
         total = p.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
     } else {
         ta_build_schedule(p, cum, p.B <= KS_LENS ? lens : nullptr, p.B <= KS_LENS ? starts : nullptr);

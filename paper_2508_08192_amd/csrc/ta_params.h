@@ -13,6 +13,7 @@
 #define TA_MERGE_ROWS 4       // rows per workgroup of the general merge kernel (one per wave)
 #define TA_MERGE128_ROWS 8    // rows per workgroup of the head_dim-128 merge kernel (half a wave per row)
 #define TA_ROW_GROUP 256      // rows (tree nodes x query heads of one KV head) one workgroup keeps
+#define TA_F32_ROWS 32        // rows one workgroup of the fp32 matrix-core kernel keeps
 #define TA_SP_MAX_BATCH 1900  // requests whose schedule fits beside the pipelined kernel's tile rings in LDS
 #define TA_STATUS_BYTES 256
 
@@ -53,6 +54,7 @@ struct TAParams {
     int32_t *status;           // sticky status word of the device
     int32_t *status2;          // the caller's own status word (ta_opts.status), or null
     int32_t basic;             // take the key-split matrix-core kernel, not the pipelined one
+    int32_t f32_mfma;          // fp32 inputs on the matrix cores (ta_f32.hip)
     int32_t merge_kind;        // TA_MERGE_*: which merge kernel follows the KV pass
     int32_t part_q15;          // the partial outputs in ws_o are 16-bit fixed point with one scale per row
                                // (matrix-core kernels) rather than fp32

@@ -1,0 +1,111 @@
+"""fp32 attention on the matrix cores (head_dim 64 and 128): sizes at the edges of its runs of 32 tokens, of the rounds of
+its four waves and of its groups of 32 rows, every way the tree tokens and the schedule reach it, and values at which a
+probability of zero is not enough, against the fp64 oracle and the scalar kernel."""
+import numpy as np
+import pytest
+
+from paper_2508_08192_amd import workloads as W
+from tests.helpers import assert_parity, run_hip, run_oracle, to_device
+
+pytestmark = pytest.mark.gpu
+GENERIC = 1
+
+
+def _check(w, what, **kw):
+    print("f32 matrix " + what, flush=True)
+    got, lse = run_hip(w, **kw)
+    ref, ref_lse = run_oracle(w)
+    assert_parity(got, lse, ref, ref_lse, "f32", what)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("T,Hq,Hkv", [(1, 1, 1), (8, 4, 1), (33, 1, 1), (11, 6, 2), (13, 5, 1), (64, 4, 2)])
+@pytest.mark.parametrize("ps", [0, 4, 64])
+def test_runs_row_groups_and_tree_ends(D, T, Hq, Hkv, ps):
+    """Prefixes at and around a run, a tile and a round of the waves; 1 to 128 rows in one to four groups, even and uneven;
+    trees of one and two runs."""
+    lens = [0, 1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 700]
+    rng = np.random.default_rng(D + T)
+    trees = np.stack([W.random_tree(T, min(T, 7), rng) for _ in lens])
+    for splits in (0, 2):
+        w = W.make_workload("runs", B=len(lens), T=T, Hq=Hq, Hkv=Hkv, D=D, seq_lens=lens, trees=trees, page_size=ps or 64,
+                            seed=41 + T, paged=ps > 0, dtype="f32")
+        _check(w, "D=%d T=%d ps=%d splits=%d" % (D, T, ps, splits), num_splits=splits)
+
+
+@pytest.mark.parametrize("B", [64, 65, 257])
+def test_schedule_in_registers_and_in_lds_with_windows(B):
+    rng = np.random.default_rng(B)
+    w = W.make_workload("sched", B=B, T=4, Hq=4, Hkv=2, D=64, seq_lens=rng.integers(0, 200, size=B), trees=W.chain_tree(4),
+                        page_size=32, seed=B, dtype="f32")
+    w.kv_start = (w.seq_lens // 3).astype(np.int32)
+    _check(w, "B=%d" % B)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_options_agree_with_the_scalar_kernel(D):
+    """Masks encoded before the call, a subset of the nodes asking, the write-back folded in, rows whose start is no multiple
+    of 16 bytes (which the scalar kernel keeps): both kernels give the same results up to the order of fp32 sums (2^-24 of
+    a value per step of sums over up to 300 terms that partly cancel: 1e-5 of the largest)."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    lens = [5, 300, 64]
+    T, Hq, Hkv, off = 12, 4, 2, 7
+    w = W.make_workload("opts", B=3, T=T, Hq=Hq, Hkv=Hkv, D=D, seq_lens=lens, trees=W.bfs_tree(T, [3], 4), page_size=16,
+                        seed=77, dtype="f32")
+    d = to_device(w)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    k_new = torch.randn(3, T, Hkv, D, generator=g, device="cuda")
+    v_new = torch.randn(3, T, Hkv, D, generator=g, device="cuda")
+    masks = torch.empty((T,), dtype=torch.int64, device="cuda")
+    ta.tree_attn_encode(d["tree_parent"], masks)
+    wide = torch.randn(3, T, Hq, D + 1, generator=g, device="cuda")
+    qs = {"whole": wide[..., :D].contiguous(), "some": wide[:, off:, :, :D].contiguous(), "unaligned": wide[..., 1:]}
+    for name, q in qs.items():
+        for kw in ({}, {"tree_masks": masks}, {"k_new": k_new, "v_new": v_new}):
+            if name == "some":
+                kw = dict(kw, q_node_offset=off)
+            res = []
+            for kernel in (0, GENERIC):
+                k, v = d["k_cache"].clone(), d["v_cache"].clone()
+                out = torch.full((3, q.shape[1], Hq, D), float("nan"), device="cuda")
+                lse = torch.full((3, Hq, q.shape[1]), float("nan"), device="cuda")
+                print("f32 options D=%d %s %s kernel=%d" % (D, name, sorted(kw), kernel), flush=True)
+                ta.tree_attn_fwd_ex(q, k, v, d["page_table"], d["seq_lens"], d["tree_parent"], out, lse, kernel=kernel, **kw)
+                torch.cuda.synchronize()
+                res.append((out, lse, k, v))
+            (o0, l0, k0, v0), (o1, l1, k1, v1) = res
+            assert torch.isfinite(o0).all() and (o0 - o1).abs().max() <= 1e-5 * o1.abs().max()
+            assert (l0 - l1).abs().max() <= 1e-5 * l1.abs().max()
+            assert torch.equal(k0, k1) and torch.equal(v0, v1)
+
+
+def test_infinities_and_nans_come_out_as_from_the_scalar_kernel():
+    """An infinite value in the last attended token of a ragged prefix (whose places after it repeat that token with
+    probability zero), an infinite score, a NaN key, keys whose scores are all -inf, a NaN in a row beyond the prefix."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    L = [37, 37, 37, 40, 33, 70]
+    w = W.make_workload("inf", B=6, T=3, Hq=2, Hkv=1, D=64, seq_lens=L, trees=W.chain_tree(3), page_size=128, seed=9,
+                        dtype="f32", paged=False)
+    d = to_device(w)
+    inf = float("inf")
+    d["q"].abs_()
+    d["v_cache"][0, 0, 36, 5] = inf
+    d["k_cache"][1, 0, 20, 3] = inf
+    d["k_cache"][2, 0, 36, 3] = float("nan")
+    d["k_cache"][3, 0, :3, 1] = -inf
+    d["k_cache"][4, 0, :36, 1] = -inf
+    d["v_cache"][5, 0, 73:] = float("nan")
+    d["k_cache"][5, 0, 73:] = float("nan")
+    res = []
+    for kernel in (0, GENERIC):
+        print("f32 infinities kernel=%d" % kernel, flush=True)
+        out, lse = torch.zeros_like(d["q"]), torch.zeros((6, 2, 3), device="cuda")
+        ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], None, d["seq_lens"], d["tree_parent"], out, lse, kernel=kernel)
+        torch.cuda.synchronize()
+        res.append((out, lse))
+    (o0, l0), (o1, l1) = res
+    torch.testing.assert_close(o0, o1, rtol=1e-5, atol=1e-5, equal_nan=True)
+    torch.testing.assert_close(l0, l1, rtol=1e-5, atol=1e-5, equal_nan=True)
+    assert torch.isinf(o0[0, :, :, 5]).all() and torch.isfinite(o0[3]).all() and torch.isfinite(o0[5]).all()
