@@ -34,7 +34,8 @@ def generate_blocks(verbose=False):
 
 
 def build_library(verbose=False, extra_flags=()):
-    """Compile every HIP source for gfx950 and link the C-ABI shared library; returns its path."""
+    """Compile every HIP source for gfx950 and link the C-ABI shared library; returns its path.  The extension module
+    through which Python calls it is built beside it."""
     generate_blocks(verbose)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + ".tmp%d" % os.getpid()
@@ -57,7 +58,28 @@ def build_library(verbose=False, extra_flags=()):
         os.remove(tmp)
         raise
     os.replace(tmp, LIB)
+    build_call_module(verbose)
     return LIB
+
+
+CALL_MODULE = os.path.join(HERE, "_call.so")
+
+
+def build_call_module(verbose=False):
+    """The extension module that describes tensors and makes the calls (csrc/ta_call.cpp); returns its path."""
+    import sysconfig
+    tmp = CALL_MODULE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", "-Werror",
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "ta_call.cpp"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        raise RuntimeError("g++ failed:\n" + proc.stdout)
+    os.replace(tmp, CALL_MODULE)
+    return CALL_MODULE
 
 
 HOST_CHECKED_LIB = os.path.join(HERE, "libtreeattn_hostcheck.so")

@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libtreeattn (argument marshalling only; every step runs in the HIP kernels).
+"""Thin binding of libtreeattn (argument marshalling only; every step runs in the HIP kernels).  The calls of a step with
+plain torch tensors go through the extension module _call (csrc/ta_call.cpp), everything else through ctypes.
 
 Function names and argument order follow include/treeattn.h.  Tensors are torch tensors on the GPU
 (torch is used for device memory and streams only) or `Desc` objects (raw pointer + shape + strides,
@@ -83,6 +84,8 @@ class TreeAttnError(RuntimeError):
 
 
 _lib = None
+_call = None                   # the extension module; None without torch, whose tensors are all it takes
+_entry = {}                    # addresses of the entry points it calls
 
 
 def load_library():
@@ -135,14 +138,35 @@ def load_library():
         lib.tree_attn_strerror.argtypes = [ctypes.c_int]
         lib.tree_attn_version.restype = ctypes.c_int
         lib.tree_attn_version.argtypes = []
+        _set_up_call_module(lib)
         _lib = lib
     return _lib
 
 
+def _set_up_call_module(lib):
+    """The extension module learns the tensor types it takes and the addresses of the library's entry points."""
+    global _call
+    try:
+        import torch
+    except ImportError:
+        return
+    try:
+        from . import _call as module
+    except ImportError as e:
+        raise ImportError("_call.so is not built: run `python -m paper_2508_08192_amd.build` (%s)" % e)
+    for name in ("tree_attn_fwd", "tree_attn_fwd_ex", "tree_attn_fwd_static", "tree_attn_append", "tree_attn_compact"):
+        _entry[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    module.setup(torch.Tensor, torch.nn.Parameter, tuple(_dtype_codes(torch).items()))
+    _call = module
+
+
+def _dtype_codes(torch):
+    return {torch.float32: TA_F32, torch.bfloat16: TA_BF16, torch.int32: TA_I32, torch.int64: TA_U64, torch.uint64: TA_U64}
+
+
 def _torch_dtype_code(t):
     import torch
-    table = {torch.float32: TA_F32, torch.bfloat16: TA_BF16, torch.int32: TA_I32, torch.int64: TA_U64,
-             torch.uint64: TA_U64}
+    table = _dtype_codes(torch)
     if t.dtype not in table:
         return -1
     return table[t.dtype]
@@ -177,6 +201,18 @@ def _stream_ptr(stream):
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+def _stream_address(stream):
+    """The same as an integer."""
+    if stream is None:
+        from torch import _C, cuda
+        if cuda.is_initialized():
+            return _C._cuda_getCurrentRawStream(_C._cuda_getDevice())
+        return cuda.current_stream().cuda_stream
+    if isinstance(stream, int):
+        return stream
+    return stream.cuda_stream
 
 
 def _opts(scale=None, num_splits=0, kernel=TA_KERNEL_AUTO, workspace=None, events=None, item_cost=0, tree_masks=None,
@@ -218,10 +254,31 @@ def tree_attn_strerror(status):
 
 def tree_attn_fwd(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse=None, stream=None, check=True):
     """include/treeattn.h: tree_attn_fwd.  Returns the status code (raises TreeAttnError if check)."""
-    ds = [_desc(x) for x in (q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse)]
-    rc = load_library().tree_attn_fwd(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None)
+    lib, rc = load_library(), None
+    if _call is not None:
+        rc = _call.fwd(_entry["tree_attn_fwd"], _stream_address(stream), q, k_cache, v_cache, page_table, seq_lens, tree_parent,
+                       out, lse)
+    if rc is None:
+        ds = [_desc(x) for x in (q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse)]
+        rc = lib.tree_attn_fwd(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None)
     if check and rc != TA_OK:
         raise TreeAttnError(rc, "tree_attn_fwd")
+    return rc
+
+
+def _fwd_with_opts(name, q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse, stream, scale, num_splits, kernel,
+                   workspace, events, check, item_cost, tree_masks, kv_start, q_node_offset, k_new, v_new, status):
+    lib, rc = load_library(), None
+    if _call is not None and workspace is None and events is None and status is None:
+        rc = _call.fwd_ex(_entry[name], _stream_address(stream), q, k_cache, v_cache, page_table, seq_lens, tree_parent, out,
+                          lse, scale, num_splits, kernel, item_cost, tree_masks, kv_start, q_node_offset, k_new, v_new)
+    if rc is None:
+        ds = [_desc(x) for x in (q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse)]
+        o = _opts(scale, num_splits, kernel, workspace, events, item_cost, tree_masks, kv_start, q_node_offset, k_new, v_new,
+                  status)
+        rc = getattr(lib, name)(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None, ctypes.byref(o))
+    if check and rc != TA_OK:
+        raise TreeAttnError(rc, name)
     return rc
 
 
@@ -229,14 +286,9 @@ def tree_attn_fwd_ex(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out
                      scale=None, num_splits=0, kernel=TA_KERNEL_AUTO, workspace=None, events=None, check=True,
                      item_cost=0, tree_masks=None, kv_start=None, q_node_offset=0, k_new=None, v_new=None, status=None):
     """include/treeattn.h: tree_attn_fwd_ex.  `events`: up to three hipEvent_t handles (ctypes.c_void_p)."""
-    ds = [_desc(x) for x in (q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse)]
-    o = _opts(scale, num_splits, kernel, workspace, events, item_cost, tree_masks, kv_start, q_node_offset, k_new, v_new,
-              status)
-    rc = load_library().tree_attn_fwd_ex(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None,
-                                         ctypes.byref(o))
-    if check and rc != TA_OK:
-        raise TreeAttnError(rc, "tree_attn_fwd_ex")
-    return rc
+    return _fwd_with_opts("tree_attn_fwd_ex", q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse, stream, scale,
+                          num_splits, kernel, workspace, events, check, item_cost, tree_masks, kv_start, q_node_offset, k_new,
+                          v_new, status)
 
 
 TA_STATIC_SCRATCH_BYTES = 48 << 20
@@ -247,14 +299,9 @@ def tree_attn_fwd_static(q, k_cache, v_cache, page_table, seq_lens, tree_parent,
                          item_cost=0, tree_masks=None, kv_start=None, q_node_offset=0, k_new=None, v_new=None,
                          status=None):
     """include/treeattn.h: tree_attn_fwd_static (the call that allocates nothing)."""
-    ds = [_desc(x) for x in (q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse)]
-    o = _opts(scale, num_splits, kernel, workspace, events, item_cost, tree_masks, kv_start, q_node_offset, k_new, v_new,
-              status)
-    rc = load_library().tree_attn_fwd_static(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None,
-                                             ctypes.byref(o))
-    if check and rc != TA_OK:
-        raise TreeAttnError(rc, "tree_attn_fwd_static")
-    return rc
+    return _fwd_with_opts("tree_attn_fwd_static", q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse, stream,
+                          scale, num_splits, kernel, workspace, events, check, item_cost, tree_masks, kv_start, q_node_offset,
+                          k_new, v_new, status)
 
 
 def tree_attn_workspace_bytes(B, T, Hq, Hkv, D, dtype, num_cus=0):
@@ -318,8 +365,13 @@ def tree_attn_encode(tree_parent, masks, stream=None, check=True):
 
 def tree_attn_append(k_new, v_new, k_cache, v_cache, page_table, seq_lens, stream=None, check=True):
     """include/treeattn.h: tree_attn_append (write-back of the tree tokens' keys and values)."""
-    ds = [_desc(x) for x in (k_new, v_new, k_cache, v_cache, page_table, seq_lens)]
-    rc = load_library().tree_attn_append(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None)
+    lib, rc = load_library(), None
+    if _call is not None:
+        rc = _call.append(_entry["tree_attn_append"], _stream_address(stream), k_new, v_new, k_cache, v_cache, page_table,
+                          seq_lens)
+    if rc is None:
+        ds = [_desc(x) for x in (k_new, v_new, k_cache, v_cache, page_table, seq_lens)]
+        rc = lib.tree_attn_append(*[_ref(d) for d in ds], _stream_ptr(stream) if stream != 0 else None)
     if check and rc != TA_OK:
         raise TreeAttnError(rc, "tree_attn_append")
     return rc
@@ -328,10 +380,15 @@ def tree_attn_append(k_new, v_new, k_cache, v_cache, page_table, seq_lens, strea
 def tree_attn_compact(k_cache, v_cache, page_table, seq_lens, accepted, n_accepted, tree_size, seq_lens_out=None,
                       stream=None, check=True):
     """include/treeattn.h: tree_attn_compact (bookkeeping after acceptance: the accepted path moves behind the prefix)."""
-    ds = [_desc(x) for x in (k_cache, v_cache, page_table, seq_lens, accepted, n_accepted)]
-    so = _desc(seq_lens_out)
-    rc = load_library().tree_attn_compact(*[_ref(d) for d in ds], int(tree_size), _ref(so),
-                                          _stream_ptr(stream) if stream != 0 else None)
+    lib, rc = load_library(), None
+    if _call is not None:
+        rc = _call.compact(_entry["tree_attn_compact"], _stream_address(stream), k_cache, v_cache, page_table, seq_lens,
+                           accepted, n_accepted, seq_lens_out, tree_size)
+    if rc is None:
+        ds = [_desc(x) for x in (k_cache, v_cache, page_table, seq_lens, accepted, n_accepted)]
+        so = _desc(seq_lens_out)
+        rc = lib.tree_attn_compact(*[_ref(d) for d in ds], int(tree_size), _ref(so),
+                                   _stream_ptr(stream) if stream != 0 else None)
     if check and rc != TA_OK:
         raise TreeAttnError(rc, "tree_attn_compact")
     return rc
