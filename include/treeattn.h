@@ -112,9 +112,10 @@ typedef struct {
                                  query heads per KV head; all products and sums stay fp32) */
 #define TA_KERNEL_MFMA 2      /* bf16 matrix-core kernel: head_dim 128 or 64, power-of-two page size (or contiguous),
                                  16-byte aligned q/k/v rows, at most 256 query heads per KV head */
-#define TA_KERNEL_MFMA_BASIC 3 /* as MFMA, but with the key-split matrix-core kernel instead of the pipelined one (the
-                                 library takes it by itself for head_dim 64, and when the batch is so large, B above 1900,
-                                 that the pipelined kernel's schedule does not fit beside the tiles in LDS) */
+#define TA_KERNEL_MFMA_BASIC 3 /* as MFMA, but with the key-split matrix-core kernel instead of the pipelined one.  AUTO
+                                 takes it for up to 32 query rows per KV head and for more rows in small batches; AUTO and
+                                 MFMA take it for head_dim 64, and when the batch is so large, B above 1900, that the
+                                 pipelined kernel's schedule does not fit beside the tiles in LDS. */
 
 typedef struct {
     float scale;              /* softmax scale; <= 0 or NaN selects 1/sqrt(head_dim) */
@@ -266,7 +267,8 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * tiles per workgroup, plan[9] = schedule units a list counts (item_cost), plan[10] = merge kernel (0 general,
  * 1 head_dim 128, 2 head_dim 128 with one workgroup per row), plan[11] = row of the dispatch table that was
  * taken (-1: none, fp32 on the matrix cores), plan[12] = workspace bytes the call needs, plan[13] = format
- * of the partial results (0: fp32; 1: 16-bit fixed point with one fp32 scale per row), plan[14..15] = 0.
+ * of the partial results (0: fp32; 1: 16-bit fixed point with one fp32 scale per row), plan[14] = 1 if the
+ * key-split matrix-core kernel runs, plan[15] = 0.
  * HOST pointers.
  */
 int tree_attn_plan(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,

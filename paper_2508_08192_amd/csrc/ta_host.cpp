@@ -60,15 +60,14 @@ int mfma_rows_group(int rows)
 // rows; nothing for the scalar one.  With few lists cut over the
 // whole chip (batch size one) the merge becomes a latency problem and one workgroup per output row is faster from
 // 13 partials per list on, while the batch has at most 1024 output rows.
-// A single list counts no fixed work: the units it would add only keep workgroups idle (a list of 129 tiles was cut
-// into 65 shares of two instead of 129 of one; KV pass + merge: 8192 tokens and 64 rows 19.7 -> 18.8 us, 2048 tokens and
-// 60 rows 15.8 -> 14.7, 16384 to 65536 tokens unchanged).
+// A single list counts less fixed work: what it adds mostly keeps workgroups idle (8000 tokens, 32 rows: 17.9 us a call
+// without any, which leaves shares of one tile, 16.3 with three to fifteen units).
 const TADispatchRow kTable[] = {
-    {TA_KERNEL_MFMA, 64, 1, 4, 1, 1, 13, 1024},
+    {TA_KERNEL_MFMA, 32, 1, 4, 1, 6, 13, 1024},
+    {TA_KERNEL_MFMA, 32, INT32_MAX, 4, 1, 9, 13, 1024},
     {TA_KERNEL_MFMA, 64, INT32_MAX, 4, 1, 9, 13, 1024},
     {TA_KERNEL_MFMA, 128, INT32_MAX, 4, 2, 9, 13, 1024},
     {TA_KERNEL_MFMA, 256, INT32_MAX, 4, 4, 9, 13, 1024},
-    {TA_KERNEL_MFMA_BASIC, 32, INT32_MAX, 4, 1, 8, 13, 1024},
     {TA_KERNEL_MFMA_BASIC, 256, INT32_MAX, 4, 1, 8, 13, 1024},
     {TA_KERNEL_GENERIC, 256, INT32_MAX, 16, 1, 1, 13, 1024},
 };
@@ -80,6 +79,18 @@ const TADispatchRow kTable[] = {
 const TADispatchRow kF32Rows[2] = {{TA_KERNEL_GENERIC, TA_F32_ROWS, 1, 4, 1, 1, 13, 1024},
                                    {TA_KERNEL_GENERIC, TA_F32_ROWS, INT32_MAX, 4, 1, 2, 13, 1024}};
 constexpr int kTableRows = (int)(sizeof(kTable) / sizeof(kTable[0]));
+
+// Workgroups of the key-split kernel along a share's length when `slices` of them, with 32 or 64 rows each, serve it side by
+// side.  These follow each other one grid row apart, and a row of a whole number of XCDs puts them on the same one, where
+// the share comes out of the L2 for all but the first (4 lists of 24000 tokens, 160 rows: 50.6 us a call with 51 workgroups
+// a row, 31.5 with 48).
+int64_t key_split_workgroups(int64_t want, int slices)
+{
+    if (slices == 1)
+        return want;
+    const int64_t n = want / slices;
+    return n > 8 ? n - n % 8 : n;
+}
 
 int find_row(int family, int rows_grp, int64_t lists)
 {
@@ -241,14 +252,40 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
                           (!pt || ps_shift >= 0) && rows16(q) && rows16(k) && rows16(v) && (!kn || (rows16(kn) && rows16(vn)));
     if (kernel == TA_KERNEL_MFMA && !mfma_ok)
         return TA_ERR_OPTS;
-    if (kernel == TA_KERNEL_AUTO)
+    const bool auto_kernel = kernel == TA_KERNEL_AUTO;
+    if (auto_kernel)
         kernel = mfma_ok ? TA_KERNEL_MFMA : TA_KERNEL_GENERIC;
     if (kernel == TA_KERNEL_MFMA && (D != 128 || B > TA_SP_MAX_BATCH))
         basic = 1;                               // what the pipelined kernel does not take: head_dim 64, very large batches
 
     TAParams &p = pr->p;
     memset(&p, 0, sizeof p);
-    p.basic = basic;
+    p.rows = (int)(Tq * (Hq / Hkv));
+    const int64_t lists = B * Hkv;
+    const int64_t tiles_cap = lists * ((capacity - T + TA_TILE - 1) / TA_TILE + 1);
+    if (tiles_cap > INT32_MAX)                              // schedule units are counted in 32 bits
+        return TA_ERR_SHAPE;
+    // Which matrix-core kernel (head_dim 128; a call that names TA_KERNEL_MFMA gets the pipelined one).  The key-split
+    // kernel has eight waves computing from the first tile on, the pipelined one as many as there are blocks of 32 rows, but
+    // the former keeps 32 rows: it walks the keys again for every further 32.  Measured, us a call, pipelined and
+    // key-split:
+    //   one block: 16 lists of 8000 tokens 26.1 and 22.0, 32 of 2000 22.1 and 17.1, 64 of 32000 179 and 174; one list of
+    //     500 to 2000 tokens, where a share is a single tile, two of the eight waves' work, 14.4 and 15.7, of 5000 equal;
+    //   two to four: blocks times tiles, per compute unit, 3: 17.2 and 18.0, 4: 22.4 and 18.2, 8: 23.6 and 20.2, 16: 27.3
+    //     and 26.3, 30: 36.6 and 40.1 (one list of 8000 tokens, where it is 1, 18.6 and 17.4);
+    //   five and more, whose tiles cost the pipelined kernel's eight waves more: 8: 25.6 and 17.6, 31: 35.5 and 31.1, 125:
+    //     58.6 and 92.9.
+    // Tiles are counted from what the page table can hold.  With more lists than workgroups in a grid row, or hardly fewer,
+    // most workgroups enter two lists: 64 lists of 500 tokens in rows of 80 workgroups 22.8 and 24.9, 48 a row 30.0 and
+    // 32.6, 64 a row 24.5 and 21.0.
+    const int slices = (p.rows + 31) / 32;
+    const int64_t ks_wg = key_split_workgroups(num_cus, slices);
+    const bool ks_fits = slices == 1 ? lists > 1 || tiles_cap > 64
+                                     : tiles_cap * slices <= (int64_t)(slices > 4 ? 32 : 16) * num_cus &&
+                                           (slices > 4 || lists == 1 || 2 * tiles_cap * slices > 7 * num_cus) &&
+                                           (ks_wg >= 2 * lists || ks_wg == lists);
+    const bool ks = kernel == TA_KERNEL_MFMA && (basic || (auto_kernel && ks_fits));
+    p.basic = ks;
     p.f32_mfma = f32_mfma;
     p.q = q->data; p.k = k->data; p.v = v->data; p.out = out->data;
     p.lse = lse ? (float *)lse->data : nullptr;
@@ -265,7 +302,6 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     p.sl_s = sl->stride[0];
     p.B = (int)B; p.T = (int)T; p.Hq = (int)Hq; p.Hkv = (int)Hkv; p.G = (int)(Hq / Hkv); p.D = (int)D;
     p.ps = (int)ps; p.ps_shift = ps_shift; p.capacity = (int)capacity; p.n_pages = (int)n_pages;
-    p.rows = (int)Tq * p.G;
     p.q_off = (int)q_off;
     p.g_magic = (1u << 24) / (uint32_t)p.G + 1u;
     p.masks_in = opts ? (const unsigned long long *)opts->tree_masks : nullptr;
@@ -294,8 +330,9 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     pl.kernel = kernel;
     const int family = kernel == TA_KERNEL_MFMA ? (basic ? TA_KERNEL_MFMA_BASIC : TA_KERNEL_MFMA) : TA_KERNEL_GENERIC;
     if (kernel == TA_KERNEL_MFMA) {
-        pl.rows_grp = basic ? (p.rows <= 32 ? 32 : 64) : mfma_rows_group(p.rows);
-        pl.threads = basic && D == 128 && pl.rows_grp == 64 ? 256 : 512;
+        p.ks_rows = D == 64 && p.rows > 32 ? 64 : 32;
+        pl.rows_grp = ks && (basic || slices <= 4) ? p.ks_rows : mfma_rows_group(p.rows);
+        pl.threads = 512;
     } else if (f32_mfma) {
         // as few groups of up to 32 rows as hold them, of equal size, so that the scratch holds no more rows than needed
         const int groups = (p.rows + TA_F32_ROWS - 1) / TA_F32_ROWS;
@@ -306,7 +343,6 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         pl.threads = 256;
     }
     pl.n_rg = (p.rows + pl.rows_grp - 1) / pl.rows_grp;
-    const int64_t lists = B * Hkv;
     const int row = f32_mfma ? -1 : find_row(family, pl.rows_grp, lists);
     if (row < 0 && !f32_mfma)
         return TA_ERR_OPTS;                                 // cannot happen: every family ends in a catch-all row
@@ -314,11 +350,12 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     pl.table_row = row;
     pl.item_cost = item_cost > 0 ? item_cost : dr.item_cost;
     p.pad = pl.item_cost - 1;
-    const int64_t tiles_cap = lists * ((capacity - T + TA_TILE - 1) / TA_TILE + 1);
-    if (tiles_cap + lists * p.pad > INT32_MAX)              // schedule units are counted in 32 bits
+    if (tiles_cap + lists * p.pad > INT32_MAX)
         return TA_ERR_SHAPE;
     int64_t want = (int64_t)num_cus * dr.wg_per_cu_x4 / 4;
-    if (kernel == TA_KERNEL_MFMA || f32_mfma)
+    if (ks)
+        want = key_split_workgroups(want, (p.rows + p.ks_rows - 1) / p.ks_rows);
+    else if (kernel == TA_KERNEL_MFMA || f32_mfma)
         want /= pl.n_rg;                                    // the row groups of a list run side by side
     if (want < 1)
         want = 1;
@@ -382,6 +419,7 @@ void ta_host_fill_plan(const TAProblem &pr, int64_t plan[16])
     plan[11] = pr.plan.table_row;
     plan[12] = (int64_t)pr.ws_bytes;
     plan[13] = pr.p.part_q15;
+    plan[14] = pr.plan.kernel == TA_KERNEL_MFMA && pr.p.basic;
 }
 
 size_t ta_host_workspace_bytes(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t D, int32_t dtype, int32_t num_cus)

@@ -1,6 +1,6 @@
 // Key-split matrix-core KV pass of libtreeattn for gfx950: bf16, head_dim 64 or 128, fp32 accumulation.
 //
-// A workgroup keeps up to 64 query rows of one (request, KV head) and its waves split the KEYS of its share: wave w takes
+// A workgroup keeps up to 32 (head_dim 64: 64) query rows of one (request, KV head) and its waves split the KEYS of its share: wave w takes
 // every NW-th run of 32 tokens, with its own running softmax over all the rows, and the waves' results meet in LDS when
 // the item ends.  Nothing is exchanged inside the loop: each wave moves its own K and V rows HBM -> LDS into a ring only
 // it reads (global_load_lds_dwordx4), waits with its own vmcnt and never meets a barrier.  Every wave computes, whatever
@@ -10,6 +10,10 @@
 //     S^T[token, row] = K . Q^T        A = K fragment (LDS), B = Q fragment (registers)
 //     O^T[d, row]    += V^T . P^T      A = V^T fragment (transposing LDS reads), B = P (registers)
 // each K and V fragment feeding RB row blocks.
+//
+// More rows are served by workgroups side by side, which share the stream through the L2 (see key_split_workgroups).
+// Head_dim 128 takes it where it is the faster of the two (the measured line stands in ta_host.cpp): calls of B 1, 32/8
+// heads, T 64, L 4096 (256 rows) 27.5 -> 21.5 us, B 128, T 8, L 256..4096 208.4 -> 206.6 against the pipelined kernel.
 //
 // What bounds it: the HBM stream.  In its loop a compute unit of head_dim 64 and 64 rows streams at the memory's rate
 // (16 lists x 16384 tokens x 8 heads, 538 MB: 93 us, 5.8 TB/s); beside it stand 4.5 us at the start without a byte on
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char *)smem);
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = blockIdx.x, rg = blockIdx.y;
+    const int w = blockIdx.x, row0 = blockIdx.y * C::ROWS;               // first of the workgroup's query rows
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, hf = lane >> 5;
     // Schedule (see ta_build_schedule).  Up to 64 requests every wave keeps it in registers, lane b for request b: no
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
     ta_wg_range(p, total, w, t, t_end);
     t = __builtin_amdgcn_readfirstlane(t);
     t_end = __builtin_amdgcn_readfirstlane(t_end);
-    const int rows_here = min(p.rows_grp, p.rows - rg * p.rows_grp);
+    const int rows_here = min(C::ROWS, p.rows - row0);
     const float c = p.scale_log2e;
     const bool paged = p.page_table != nullptr;
     const uint32_t ksp = (uint32_t)p.k_sp, kss = (uint32_t)p.k_ss, vsp = (uint32_t)p.v_sp, vss = (uint32_t)p.v_ss;
@@ -255,7 +259,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             for (int rb = 0; rb < RB; ++rb) {
                 // Q fragments; rows past the group's end repeat its first row (their results are never stored)
                 const int row = rb * 32 + (l & 31);
-                const int R = rg * p.rows_grp + (row < rows_here ? row : 0);
+                const int R = row0 + (row < rows_here ? row : 0);
                 const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);          // R / G
                 const uint16_t *qp = (const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
                                      (int64_t)(g * p.G + R - node * p.G) * p.q_sh + (l >> 5) * 8;
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 const int row = rb * 32 + (l & 31);
-                const int node = p.q_off + (int)__umulhi((uint32_t)(rg * p.rows_grp + row) << 8, p.g_magic);
+                const int node = p.q_off + (int)__umulhi((uint32_t)(row0 + row) << 8, p.g_magic);
                 const uint32_t m_lo = __shfl((uint32_t)m, node & 63, TA_WAVE), m_hi = __shfl((uint32_t)(m >> 32), node & 63, TA_WAVE);
                 if (row < rows_here)
                     tmask[rb] = ((unsigned long long)m_hi << 32) | m_lo;
@@ -645,7 +649,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             float scale, to_q;
             ta_q15_scale(amax, nan_seen > 0.f, scale, to_q);
             if (row < rows_here) {
-                const int64_t wrow = ta_ws_row(p, slot_e, rg, row);
+                const int64_t wrow = ta_ws_row(p, slot_e, 0, row0 + row);
                 uint32_t *dst = (uint32_t *)(ta_part_row(p, wrow) + 8 * c0);
 #pragma unroll
                 for (int q = 0; q < CPT / 4; ++q)
@@ -677,7 +681,8 @@ static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
             return e;
         attr_set[dev] = true;
     }
-    hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC>), dim3(p.n_wg, p.n_rg), dim3(64 * NW), smem, stream, p);
+    hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC>), dim3(p.n_wg, (p.rows + 32 * RB - 1) / (32 * RB)), dim3(64 * NW), smem,
+                       stream, p);
     return hipGetLastError();
 }
 
@@ -685,9 +690,9 @@ hipError_t ta_launch_mfma_ks(const TAParams &p, hipStream_t stream, int dev)
 {
     if (dev < 0 || dev >= 64)
         return hipErrorInvalidDevice;
-    if ((p.rows_grp != 32 && p.rows_grp != 64) || !p.part_q15 || p.ls != 2)
+    if ((p.ks_rows != 32 && p.ks_rows != 64) || p.rows_grp % p.ks_rows != 0 || !p.part_q15 || p.ls != 2)
         return hipErrorInvalidValue;
     if (p.D == 64)
-        return p.rows_grp == 32 ? launch_ks<64, 1, 8, 1>(p, stream, dev) : launch_ks<64, 2, 8, 1>(p, stream, dev);
-    return p.rows_grp == 32 ? launch_ks<128, 1, 8, 1>(p, stream, dev) : launch_ks<128, 2, 4, 1>(p, stream, dev);
+        return p.ks_rows == 32 ? launch_ks<64, 1, 8, 1>(p, stream, dev) : launch_ks<64, 2, 8, 1>(p, stream, dev);
+    return p.ks_rows == 32 ? launch_ks<128, 1, 8, 1>(p, stream, dev) : hipErrorInvalidValue;
 }

@@ -1,0 +1,77 @@
+"""Calls that choose their kernel by themselves: one to sixteen blocks of 32 query rows on the key-split kernel, in row
+groups of 32 and in groups of 256 whose parts lie in several workgroups, with every option, against the fp64 oracle and the
+pipelined kernel; and the sizes at which the choice falls."""
+import numpy as np
+import pytest
+
+from paper_2508_08192_amd import workloads as W
+from tests.helpers import assert_parity, run_hip, run_oracle, to_device
+
+pytestmark = pytest.mark.gpu
+MFMA = 2
+
+
+def _plan(w, d, kernel=0):
+    from paper_2508_08192_amd import treeattn as ta
+    return ta.tree_attn_plan(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"],
+                             d["lse"], kernel=kernel)
+
+
+@pytest.mark.parametrize("T,Hq,Hkv", [(1, 3, 1), (32, 1, 1), (33, 1, 1), (32, 5, 1), (64, 4, 1), (43, 6, 1), (64, 16, 2), (63, 8, 1)])
+@pytest.mark.parametrize("ps,scale_up", [(16, 1), (0, 7)])
+def test_row_blocks_of_the_key_split_kernel(T, Hq, Hkv, ps, scale_up):
+    lens = [0, 65, 300, 128 * scale_up]
+    rng = np.random.default_rng(T)
+    trees = np.stack([W.random_tree(T, min(T, 7), rng) for _ in lens])
+    w = W.make_workload("blocks", B=len(lens), T=T, Hq=Hq, Hkv=Hkv, D=128, seq_lens=lens, trees=trees, page_size=ps or 64,
+                        seed=T, paged=ps > 0)
+    w.kv_start = np.int32([0, 64, 33, 0])
+    d = to_device(w)
+    rows = T * Hq // Hkv
+    plan = _plan(w, d)
+    blocks = -(-rows // 32)
+    if blocks == 1 or blocks > 4:
+        assert plan["key_split"] == 1 and plan["rows_per_group"] == (32 if blocks == 1 else 256), plan
+    assert _plan(w, d, MFMA)["key_split"] == 0
+    ref, ref_lse = run_oracle(w)
+    for kernel in (0, MFMA):
+        print("kernel choice T=%d %d/%d ps=%d kernel=%d" % (T, Hq, Hkv, ps, kernel), flush=True)
+        got, lse = run_hip(w, d, kernel=kernel)
+        assert_parity(got, lse, ref, ref_lse, "bf16", "rows %d kernel %d" % (rows, kernel))
+
+
+def test_parts_of_a_row_group_with_every_option():
+    """320 query rows in two groups of 256 whose ten parts lie in ten workgroups: a subset of the nodes, given masks, the
+    write-back folded in, a bad page and a bad length each spoiling its own request only."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    T, Hq, lens = 64, 6, [200, 70, 129, 40]
+    w = W.make_workload("parts", B=4, T=T, Hq=Hq, Hkv=1, D=128, seq_lens=lens, trees=W.bfs_tree(T, [4, 2], 8), page_size=32,
+                        seed=3)
+    d = to_device(w)
+    masks = torch.empty((T,), dtype=torch.int64, device="cuda")
+    ta.tree_attn_encode(d["tree_parent"], masks)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    k_new = torch.randn(4, T, 1, 128, generator=g, device="cuda").bfloat16()
+    v_new = torch.randn(4, T, 1, 128, generator=g, device="cuda").bfloat16()
+    q = d["q"][:, 10:].contiguous()
+    d["page_table"][1, 1] = 1 << 30
+    d["seq_lens"][3] = -5
+    res = []
+    for kernel in (0, MFMA):
+        k, v = d["k_cache"].clone(), d["v_cache"].clone()
+        out, lse = torch.zeros_like(q), torch.zeros((4, Hq, T - 10), device="cuda")
+        ta.tree_attn_last_status()
+        print("kernel choice: every option, kernel=%d" % kernel, flush=True)
+        ta.tree_attn_fwd_ex(q, k, v, d["page_table"], d["seq_lens"], d["tree_parent"], out, lse, kernel=kernel,
+                            tree_masks=masks, q_node_offset=10, k_new=k_new, v_new=v_new)
+        torch.cuda.synchronize()
+        assert ta.tree_attn_last_status() == ta.TA_STATUS_BAD_PAGE | ta.TA_STATUS_BAD_SEQLEN
+        res.append((out.float(), lse, k, v))
+    (o0, l0, k0, v0), (o1, l1, k1, v1) = res
+    for b in (1, 3):
+        assert torch.isnan(o0[b]).all() and torch.isnan(l0[b]).all()
+    for b in (0, 2):
+        # both kernels take the probabilities as bf16 (2^-9 each) and round the result to bf16 (2^-9): 1e-2 as elsewhere
+        assert (o0[b] - o1[b]).abs().max() <= 1e-2 * o1[b].abs().max() and (l0[b] - l1[b]).abs().max() <= 1e-3
+    assert torch.equal(k0, k1) and torch.equal(v0, v1)
