@@ -2,6 +2,8 @@
 // and the stand-alone tree encoder.  The KV pass here is the portable path (fp32 inputs, head dims other
 // than 128, page sizes that are not powers of two); the matrix-core path lives in ta_mfma.hip and shares
 // the schedule and the merge.
+#include <type_traits>
+
 #include "ta_common.h"
 
 #define GEN_THREADS 256
@@ -463,20 +465,21 @@ __global__ __launch_bounds__(GEN_THREADS) void ta_merge_kernel(TAParams p)
         p.lse[(int64_t)b * p.lse_sb + (int64_t)h * p.lse_sh + (int64_t)node * p.lse_st] = lse2 * LN2;
 }
 
-// The same merge for head_dim 128 and 16-byte aligned outputs: half a wave per output row, so that a lane holds four
-// neighbouring columns (one 16-byte load per partial and lane) and a workgroup of four waves merges eight rows.
-#define MG_ROWS TA_MERGE128_ROWS
-
-__device__ __forceinline__ float ta_half_max(float x)          // over the 32 lanes of this lane's half-wave
+// The same merge for head_dim 128 and 64 and 16-byte aligned outputs: half (a quarter of) a wave per output row, so that a
+// lane holds four neighbouring columns (one 16- or 8-byte load per partial and lane) and a workgroup of four waves merges
+// eight (sixteen) rows.  Head_dim 64, 128 lists of 64 rows in three 16-bit partials each: 3.9 us, 6.9 with a wave per row.
+template <int LPR>
+__device__ __forceinline__ float ta_part_max(float x)          // over the LPR lanes that share a row
 {
-    for (int off = 16; off > 0; off >>= 1)
+    for (int off = LPR / 2; off > 0; off >>= 1)
         x = fmaxf(x, __shfl_xor(x, off, TA_WAVE));
     return x;
 }
 
-__device__ __forceinline__ float ta_half_sum(float x)
+template <int LPR>
+__device__ __forceinline__ float ta_part_sum(float x)
 {
-    for (int off = 16; off > 0; off >>= 1)
+    for (int off = LPR / 2; off > 0; off >>= 1)
         x += __shfl_xor(x, off, TA_WAVE);
     return x;
 }
@@ -501,13 +504,14 @@ __device__ __forceinline__ float4 ta_part_f4(const ta_s4 &x)
     return make_float4((float)x.x, (float)x.y, (float)x.z, (float)x.w);
 }
 
-template <bool NEW, bool HP>
-__global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
+template <int D, bool NEW, bool HP>
+__global__ __launch_bounds__(256) void ta_merge_row_kernel(TAParams p)
 {
+    constexpr int LPR = D / 4, RPW = TA_WAVE / LPR;       // lanes per row, rows per wave
     const int seg = blockIdx.x;
     const int b = seg / p.Hkv, g = seg % p.Hkv;
     const int lane = threadIdx.x % TA_WAVE, wave = threadIdx.x / TA_WAVE;
-    const int hl = lane & 31, half = lane >> 5;
+    const int hl = lane % LPR, part = lane / LPR;
     const int w_first = p.ws_parts[2 * seg];                             // left by the KV pass
     const int n_parts = p.ws_parts[2 * seg + 1] - w_first + 1;
     const float LN2 = 0.6931471805599453f;
@@ -516,8 +520,8 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
     if constexpr (NEW)
         ta_scatter_load(p, b, g, blockIdx.y, gridDim.y, sc);
-    const int R_raw = blockIdx.y * MG_ROWS + wave * 2 + half;
-    if (R_raw - half >= p.rows) {                          // the whole wave is past the last row
+    const int R_raw = (blockIdx.y * 4 + wave) * RPW + part;
+    if (R_raw - part >= p.rows) {                          // the whole wave is past the last row
         if constexpr (NEW) {
             ta_scatter_locate(p, b, g, sc);
             ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
@@ -525,20 +529,20 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
         return;
     }
     const bool live = R_raw < p.rows;
-    const int R = live ? R_raw : p.rows - 1;               // an odd last row: its idle partner half repeats it
+    const int R = live ? R_raw : p.rows - 1;               // past the last row: an idle part of the wave repeats it
     const int rg = R / p.rows_grp, r = R % p.rows_grp;
     const int node = R / p.G, h = g * p.G + R % p.G;
     const int64_t row0 = ta_ws_row(p, w_first + seg, rg, r);              // partial k of this row: row0 + k*pstride
     const int64_t pstride = (int64_t)p.n_rg * p.rows_grp;
     constexpr int EB = HP ? 2 : 4;                         // bytes per element of a partial output
     constexpr int LS = HP ? 2 : 1;                         // floats per row of ws_lse: {log-sum-exp, scale} or the former
-    const char *o0 = (const char *)p.ws_o + (row0 * 128 + 4 * hl) * EB;
-    const int64_t ostride = pstride * 128 * EB;
+    const char *o0 = (const char *)p.ws_o + (row0 * D + 4 * hl) * EB;
+    const int64_t ostride = pstride * D * EB;
 
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float lse2;
-    if (n_parts <= 32) {
-        // lane k of the half owns partial k
+    if (n_parts <= LPR) {
+        // lane k of the row's owns partial k
         float lk = -INFINITY, sk = 1.f;                                   // sk: scale of the partial's 16-bit values
         if (hl < n_parts) {
             if constexpr (HP) {
@@ -551,13 +555,13 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
         }
         if constexpr (NEW)
             ta_scatter_locate(p, b, g, sc);
-        const bool nan_seen = ta_half_max(lk != lk ? 1.f : 0.f) > 0.f;
-        const float mx = ta_half_max(lk);
+        const bool nan_seen = ta_part_max<LPR>(lk != lk ? 1.f : 0.f) > 0.f;
+        const float mx = ta_part_max<LPR>(lk);
         const float ek = exp2f(lk - mx);                                  // 0 for the idle lanes
-        const float den = ta_half_sum(ek);
+        const float den = ta_part_sum<LPR>(ek);
         lse2 = nan_seen ? QNAN : mx + log2f(den);
         const float wk = nan_seen ? QNAN : ek / den * sk;
-        const int src0 = lane & 32;
+        const int src0 = lane - hl;
         int k = 0;
         for (; k + 4 <= n_parts; k += 4) {
             typename ta_part_raw<HP>::type v[4];
@@ -574,7 +578,7 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
                 acc.w = fmaf(wgt, x.w, acc.w);
             }
         }
-        // The tail's loads go out together as well.  (Both halves of a wave merge rows of the same list, so
+        // The tail's loads go out together as well.  (All rows of a wave belong to the same list, so
         // n_parts and with it every branch here is uniform over the wave.)
         typename ta_part_raw<HP>::type v[3];
 #pragma unroll
@@ -594,9 +598,9 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
     } else {
         if constexpr (NEW)
             ta_scatter_locate(p, b, g, sc);
-        // more partials than lanes in a half: two sweeps over the log-sum-exps, then one over the outputs
+        // more partials than lanes in a row's part: two sweeps over the log-sum-exps, then one over the outputs
         float mx = -INFINITY, bad = 0.f;
-        for (int q0 = 0; q0 < n_parts; q0 += 32) {
+        for (int q0 = 0; q0 < n_parts; q0 += LPR) {
             const int k = q0 + hl;
             if (k < n_parts) {
                 const float v = p.ws_lse[(row0 + k * pstride) * LS];
@@ -604,18 +608,18 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
                 mx = fmaxf(mx, v);
             }
         }
-        mx = ta_half_max(mx);
-        const bool nan_seen = ta_half_max(bad) > 0.f;
+        mx = ta_part_max<LPR>(mx);
+        const bool nan_seen = ta_part_max<LPR>(bad) > 0.f;
         float den = 0.f;
-        for (int q0 = 0; q0 < n_parts; q0 += 32) {
+        for (int q0 = 0; q0 < n_parts; q0 += LPR) {
             const int k = q0 + hl;
             if (k < n_parts)
                 den += exp2f(p.ws_lse[(row0 + k * pstride) * LS] - mx);
         }
-        den = ta_half_sum(den);
+        den = ta_part_sum<LPR>(den);
         lse2 = nan_seen ? QNAN : mx + log2f(den);
         for (int k = 0; k < n_parts; ++k) {
-            float wgt = exp2f(p.ws_lse[(row0 + k * pstride) * LS] - lse2);        // same address in every lane of the half
+            float wgt = exp2f(p.ws_lse[(row0 + k * pstride) * LS] - lse2);        // same address in all of the row's lanes
             if constexpr (HP)
                 wgt *= p.ws_lse[(row0 + k * pstride) * LS + 1];
             const float4 v = ta_part_f4(ta_part_load4<HP>(o0 + k * ostride));
@@ -643,19 +647,20 @@ __global__ __launch_bounds__(256) void ta_merge128_kernel(TAParams p)
 }
 
 // Many partials per list (few lists cut over the whole chip: the batch-size-one regime): one workgroup per output row,
-// its eight half-waves take every eighth partial each, up to MW_FLIGHT loads in flight per lane, and their sums meet
+// its eight half-waves (head_dim 64: sixteen quarter-waves) take every eighth (sixteenth) partial each, up to MW_FLIGHT loads in flight per lane, and their sums meet
 // in LDS.  The loads of the first round are issued before the log-sum-exps are reduced, so the two latencies overlap.
 // (With the kernel above a half-wave walks all partials of its row alone: 256 partials took 38 us, now about 7.)
-constexpr int MW_HALVES = 8, MW_FLIGHT = 8;
+constexpr int MW_FLIGHT = 8;
 
-template <bool NEW, bool HP>
-__global__ __launch_bounds__(256) void ta_merge128_wide_kernel(TAParams p)
+template <int D, bool NEW, bool HP>
+__global__ __launch_bounds__(256) void ta_merge_wide_kernel(TAParams p)
 {
+    constexpr int LPR = D / 4, MW_PARTS = 256 / LPR;      // lanes per partial, partials at a time
     __shared__ float red[8];
-    __shared__ float4 part[MW_HALVES][32];
+    __shared__ float4 part[MW_PARTS][LPR];
     const int seg = blockIdx.x, R = blockIdx.y;
     const int b = seg / p.Hkv, g = seg % p.Hkv;
-    const int tid = threadIdx.x, hw = tid >> 5, hl = tid & 31, wave = tid >> 6;
+    const int tid = threadIdx.x, hw = tid / LPR, hl = tid % LPR, wave = tid >> 6;
     const int w_first = p.ws_parts[2 * seg];                             // left by the KV pass
     const int n_parts = p.ws_parts[2 * seg + 1] - w_first + 1;
     const float LN2 = 0.6931471805599453f;
@@ -669,15 +674,15 @@ __global__ __launch_bounds__(256) void ta_merge128_wide_kernel(TAParams p)
     const int64_t pstride = (int64_t)p.n_rg * p.rows_grp;
     constexpr int EB = HP ? 2 : 4;                         // bytes per element of a partial output
     constexpr int LS = HP ? 2 : 1;                         // floats per row of ws_lse: {log-sum-exp, scale} or the former
-    const char *o0 = (const char *)p.ws_o + (row0 * 128 + 4 * hl) * EB;
-    const int64_t ostride = pstride * 128 * EB;
+    const char *o0 = (const char *)p.ws_o + (row0 * D + 4 * hl) * EB;
+    const int64_t ostride = pstride * D * EB;
 
-    // first round of this half-wave's partials (hw, hw + 8, ...): outputs and their log-sum-exps
+    // first round of this part's partials (hw, hw + MW_PARTS, ...): outputs and their log-sum-exps
     typename ta_part_raw<HP>::type v[MW_FLIGHT];
     float2 ls[MW_FLIGHT];                                  // log-sum-exps and (16-bit partials: one 8-byte load) scales
 #pragma unroll
     for (int u = 0; u < MW_FLIGHT; ++u) {
-        const int k = hw + MW_HALVES * u;
+        const int k = hw + MW_PARTS * u;
         if (k < n_parts) {
             v[u] = ta_part_load4<HP>(o0 + k * ostride);
             if constexpr (HP)
@@ -718,11 +723,11 @@ __global__ __launch_bounds__(256) void ta_merge128_wide_kernel(TAParams p)
     const float lse2 = nan_seen ? QNAN : mx + log2f(den);
 
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k0 = hw; k0 < n_parts; k0 += MW_HALVES * MW_FLIGHT) {
+    for (int k0 = hw; k0 < n_parts; k0 += MW_PARTS * MW_FLIGHT) {
         if (k0 != hw) {
 #pragma unroll
             for (int u = 0; u < MW_FLIGHT; ++u) {
-                const int k = k0 + MW_HALVES * u;
+                const int k = k0 + MW_PARTS * u;
                 if (k < n_parts) {
                     v[u] = ta_part_load4<HP>(o0 + k * ostride);
                     if constexpr (HP)
@@ -734,7 +739,7 @@ __global__ __launch_bounds__(256) void ta_merge128_wide_kernel(TAParams p)
         }
 #pragma unroll
         for (int u = 0; u < MW_FLIGHT; ++u) {
-            if (k0 + MW_HALVES * u < n_parts) {
+            if (k0 + MW_PARTS * u < n_parts) {
                 const float wgt = nan_seen ? QNAN : exp2f(ls[u].x - lse2) * (HP ? ls[u].y : 1.f);
                 const float4 x = ta_part_f4(v[u]);
                 acc.x = fmaf(wgt, x.x, acc.x);
@@ -748,11 +753,11 @@ __global__ __launch_bounds__(256) void ta_merge128_wide_kernel(TAParams p)
     if constexpr (NEW)
         ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
     __syncthreads();
-    if (tid >= 32)
+    if (tid >= LPR)
         return;
     acc = part[0][hl];
 #pragma unroll
-    for (int k = 1; k < MW_HALVES; ++k) {
+    for (int k = 1; k < MW_PARTS; ++k) {
         const float4 x = part[k][hl];
         acc.x += x.x;
         acc.y += x.y;
@@ -778,24 +783,31 @@ hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream)
     const int rows_wg = ta_host_merge_rows(p);             // the plan chose the kernel (p.merge_kind)
     dim3 grid(p.B * p.Hkv, (p.rows + rows_wg - 1) / rows_wg);
     // (the instances with the write-back folded in also copy the tree tokens' K/V into the caches)
-    if (p.merge_kind == TA_MERGE_D128_WIDE) {
-        if (p.kn && p.part_q15)
-            hipLaunchKernelGGL((ta_merge128_wide_kernel<true, true>), grid, dim3(256), smem, stream, p);
-        else if (p.kn)
-            hipLaunchKernelGGL((ta_merge128_wide_kernel<true, false>), grid, dim3(256), smem, stream, p);
-        else if (p.part_q15)
-            hipLaunchKernelGGL((ta_merge128_wide_kernel<false, true>), grid, dim3(256), smem, stream, p);
+    if (p.merge_kind == TA_MERGE_WIDE || p.merge_kind == TA_MERGE_ROW) {
+        auto launch = [&](auto d, auto fold, auto hp) {
+            constexpr int D = decltype(d)::value;
+            constexpr bool NEW = decltype(fold)::value, HP = decltype(hp)::value;
+            if (p.merge_kind == TA_MERGE_WIDE)
+                hipLaunchKernelGGL((ta_merge_wide_kernel<D, NEW, HP>), grid, dim3(256), smem, stream, p);
+            else
+                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP>), grid, dim3(256), smem, stream, p);
+        };
+        auto with = [&](auto d) {
+            if (p.kn && p.part_q15)
+                launch(d, std::true_type{}, std::true_type{});
+            else if (p.kn)
+                launch(d, std::true_type{}, std::false_type{});
+            else if (p.part_q15)
+                launch(d, std::false_type{}, std::true_type{});
+            else
+                launch(d, std::false_type{}, std::false_type{});
+        };
+        if (p.D == 128)
+            with(std::integral_constant<int, 128>{});
+        else if (p.D == 64)
+            with(std::integral_constant<int, 64>{});
         else
-            hipLaunchKernelGGL((ta_merge128_wide_kernel<false, false>), grid, dim3(256), smem, stream, p);
-    } else if (p.merge_kind == TA_MERGE_D128) {
-        if (p.kn && p.part_q15)
-            hipLaunchKernelGGL((ta_merge128_kernel<true, true>), grid, dim3(256), smem, stream, p);
-        else if (p.kn)
-            hipLaunchKernelGGL((ta_merge128_kernel<true, false>), grid, dim3(256), smem, stream, p);
-        else if (p.part_q15)
-            hipLaunchKernelGGL((ta_merge128_kernel<false, true>), grid, dim3(256), smem, stream, p);
-        else
-            hipLaunchKernelGGL((ta_merge128_kernel<false, false>), grid, dim3(256), smem, stream, p);
+            return hipErrorInvalidValue;
     } else {
         if (p.kn)
             hipLaunchKernelGGL(ta_merge_kernel<true>, grid, dim3(GEN_THREADS), smem, stream, p);

@@ -110,7 +110,7 @@ const TADispatchRow *ta_host_dispatch_table(int *n_rows)
 
 int ta_host_merge_rows(const TAParams &p)
 {
-    return p.merge_kind == TA_MERGE_D128_WIDE ? 1 : p.merge_kind == TA_MERGE_D128 ? TA_MERGE128_ROWS : TA_MERGE_ROWS;
+    return p.merge_kind == TA_MERGE_WIDE ? 1 : p.merge_kind == TA_MERGE_ROW ? 1024 / p.D : TA_MERGE_ROWS;
 }
 
 // Everything that can be decided from the descriptors alone.
@@ -369,18 +369,18 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // merge kernel: partials per list the schedule produces on average = the KV pass's workgroups spread over the
     // lists, plus the one boundary each list shares with its neighbour
     const bool out_aligned = ((uintptr_t)out->data % 16) == 0 && p.o_sb % 4 == 0 && p.o_st % 4 == 0 && p.o_sh % 4 == 0;
-    pl.merge_kind = TA_MERGE_GENERAL;
-    if (D == 128 && out_aligned) {
+    p.merge_kind = TA_MERGE_GENERAL;
+    if ((D == 128 || D == 64) && out_aligned) {
         const int64_t l1 = lists > 0 ? lists : 1;
         const int64_t parts = (pl.n_wg + l1 - 1) / l1 + 1;
         const bool wide = dr.wide_from_parts > 0 && parts >= dr.wide_from_parts && lists * p.rows <= dr.wide_max_rows;
-        pl.merge_kind = wide ? TA_MERGE_D128_WIDE : TA_MERGE_D128;
+        p.merge_kind = wide ? TA_MERGE_WIDE : TA_MERGE_ROW;
     }
     // Partial format of the matrix-core kernels: 16-bit fixed point with a scale per row, which halves what the KV pass
     // writes (C3 128.6 -> 125.0 us, p4 215.1 -> 210.2, C2 26.5 -> 24.1; batch-one shapes 1 to 2 us of 35).  The scalar
     // kernel, whose inputs may be fp32, keeps fp32 partials.
     p.part_q15 = kernel == TA_KERNEL_MFMA ? 1 : 0;
-    p.merge_kind = pl.merge_kind;
+    pl.merge_kind = D == 128 ? p.merge_kind : TA_MERGE_GENERAL;     // (what a plan says is which one of head_dim 128)
     const int mrows = ta_host_merge_rows(p);
     pl.merge_wgs = (int)lists * ((p.rows + mrows - 1) / mrows);
 

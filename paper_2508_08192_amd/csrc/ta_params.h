@@ -11,7 +11,6 @@
 #define TA_WAVE 64
 #define TA_TILE 64            // KV tokens per tile of the KV pass (the tree tokens form one more tile)
 #define TA_MERGE_ROWS 4       // rows per workgroup of the general merge kernel (one per wave)
-#define TA_MERGE128_ROWS 8    // rows per workgroup of the head_dim-128 merge kernel (half a wave per row)
 #define TA_ROW_GROUP 256      // rows (tree nodes x query heads of one KV head) one workgroup keeps
 #define TA_F32_ROWS 32        // rows one workgroup of the fp32 matrix-core kernel keeps
 #define TA_SP_MAX_BATCH 1900  // requests whose schedule fits beside the pipelined kernel's tile rings in LDS
@@ -89,8 +88,8 @@ struct TACompact {
 
 // Which merge kernel combines the partial results.
 #define TA_MERGE_GENERAL 0    // one wave per output row, any head_dim and alignment
-#define TA_MERGE_D128 1       // head_dim 128, aligned outputs: half a wave per row, eight rows per workgroup
-#define TA_MERGE_D128_WIDE 2  // the same shapes when few lists are cut into many shares: one workgroup per row
+#define TA_MERGE_ROW 1        // head_dim 128 or 64, aligned outputs: head_dim / 4 lanes per row, 1024 / head_dim rows per workgroup
+#define TA_MERGE_WIDE 2       // the same shapes when few lists are cut into many shares: one workgroup per row
 
 // ---------------------------------------------------------------------------------------------
 // Dispatch table (section 3.4, "Attention kernel": the kernel and its split are chosen by a heuristic on batch size,
