@@ -157,7 +157,9 @@ __device__ __forceinline__ int ta_find_request(const TAParams &p, const int *cum
 // The KV pass tells the merge pass which workgroups hold partial results of list (b, g): the owner of the list's
 // first tile and the owner of its last one say so (row group 0 speaks for all).  Saves the merge pass rebuilding
 // the schedule from the prefix lengths in each of its many small workgroups.
-__device__ __forceinline__ void ta_note_owner(const TAParams &p, int b, int g, int w, int j0, int j1, int n_b)
+// done: the owner of the whole list writes its outputs itself and leaves the merge pass no partial results.
+__device__ __forceinline__ void ta_note_owner(const TAParams &p, int b, int g, int w, int j0, int j1, int n_b,
+                                              bool done = false)
 {
     if (threadIdx.x == 0 && blockIdx.y == 0) {
         int wv = w;
@@ -166,7 +168,7 @@ __device__ __forceinline__ void ta_note_owner(const TAParams &p, int b, int g, i
         if (j0 == 0)
             p.ws_parts[2 * (b * p.Hkv + g)] = wv;
         if (j1 == n_b)
-            p.ws_parts[2 * (b * p.Hkv + g) + 1] = wv;
+            p.ws_parts[2 * (b * p.Hkv + g) + 1] = done ? wv - 1 : wv;
     }
 }
 

@@ -520,6 +520,13 @@ __global__ __launch_bounds__(256) void ta_merge_row_kernel(TAParams p)
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
     if constexpr (NEW)
         ta_scatter_load(p, b, g, blockIdx.y, gridDim.y, sc);
+    if (n_parts <= 0) {                                    // the KV pass has written this list's outputs
+        if constexpr (NEW) {
+            ta_scatter_locate(p, b, g, sc);
+            ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
+        }
+        return;
+    }
     const int R_raw = (blockIdx.y * 4 + wave) * RPW + part;
     if (R_raw - part >= p.rows) {                          // the whole wave is past the last row
         if constexpr (NEW) {
@@ -668,6 +675,13 @@ __global__ __launch_bounds__(256) void ta_merge_wide_kernel(TAParams p)
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
     if constexpr (NEW)
         ta_scatter_load(p, b, g, blockIdx.y, gridDim.y, sc);
+    if (n_parts <= 0) {                                    // the KV pass has written this list's outputs
+        if constexpr (NEW) {
+            ta_scatter_locate(p, b, g, sc);
+            ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
+        }
+        return;
+    }
     const int rg = R / p.rows_grp, r = R % p.rows_grp;
     const int node = R / p.G, h = g * p.G + R % p.G;
     const int64_t row0 = ta_ws_row(p, w_first + seg, rg, r);              // partial k of this row: row0 + k*pstride

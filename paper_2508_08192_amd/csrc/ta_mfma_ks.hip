@@ -111,7 +111,9 @@ static size_t ks_smem(int B)
            (B <= TA_WAVE ? 0 : sizeof(int) * (B + 2 + (B <= KS_LENS ? 2 * B : 0)));
 }
 
-template <int DH, int RB, int NW, int OCC>
+// DIRECT: the outputs of a list that lies in one share are written here (an instance of its own: calls without many lists
+// are 1 % slower with that code in the kernel)
+template <int DH, int RB, int NW, int OCC, bool DIRECT>
 __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAParams p)
 {
     using C = KsShape<DH, RB, NW, OCC>;
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
     // ---- the current item: a list (b, g), its tiles [j0, j1), i.e. the prefix tokens [max(lo, S), hi), walked in runs of
     // 32 from lo, and the T tree tokens; run u belongs to wave u % NW
     int b = -1, g = 0, slot = 0, L = 0, S = 0, lo = 0, hi = 0, n_pre = 0, n_sub = 0, n_full = 0, bad = 0;
-    bool has_tree = false;
+    bool has_tree = false, whole = false;                  // whole: a list that lies in this share alone
     uint4 qf[RB][NKK];
     int pg = 0, pg_first = 0, pg_last = 0, parent = 0;     // pages of full runs, of the first and of the last run; tree
     unsigned long long gmask = 0;
@@ -233,7 +235,8 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             }
             t = seg_start + (j1 == n_b ? n_u : j1);
             slot = w + b * p.Hkv + g;
-            ta_note_owner(p, b, g, w, j0, j1, n_b);
+            whole = DIRECT && j0 == 0 && j1 == n_b;
+            ta_note_owner(p, b, g, w, j0, j1, n_b, whole);
             if (in_regs) {
                 L = __builtin_amdgcn_readlane(s_len, b);
                 S = __builtin_amdgcn_readlane(s_start, b);
@@ -598,7 +601,8 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
                     }
             }
         }
-        const int slot_e = slot;
+        const int slot_e = slot, b_e = b, g_e = g;
+        const bool whole_e = whole;
         more = next_item();                                    // its requests are on their way during the rest
         ks_lds_barrier();
         int any_bad = 0;
@@ -648,7 +652,22 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             }
             float scale, to_q;
             ta_q15_scale(amax, nan_seen > 0.f, scale, to_q);
-            if (row < rows_here) {
+            const float lse2 = any_bad ? __uint_as_float(0x7fc00000u) : big + log2f(l_tot);
+            if (DIRECT && whole_e) {
+                // no merge: the rows go out as they are (a NaN spoils its row, as it does there)
+                if (row < rows_here) {
+                    const int R = row0 + row, node = (int)__umulhi((uint32_t)R << 8, p.g_magic), h = g_e * p.G + R - node * p.G;
+                    const bool nan = any_bad || nan_seen > 0.f || lse2 != lse2;
+                    uint32_t *dst = (uint32_t *)((uint16_t *)p.out + (int64_t)b_e * p.o_sb + (int64_t)node * p.o_st +
+                                                 (int64_t)h * p.o_sh + 4 * c0);
+#pragma unroll
+                    for (int q = 0; q < CPT / 4; ++q)
+                        *(uint2 *)(dst + 2 * q) = nan ? make_uint2(0x7fc07fc0u, 0x7fc07fc0u)
+                                                      : make_uint2(ks_pack(acc[4 * q], acc[4 * q + 1]), ks_pack(acc[4 * q + 2], acc[4 * q + 3]));
+                    if (p.lse && x_e % TPR == 0)
+                        p.lse[(int64_t)b_e * p.lse_sb + (int64_t)h * p.lse_sh + (int64_t)node * p.lse_st] = lse2 * 0.6931471805599453f;
+                }
+            } else if (row < rows_here) {
                 const int64_t wrow = ta_ws_row(p, slot_e, 0, row0 + row);
                 uint32_t *dst = (uint32_t *)(ta_part_row(p, wrow) + 8 * c0);
 #pragma unroll
@@ -658,7 +677,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
                 // (a NaN log-sum-exp poisons the row in the merge)
                 if (x_e % TPR == 0)
                     *(float2 *)&p.ws_lse[2 * wrow] =
-                        make_float2(any_bad ? __uint_as_float(0x7fc00000u) : big + log2f(l_tot), scale);
+                        make_float2(lse2, scale);
             }
             if (any_bad && x_e == 0)
                 ta_raise(p, any_bad);
@@ -667,7 +686,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
     }
 }
 
-template <int DH, int RB, int NW, int OCC>
+template <int DH, int RB, int NW, int OCC, bool DIRECT>
 static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
 {
     const size_t smem = ks_smem<DH, RB, NW, OCC>(p.B);
@@ -675,13 +694,13 @@ static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
         return hipErrorInvalidValue;
     static bool attr_set[64] = {};      // per device and instance; setting it twice is harmless
     if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void *)ta_mfma_ks_kernel<DH, RB, NW, OCC>,
+        hipError_t e = hipFuncSetAttribute((const void *)ta_mfma_ks_kernel<DH, RB, NW, OCC, DIRECT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess)
             return e;
         attr_set[dev] = true;
     }
-    hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC>), dim3(p.n_wg, (p.rows + 32 * RB - 1) / (32 * RB)), dim3(64 * NW), smem,
+    hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC, DIRECT>), dim3(p.n_wg, (p.rows + 32 * RB - 1) / (32 * RB)), dim3(64 * NW), smem,
                        stream, p);
     return hipGetLastError();
 }
@@ -692,7 +711,9 @@ hipError_t ta_launch_mfma_ks(const TAParams &p, hipStream_t stream, int dev)
         return hipErrorInvalidDevice;
     if ((p.ks_rows != 32 && p.ks_rows != 64) || p.rows_grp % p.ks_rows != 0 || !p.part_q15 || p.ls != 2)
         return hipErrorInvalidValue;
-    if (p.D == 64)
-        return p.ks_rows == 32 ? launch_ks<64, 1, 8, 1>(p, stream, dev) : launch_ks<64, 2, 8, 1>(p, stream, dev);
-    return p.ks_rows == 32 ? launch_ks<128, 1, 8, 1>(p, stream, dev) : hipErrorInvalidValue;
+    if (p.D == 128 && p.ks_rows == 32)
+        return p.direct ? launch_ks<128, 1, 8, 1, true>(p, stream, dev) : launch_ks<128, 1, 8, 1, false>(p, stream, dev);
+    if (p.D != 64 || p.direct)
+        return hipErrorInvalidValue;
+    return p.ks_rows == 32 ? launch_ks<64, 1, 8, 1, false>(p, stream, dev) : launch_ks<64, 2, 8, 1, false>(p, stream, dev);
 }

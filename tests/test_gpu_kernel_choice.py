@@ -75,3 +75,49 @@ def test_parts_of_a_row_group_with_every_option():
         # both kernels take the probabilities as bf16 (2^-9 each) and round the result to bf16 (2^-9): 1e-2 as elsewhere
         assert (o0[b] - o1[b]).abs().max() <= 1e-2 * o1[b].abs().max() and (l0[b] - l1[b]).abs().max() <= 1e-3
     assert torch.equal(k0, k1) and torch.equal(v0, v1)
+
+
+@pytest.mark.parametrize("T,Hq,Hkv,ps", [(8, 12, 3, 16), (23, 4, 4, 0), (50, 4, 4, 32)])
+def test_many_lists_are_finished_without_a_merge(T, Hq, Hkv, ps):
+    """At least two lists per workgroup: the ones that lie whole in a share are written by the KV pass, the others merged,
+    with the write-back folded in, a strided output, bad requests among them and no log-sum-exp asked for."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    B = 200
+    rng = np.random.default_rng(T)
+    w = W.make_workload("many", B=B, T=T, Hq=Hq, Hkv=Hkv, D=128, seq_lens=rng.integers(0, 200, size=B),
+                        trees=W.random_tree(T, 5, rng), page_size=ps or 64, seed=T, paged=ps > 0)
+    w.seq_lens[5] = 900 if ps == 0 else w.seq_lens[5]
+    w = W.make_workload("many", B=B, T=T, Hq=Hq, Hkv=Hkv, D=128, seq_lens=w.seq_lens, trees=w.tree_parent, page_size=ps or 64,
+                        seed=T, paged=ps > 0)
+    d = to_device(w)
+    ref, ref_lse = run_oracle(w)
+    d["out"] = torch.zeros((B, T, Hq, 132), dtype=d["q"].dtype, device="cuda")[..., 4:132] if T == 8 else d["out"]
+    print("kernel choice: many lists T=%d" % T, flush=True)
+    got, lse = run_hip(w, d)
+    assert_parity(got, lse, ref, ref_lse, "bf16", "many lists T=%d" % T)
+    for _ in range(3):                                  # repeated calls leave the same
+        again, lse2 = run_hip(w, d)
+        assert np.array_equal(again, got) and np.array_equal(lse2, lse)
+    ta.tree_attn_fwd(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"], None)
+    torch.cuda.synchronize()
+    assert np.array_equal(d["out"].float().cpu().numpy().astype(np.float64), got)
+    d["seq_lens"][7] = -1
+    ta.tree_attn_last_status()
+    bad, bad_lse = run_hip(w, d)
+    assert ta.tree_attn_last_status() == ta.TA_STATUS_BAD_SEQLEN
+    assert np.isnan(bad[7]).all() and np.isnan(bad_lse[7]).all()
+    keep = [b for b in range(B) if b != 7]
+    assert_parity(bad[keep], bad_lse[keep], ref[keep], ref_lse[keep], "bf16", "beside a bad request")
+    d["seq_lens"][7] = int(w.seq_lens[7])
+    k_new = torch.randn(B, T, Hkv, 128, device="cuda").bfloat16()
+    v_new = torch.randn(B, T, Hkv, 128, device="cuda").bfloat16()
+    args = (d["page_table"], d["seq_lens"], d["tree_parent"])
+    k1, v1 = d["k_cache"].clone(), d["v_cache"].clone()
+    o1, l1 = torch.zeros_like(d["q"]), torch.zeros_like(d["lse"])
+    ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], *args, o1, l1, k_new=k_new, v_new=v_new)
+    ta.tree_attn_append(k_new, v_new, k1, v1, d["page_table"], d["seq_lens"])
+    o2, l2 = torch.zeros_like(o1), torch.zeros_like(l1)
+    ta.tree_attn_fwd(d["q"], k1, v1, *args, o2, l2)
+    torch.cuda.synchronize()
+    assert torch.equal(k1, d["k_cache"]) and torch.equal(v1, d["v_cache"]) and torch.equal(o1, o2) and torch.equal(l1, l2)
