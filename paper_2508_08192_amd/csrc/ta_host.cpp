@@ -271,7 +271,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // key-split:
     //   one block: 16 lists of 8000 tokens 26.1 and 22.0, 32 of 2000 22.1 and 17.1, 64 of 32000 179 and 174; one list of
     //     500 to 2000 tokens, where a share is a single tile, two of the eight waves' work, 14.4 and 15.7, of 5000 equal;
-    //   two to four: blocks times tiles, per compute unit, 3: 17.2 and 18.0, 4: 22.4 and 18.2, 8: 23.6 and 20.2, 16: 27.3
+    //   two to four: blocks times tiles, per compute unit, 3: 17.2 and 18.0, 4: 19.9 and 16.9, 8: 23.6 and 20.2, 16: 27.3
     //     and 26.3, 30: 36.6 and 40.1 (one list of 8000 tokens, where it is 1, 18.6 and 17.4);
     //   five and more, whose tiles cost the pipelined kernel's eight waves more: 8: 25.6 and 17.6, 31: 35.5 and 31.1, 125:
     //     58.6 and 92.9.
@@ -280,10 +280,10 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // 32.6, 64 a row 24.5 and 21.0.
     const int slices = (p.rows + 31) / 32;
     const int64_t ks_wg = key_split_workgroups(num_cus, slices);
+    const bool ks_even = ks_wg >= 2 * lists || ks_wg == lists;
     const bool ks_fits = slices == 1 ? lists > 1 || tiles_cap > 64
-                                     : tiles_cap * slices <= (int64_t)(slices > 4 ? 32 : 16) * num_cus &&
-                                           (slices > 4 || lists == 1 || 2 * tiles_cap * slices > 7 * num_cus) &&
-                                           (ks_wg >= 2 * lists || ks_wg == lists);
+                                     : tiles_cap * slices <= (int64_t)(slices > 4 ? 32 : 16) * num_cus && ks_even &&
+                                           (slices > 4 || lists == 1 || 2 * tiles_cap * slices > 7 * num_cus);
     const bool ks = kernel == TA_KERNEL_MFMA && (basic || (auto_kernel && ks_fits));
     p.basic = ks;
     p.f32_mfma = f32_mfma;
@@ -330,7 +330,9 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     pl.kernel = kernel;
     const int family = kernel == TA_KERNEL_MFMA ? (basic ? TA_KERNEL_MFMA_BASIC : TA_KERNEL_MFMA) : TA_KERNEL_GENERIC;
     if (kernel == TA_KERNEL_MFMA) {
-        p.ks_rows = D == 64 && p.rows > 32 ? 64 : 32;
+        // head_dim 64 can keep 64 rows; 32 are faster where the same few tiles fall on a compute unit (blocks times tiles 1
+        // to 10: 14.5 to 19.4 us a call and 13.3 to 16.3, 16: 19.0 and 18.6, 47: 28.4 and 31.1)
+        p.ks_rows = D == 64 && slices > 1 && !(tiles_cap * slices <= (int64_t)16 * num_cus && ks_even) ? 64 : 32;
         pl.rows_grp = ks && (basic || slices <= 4) ? p.ks_rows : mfma_rows_group(p.rows);
         pl.threads = 512;
     } else if (f32_mfma) {

@@ -121,3 +121,18 @@ def test_many_lists_are_finished_without_a_merge(T, Hq, Hkv, ps):
     ta.tree_attn_fwd(d["q"], k1, v1, *args, o2, l2)
     torch.cuda.synchronize()
     assert torch.equal(k1, d["k_cache"]) and torch.equal(v1, d["v_cache"]) and torch.equal(o1, o2) and torch.equal(l1, l2)
+
+
+@pytest.mark.parametrize("T,Hq,L", [(33, 1, 500), (64, 2, 4000), (50, 5, 130), (64, 8, 20000)])
+def test_head_dim_64_with_32_and_64_rows_a_workgroup(T, Hq, L):
+    """Small batches of head_dim 64 keep 32 rows per workgroup whatever their number, larger ones 64."""
+    lens = [L, L // 7]
+    w = W.make_workload("d64", B=2, T=T, Hq=Hq, Hkv=1, D=64, seq_lens=lens, trees=W.chain_tree(T), page_size=64, seed=T)
+    d = to_device(w)
+    blocks = -(-T * Hq // 32)
+    small = 2 * (-(-L // 64) + 1) * blocks <= 16 * 256
+    assert _plan(w, d)["rows_per_group"] == (32 if small else 64)
+    print("kernel choice: head_dim 64, T=%d Hq=%d L=%d" % (T, Hq, L), flush=True)
+    got, lse = run_hip(w, d)
+    ref, ref_lse = run_oracle(w)
+    assert_parity(got, lse, ref, ref_lse, "bf16", "T=%d Hq=%d L=%d" % (T, Hq, L))
