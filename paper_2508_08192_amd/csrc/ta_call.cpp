@@ -1,9 +1,9 @@
 // The way from Python into libtreeattn for calls that pass plain torch tensors: an extension module that writes the
 // descriptors of a call and makes it.  A step of one request keeps the GPU busy for some 15 to 20 us, and the same
-// descriptors put together with ctypes, field by field, took the host 22 us a call (57 for write-back, attention and
-// bookkeeping); here they take 11.5 (23.8), the launches
-// included.  What is not of the simple form -- a subclass, an object that only describes a
-// tensor, an option given in an unusual type -- is left to the caller: the function then returns None and has done nothing.
+// descriptors put together with ctypes, field by field, took the host 22.5 us a call (57 for write-back, attention and
+// bookkeeping); here they take 11.5 (24), the launches included.  What is not of the simple form -- a subclass, an object
+// that only describes a tensor, an option given in an unusual type -- is left to the caller: the function then returns None
+// and has done nothing.
 //
 // Only attributes that any Python code could read are used (shape, stride(), dtype, data_ptr()), so the module is tied to
 // no version of torch.

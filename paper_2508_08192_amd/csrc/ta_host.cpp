@@ -55,9 +55,8 @@ int mfma_rows_group(int rows)
 // The pipelined matrix-core kernel runs one workgroup per compute unit (its tile rings fill the LDS).  A partial
 // result costs rows * D * 4 bytes written and read again against TA_TILE * D * 4 bytes per tile of keys and values,
 // hence the longer smallest shares of the larger row groups; the fixed work of entering a list is worth about eight
-// tiles' time there, and seven in the key-split kernel (its family is MFMA_BASIC; head_dim 64, L 730..12152 with 40 lists:
-// 21.8 us with a cost of 3, 19.8 with 8; one list of 14265 tokens 14.6 and 12.3), which keeps row groups of 32 or 64
-// rows; nothing for the scalar one.  With few lists cut over the
+// tiles' time there, and seven to eight in the key-split kernel (head_dim 64, L 730..12152 with 40 lists: 21.8 us with a
+// cost of 3, 19.8 with 8; one list of 14265 tokens 14.6 and 12.3); nothing for the scalar one.  With few lists cut over the
 // whole chip (batch size one) the merge becomes a latency problem and one workgroup per output row is faster from
 // 13 partials per list on, while the batch has at most 1024 output rows.
 // A single list counts less fixed work: what it adds mostly keeps workgroups idle (8000 tokens, 32 rows: 17.9 us a call
@@ -272,7 +271,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     //   one block: 16 lists of 8000 tokens 26.1 and 22.0, 32 of 2000 22.1 and 17.1, 64 of 32000 179 and 174; one list of
     //     500 to 2000 tokens, where a share is a single tile, two of the eight waves' work, 14.4 and 15.7, of 5000 equal;
     //   two to four: blocks times tiles, per compute unit, 3: 17.2 and 18.0, 4: 19.9 and 16.9, 8: 23.6 and 20.2, 16: 27.3
-    //     and 26.3, 30: 36.6 and 40.1 (one list of 8000 tokens, where it is 1, 18.6 and 17.4);
+    //     and 26.3, 30: 36.6 and 40.1; one list, 1: 18.6 and 17.4, 16: 30.4 and 26.3, 31: 34.3 and 33.4;
     //   five and more, whose tiles cost the pipelined kernel's eight waves more: 8: 25.6 and 17.6, 31: 35.5 and 31.1, 125:
     //     58.6 and 92.9.
     // Tiles are counted from what the page table can hold.  With more lists than workgroups in a grid row, or hardly fewer,
@@ -282,7 +281,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     const int64_t ks_wg = key_split_workgroups(num_cus, slices);
     const bool ks_even = ks_wg >= 2 * lists || ks_wg == lists;
     const bool ks_fits = slices == 1 ? lists > 1 || tiles_cap > 64
-                                     : tiles_cap * slices <= (int64_t)(slices > 4 ? 32 : 16) * num_cus && ks_even &&
+                                     : tiles_cap * slices <= (int64_t)(slices > 4 || lists == 1 ? 32 : 16) * num_cus && ks_even &&
                                            (slices > 4 || lists == 1 || 2 * tiles_cap * slices > 7 * num_cus);
     const bool ks = kernel == TA_KERNEL_MFMA && (basic || (auto_kernel && ks_fits));
     p.basic = ks;
