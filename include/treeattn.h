@@ -240,14 +240,16 @@ int tree_attn_append(const ta_tensor *k_new, const ta_tensor *v_new, ta_tensor *
  * tree_attn_fwd (NULL = contiguous).  Every row is read before any is written, so sources and destinations may
  * overlap; nothing else in the caches changes.
  *
- *   accepted      TA_I32 [B, A], 1 <= A <= TA_MAX_TREE, unit inner stride; entries past n_b are not read
+ *   accepted      TA_I32 [B, A], 1 <= A <= TA_MAX_TREE, unit inner stride; entries past n_b are not read; a node may be
+ *                 named more than once, and n_b may exceed T
  *   n_accepted    TA_I32 [B]
  *   tree_size     T: node ids must lie in [0, T); 1 <= T <= TA_MAX_TREE
  *   seq_lens_out  TA_I32 [B] or NULL: receives L_b + n_b.  May be seq_lens itself (same pointer and stride), must not
  *                 overlap it otherwise.
  *
- * A request with L_b < 0, L_b + T beyond what its page-table row can address (TA_STATUS_BAD_SEQLEN), n_b outside
- * [0, A] or a node id outside [0, T) (TA_STATUS_BAD_PATH) is left alone and its length is passed through unchanged.
+ * A request with L_b < 0, L_b + max(T, n_b) beyond what its page-table row can address (TA_STATUS_BAD_SEQLEN), n_b outside
+ * [0, A] or a node id outside [0, T) (TA_STATUS_BAD_PATH), or a page outside the cache under those positions
+ * (TA_STATUS_BAD_PAGE) is left alone and its length is passed through unchanged.
  * One launch on `stream` (one workgroup per request), no allocation, no synchronisation.
  */
 int tree_attn_compact(ta_tensor *k_cache, ta_tensor *v_cache, const ta_tensor *page_table, const ta_tensor *seq_lens,

@@ -10,7 +10,8 @@ L_b + n.  Everything else in the cache keeps its bytes.
 All rows are read before any is written: a destination may be another accepted node's source.
 
 Readings the paper leaves open: the accepted nodes are given as node ids in path order (any ids in [0, T), repeats
-allowed); a request whose L_b, n or ids are out of range is left alone, its length unchanged, and reported.
+allowed, so that a path may be longer than the tree); a request whose L_b, n or ids are out of range, or whose rows would go
+beyond what its page table addresses, is left alone, its length unchanged, and reported.
 
 Nothing here is shared with the HIP path.  Pins: tests/test_compact_oracle_pins.py (attention over the rewound cache
 equals the tree attention of the path's nodes; a library gather on the contiguous layout; untouched bytes).
@@ -39,7 +40,7 @@ def kv_compact_oracle(k_cache, v_cache, page_table, seq_lens, accepted, n_accept
     for b in range(B):
         L, n = int(seq_lens[b]), int(n_accepted[b])
         ids = [int(x) for x in accepted[b, :max(0, min(n, A))]]
-        if L < 0 or L + T > capacity or n < 0 or n > A or any(i < 0 or i >= T for i in ids):
+        if L < 0 or L + max(T, n) > capacity or n < 0 or n > A or any(i < 0 or i >= T for i in ids):
             skipped.append(b)
             continue
         rows = []

@@ -912,32 +912,36 @@ template <typename P>
 __global__ __launch_bounds__(CP_THREADS) void ta_compact_kernel(TACompact c)
 {
     __shared__ int ids[TA_MAX_TREE];
-    __shared__ int64_t k_at[TA_MAX_TREE], v_at[TA_MAX_TREE];       // element offsets of tree token i's rows of KV head 0
+    __shared__ int64_t k_at[TA_MAX_TREE], v_at[TA_MAX_TREE];       // element offsets of position L + i's rows of KV head 0
     __shared__ int bad;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int L = c.seq_lens[(int64_t)b * c.sl_s];
     const int n = c.n_accepted[(int64_t)b * c.na_s];
-    const int id = tid < c.A ? c.accepted[(int64_t)b * c.acc_sb + tid] : 0;
-    const bool len_ok = L >= 0 && (int64_t)L + c.T <= (int64_t)c.capacity;
     const bool n_ok = n >= 0 && n <= c.A;
+    // the positions rows come from (L .. L+T-1) and go to (L .. L+n-1; a path may name a node twice and be longer than T)
+    const int span = n_ok ? max(c.T, n) : c.T;
+    const bool len_ok = L >= 0 && (int64_t)L + span <= (int64_t)c.capacity;
+    const bool has_id = n_ok && tid < n, has_pos = len_ok && tid < span;
+    int id = 0;
+    int64_t page = b, slot = (int64_t)L + tid;
+    if (tid < c.A)
+        id = c.accepted[(int64_t)b * c.acc_sb + tid];
+    if (has_pos && c.page_table) {
+        page = c.page_table[(int64_t)b * c.pt_sb + (L + tid) / c.ps];
+        slot = (L + tid) % c.ps;
+    }
     if (tid == 0)
         bad = 0;
     __syncthreads();
-    if (n_ok && tid < n) {
+    if (has_id) {
         ids[tid] = id;
         if (id < 0 || id >= c.T)
             atomicOr(&bad, 1);
     }
-    // every page a row may come from or go to (positions L .. L+T-1) must be a page of the cache
-    if (len_ok && tid < c.T) {
-        int64_t page = b, slot = L + tid;
-        if (c.page_table) {
-            page = c.page_table[(int64_t)b * c.pt_sb + (L + tid) / c.ps];
-            slot = (L + tid) % c.ps;
-            if (page < 0 || page >= c.n_pages) {
-                atomicOr(&bad, 2);
-                page = 0;
-            }
+    if (has_pos) {
+        if (c.page_table && (page < 0 || page >= c.n_pages)) {     // a page the cache does not have
+            atomicOr(&bad, 2);
+            page = 0;
         }
         k_at[tid] = page * c.k_sp + slot * c.k_ss;
         v_at[tid] = page * c.v_sp + slot * c.v_ss;

@@ -111,6 +111,19 @@ def test_only_the_accepted_positions_change_and_bad_requests_are_left_alone(orac
     assert _compact(w, acc, np.int32([1, 0, 0, 0]), oracle_fn)[3] == [0]
 
 
+def test_a_path_longer_than_the_tree(oracle_fn=None):
+    """n may exceed T when nodes repeat: a gather in the contiguous layout, and left alone where the rows do not fit."""
+    w = _problem(paged=False, ps=48, dtype="f32", seed=4, T=3, lens=(37, 44, 0))
+    acc = np.int32([[2, 0, 1, 1, 2, 0, 2]] * 3)
+    k2, v2, new_lens, skipped = (oracle_fn or KC.kv_compact_oracle)(w.k_cache, w.v_cache, None, w.seq_lens, acc, np.int32([7, 5, 4]), 3)
+    assert skipped == [1] and list(new_lens) == [44, 44, 4]            # request 1: 44 + 5 > 48, though 44 + 3 fits
+    for src, got in ((w.k_cache, k2), (w.v_cache, v2)):
+        exp = src.copy()
+        exp[0][:, 37:44] = src[0][:, 37 + acc[0]]
+        exp[2][:, 0:4] = src[2][:, acc[2, :4]]
+        assert np.array_equal(exp, got)
+
+
 # --- the pins must be able to see a mistake: each one planted in a copy of the oracle's source has to fail one of them
 MUTATIONS = [
     ("rows written while later sources are still unread", "rows.append((k_cache[page, :, slot, :].copy(), v_cache[page, :, slot, :].copy()))",

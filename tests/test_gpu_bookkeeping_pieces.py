@@ -70,3 +70,47 @@ def test_rows_move_whole_whatever_their_alignment(dtype, D, Hkv, T, ps, shift):
     assert np.array_equal(host(kc), k_ref.view(raw)) and np.array_equal(host(vc), v_ref.view(raw))
     assert np.array_equal(out.cpu().numpy(), lens_ref)
     assert ta.tree_attn_last_status() == 0
+
+
+@pytest.mark.parametrize("dtype,ps", [("bf16", 16), ("f32", 8), ("bf16", 0)])
+def test_a_path_longer_than_the_tree(dtype, ps):
+    """Nodes may repeat, so a path can be longer than the tree: its rows go to positions behind the tree's, through pages of
+    their own; where those do not exist, or the table ends before them, the request is left alone.  The entries behind a
+    path's end name no nodes at all."""
+    import torch
+    from oracle import kv_compact_oracle as KC
+    from paper_2508_08192_amd import treeattn as ta
+    B, T, A, Hkv, D = 5, 4, 40, 2, 64
+    lens = np.int32([3, 0, 41, 30, 50])
+    per = ps or 128
+    rng = np.random.default_rng(3)
+    table, n_pages = None, B
+    if ps:
+        n_pages = B * (96 // ps)
+        table = rng.permutation(n_pages).astype(np.int32).reshape(B, -1)
+        table[3, 48 // ps] = n_pages + 1                # request 3's positions from 48 on; its tree ends at 34
+    kc, bits = _pool((n_pages, Hkv, per, D), dtype, 0, 1)
+    vc, _ = _pool((n_pages, Hkv, per, D), dtype, 0, 2)
+    raw = np.int16 if dtype == "bf16" else np.int32
+
+    def host(t):
+        return t.view(bits).cpu().numpy().copy()
+    n = np.int32([40, 1, 6, 19, 40])
+    capacity = 96 if ps else per
+    lens[4] = capacity - T                              # room for the tree, none for the path
+    acc = rng.integers(0, T, size=(B, A)).astype(np.int32)
+    for b in range(B):
+        acc[b, n[b]:] = 1 << 30
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    healthy = [0, 1, 2] if ps else [0, 1, 2, 3]
+    k_ref, v_ref, lens_ref, skipped = KC.kv_compact_oracle(host(kc), host(vc), None if table is None else table, lens, acc,
+                                                           np.where(np.isin(np.arange(B), healthy), n, 0).astype(np.int32), T)
+    assert not skipped
+    ta.tree_attn_last_status()
+    print("path longer than the tree %s ps=%d" % (dtype, ps), flush=True)
+    ta.tree_attn_compact(kc, vc, None if table is None else torch.from_numpy(table).cuda(), torch.from_numpy(lens).cuda(),
+                         torch.from_numpy(acc).cuda(), torch.from_numpy(n).cuda(), T, seq_lens_out=out)
+    status = ta.tree_attn_last_status()
+    assert status == ta.TA_STATUS_BAD_SEQLEN | (ta.TA_STATUS_BAD_PAGE if ps else 0)
+    assert np.array_equal(host(kc), k_ref.view(raw)) and np.array_equal(host(vc), v_ref.view(raw))
+    assert np.array_equal(out.cpu().numpy(), lens_ref)
