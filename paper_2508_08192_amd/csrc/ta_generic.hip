@@ -921,10 +921,11 @@ __global__ __launch_bounds__(CP_THREADS) void ta_compact_kernel(TACompact c)
     // the positions rows come from (L .. L+T-1) and go to (L .. L+n-1; a path may name a node twice and be longer than T)
     const int span = n_ok ? max(c.T, n) : c.T;
     const bool len_ok = L >= 0 && (int64_t)L + span <= (int64_t)c.capacity;
+    // (entries of the path past its end are not read; both loads are on their way before either is looked at)
     const bool has_id = n_ok && tid < n, has_pos = len_ok && tid < span;
     int id = 0;
     int64_t page = b, slot = (int64_t)L + tid;
-    if (tid < c.A)
+    if (has_id)
         id = c.accepted[(int64_t)b * c.acc_sb + tid];
     if (has_pos && c.page_table) {
         page = c.page_table[(int64_t)b * c.pt_sb + (L + tid) / c.ps];
