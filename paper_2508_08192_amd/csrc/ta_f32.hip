@@ -21,6 +21,8 @@
 // KV pass by kernel trace: B 8, 8/2 heads, head_dim 128, T 8, L 200..4000 (36 MB) 17.9 us, where the vector-ALU kernel took
 // 122; one list of 128 tokens, head_dim 64, 28 rows 7.2, 27.5 there.  Error against 64 bits over sizes of all these ranges:
 // 2.9e-7 of the result (2-norm) where that kernel had 4.0e-7, the first product being summed in two chains.
+#include <type_traits>
+
 #include "ta_common.h"
 
 typedef float f32_x4 __attribute__((ext_vector_type(4)));
@@ -34,8 +36,8 @@ __device__ __forceinline__ void f32_lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// RB: blocks of 16 query rows
-template <int DH, int RB>
+// RB: blocks of 16 query rows; NEW: the tree tokens of this step lie in tensors of their own (ta_opts.k_new)
+template <int DH, int RB, bool NEW>
 __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
 {
     constexpr int NJ = DH / 16;                  // 16-byte pieces of a K row a lane loads
@@ -133,17 +135,11 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
         };
         auto request_page = [&](int u) {
             const int pos = token_at(u);
-            return p.page_table && !(p.kn && u >= n_pre)
-                       ? p.page_table[(int64_t)b * p.pt_sb + (pos >> p.ps_shift)] : b;
+            return p.page_table ? p.page_table[(int64_t)b * p.pt_sb + (pos >> p.ps_shift)] : b;
         };
         gfloat ka, va;
         auto locate = [&](int u, int page) {
             const int pos = token_at(u);
-            if (p.kn && u >= n_pre) {              // the tree tokens of this step lie in tensors of their own
-                ka = (gfloat)p.kn + (int64_t)b * p.kn_sb + (int64_t)(pos - L) * p.kn_st + (int64_t)g * p.kn_sh;
-                va = (gfloat)p.vn + (int64_t)b * p.vn_sb + (int64_t)(pos - L) * p.vn_st + (int64_t)g * p.vn_sh;
-                return;
-            }
             int at = pos;
             if (p.page_table) {
                 if (!ta_page_ok(p, page)) {        // must never become an address
@@ -152,6 +148,14 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
                 }
                 at = pos & (p.ps - 1);
             }
+            if constexpr (NEW)
+                // (their pages have been checked like any: the merge pass, which writes the rows there, leaves out without a
+                // word those whose page does not exist)
+                if (u >= n_pre) {
+                    ka = (gfloat)p.kn + (int64_t)b * p.kn_sb + (int64_t)(pos - L) * p.kn_st + (int64_t)g * p.kn_sh;
+                    va = (gfloat)p.vn + (int64_t)b * p.vn_sb + (int64_t)(pos - L) * p.vn_st + (int64_t)g * p.vn_sh;
+                    return;
+                }
             ka = (gfloat)p.k + (int64_t)page * p.k_sp + (int64_t)g * p.k_sh + (int64_t)at * p.k_ss;
             va = (gfloat)p.v + (int64_t)page * p.v_sp + (int64_t)g * p.v_sh + (int64_t)at * p.v_ss;
         };
@@ -428,7 +432,7 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
     }
 }
 
-template <int DH, int RB>
+template <int DH, int RB, bool NEW>
 static hipError_t launch_f32(const TAParams &p, hipStream_t stream, int dev)
 {
     constexpr size_t fixed = F32_NW * (16 * RB * DH + 2 * 16 * RB + 1) * sizeof(float);
@@ -436,13 +440,13 @@ static hipError_t launch_f32(const TAParams &p, hipStream_t stream, int dev)
     const size_t smem = fixed + (p.B <= TA_WAVE ? 0 : sizeof(int) * (3 * (size_t)p.B + 1));
     static bool attr_set[64] = {};      // per device and instance; setting it twice is harmless
     if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void *)ta_f32_kv_kernel<DH, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        hipError_t e = hipFuncSetAttribute((const void *)ta_f32_kv_kernel<DH, RB, NEW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            160 * 1024);
         if (e != hipSuccess)
             return e;
         attr_set[dev] = true;
     }
-    hipLaunchKernelGGL((ta_f32_kv_kernel<DH, RB>), dim3(p.n_wg, p.n_rg), dim3(64 * F32_NW), smem, stream, p);
+    hipLaunchKernelGGL((ta_f32_kv_kernel<DH, RB, NEW>), dim3(p.n_wg, p.n_rg), dim3(64 * F32_NW), smem, stream, p);
     return hipGetLastError();
 }
 
@@ -452,7 +456,11 @@ hipError_t ta_launch_f32(const TAParams &p, hipStream_t stream, int dev)
         return hipErrorInvalidDevice;
     if (p.rows_grp > F32_ROWS || p.part_q15 || p.ls != 1 || (p.D != 64 && p.D != 128))
         return hipErrorInvalidValue;
-    if (p.D == 64)
-        return p.rows_grp <= 16 ? launch_f32<64, 1>(p, stream, dev) : launch_f32<64, 2>(p, stream, dev);
-    return p.rows_grp <= 16 ? launch_f32<128, 1>(p, stream, dev) : launch_f32<128, 2>(p, stream, dev);
+    auto launch = [&](auto d, auto fold) {
+        constexpr int DH = decltype(d)::value;
+        constexpr bool NEW = decltype(fold)::value;
+        return p.rows_grp <= 16 ? launch_f32<DH, 1, NEW>(p, stream, dev) : launch_f32<DH, 2, NEW>(p, stream, dev);
+    };
+    auto with = [&](auto d) { return p.kn ? launch(d, std::true_type{}) : launch(d, std::false_type{}); };
+    return p.D == 64 ? with(std::integral_constant<int, 64>{}) : with(std::integral_constant<int, 128>{});
 }
