@@ -654,10 +654,11 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             ta_q15_scale(amax, nan_seen > 0.f, scale, to_q);
             const float lse2 = any_bad ? __uint_as_float(0x7fc00000u) : big + log2f(l_tot);
             if (DIRECT && whole_e) {
-                // no merge: the rows go out as they are (a NaN spoils its row, as it does there)
+                // no merge: the rows go out as they are, by its rules: a NaN or an infinity spoils its row (the 16-bit format
+                // holds neither), and no score above -inf leaves no log-sum-exp either
                 if (row < rows_here) {
                     const int R = row0 + row, node = (int)__umulhi((uint32_t)R << 8, p.g_magic), h = g_e * p.G + R - node * p.G;
-                    const bool nan = any_bad || nan_seen > 0.f || lse2 != lse2;
+                    const bool nan = any_bad || nan_seen > 0.f || amax == INFINITY || lse2 != lse2;
                     uint32_t *dst = (uint32_t *)((uint16_t *)p.out + (int64_t)b_e * p.o_sb + (int64_t)node * p.o_st +
                                                  (int64_t)h * p.o_sh + 4 * c0);
 #pragma unroll
@@ -665,7 +666,8 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
                         *(uint2 *)(dst + 2 * q) = nan ? make_uint2(0x7fc07fc0u, 0x7fc07fc0u)
                                                       : make_uint2(ks_pack(acc[4 * q], acc[4 * q + 1]), ks_pack(acc[4 * q + 2], acc[4 * q + 3]));
                     if (p.lse && x_e % TPR == 0)
-                        p.lse[(int64_t)b_e * p.lse_sb + (int64_t)h * p.lse_sh + (int64_t)node * p.lse_st] = lse2 * 0.6931471805599453f;
+                        p.lse[(int64_t)b_e * p.lse_sb + (int64_t)h * p.lse_sh + (int64_t)node * p.lse_st] =
+                            lse2 == -INFINITY ? __uint_as_float(0x7fc00000u) : lse2 * 0.6931471805599453f;
                 }
             } else if (row < rows_here) {
                 const int64_t wrow = ta_ws_row(p, slot_e, 0, row0 + row);

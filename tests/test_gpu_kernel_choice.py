@@ -136,3 +136,41 @@ def test_head_dim_64_with_32_and_64_rows_a_workgroup(T, Hq, L):
     got, lse = run_hip(w, d)
     ref, ref_lse = run_oracle(w)
     assert_parity(got, lse, ref, ref_lse, "bf16", "T=%d Hq=%d L=%d" % (T, Hq, L))
+
+
+def test_values_that_are_not_finite_come_out_alike_with_and_without_a_merge():
+    """Lists that the KV pass finishes by itself follow the same rules as merged ones: an infinity or a NaN among the attended
+    values spoils the whole row and leaves the log-sum-exp; scores that are all minus infinity leave neither."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    B, T, Hq, Hkv = 160, 8, 16, 4
+    w = W.make_workload("nonfinite", B=B, T=T, Hq=Hq, Hkv=Hkv, D=128, seq_lens=[40 + 3 * b for b in range(B)],
+                        trees=W.chain_tree(T), page_size=1024, seed=12, paged=False)
+    d = to_device(w)
+    d["q"].abs_()
+    inf = float("inf")
+    for b in range(0, B, 8):                        # in every eighth request, so that some of each lie whole in a share
+        d["v_cache"][b, 1, 20, 5] = inf
+        d["v_cache"][b + 1, 2, 7, 9] = float("nan")
+        d["k_cache"][b + 2, 3, :, 1] = -inf
+        d["v_cache"][b + 3, 0, 30, :] = -inf
+    hurt = {0: 1, 1: 2, 2: 3, 3: 0}
+    res = []
+    for kw in ({}, {"num_splits": 256}):            # 640 lists: at 256 shares most are finished by the KV pass
+        out, lse = torch.zeros_like(d["q"]), torch.zeros_like(d["lse"])
+        for kernel in (0, MFMA):
+            print("kernel choice: not finite, kernel=%d %s" % (kernel, kw), flush=True)
+            ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], None, d["seq_lens"], d["tree_parent"], out, lse,
+                                kernel=kernel, **kw)
+            torch.cuda.synchronize()
+            res.append((out.float().clone(), lse.clone()))
+    G = Hq // Hkv
+    for out, lse in res:
+        for b in range(B):
+            for g in range(Hkv):
+                rows, l = out[b, :, g * G:(g + 1) * G], lse[b, g * G:(g + 1) * G]
+                if hurt.get(b % 8) == g:
+                    assert torch.isnan(rows).all(), (b, g)
+                    assert (torch.isnan(l) if b % 8 == 2 else torch.isfinite(l)).all(), (b, g)
+                else:
+                    assert torch.isfinite(rows).all() and torch.isfinite(l).all(), (b, g)
