@@ -153,7 +153,8 @@ typedef struct {
                                  these tensors, never from the cache, and also stores them at logical positions
                                  L_b .. L_b+T-1 of k_cache / v_cache (which it therefore writes), exactly as
                                  tree_attn_append would have before the call; out and lse are bit for bit those of
-                                 append followed by the plain call.  A request that is NaN-filled for a bad length
+                                 append followed by the plain call (bf16: where their rows start on 16 bytes; with
+                                 others the call runs on the scalar kernel).  A request that is NaN-filled for a bad length
                                  is not written.  Both NULL = the tree tokens are already in the cache. */
     const ta_tensor *v_new;
     int32_t *status;          /* optional DEVICE pointer to one 32-bit word, 4-byte aligned: the call ORs the TA_STATUS_*

@@ -46,7 +46,9 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
     constexpr int ROWS = 16 * RB;
     // (global memory by type: an address put together from integers would be loaded as a flat one, and its wait is for all)
     typedef const __attribute__((address_space(1))) float *gfloat;
-    typedef const __attribute__((address_space(1))) f32_x4 *gpiece;
+    // (rows of k_new and v_new start at any element, those of the caches on 16 bytes: both are loaded 16 bytes at a time)
+    typedef f32_x4 f32_piece __attribute__((aligned(4)));
+    typedef const __attribute__((address_space(1))) f32_piece *gpiece;
     // Q rows while an item is walked, then the waves' results; row r's chunk c lies at chunk c ^ (r & 15)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float (*lds)[ROWS * DH] = (float (*)[ROWS * DH])smem;

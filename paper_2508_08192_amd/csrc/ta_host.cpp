@@ -242,13 +242,14 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     int basic = kernel == TA_KERNEL_MFMA_BASIC ? 1 : 0;
     if (basic)
         kernel = TA_KERNEL_MFMA;
-    // fp32 goes to the matrix cores where rows can be loaded in 16-byte pieces (a call that names the scalar kernel gets it)
+    // fp32 goes to the matrix cores where rows can be loaded in 16-byte pieces (a call that names the scalar kernel gets it).
+    // Rows of k_new and v_new may start anywhere: a call with the write-back folded in runs the kernel of the plain call.
     auto rows16 = [](const ta_tensor *n) {
         return (uintptr_t)n->data % 16 == 0 && n->stride[0] % 4 == 0 && n->stride[1] % 4 == 0 && n->stride[2] % 4 == 0 &&
                n->stride[3] == 1;
     };
     const bool f32_mfma = kernel == TA_KERNEL_AUTO && q->dtype == TA_F32 && (D == 128 || D == 64) && Hq / Hkv <= 256 &&
-                          (!pt || ps_shift >= 0) && rows16(q) && rows16(k) && rows16(v) && (!kn || (rows16(kn) && rows16(vn)));
+                          (!pt || ps_shift >= 0) && rows16(q) && rows16(k) && rows16(v);
     if (kernel == TA_KERNEL_MFMA && !mfma_ok)
         return TA_ERR_OPTS;
     const bool auto_kernel = kernel == TA_KERNEL_AUTO;

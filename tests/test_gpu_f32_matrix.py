@@ -186,3 +186,33 @@ def test_requests_with_mistakes_are_spoiled_and_reported(D, folded):
                 # 6 of request 1's tokens lie on its bad page, 16 of request 2's last, 16 of request 4's first
                 lost = sum(int(table[b, (lens[b] + i) // ps] not in range(n_pages)) for b in range(B) for i in range(T))
                 assert lost > 0 and rows == B * T - lost
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("offset,row", [(1, 0), (0, 1), (3, 2)])
+def test_folded_write_back_of_unaligned_rows_gives_the_bits_of_append_and_the_plain_call(D, offset, row):
+    """k_new and v_new whose rows start anywhere: the same kernel runs as for the plain call, so out, lse and the caches are
+    bit for bit those of tree_attn_append followed by it."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    B, T, Hkv = 3, 18, 2
+    w = W.make_workload("f32fold", B=B, T=T, Hq=4, Hkv=Hkv, D=D, seq_lens=[5, 300, 64], trees=W.bfs_tree(T, [3], 5),
+                        page_size=16, seed=7, dtype="f32")
+    d = to_device(w)
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def dense():
+        flat = torch.randn(offset + B * T * Hkv * (D + row), generator=g, device="cuda")
+        return flat[offset:].view(B, T, Hkv, D + row)[..., :D]
+    k_new, v_new = dense(), dense()
+    args = (d["page_table"], d["seq_lens"], d["tree_parent"])
+    k1, v1 = d["k_cache"].clone(), d["v_cache"].clone()
+    o1, l1 = torch.zeros_like(d["q"]), torch.zeros_like(d["lse"])
+    o2, l2 = torch.zeros_like(o1), torch.zeros_like(l1)
+    print("f32 unaligned k_new D=%d offset=%d row=%d" % (D, offset, row), flush=True)
+    ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], *args, o1, l1, k_new=k_new, v_new=v_new)
+    ta.tree_attn_append(k_new, v_new, k1, v1, d["page_table"], d["seq_lens"])
+    ta.tree_attn_fwd(d["q"], k1, v1, *args, o2, l2)
+    torch.cuda.synchronize()
+    assert torch.equal(k1, d["k_cache"]) and torch.equal(v1, d["v_cache"])
+    assert torch.equal(o1, o2) and torch.equal(l1, l2)
