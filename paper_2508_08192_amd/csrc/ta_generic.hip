@@ -504,7 +504,10 @@ __device__ __forceinline__ float4 ta_part_f4(const ta_s4 &x)
     return make_float4((float)x.x, (float)x.y, (float)x.z, (float)x.w);
 }
 
-template <int D, bool NEW, bool HP>
+// DONE: some lists' outputs were written by the KV pass (p.direct).  Instances of their own: with the early way out in all of
+// them, and in the kernel below, other calls' merges took longer (one list of 512 rows, folded write-back, a workgroup per
+// row: 7.7 -> 8.4 us).
+template <int D, bool NEW, bool HP, bool DONE>
 __global__ __launch_bounds__(256) void ta_merge_row_kernel(TAParams p)
 {
     constexpr int LPR = D / 4, RPW = TA_WAVE / LPR;       // lanes per row, rows per wave
@@ -520,12 +523,14 @@ __global__ __launch_bounds__(256) void ta_merge_row_kernel(TAParams p)
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
     if constexpr (NEW)
         ta_scatter_load(p, b, g, blockIdx.y, gridDim.y, sc);
-    if (n_parts <= 0) {                                    // the KV pass has written this list's outputs
-        if constexpr (NEW) {
-            ta_scatter_locate(p, b, g, sc);
-            ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
+    if constexpr (DONE) {
+        if (n_parts <= 0) {                                // the KV pass has written this list's outputs
+            if constexpr (NEW) {
+                ta_scatter_locate(p, b, g, sc);
+                ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
+            }
+            return;
         }
-        return;
     }
     const int R_raw = (blockIdx.y * 4 + wave) * RPW + part;
     if (R_raw - part >= p.rows) {                          // the whole wave is past the last row
@@ -675,13 +680,6 @@ __global__ __launch_bounds__(256) void ta_merge_wide_kernel(TAParams p)
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
     if constexpr (NEW)
         ta_scatter_load(p, b, g, blockIdx.y, gridDim.y, sc);
-    if (n_parts <= 0) {                                    // the KV pass has written this list's outputs
-        if constexpr (NEW) {
-            ta_scatter_locate(p, b, g, sc);
-            ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, sc);
-        }
-        return;
-    }
     const int rg = R / p.rows_grp, r = R % p.rows_grp;
     const int node = R / p.G, h = g * p.G + R % p.G;
     const int64_t row0 = ta_ws_row(p, w_first + seg, rg, r);              // partial k of this row: row0 + k*pstride
@@ -796,6 +794,8 @@ hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream)
     const size_t smem = 0;
     const int rows_wg = ta_host_merge_rows(p);             // the plan chose the kernel (p.merge_kind)
     dim3 grid(p.B * p.Hkv, (p.rows + rows_wg - 1) / rows_wg);
+    if (p.direct && (p.merge_kind != TA_MERGE_ROW || p.D != 128 || !p.part_q15))
+        return hipErrorInvalidValue;                       // only those instances know of lists that are done
     // (the instances with the write-back folded in also copy the tree tokens' K/V into the caches)
     if (p.merge_kind == TA_MERGE_WIDE || p.merge_kind == TA_MERGE_ROW) {
         auto launch = [&](auto d, auto fold, auto hp) {
@@ -803,8 +803,10 @@ hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream)
             constexpr bool NEW = decltype(fold)::value, HP = decltype(hp)::value;
             if (p.merge_kind == TA_MERGE_WIDE)
                 hipLaunchKernelGGL((ta_merge_wide_kernel<D, NEW, HP>), grid, dim3(256), smem, stream, p);
+            else if (p.direct)
+                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP, D == 128 && HP>), grid, dim3(256), smem, stream, p);
             else
-                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP>), grid, dim3(256), smem, stream, p);
+                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP, false>), grid, dim3(256), smem, stream, p);
         };
         auto with = [&](auto d) {
             if (p.kn && p.part_q15)

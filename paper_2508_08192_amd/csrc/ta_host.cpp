@@ -385,7 +385,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // With at least two lists per workgroup most lie whole in a share, and their partial results need not be written,
     // merged and read again (its stores need the alignment that the row merge needs): B 128, 32/8 heads, T 8, L 256..4096
     // 212.5 -> 205.8 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
-    p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind != TA_MERGE_GENERAL && lists >= 2 * (int64_t)pl.n_wg;
+    p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind == TA_MERGE_ROW && lists >= 2 * (int64_t)pl.n_wg;
     pl.merge_kind = D == 128 ? p.merge_kind : TA_MERGE_GENERAL;     // (what a plan says is which one of head_dim 128)
     const int mrows = ta_host_merge_rows(p);
     pl.merge_wgs = (int)lists * ((p.rows + mrows - 1) / mrows);
