@@ -267,23 +267,34 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         return TA_ERR_SHAPE;
     // Which matrix-core kernel (head_dim 128; a call that names TA_KERNEL_MFMA gets the pipelined one).  The key-split
     // kernel has eight waves computing from the first tile on, the pipelined one as many as there are blocks of 32 rows, but
-    // the former keeps 32 rows: it walks the keys again for every further 32.  Measured, us a call, pipelined and
-    // key-split:
-    //   one block: 16 lists of 8000 tokens 26.1 and 22.0, 32 of 2000 22.1 and 17.1, 64 of 32000 179 and 174; one list of
-    //     500 to 2000 tokens, where a share is a single tile, two of the eight waves' work, 14.4 and 15.7, of 5000 equal;
-    //   two to four: blocks times tiles, per compute unit, 3: 17.2 and 18.0, 4: 19.9 and 16.9, 8: 23.6 and 20.2, 16: 27.3
-    //     and 26.3, 30: 36.6 and 40.1; one list, 1: 18.6 and 17.4, 16: 30.4 and 26.3, 31: 34.3 and 33.4;
-    //   five and more, whose tiles cost the pipelined kernel's eight waves more: 8: 25.6 and 17.6, 31: 35.5 and 31.1, 125:
-    //     58.6 and 92.9.
-    // Tiles are counted from what the page table can hold.  With more lists than workgroups in a grid row, or hardly fewer,
-    // most workgroups enter two lists: 64 lists of 500 tokens in rows of 80 workgroups 22.8 and 24.9, 48 a row 30.0 and
-    // 32.6, 64 a row 24.5 and 21.0.
+    // the former keeps 32 rows: it walks the keys again for every further 32.  The line is drawn by `units`, blocks times
+    // tiles per compute unit.  The host does not see the lengths, so tiles are counted from what the page table can hold: a
+    // table much wider than its requests may give a small batch to the kernel of a larger one.  Beside each line the time
+    // of the key-split kernel over the pipelined one's, by units:
+    //   one block: 0.85 to 0.98 from two units on, 0.91 to 1.04 below with two lists and more, one list 1.01 to 1.03 up to
+    //     one unit and 0.94 at two (in a table of 32768 tokens, contexts of 100 to 1000 and few lists 1.08 to 1.10);
+    //   one list of more: 0.95 to 1.0 up to two units, 0.82 to 0.98 from three to seventeen;
+    //   two blocks: 0.95 to 1.05 up to three units; above, with a whole number of workgroups per list, lists of equal
+    //     length 0.80 to 0.98 (1.05 up to five units), uneven ones 0.94 to 1.03, with sixteen per list and more 0.83 to 1.04;
+    //     otherwise 0.91 to 1.10 (28, 48 and 56 lists);
+    //   three and four: whole numbers of workgroups and equal lengths 0.83 to 1.02 from seven units on, 0.92 to 1.13 at four
+    //     to six; uneven lists 0.99 to 1.03 up to five units, 1.05 to 1.20 from seven to sixteen, with sixteen workgroups per
+    //     list and more 0.93 to 1.03 up to ten;
+    //   five and more, whose tiles cost the pipelined kernel's eight waves more: 0.73 to 0.98 up to ten units for all lists,
+    //     one list 0.80 to 0.97 up to 31, whole numbers and equal lengths 0.80 to 1.0 up to 26, uneven 1.0 to 1.2 from 20 on.
+    // One workgroup per list and fewer than two is for none of them: uneven lists then take 1.2 to 1.35 times as long.
     const int slices = (p.rows + 31) / 32;
     const int64_t ks_wg = key_split_workgroups(num_cus, slices);
-    const bool ks_even = ks_wg >= 2 * lists || ks_wg == lists;
-    const bool ks_fits = slices == 1 ? lists > 1 || tiles_cap > 64
-                                     : tiles_cap * slices <= (int64_t)(slices > 4 || lists == 1 ? 32 : 16) * num_cus && ks_even &&
-                                           (slices > 4 || lists == 1 || 2 * tiles_cap * slices > 7 * num_cus);
+    const int64_t units = tiles_cap * slices;
+    const bool whole = lists > 0 && ks_wg % lists == 0, many = ks_wg >= 16 * lists;
+    const bool equal = B == 1 && whole;                     // (the lists of one request are of one length)
+    auto within = [&](int64_t from_x2, int64_t to) { return 2 * units > from_x2 * num_cus && units <= to * num_cus; };
+    const bool ks_fits = slices == 1 ? lists > 1 || units > num_cus
+                         : ks_wg < 2 * lists ? false
+                         : lists == 1 ? within(0, 32)
+                         : slices > 4 ? within(0, equal ? 28 : 12)
+                         : slices == 2 ? (whole || many) && within(7, 16)
+                         : equal ? within(13, 16) : many && within(7, 10);
     const bool ks = kernel == TA_KERNEL_MFMA && (basic || (auto_kernel && ks_fits));
     p.basic = ks;
     p.f32_mfma = f32_mfma;
@@ -330,9 +341,11 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     pl.kernel = kernel;
     const int family = kernel == TA_KERNEL_MFMA ? (basic ? TA_KERNEL_MFMA_BASIC : TA_KERNEL_MFMA) : TA_KERNEL_GENERIC;
     if (kernel == TA_KERNEL_MFMA) {
-        // head_dim 64 can keep 64 rows; 32 are faster where the same few tiles fall on a compute unit (blocks times tiles 1
-        // to 10: 14.5 to 19.4 us a call and 13.3 to 16.3, 16: 19.0 and 18.6, 47: 28.4 and 31.1)
-        p.ks_rows = D == 64 && slices > 1 && !(tiles_cap * slices <= (int64_t)16 * num_cus && ks_even) ? 64 : 32;
+        // head_dim 64 can keep 64 rows; 32 are faster where the same few tiles fall on a compute unit (time with 32 rows over
+        // that with 64: up to four units 0.83 to 1.04, at eight 0.76 to 1.05, at twelve 0.74 to 1.08, one list 0.79 to 0.93,
+        // at sixteen 0.74 to 1.18, mostly 1.0 to 1.08), but not with one workgroup per list (equal lists 0.84 to 1.08, uneven
+        // ones 1.13 to 1.37) and fewer (1.2 to 1.5)
+        p.ks_rows = D == 64 && slices > 1 && !(units <= (int64_t)16 * num_cus && ks_wg >= 2 * lists) ? 64 : 32;
         pl.rows_grp = ks && (basic || slices <= 4) ? p.ks_rows : mfma_rows_group(p.rows);
         pl.threads = 512;
     } else if (f32_mfma) {

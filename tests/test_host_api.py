@@ -267,6 +267,26 @@ def test_dispatch_table_rows_and_the_plans_they_give():
     assert _plan(_good(D=64, dtype=ta.TA_F32))["merge_kernel"] == ta.TA_MERGE_GENERAL
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,max_pages,want", [
+    (1, 8, 8, 1, 129, 1),            # one list of two row blocks
+    (1, 4, 8, 1, 129, 0), (1, 4, 8, 1, 400, 1),    # one list of one block: below and above a tile per compute unit
+    (8, 16, 32, 8, 20, 1), (8, 16, 32, 8, 6, 0), (6, 16, 32, 8, 20, 0),   # two blocks: two, and 2.67 workgroups per list
+    (8, 32, 32, 8, 10, 0),           # four blocks, one workgroup per list
+    (4, 32, 32, 8, 20, 0),           # two per list, but lists that may be uneven
+    (1, 32, 32, 8, 100, 1), (1, 32, 32, 8, 50, 0),  # of one length, and too few tiles for it
+    (4, 32, 4, 1, 100, 1), (4, 32, 4, 1, 170, 0),   # sixteen per list
+    (1, 64, 32, 8, 65, 1), (4, 64, 32, 8, 10, 0), (2, 64, 32, 8, 20, 1), (2, 64, 32, 8, 40, 0)])   # eight blocks
+def test_which_matrix_core_kernel_takes_a_call(B, T, Hq, Hkv, max_pages, want):
+    """Head_dim 128 on 256 compute units: the key-split kernel where it is measured to be no slower whatever the lengths."""
+    p = _plan(_good(B=B, T=T, Hq=Hq, Hkv=Hkv, max_pages=max_pages, pages=B * max_pages), num_cus=256)
+    assert p["key_split"] == want, p
+
+
+def test_head_dim_64_keeps_32_rows_only_with_two_workgroups_per_list():
+    for B, rows in ((8, 32), (16, 64)):
+        assert _plan(_good(B=B, T=16, Hq=32, Hkv=8, D=64, max_pages=5, pages=B * 5), num_cus=256)["rows_per_group"] == rows
+
+
 def test_status_word_option_is_checked():
     a = _good()
     assert _plan(a, status=Desc((1,), ta.TA_I32, ptr=0x2002), check=False) == ta.TA_ERR_OPTS     # not 4-byte aligned
