@@ -265,13 +265,14 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * Host-only launch plan for a call (no device access): which kernel family would run and how the work
  * is cut (section 3.4, "Attention kernel": the choice by batch size, tree size and GPU; here one row of the
  * library's dispatch table, see tree_attn_dispatch_row).  plan[0] = kernel family, plan[1] = workgroups of the
- * KV pass, plan[2] = threads per workgroup, plan[3] = KV tokens per tile, plan[4] = row groups, plan[5] = padded
- * rows per group, plan[6] = partial slots, plan[7] = workgroups of the merge pass, plan[8] = smallest share of
- * tiles per workgroup, plan[9] = schedule units a list counts (item_cost), plan[10] = merge kernel of head_dim 128
- * (1; 2 with one workgroup per row; 0 general, and all other head dims), plan[11] = row of the dispatch table that was
- * taken (-1: none, fp32 on the matrix cores), plan[12] = workspace bytes the call needs, plan[13] = format
- * of the partial results (0: fp32; 1: 16-bit fixed point with one fp32 scale per row), plan[14] = 1 if the
- * key-split matrix-core kernel runs, plan[15] = 0.
+ * KV pass for each block of plan[15] query rows, plan[2] = threads per workgroup, plan[3] = KV tokens per tile,
+ * plan[4] = row groups of the partial results, plan[5] = padded rows per group, plan[6] = partial slots,
+ * plan[7] = workgroups of the merge pass, plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units
+ * a list counts (item_cost), plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
+ * workgroup per row, 0 general), plan[11] = row of the dispatch table that was taken (-1: none, the fp32 matrix-core
+ * kernel runs), plan[12] = workspace bytes the call needs, plan[13] = format of the partial results (0: fp32; 1: 16-bit
+ * fixed point with one fp32 scale per row), plan[14] = 1 if the key-split matrix-core kernel runs, plan[15] = query rows
+ * a workgroup of the KV pass keeps.
  * HOST pointers.
  */
 int tree_attn_plan(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,

@@ -399,7 +399,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // merged and read again (its stores need the alignment that the row merge needs): B 128, 32/8 heads, T 8, L 256..4096
     // 212.5 -> 205.8 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
     p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind == TA_MERGE_ROW && lists >= 2 * (int64_t)pl.n_wg;
-    pl.merge_kind = D == 128 ? p.merge_kind : TA_MERGE_GENERAL;     // (what a plan says is which one of head_dim 128)
+    pl.merge_kind = p.merge_kind;
     const int mrows = ta_host_merge_rows(p);
     pl.merge_wgs = (int)lists * ((p.rows + mrows - 1) / mrows);
 
@@ -438,7 +438,9 @@ void ta_host_fill_plan(const TAProblem &pr, int64_t plan[16])
     plan[11] = pr.plan.table_row;
     plan[12] = (int64_t)pr.ws_bytes;
     plan[13] = pr.p.part_q15;
-    plan[14] = pr.plan.kernel == TA_KERNEL_MFMA && pr.p.basic;
+    const bool ks = pr.plan.kernel == TA_KERNEL_MFMA && pr.p.basic;
+    plan[14] = ks;
+    plan[15] = ks ? pr.p.ks_rows : pr.plan.rows_grp;
 }
 
 size_t ta_host_workspace_bytes(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t D, int32_t dtype, int32_t num_cus)

@@ -100,9 +100,9 @@ def test_option_errors():
     # the matrix-core kernel is bf16, head_dim 128, power-of-two pages only
     assert _plan(_good(dtype=ta.TA_F32), kernel=ta.TA_KERNEL_MFMA, check=False) == ta.TA_ERR_OPTS
     assert _plan(_good(D=96), kernel=ta.TA_KERNEL_MFMA, check=False) == ta.TA_ERR_OPTS
-    # head_dim 64 runs on the matrix cores too, on the register-staged kernel (its row of the dispatch table)
+    # head_dim 64 runs on the matrix cores too, on the key-split kernel (its row of the dispatch table)
     p64 = _plan(_good(D=64))
-    assert p64["kernel"] == ta.TA_KERNEL_MFMA and p64["merge_kernel"] == ta.TA_MERGE_GENERAL
+    assert p64["kernel"] == ta.TA_KERNEL_MFMA and p64["merge_kernel"] == ta.TA_MERGE_D128
     assert ta.tree_attn_dispatch_table()[p64["table_row"]]["family"] == ta.TA_KERNEL_MFMA_BASIC
     assert _plan(_good(ps=48), kernel=ta.TA_KERNEL_MFMA, check=False) == ta.TA_ERR_OPTS
 
@@ -264,7 +264,19 @@ def test_dispatch_table_rows_and_the_plans_they_give():
             p2 = _plan(a, kernel=kern, num_cus=cus, num_splits=5, item_cost=3)
             assert p2["kv_workgroups"] == 5 and p2["min_share"] == 1 and p2["item_cost"] == 3
     assert seen == set(range(len(table))), "rows never taken: %r" % (set(range(len(table))) - seen)
-    assert _plan(_good(D=64, dtype=ta.TA_F32))["merge_kernel"] == ta.TA_MERGE_GENERAL
+    # the merge of head_dim 64 is that of 128 where the outputs are aligned for it
+    assert _plan(_good(D=64, dtype=ta.TA_F32))["merge_kernel"] == ta.TA_MERGE_D128
+    odd = _good(D=64, dtype=ta.TA_F32)
+    odd["out"] = Desc(odd["out"].shape, ta.TA_F32, stride=(8 * 8 * 65, 8 * 65, 65, 1))
+    assert _plan(odd)["merge_kernel"] == ta.TA_MERGE_GENERAL
+    assert _plan(_good(D=96, dtype=ta.TA_F32))["merge_kernel"] == ta.TA_MERGE_GENERAL
+    # what a workgroup keeps: a row group, or 32 or 64 of its rows on the key-split kernel
+    for kw, rows, group in ((dict(B=1, T=64, Hq=32, Hkv=8, max_pages=65, pages=65), 32, 256),
+                            (dict(B=4, T=64, Hq=32, Hkv=8, max_pages=129, pages=516), 256, 256),
+                            (dict(B=16, T=16, Hq=32, Hkv=8, D=64, max_pages=65, pages=1040), 64, 64),
+                            (dict(B=1, T=9, Hq=4, Hkv=1, dtype=ta.TA_F32), 18, 18), (dict(B=1, T=9, Hq=4, Hkv=1, D=96), 36, 36)):
+        p = _plan(_good(**kw), num_cus=cus)
+        assert p["workgroup_rows"] == rows and p["rows_per_group"] == group, p
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,max_pages,want", [
