@@ -117,3 +117,41 @@ def test_what_is_not_of_the_simple_form_goes_through_ctypes(captured, monkeypatc
     assert _both(lambda: ta.tree_attn_fwd_ex(*t, stream=0, num_splits="x"), captured, monkeypatch)[0] is ValueError
     with pytest.raises(ta.TreeAttnError):
         ta.tree_attn_fwd(*t, stream=0)
+
+
+def test_the_library_works_without_the_module():
+    """Where the extension module cannot be imported the binding warns and calls through ctypes.  In a process of its own."""
+    import os
+    import subprocess
+    import sys
+    code = ("import sys, warnings\n"
+            "sys.modules['paper_2508_08192_amd._call'] = None\n"
+            "import torch\n"
+            "from paper_2508_08192_amd import treeattn as ta\n"
+            "with warnings.catch_warnings(record=True) as seen:\n"
+            "    warnings.simplefilter('always')\n"
+            "    assert ta.tree_attn_version() > 0\n"
+            "assert ta._call is None and any('ctypes' in str(w.message) for w in seen)\n"
+            "q = torch.zeros(2, 3, 4, 64)\n"
+            "assert ta.tree_attn_fwd(q, q, None, None, q, q, q, stream=0, check=False) == ta.TA_ERR_NULL\n"
+            "assert ta.tree_attn_append(q, q, q, q, None, q, stream=0, check=False) == ta.TA_ERR_DTYPE\n"
+            "print('ok')\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], cwd=root, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert out.returncode == 0 and "ok" in out.stdout, out.stdout
+
+
+def test_a_build_without_a_host_compiler_leaves_the_library(monkeypatch, tmp_path):
+    from paper_2508_08192_amd import build
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "CALL_MODULE", str(tmp_path / "_call.so"))
+    monkeypatch.setattr(build, "generate_blocks", lambda verbose: None)
+    monkeypatch.setattr(build, "verify_register_partition", lambda verbose: None)
+    hipcc = tmp_path / "hipcc"
+    hipcc.write_text('#!/bin/sh\nwhile [ $# -gt 1 ]; do [ "$1" = -o ] && : > "$2"; shift; done\n')
+    hipcc.chmod(0o755)
+    monkeypatch.setenv("HIPCC", str(hipcc))
+    monkeypatch.setenv("CXX", str(tmp_path / "no_such_compiler"))
+    (tmp_path / "_call.so").write_text("of other sources")
+    assert build.build_library() == str(tmp_path / "lib.so") and (tmp_path / "lib.so").exists()
+    assert not (tmp_path / "_call.so").exists()
