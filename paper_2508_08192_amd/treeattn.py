@@ -217,7 +217,7 @@ def _stream_address(stream):
         return cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
-    return stream.cuda_stream
+    return stream.cuda_stream if stream != 0 else 0        # (a zero of any type is the default stream)
 
 
 def _opts(scale=None, num_splits=0, kernel=TA_KERNEL_AUTO, workspace=None, events=None, item_cost=0, tree_masks=None,

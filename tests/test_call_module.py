@@ -155,3 +155,12 @@ def test_a_build_without_a_host_compiler_leaves_the_library(monkeypatch, tmp_pat
     (tmp_path / "_call.so").write_text("of other sources")
     assert build.build_library() == str(tmp_path / "lib.so") and (tmp_path / "lib.so").exists()
     assert not (tmp_path / "_call.so").exists()
+
+
+def test_any_zero_is_the_default_stream(captured, monkeypatch):
+    import numpy as np
+    t = _tensors()
+    for zero in (0, 0.0, np.int64(0), False):
+        assert _both(lambda: ta.tree_attn_fwd(*t, stream=zero, check=False), captured, monkeypatch)[0] == 7
+        assert _both(lambda: ta.tree_attn_fwd_ex(*t, stream=zero, check=False), captured, monkeypatch)[0] == 7
+    assert _both(lambda: ta.tree_attn_fwd(*t, stream="x", check=False), captured, monkeypatch)[0] is AttributeError
