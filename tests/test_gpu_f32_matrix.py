@@ -1,6 +1,6 @@
-"""fp32 attention on the matrix cores (head_dim 64 and 128): sizes at the edges of its runs of 32 tokens, of the rounds of
-its four waves and of its groups of 32 rows, every way the tree tokens and the schedule reach it, and values at which a
-probability of zero is not enough, against the fp64 oracle and the scalar kernel."""
+"""fp32 attention on the matrix cores (head_dim 64 and 128): sizes at the edges of its runs of 16 tokens, of the rounds of
+its four waves and of its groups of 32 rows, every way the tree tokens and the schedule reach it, values at which a
+probability of zero is not enough, and requests with mistakes, against the fp64 oracle and the scalar kernel."""
 import numpy as np
 import pytest
 
@@ -183,7 +183,7 @@ def test_requests_with_mistakes_are_spoiled_and_reported(D, folded):
                     assert (out[b] - good[0][b]).abs().max() <= 1e-5 and (lse[b] - good[1][b]).abs().max() <= 1e-5, (what, b)
             if what == "page of the tree" and folded:
                 rows = (k != to_device(w)["k_cache"]).any(dim=3).any(dim=1).sum().item()
-                # 6 of request 1's tokens lie on its bad page, 16 of request 2's last, 16 of request 4's first
+                # (6 of request 1's tokens lie on its bad page, 16 of request 2's, 16 of request 4's)
                 lost = sum(int(table[b, (lens[b] + i) // ps] not in range(n_pages)) for b in range(B) for i in range(T))
                 assert lost > 0 and rows == B * T - lost
 
@@ -216,3 +216,37 @@ def test_folded_write_back_of_unaligned_rows_gives_the_bits_of_append_and_the_pl
     torch.cuda.synchronize()
     assert torch.equal(k1, d["k_cache"]) and torch.equal(v1, d["v_cache"])
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
+
+
+@pytest.mark.parametrize("D,ps", [(64, 4), (64, 64), (128, 16)])
+def test_pages_before_the_window_are_never_read(D, ps):
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    lens, starts = [700, 333, 90, 130], np.int32([333, 200, 90, 7])
+    w = W.make_workload("f32released", B=4, T=8, Hq=8, Hkv=2, D=D, seq_lens=lens, trees=W.chain_tree(8), page_size=ps,
+                        seed=15, dtype="f32")
+    w.kv_start = starts
+    d = _decoys(to_device(w))
+    pt = w.page_table.copy()
+    for b in range(4):
+        pt[b, :int(starts[b]) // ps] = w.k_cache.shape[0] + 1
+    d["page_table"] = torch.from_numpy(pt).cuda()
+    ref, ref_lse = run_oracle(w)
+    ta.tree_attn_last_status()
+    for splits in (0, 3):
+        print("f32 released pages D=%d ps=%d splits=%d" % (D, ps, splits), flush=True)
+        got, lse = run_hip(w, d, num_splits=splits)
+        assert ta.tree_attn_last_status() == 0
+        assert_parity(got, lse, ref, ref_lse, "f32", "released pages")
+
+
+@pytest.mark.parametrize("T", [16, 17, 48, 49])
+def test_edges_of_the_runs_of_sixteen_tokens(T):
+    lens = [15, 16, 17, 47, 48, 49, 79, 80, 81]
+    rng = np.random.default_rng(T)
+    trees = np.stack([W.random_tree(T, 7, rng) for _ in lens])
+    for D in (64, 128):
+        for splits in (0, 2):
+            w = W.make_workload("runs16", B=len(lens), T=T, Hq=2, Hkv=1, D=D, seq_lens=lens, trees=trees, page_size=8, seed=T,
+                                dtype="f32")
+            _check(w, "runs of 16: D=%d T=%d splits=%d" % (D, T, splits), num_splits=splits)

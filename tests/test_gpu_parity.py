@@ -127,7 +127,8 @@ def test_256_row_kernel_contiguous_layout():
 
 @pytest.mark.parametrize("splits", [0, 3])
 def test_256_row_groups_on_the_register_staged_kernel(splits):
-    """The fallback for 256-row groups (taken by itself when the pipelined kernel's LDS need is too large)."""
+    """256 query rows on the key-split kernel (which replaced a register-staged one as the fallback), taken by itself when the
+    pipelined kernel's LDS need is too large: eight workgroups of 32 rows side by side."""
     rng = np.random.default_rng(14)
     T = 64
     w = W.make_workload("basic256", B=3, T=T, Hq=8, Hkv=2, D=128, seq_lens=[1500, 0, 777],
@@ -138,7 +139,7 @@ def test_256_row_groups_on_the_register_staged_kernel(splits):
 
 @pytest.mark.parametrize("T,Hq,Hkv", [(7, 4, 1), (16, 8, 2), (64, 8, 2), (33, 10, 2)])
 def test_head_dim_64_on_the_matrix_cores(T, Hq, Hkv):
-    """bf16 with head_dim 64 takes the register-staged matrix-core kernel (28, 64, 256 and 165 rows per KV head)."""
+    """bf16 with head_dim 64 takes the key-split matrix-core kernel (28, 64, 256 and 165 rows per KV head)."""
     import torch
     from paper_2508_08192_amd import treeattn as ta
     rng = np.random.default_rng(64 + T)
@@ -768,7 +769,7 @@ def test_queries_are_a_range_of_the_tree_nodes(kernel):
 
 def test_very_large_batch_falls_back_to_the_register_staged_kernel():
     """With more than about 1900 requests the schedule no longer fits beside the tile rings in LDS and the library
-    takes the register-staged matrix-core kernel by itself (kernel = MFMA is still what the caller asked for)."""
+    takes the key-split matrix-core kernel by itself (kernel = MFMA is still what the caller asked for)."""
     rng = np.random.default_rng(71)
     B, T = 2100, 4
     lens = rng.integers(0, 200, size=B)

@@ -37,7 +37,7 @@ def test_static_scratch_call_equals_the_allocating_call_on_calls_in_a_row():
     mid = W.make_workload("static_mid", B=3, T=16, Hq=8, Hkv=2, D=128, seq_lens=[900, 64, 2000],
                           trees=np.stack([W.random_tree(16, 5, rng) for _ in range(3)]), page_size=64, dtype="bf16",
                           seed=2101)
-    tiny = W.make_config(0)                                     # fp32, scalar kernels
+    tiny = W.make_config(0)                                     # fp32
     ta.tree_attn_last_status()
     for w, opts in ((big, {}), (mid, {}), (mid, dict(num_splits=7)), (tiny, {}), (mid, dict(kernel=1))):
         print("\n[case] static scratch, %s %r" % (w.name, opts), flush=True)
