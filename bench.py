@@ -405,7 +405,7 @@ def main():
                 "unit": "TFLOP/s", "frac": m["mfma_frac"], "traffic": traffic}
     src = m["region"] if m["in_region"] else m["kernel_pass"]
     med_us = src["kv_pass_us"]["median"]
-    roof.update({"kernel": "ta_mfma_sp_kernel" if plan["kernel"] == 2
+    roof.update({"kernel": ("ta_mfma_ks_kernel" if plan["key_split"] else "ta_mfma_sp_kernel") if plan["kernel"] == 2
                  else "ta_f32_kv_kernel" if plan["table_row"] < 0 else "ta_generic_kv_kernel",
                  "avg_launch_us": kv_us, "median_launch_us": med_us, "min_launch_us": src["kv_pass_us"]["min"],
                  "launches_timed": src["kv_pass_us"]["n"],
