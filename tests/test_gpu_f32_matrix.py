@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2508_08192_amd import workloads as W
-from tests.helpers import assert_parity, run_hip, run_oracle, to_device
+from tests.helpers import assert_parity, check_requests_with_mistakes, run_hip, run_oracle, to_device, with_decoy_pages
 
 pytestmark = pytest.mark.gpu
 GENERIC = 1
@@ -111,81 +111,10 @@ def test_infinities_and_nans_come_out_as_from_the_scalar_kernel():
     assert torch.isinf(o0[0, :, :, 5]).all() and torch.isfinite(o0[3]).all() and torch.isfinite(o0[5]).all()
 
 
-def _decoys(dev):
-    """The caches as views of larger allocations of NaN: page ids just past them lie in memory this process owns."""
-    import torch
-    for key in ("k_cache", "v_cache"):
-        t = dev[key]
-        full = torch.full((t.shape[0] + 4,) + tuple(t.shape[1:]), float("nan"), device="cuda")
-        full[:t.shape[0]] = t
-        dev[key] = full[:t.shape[0]]
-    return dev
-
-
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("folded", [False, True])
 def test_requests_with_mistakes_are_spoiled_and_reported(D, folded):
-    """A page id outside the cache in a prefix and under the tree tokens (also where their rows come from k_new and the page
-    only receives them), a bad length, a cyclic tree given as parents and as masks: NaN rows, the status bit, nothing written
-    for the tokens whose page does not exist, and every other request as it was."""
-    import torch
-    from paper_2508_08192_amd import treeattn as ta
-    B, T, Hq, Hkv, ps = 6, 19, 4, 2, 16
-    lens = [300, 90, 61, 40, 128, 33]
-    trees = np.stack([W.bfs_tree(T, [3], 5)] * B)
-    w = W.make_workload("f32bad", B=B, T=T, Hq=Hq, Hkv=Hkv, D=D, seq_lens=lens, trees=trees, page_size=ps, seed=91, dtype="f32")
-    n_pages = w.k_cache.shape[0]
-    k_new, v_new = (torch.randn(B, T, Hkv, D, generator=torch.Generator().manual_seed(s)).cuda() for s in (1, 2))
-
-    def call(table, seq, tree, **kw):
-        d = _decoys(to_device(w))
-        d["page_table"], d["seq_lens"], d["tree_parent"] = (torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (table, seq, tree))
-        if folded:
-            kw = dict(kw, k_new=k_new, v_new=v_new)
-        out, lse = torch.zeros_like(d["q"]), torch.zeros_like(d["lse"])
-        own = torch.zeros(1, dtype=torch.int32, device="cuda")
-        ta.tree_attn_last_status()
-        ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], out, lse,
-                            status=own, **kw)
-        bits = ta.tree_attn_last_status()
-        assert bits == int(own.item())
-        return out, lse, d["k_cache"], d["v_cache"], bits
-
-    good = call(w.page_table, w.seq_lens, trees)
-    assert good[4] == 0 and torch.isfinite(good[0]).all()
-    tree_page = w.page_table.copy()
-    tree_page[1, 90 // ps] = n_pages                            # holds the last prefix tokens and the first of the tree
-    tree_page[2, (61 + T - 1) // ps] = n_pages + 3              # holds the last tokens of the tree alone
-    tree_page[4, 128 // ps] = -1                                # the prefix ends on a page: the tree's alone
-    prefix = w.page_table.copy()
-    prefix[0, 7] = n_pages
-    bad_len = w.seq_lens.copy()
-    bad_len[3] = -1
-    bad_len[5] = w.page_table.shape[1] * ps
-    cyc = trees.copy()
-    cyc[2, 1], cyc[2, 2] = 2, 1
-    masks = torch.zeros((B, T), dtype=torch.int64, device="cuda")
-    ta.tree_attn_encode(torch.from_numpy(cyc).cuda(), masks)
-    for what, table, seq, tree, kw, hit, bit in (
-            ("page of the tree", tree_page, w.seq_lens, trees, {}, [1, 2, 4], ta.TA_STATUS_BAD_PAGE),
-            ("page of the prefix", prefix, w.seq_lens, trees, {}, [0], ta.TA_STATUS_BAD_PAGE),
-            ("length", w.page_table, bad_len, trees, {}, [3, 5], ta.TA_STATUS_BAD_SEQLEN),
-            ("parents", w.page_table, w.seq_lens, cyc, {}, [2], ta.TA_STATUS_BAD_PARENT),
-            ("masks", w.page_table, w.seq_lens, trees, {"tree_masks": masks}, [2], ta.TA_STATUS_BAD_PARENT)):
-        for splits in (0, 1):
-            print("f32 mistakes D=%d folded=%s splits=%d: %s" % (D, folded, splits, what), flush=True)
-            out, lse, k, v, bits = call(table, seq, tree, num_splits=splits, **kw)
-            assert bits == bit, (what, bits)
-            for b in range(B):
-                if b in hit:
-                    assert torch.isnan(out[b]).all() and torch.isnan(lse[b]).all(), (what, b)
-                else:
-                    assert (out[b] - good[0][b]).abs().max() <= 1e-5 and (lse[b] - good[1][b]).abs().max() <= 1e-5, (what, b)
-            if what == "page of the tree" and folded:
-                rows = (k != to_device(w)["k_cache"]).any(dim=3).any(dim=1).sum().item()
-                # (6 of request 1's tokens lie on its bad page, 16 of request 2's, 16 of request 4's)
-                lost = sum(int(table[b, (lens[b] + i) // ps] not in range(n_pages)) for b in range(B) for i in range(T))
-                assert lost > 0 and rows == B * T - lost
+    check_requests_with_mistakes("f32", D, folded)
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -226,7 +155,7 @@ def test_pages_before_the_window_are_never_read(D, ps):
     w = W.make_workload("f32released", B=4, T=8, Hq=8, Hkv=2, D=D, seq_lens=lens, trees=W.chain_tree(8), page_size=ps,
                         seed=15, dtype="f32")
     w.kv_start = starts
-    d = _decoys(to_device(w))
+    d = with_decoy_pages(to_device(w))
     pt = w.page_table.copy()
     for b in range(4):
         pt[b, :int(starts[b]) // ps] = w.k_cache.shape[0] + 1

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2508_08192_amd import workloads as W
-from tests.helpers import assert_parity, run_hip, run_oracle
+from tests.helpers import assert_parity, check_requests_with_mistakes, run_hip, run_oracle
 
 pytestmark = pytest.mark.gpu
 MFMA_BASIC = 3
@@ -47,3 +47,9 @@ def test_schedule_in_registers_and_in_lds(B):
                         page_size=32, seed=B)
     w.kv_start = (w.seq_lens // 3).astype(np.int32)
     _check(w, "B=%d" % B)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("folded", [False, True])
+def test_requests_with_mistakes_are_spoiled_and_reported(D, folded):
+    check_requests_with_mistakes("bf16", D, folded, MFMA_BASIC)
