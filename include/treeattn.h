@@ -109,13 +109,20 @@ typedef struct {
 #define TA_KERNEL_GENERIC 1   /* scalar fp32-accumulating kernel: any dtype, head_dim, page size.  A plan names this
                                  family also for the fp32 calls that AUTO gives to a matrix-core kernel of their own
                                  (head_dim 64 or 128, power-of-two pages or contiguous, 16-byte aligned rows, at most 256
-                                 query heads per KV head; all products and sums stay fp32) */
+                                 query heads per KV head; all products and sums stay fp32): its table row, plan[11],
+                                 is then -1 */
 #define TA_KERNEL_MFMA 2      /* bf16 matrix-core kernel: head_dim 128 or 64, power-of-two page size (or contiguous),
                                  16-byte aligned q/k/v rows, at most 256 query heads per KV head */
 #define TA_KERNEL_MFMA_BASIC 3 /* as MFMA, but with the key-split matrix-core kernel instead of the pipelined one.  AUTO
                                  takes it for up to 32 query rows per KV head and for more rows in small batches; AUTO and
                                  MFMA take it for head_dim 64, and when the batch is so large, B above 1900, that the
-                                 pipelined kernel's schedule does not fit beside the tiles in LDS. */
+                                 pipelined kernel's schedule does not fit beside the tiles in LDS.  The lengths are not
+                                 known when the choice is made: AUTO takes a batch for as large as its page table
+                                 (max_pages * page_size) allows.  A caller whose tables are many times wider than its
+                                 requests are long, and whose batches are small, can name the kernel instead: with more
+                                 than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 21.5 us
+                                 a call and 27.5), with 32 rows and a few requests of some hundred tokens the pipelined
+                                 kernel a tenth. */
 
 typedef struct {
     float scale;              /* softmax scale; <= 0 or NaN selects 1/sqrt(head_dim) */

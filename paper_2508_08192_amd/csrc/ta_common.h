@@ -192,7 +192,7 @@ __device__ __forceinline__ int64_t ta_ws_row(const TAParams &p, int slot, int rg
 // its read stream (halving the partials took 4.5 % off the KV pass of batches with many short lists), the error is at
 // most 2^-16 of the row's largest value (fp16 would give 2^-11 of each value, too coarse beside the final rounding to
 // bf16 when outputs reach 2 and more), and there is no range to overflow.  A row with a NaN gets a NaN scale.
-// The scalar kernel, whose inputs may be fp32, keeps fp32 partials.
+// The fp32 matrix-core kernel and the scalar one, whose inputs may be fp32, keep fp32 partials.
 typedef short ta_s4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ char *ta_part_row(const TAParams &p, int64_t wrow)      // first byte of partial row wrow

@@ -1,5 +1,5 @@
 // Matrix-core KV pass of libtreeattn for gfx950, fp32 inputs: head_dim 64 or 128, fp32 products and sums throughout
-// (v_mfma_f32_32x32x2_f32, a chain of fp32 multiply-adds per element, rounded as the vector ALU rounds them).
+// (v_mfma_f32_16x16x4_f32, a chain of fp32 multiply-adds per element, rounded as the vector ALU rounds them).
 //
 // A workgroup keeps up to 32 query rows of one (request, KV head); its four waves split the KEYS of its share, each takes
 // every fourth run of 16 tokens with its own running softmax, and their results meet in LDS when the item ends, like in
@@ -17,7 +17,7 @@
 // rows, the products of a run (4096 clocks at head_dim 128 and 32 rows, 3.0 us with everything around them in a wave that
 // has its SIMD for itself), the waves' meeting -- so runs are short and a tile of 64 tokens occupies all four waves at once
 // (runs of 32 tokens: 25.1 us for the call below).  Far above, the memory: at 32 rows a compute unit's products consume
-// 32 KB in 1.7 us and less when two workgroups fill each other's gaps.
+// 64 KB in 1.7 us (four runs of 16 tokens at 1 KB), and its share of 6.8 TB/s in that time is 45 KB.
 // KV pass by kernel trace: B 8, 8/2 heads, head_dim 128, T 8, L 200..4000 (36 MB) 17.9 us, where the vector-ALU kernel took
 // 122; one list of 128 tokens, head_dim 64, 28 rows 7.2, 27.5 there.  Error against 64 bits over sizes of all these ranges:
 // 2.9e-7 of the result (2-norm) where that kernel had 4.0e-7, the first product being summed in two chains.

@@ -1,7 +1,7 @@
 // Scalar (vector-ALU, fp32-accumulating) kernels of libtreeattn: the any-shape KV pass, the merge pass
-// and the stand-alone tree encoder.  The KV pass here is the portable path (fp32 inputs, head dims other
-// than 128, page sizes that are not powers of two); the matrix-core path lives in ta_mfma.hip and shares
-// the schedule and the merge.
+// and the stand-alone tree encoder, write-back and bookkeeping.  The KV pass here is the portable path (head dims other than 64
+// and 128, page sizes that are not powers of two, rows that do not start on 16 bytes); the matrix-core ones live in
+// ta_mfma.hip, ta_mfma_ks.hip and ta_f32.hip and share the schedule and the merge.
 #include <type_traits>
 
 #include "ta_common.h"

@@ -392,12 +392,12 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         p.merge_kind = wide ? TA_MERGE_WIDE : TA_MERGE_ROW;
     }
     // Partial format of the matrix-core kernels: 16-bit fixed point with a scale per row, which halves what the KV pass
-    // writes (C3 128.6 -> 125.0 us, p4 215.1 -> 210.2, C2 26.5 -> 24.1; batch-one shapes 1 to 2 us of 35).  The scalar
-    // kernel, whose inputs may be fp32, keeps fp32 partials.
+    // writes (C3 128.6 -> 125.0 us, p4 215.1 -> 210.2, C2 26.5 -> 24.1; batch-one shapes 1 to 2 us of 35).  The kernels
+    // whose inputs may be fp32 keep fp32 partials.
     p.part_q15 = kernel == TA_KERNEL_MFMA ? 1 : 0;
     // With at least two lists per workgroup most lie whole in a share, and their partial results need not be written,
     // merged and read again (its stores need the alignment that the row merge needs): B 128, 32/8 heads, T 8, L 256..4096
-    // 212.5 -> 205.8 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
+    // 206.6 -> 202.5 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
     p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind == TA_MERGE_ROW && lists >= 2 * (int64_t)pl.n_wg;
     pl.merge_kind = p.merge_kind;
     const int mrows = ta_host_merge_rows(p);
