@@ -68,23 +68,28 @@ int device_state(DeviceState **out, int *dev_out = nullptr)
     return TA_OK;
 }
 
-// Grows the library-owned workspace (caller holds ws_mu).  The old buffer is kept, never freed here.  In steps of 32 MB:
-// fewer buffers on the way, and large pages whatever the calls before needed (steps of 1 MB: the same kernels took up to
-// 1 % longer in one of two sequences of calls, 111.0 us against 109.8, 108.4 and 109.1 with this step).
+void *device_alloc(size_t bytes)
+{
+    void *p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess)
+        return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+// Grows the library-owned workspace (caller holds ws_mu).  The old buffer is kept, never freed here.
 int reserve_locked(DeviceState *s, size_t bytes)
 {
     if (bytes <= s->ws_bytes)
         return TA_OK;
-    bytes = ta_host_align_up(bytes, (size_t)32 << 20);
     void *fresh = nullptr;
-    if (hipMalloc(&fresh, bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    const size_t got = ta_host_grow(bytes, device_alloc, &fresh);
+    if (!got)
         return TA_ERR_HIP;
-    }
     if (s->ws)
         s->retired.push_back(s->ws);
     s->ws = fresh;
-    s->ws_bytes = bytes;
+    s->ws_bytes = got;
     return TA_OK;
 }
 

@@ -140,4 +140,5 @@ void ta_host_fill_plan(const TAProblem &pr, int64_t plan[16]);
 const TADispatchRow *ta_host_dispatch_table(int *n_rows);
 int ta_host_merge_rows(const TAParams &p);       // output rows one workgroup of the merge pass handles
 size_t ta_host_align_up(size_t x, size_t a);
+size_t ta_host_grow(size_t bytes, void *(*alloc)(size_t), void **buf);
 }
