@@ -14,6 +14,8 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # hipcc must not form packed-fp32 instructions on these machines
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first arguments of a kernel are in registers when it starts (see TASched in ta_common.h)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument",
 ]
 

@@ -16,6 +16,38 @@ __device__ __forceinline__ void ta_raise(const TAParams &p, int bits)
         atomicOr(p.status2, bits);
 }
 
+// What a kernel's first loads need is handed over as parameters of its own in front of the argument block: the first words of
+// the arguments are in scalar registers when a wave starts (-amdgpu-kernarg-preload-count in build.py), the block has to be
+// fetched from memory, cold at every launch.  So the lengths (or, in a merge pass, the owners of a list's partial results)
+// and the block are under way together, and not one behind the other.  Measured, calls back to back, without and with:
+// one request, T 64, L 4096 21.4 -> 21.1 us, one KV head and 8192 tokens, folded write-back 16.9 -> 16.3, fp32, three tiles
+// 10.5 -> 10.1, B 32, T 21, L 512..8192 100.9 -> 99.9.
+struct TASched {
+    const int32_t *seq_lens, *kv_start;
+    int64_t sl_s;
+    int32_t B, T, capacity, pad, Hkv, n_wg, min_q;
+};
+#define TA_SCHED_PARAMS                                                                                                  \
+    const int32_t *sc_lens, const int32_t *sc_start, int64_t sc_sl_s, int sc_B, int sc_T, int sc_cap, int sc_pad, int sc_Hkv, \
+        int sc_n_wg, int sc_min_q
+#define TA_SCHED_ARGS(p) \
+    (p).seq_lens, (p).kv_start, (p).sl_s, (p).B, (p).T, (p).capacity, (p).pad, (p).Hkv, (p).n_wg, (p).min_q
+#define TA_SCHED TASched{sc_lens, sc_start, sc_sl_s, sc_B, sc_T, sc_cap, sc_pad, sc_Hkv, sc_n_wg, sc_min_q}
+
+// Reads the argument block's lines at once, and waits for them (and for `x`): called where the first loads are on their way.
+// (The compiler loads an argument where it is first used, so lines that are missing would be waited for one by one.)
+template <typename Args>
+__device__ __forceinline__ void ta_touch_args(int x = 0)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *words;
+    const words a = (words)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr unsigned last = sizeof(Args) / 4 - 1;
+    static_assert(last < 8 * 16, "a word of each line");
+    auto line = [](unsigned i) { return 16 * i < last ? 16 * i : last; };
+    asm volatile("" ::"s"(a[line(1)]), "s"(a[line(2)]), "s"(a[line(3)]), "s"(a[line(4)]), "s"(a[line(5)]), "s"(a[line(6)]),
+                 "s"(a[line(7)]), "s"(x));
+}
+
 // ---------------------------------------------------------------------------------------------
 // Work schedule.  The KV pass walks, for every (request b, KV head g), a list of tiles:
 // ceil(L_b / TA_TILE) prefix tiles followed by one tile holding the T tree tokens.  A malformed
@@ -28,19 +60,22 @@ __device__ __forceinline__ void ta_raise(const TAParams &p, int bits)
 
 // S: first prefix position the request's nodes still attend to (section 3.4, iRoPE for Llama4: the prefix is the current
 // sub-sequence only); 0 unless the caller gave kv_start.
-__device__ __forceinline__ int ta_kv_start(const TAParams &p, int b)
+template <typename P>
+__device__ __forceinline__ int ta_kv_start(const P &p, int b)
 {
     return p.kv_start ? p.kv_start[b] : 0;
 }
 
-__device__ __forceinline__ bool ta_request_ok(const TAParams &p, int L, int S)
+template <typename P>
+__device__ __forceinline__ bool ta_request_ok(const P &p, int L, int S)
 {
     return L >= 0 && (int64_t)L + p.T <= (int64_t)p.capacity && S >= 0 && S <= L;
 }
 
 // Tiles of one list: the 64-token tiles that hold prefix positions S..L-1 (tile S/64 is the first), then the tree
 // tile.  A malformed request owns one tile.
-__device__ __forceinline__ int ta_list_tiles(const TAParams &p, int L, int S)
+template <typename P>
+__device__ __forceinline__ int ta_list_tiles(const P &p, int L, int S)
 {
     if (!ta_request_ok(p, L, S))
         return 1;
@@ -54,43 +89,6 @@ __device__ __forceinline__ int ta_list_tiles(const TAParams &p, int L, int S)
 // and once more per list boundary inside its range -- which is exactly where it meets a padding.  A workgroup whose
 // range touches only the padding of a list has no work in it and writes no partial result.
 //
-// cum[0..B]: exclusive prefix sums of the per-request unit counts (per KV head).  Needs blockDim.x >= 64; ends
-// with a barrier.  If `lens` is given, it also receives the B prefix lengths as they were read, and `starts` the B
-// window starts.
-__device__ __forceinline__ void ta_build_schedule(const TAParams &p, int *cum, int *lens = nullptr,
-                                                  int *starts = nullptr)
-{
-    const int tid = threadIdx.x;
-    for (int b = tid; b < p.B; b += blockDim.x) {
-        const int L = p.seq_lens[(int64_t)b * p.sl_s];
-        const int S = ta_kv_start(p, b);
-        cum[b + 1] = ta_list_tiles(p, L, S) + p.pad;
-        if (lens)
-            lens[b] = L;
-        if (starts)
-            starts[b] = S;
-    }
-    if (tid == 0)
-        cum[0] = 0;
-    __syncthreads();
-    if (tid < TA_WAVE) {
-        int carry = 0;
-        for (int base = 0; base < p.B; base += TA_WAVE) {
-            int idx = base + tid;
-            int x = idx < p.B ? cum[idx + 1] : 0;
-            for (int off = 1; off < TA_WAVE; off <<= 1) {
-                int y = __shfl_up(x, off, TA_WAVE);
-                if (tid >= off)
-                    x += y;
-            }
-            if (idx < p.B)
-                cum[idx + 1] = x + carry;
-            carry += __shfl(x, TA_WAVE - 1, TA_WAVE);
-        }
-    }
-    __syncthreads();
-}
-
 // Inclusive prefix sum over the lanes of a wave.
 __device__ __forceinline__ int ta_wave_scan(int x)
 {
@@ -103,7 +101,65 @@ __device__ __forceinline__ int ta_wave_scan(int x)
     return x;
 }
 
-__device__ __forceinline__ int ta_share(const TAParams &p, int total)
+// cum[0..B]: exclusive prefix sums of the per-request unit counts (per KV head).  Needs blockDim.x >= 64; ends
+// with a barrier.  If `lens` is given, it also receives the B prefix lengths as they were read, and `starts` the B
+// window starts.  Returns the total, cum[B].  Up to 64 requests every wave adds up for itself, in registers.
+__device__ __forceinline__ int ta_build_schedule(const TASched &p, int *cum, int *lens = nullptr, int *starts = nullptr)
+{
+    const int tid = threadIdx.x;
+    const bool wave_each = p.B <= TA_WAVE;
+    int b = wave_each ? tid & (TA_WAVE - 1) : tid;
+    int L = 0, S = 0;
+    if (b < p.B) {
+        L = p.seq_lens[(int64_t)b * p.sl_s];
+        S = ta_kv_start(p, b);
+    }
+    ta_touch_args<TAParams>();
+    if (wave_each) {
+        const int units = b < p.B ? ta_list_tiles(p, L, S) + p.pad : 0;
+        const int x = ta_wave_scan(units);
+        if (tid < p.B) {
+            cum[tid + 1] = x;
+            if (lens)
+                lens[tid] = L;
+            if (starts)
+                starts[tid] = S;
+        }
+        if (tid == 0)
+            cum[0] = 0;
+        __syncthreads();
+        return __builtin_amdgcn_readlane(x, TA_WAVE - 1);
+    }
+    for (; b < p.B; b += blockDim.x) {
+        if (b != tid) {
+            L = p.seq_lens[(int64_t)b * p.sl_s];
+            S = ta_kv_start(p, b);
+        }
+        cum[b + 1] = ta_list_tiles(p, L, S) + p.pad;
+        if (lens)
+            lens[b] = L;
+        if (starts)
+            starts[b] = S;
+    }
+    if (tid == 0)
+        cum[0] = 0;
+    __syncthreads();
+    if (tid < TA_WAVE) {
+        int carry = 0;
+        for (int base = 0; base < p.B; base += TA_WAVE) {
+            const int idx = base + tid;
+            const int x = ta_wave_scan(idx < p.B ? cum[idx + 1] : 0) + carry;
+            if (idx < p.B)
+                cum[idx + 1] = x;
+            carry = __builtin_amdgcn_readlane(x, TA_WAVE - 1);
+        }
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(cum[p.B]);
+}
+
+template <typename P>
+__device__ __forceinline__ int ta_share(const P &p, int total)
 {
     int share = (total + p.n_wg - 1) / p.n_wg;
     return share < p.min_q ? p.min_q : share;
@@ -117,7 +173,8 @@ __device__ __forceinline__ int ta_share(const TAParams &p, int total)
 // ends j tiles inside list j and almost every workgroup enters a second list for a few tiles, at the full fixed cost
 // of an item); cut evenly, every second boundary falls on a list's edge.
 #define TA_EVEN_CUT_FROM 8
-__device__ __forceinline__ void ta_wg_range(const TAParams &p, int total, int w, int &t, int &t_end)
+template <typename P>
+__device__ __forceinline__ void ta_wg_range(const P &p, int total, int w, int &t, int &t_end)
 {
     const int share = ta_share(p, total);
     const int floor_share = p.min_q > TA_EVEN_CUT_FROM ? p.min_q : TA_EVEN_CUT_FROM;
@@ -137,7 +194,8 @@ __device__ __forceinline__ void ta_wg_range(const TAParams &p, int total, int w,
 // Request whose tile lists contain global tile t (0 <= t < Hkv * cum[B]): the number of requests whose lists end at
 // or before t (cum does not decrease), counted 64 requests at a time by the lanes of each wave -- one LDS read and a
 // ballot instead of a binary search's chain of dependent reads.  Every lane of the wave calls this together.
-__device__ __forceinline__ int ta_find_request(const TAParams &p, const int *cum, int t)
+template <typename P>
+__device__ __forceinline__ int ta_find_request(const P &p, const int *cum, int t)
 {
     int x = threadIdx.x;
     asm volatile("" : "+v"(x));           // derived here: a caller short of registers must not keep the lane id alive

@@ -73,8 +73,7 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
         s_cum = ta_wave_scan(s_units);
         total = p.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
     } else {
-        ta_build_schedule(p, cum, lens, starts);
-        total = __builtin_amdgcn_readfirstlane(p.Hkv * cum[p.B]);
+        total = p.Hkv * ta_build_schedule(TASched{TA_SCHED_ARGS(p)}, cum, lens, starts);
     }
     int t, t_end;
     ta_wg_range(p, total, w, t, t_end);

@@ -53,7 +53,7 @@ __device__ __forceinline__ void gen_lds_barrier()
 // tokens of every tile; their loads go out one tile ahead, so that a tile's global round trip runs under the
 // arithmetic of the tile before it, and Q's under the first tile's.
 template <bool BF16, int DCH>
-__global__ __launch_bounds__(GEN_THREADS) void ta_generic_kv_kernel(TAParams p)
+__global__ __launch_bounds__(GEN_THREADS) void ta_generic_kv_kernel(TA_SCHED_PARAMS, TAParams p)
 {
     constexpr int RB = DCH == 1 ? 8 : 4;
     extern __shared__ int smem_i[];
@@ -68,8 +68,7 @@ __global__ __launch_bounds__(GEN_THREADS) void ta_generic_kv_kernel(TAParams p)
     float *vt = kt + TA_TILE * (p.D + 1);                                // [64][D]
     const int ldk = p.D + 1;
 
-    ta_build_schedule(p, cum, lens, starts);
-    const int total = p.Hkv * cum[p.B];
+    const int total = p.Hkv * ta_build_schedule(TA_SCHED, cum, lens, starts);
     const int w = blockIdx.x, rg = blockIdx.y;
     // (the wave index as a scalar: the addresses of a wave's rows and tokens are then scalar arithmetic)
     const int lane = threadIdx.x % TA_WAVE, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / TA_WAVE);
@@ -328,7 +327,7 @@ static hipError_t launch_generic_instance(const TAParams &p, hipStream_t stream,
             return e;
         *attr_done = true;
     }
-    hipLaunchKernelGGL((ta_generic_kv_kernel<BF16, DCH>), dim3(p.n_wg, p.n_rg), dim3(GEN_THREADS), smem, stream, p);
+    hipLaunchKernelGGL((ta_generic_kv_kernel<BF16, DCH>), dim3(p.n_wg, p.n_rg), dim3(GEN_THREADS), smem, stream, TA_SCHED_ARGS(p), p);
     return hipGetLastError();
 }
 
@@ -353,13 +352,14 @@ hipError_t ta_launch_generic(const TAParams &p, hipStream_t stream, int dev)
 // (wave-wide max and sum of the partial log-sum-exps give every partial its weight), then span
 // head-dim columns, with the loads of several partials in flight at once.
 template <bool NEW>
-__global__ __launch_bounds__(GEN_THREADS) void ta_merge_kernel(TAParams p)
+__global__ __launch_bounds__(GEN_THREADS) void ta_merge_kernel(const int32_t *mg_parts, int mg_Hkv, TAParams p)
 {
     const int seg = blockIdx.x;
-    const int b = seg / p.Hkv, g = seg % p.Hkv;
+    const int b = seg / mg_Hkv, g = seg % mg_Hkv;
     const int lane = threadIdx.x % TA_WAVE, wave = threadIdx.x / TA_WAVE;
-    const int w_first = p.ws_parts[2 * seg];                             // left by the KV pass
-    const int n_parts = p.ws_parts[2 * seg + 1] - w_first + 1;
+    const int w_first = mg_parts[2 * seg];                               // left by the KV pass
+    const int n_parts = mg_parts[2 * seg + 1] - w_first + 1;
+    ta_touch_args<TAParams>(n_parts);
     const float LN2 = 0.6931471805599453f;
     const float QNAN = __uint_as_float(0x7fc00000u);
 
@@ -508,15 +508,16 @@ __device__ __forceinline__ float4 ta_part_f4(const ta_s4 &x)
 // them, and in the kernel below, other calls' merges took longer (one list of 512 rows, folded write-back, a workgroup per
 // row: 7.7 -> 8.4 us).
 template <int D, bool NEW, bool HP, bool DONE>
-__global__ __launch_bounds__(256) void ta_merge_row_kernel(TAParams p)
+__global__ __launch_bounds__(256) void ta_merge_row_kernel(const int32_t *mg_parts, int mg_Hkv, TAParams p)
 {
     constexpr int LPR = D / 4, RPW = TA_WAVE / LPR;       // lanes per row, rows per wave
     const int seg = blockIdx.x;
-    const int b = seg / p.Hkv, g = seg % p.Hkv;
+    const int b = seg / mg_Hkv, g = seg % mg_Hkv;
     const int lane = threadIdx.x % TA_WAVE, wave = threadIdx.x / TA_WAVE;
     const int hl = lane % LPR, part = lane / LPR;
-    const int w_first = p.ws_parts[2 * seg];                             // left by the KV pass
-    const int n_parts = p.ws_parts[2 * seg + 1] - w_first + 1;
+    const int w_first = mg_parts[2 * seg];                               // left by the KV pass
+    const int n_parts = mg_parts[2 * seg + 1] - w_first + 1;
+    ta_touch_args<TAParams>(n_parts);
     const float LN2 = 0.6931471805599453f;
     const float QNAN = __uint_as_float(0x7fc00000u);
 
@@ -665,16 +666,17 @@ __global__ __launch_bounds__(256) void ta_merge_row_kernel(TAParams p)
 constexpr int MW_FLIGHT = 8;
 
 template <int D, bool NEW, bool HP>
-__global__ __launch_bounds__(256) void ta_merge_wide_kernel(TAParams p)
+__global__ __launch_bounds__(256) void ta_merge_wide_kernel(const int32_t *mg_parts, int mg_Hkv, TAParams p)
 {
     constexpr int LPR = D / 4, MW_PARTS = 256 / LPR;      // lanes per partial, partials at a time
     __shared__ float red[8];
     __shared__ float4 part[MW_PARTS][LPR];
     const int seg = blockIdx.x, R = blockIdx.y;
-    const int b = seg / p.Hkv, g = seg % p.Hkv;
+    const int b = seg / mg_Hkv, g = seg % mg_Hkv;
     const int tid = threadIdx.x, hw = tid / LPR, hl = tid % LPR, wave = tid >> 6;
-    const int w_first = p.ws_parts[2 * seg];                             // left by the KV pass
-    const int n_parts = p.ws_parts[2 * seg + 1] - w_first + 1;
+    const int w_first = mg_parts[2 * seg];                               // left by the KV pass
+    const int n_parts = mg_parts[2 * seg + 1] - w_first + 1;
+    ta_touch_args<TAParams>(n_parts);
     const float LN2 = 0.6931471805599453f;
     const float QNAN = __uint_as_float(0x7fc00000u);
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
@@ -802,11 +804,11 @@ hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream)
             constexpr int D = decltype(d)::value;
             constexpr bool NEW = decltype(fold)::value, HP = decltype(hp)::value;
             if (p.merge_kind == TA_MERGE_WIDE)
-                hipLaunchKernelGGL((ta_merge_wide_kernel<D, NEW, HP>), grid, dim3(256), smem, stream, p);
+                hipLaunchKernelGGL((ta_merge_wide_kernel<D, NEW, HP>), grid, dim3(256), smem, stream, p.ws_parts, p.Hkv, p);
             else if (p.direct)
-                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP, D == 128 && HP>), grid, dim3(256), smem, stream, p);
+                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP, D == 128 && HP>), grid, dim3(256), smem, stream, p.ws_parts, p.Hkv, p);
             else
-                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP, false>), grid, dim3(256), smem, stream, p);
+                hipLaunchKernelGGL((ta_merge_row_kernel<D, NEW, HP, false>), grid, dim3(256), smem, stream, p.ws_parts, p.Hkv, p);
         };
         auto with = [&](auto d) {
             if (p.kn && p.part_q15)
@@ -826,9 +828,9 @@ hipError_t ta_launch_merge(const TAParams &p, hipStream_t stream)
             return hipErrorInvalidValue;
     } else {
         if (p.kn)
-            hipLaunchKernelGGL(ta_merge_kernel<true>, grid, dim3(GEN_THREADS), smem, stream, p);
+            hipLaunchKernelGGL(ta_merge_kernel<true>, grid, dim3(GEN_THREADS), smem, stream, p.ws_parts, p.Hkv, p);
         else
-            hipLaunchKernelGGL(ta_merge_kernel<false>, grid, dim3(GEN_THREADS), smem, stream, p);
+            hipLaunchKernelGGL(ta_merge_kernel<false>, grid, dim3(GEN_THREADS), smem, stream, p.ws_parts, p.Hkv, p);
     }
     return hipGetLastError();
 }
@@ -860,9 +862,11 @@ hipError_t ta_launch_encode(const int32_t *parent, int64_t par_sb, int B, int T,
 // (length, page id, store); a thread's first piece is on its way meanwhile, and with 16-byte pieces it is usually the only
 // one (Hkv 8, head_dim 128: 256 pieces).  B 8, T 16, Hkv 8: 4.0 us by single elements, 3.4 now.
 template <typename P>
-__global__ __launch_bounds__(256) void ta_append_kernel(TAAppend a)
+__global__ __launch_bounds__(256) void ta_append_kernel(const int32_t *seq_lens, int64_t sl_s, TAAppend a)
 {
     const int b = blockIdx.x, i = blockIdx.y;
+    const int L = seq_lens[(int64_t)b * sl_s];
+    ta_touch_args<TAAppend>(L);
     const int es = a.elem_bytes;
     const int per_row = a.D * es / (int)sizeof(P), half = a.Hkv * per_row;        // pieces of a row; of all K (or V) rows
     auto source = [&](int x) {
@@ -874,7 +878,6 @@ __global__ __launch_bounds__(256) void ta_append_kernel(TAAppend a)
     P first;
     if ((int)threadIdx.x < 2 * half)
         first = *source(threadIdx.x);
-    const int L = a.seq_lens[(int64_t)b * a.sl_s];
     if (L < 0 || (int64_t)L + a.T > (int64_t)a.capacity) {
         if (threadIdx.x == 0 && i == 0)
             atomicOr(a.status, TA_STATUS_BAD_SEQLEN);
@@ -911,14 +914,16 @@ __global__ __launch_bounds__(256) void ta_append_kernel(TAAppend a)
 constexpr int CP_THREADS = 512, CP_REGS = 8;
 
 template <typename P>
-__global__ __launch_bounds__(CP_THREADS) void ta_compact_kernel(TACompact c)
+__global__ __launch_bounds__(CP_THREADS) void ta_compact_kernel(const int32_t *seq_lens, int64_t sl_s, const int32_t *n_accepted,
+                                                                int64_t na_s, TACompact c)
 {
     __shared__ int ids[TA_MAX_TREE];
     __shared__ int64_t k_at[TA_MAX_TREE], v_at[TA_MAX_TREE];       // element offsets of position L + i's rows of KV head 0
     __shared__ int bad;
     const int b = blockIdx.x, tid = threadIdx.x;
-    const int L = c.seq_lens[(int64_t)b * c.sl_s];
-    const int n = c.n_accepted[(int64_t)b * c.na_s];
+    const int L = seq_lens[(int64_t)b * sl_s];
+    const int n = n_accepted[(int64_t)b * na_s];
+    ta_touch_args<TACompact>(L + n);
     const bool n_ok = n >= 0 && n <= c.A;
     // the positions rows come from (L .. L+T-1) and go to (L .. L+n-1; a path may name a node twice and be longer than T)
     const int span = n_ok ? max(c.T, n) : c.T;
@@ -994,11 +999,11 @@ hipError_t ta_launch_compact(const TACompact &c, hipStream_t stream)
 {
     const dim3 grid(c.B), block(CP_THREADS);
     if (c.vec)                          // rows in 16-byte pieces
-        hipLaunchKernelGGL(ta_compact_kernel<uint4>, grid, block, 0, stream, c);
+        hipLaunchKernelGGL(ta_compact_kernel<uint4>, grid, block, 0, stream, c.seq_lens, c.sl_s, c.n_accepted, c.na_s, c);
     else if (c.elem_bytes == 2)
-        hipLaunchKernelGGL(ta_compact_kernel<uint16_t>, grid, block, 0, stream, c);
+        hipLaunchKernelGGL(ta_compact_kernel<uint16_t>, grid, block, 0, stream, c.seq_lens, c.sl_s, c.n_accepted, c.na_s, c);
     else
-        hipLaunchKernelGGL(ta_compact_kernel<uint32_t>, grid, block, 0, stream, c);
+        hipLaunchKernelGGL(ta_compact_kernel<uint32_t>, grid, block, 0, stream, c.seq_lens, c.sl_s, c.n_accepted, c.na_s, c);
     return hipGetLastError();
 }
 
@@ -1006,11 +1011,11 @@ hipError_t ta_launch_append(const TAAppend &a, hipStream_t stream)
 {
     const dim3 grid(a.B, a.T), block(256);
     if (a.vec)                          // rows in 16-byte pieces
-        hipLaunchKernelGGL(ta_append_kernel<uint4>, grid, block, 0, stream, a);
+        hipLaunchKernelGGL(ta_append_kernel<uint4>, grid, block, 0, stream, a.seq_lens, a.sl_s, a);
     else if (a.elem_bytes == 2)
-        hipLaunchKernelGGL(ta_append_kernel<uint16_t>, grid, block, 0, stream, a);
+        hipLaunchKernelGGL(ta_append_kernel<uint16_t>, grid, block, 0, stream, a.seq_lens, a.sl_s, a);
     else
-        hipLaunchKernelGGL(ta_append_kernel<uint32_t>, grid, block, 0, stream, a);
+        hipLaunchKernelGGL(ta_append_kernel<uint32_t>, grid, block, 0, stream, a.seq_lens, a.sl_s, a);
     return hipGetLastError();
 }
 

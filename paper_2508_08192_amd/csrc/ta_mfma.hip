@@ -91,22 +91,22 @@ struct SpTag {
 // NEW: the tree tokens' K/V come from the dense tensors of ta_opts.k_new / v_new (an instance of its own, so that the
 // ordinary call carries none of that addressing).
 template <bool NEW>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_mfma_sp_kernel(TAParams p)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_mfma_sp_kernel(TA_SCHED_PARAMS, TAParams p)
 {
+    const TASched sc = TA_SCHED;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     unsigned long long *masks = (unsigned long long *)(smem + SP_AUX_OFF);
     int *flag = (int *)(masks + TA_MAX_TREE);
     int *par_s = flag + 4;                                                // [TA_MAX_TREE]
     int *pcache = par_s + TA_MAX_TREE;                                    // [PP_PAGES] page ids of the current span
     int *cum = pcache + PP_PAGES;                                         // [B + 1] schedule, then [B] prefix lengths
-    int *lens = cum + p.B + 1;
-    int *starts = lens + p.B;                                             // [B] window starts
+    int *lens = cum + sc.B + 1;
+    int *starts = lens + sc.B;                                            // [B] window starts
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char *)smem);
 
     if (threadIdx.x == 0)
         flag[1] = 0;                   // set by an item that meets a bad page id or a bad given mask; see `bad` below
-    ta_build_schedule(p, cum, lens, starts);
-    const int total = __builtin_amdgcn_readfirstlane(p.Hkv * cum[p.B]);
+    const int total = sc.Hkv * ta_build_schedule(sc, cum, lens, starts);
     const int w = blockIdx.x, rg = blockIdx.y;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
     int t, t_end;
     {
         int t0, t1;
-        ta_wg_range(p, total, w, t0, t1);
+        ta_wg_range(sc, total, w, t0, t1);
         t = __builtin_amdgcn_readfirstlane(t0);
         t_end = __builtin_amdgcn_readfirstlane(t1);
     }
@@ -616,8 +616,8 @@ hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
     }
     const dim3 grid(p.n_wg, p.n_rg);
     if (p.kn)
-        hipLaunchKernelGGL((ta_mfma_sp_kernel<true>), grid, dim3(512), smem, stream, p);
+        hipLaunchKernelGGL((ta_mfma_sp_kernel<true>), grid, dim3(512), smem, stream, TA_SCHED_ARGS(p), p);
     else
-        hipLaunchKernelGGL((ta_mfma_sp_kernel<false>), grid, dim3(512), smem, stream, p);
+        hipLaunchKernelGGL((ta_mfma_sp_kernel<false>), grid, dim3(512), smem, stream, TA_SCHED_ARGS(p), p);
     return hipGetLastError();
 }

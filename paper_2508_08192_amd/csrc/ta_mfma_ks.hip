@@ -114,15 +114,16 @@ static size_t ks_smem(int B)
 // DIRECT: the outputs of a list that lies in one share are written here (an instance of its own: calls without many lists
 // are 1 % slower with that code in the kernel)
 template <int DH, int RB, int NW, int OCC, bool DIRECT>
-__global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAParams p)
+__global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SCHED_PARAMS, TAParams p)
 {
+    const TASched sc = TA_SCHED;
     using C = KsShape<DH, RB, NW, OCC>;
     constexpr int NKK = DH / 16, NDB = DH / 32, SLOTS = DH / 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float *stat = (float *)(smem + C::RING);                            // [NW][3][ROWS]: reference, sum, sum of rounded
     int *wbad = (int *)(stat + 3 * NW * C::ROWS);                        // [NW]: TA_STATUS_* bits a wave has met
     int *cum = wbad + NW;                                                 // more than 64 requests: [B + 1] schedule
-    int *lens = cum + p.B + 1, *starts = lens + p.B;                      // and, up to KS_LENS, lengths and window starts
+    int *lens = cum + sc.B + 1, *starts = lens + sc.B;                      // and, up to KS_LENS, lengths and window starts
     const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) char *)smem);
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -131,22 +132,23 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
     const int r32 = lane & 31, hf = lane >> 5;
     // Schedule (see ta_build_schedule).  Up to 64 requests every wave keeps it in registers, lane b for request b: no
     // exchange between the waves, which start on their own.
-    const bool in_regs = p.B <= TA_WAVE;
+    const bool in_regs = sc.B <= TA_WAVE;
     int s_len = 0, s_start = 0, s_units = 0, s_cum = 0, total;
     if (in_regs) {
-        if (lane < p.B) {
-            s_len = p.seq_lens[(int64_t)lane * p.sl_s];
-            s_start = ta_kv_start(p, lane);
-            s_units = ta_list_tiles(p, s_len, s_start) + p.pad;
+        if (lane < sc.B) {
+            s_len = sc.seq_lens[(int64_t)lane * sc.sl_s];
+            s_start = ta_kv_start(sc, lane);
         }
+        ta_touch_args<TAParams>();
+        if (lane < sc.B)
+            s_units = ta_list_tiles(sc, s_len, s_start) + sc.pad;
         s_cum = ta_wave_scan(s_units);
-        total = p.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
+        total = sc.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
     } else {
-        ta_build_schedule(p, cum, p.B <= KS_LENS ? lens : nullptr, p.B <= KS_LENS ? starts : nullptr);
-        total = __builtin_amdgcn_readfirstlane(p.Hkv * cum[p.B]);
+        total = sc.Hkv * ta_build_schedule(sc, cum, sc.B <= KS_LENS ? lens : nullptr, sc.B <= KS_LENS ? starts : nullptr);
     }
     int t, t_end;
-    ta_wg_range(p, total, w, t, t_end);
+    ta_wg_range(sc, total, w, t, t_end);
     t = __builtin_amdgcn_readfirstlane(t);
     t_end = __builtin_amdgcn_readfirstlane(t_end);
     const int rows_here = min(C::ROWS, p.rows - row0);
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
     unsigned long long gmask = 0;
     const uint16_t *kgp = nullptr, *vgp = nullptr;
     auto sub_pos = [&](int u) { return u < n_pre ? lo + u * KS_SUB : L + (u - n_pre) * KS_SUB; };
-    auto sub_end = [&](int u) { return u < n_pre ? min(hi, lo + (u + 1) * KS_SUB) : L + min(p.T, (u - n_pre + 1) * KS_SUB); };
+    auto sub_end = [&](int u) { return u < n_pre ? min(hi, lo + (u + 1) * KS_SUB) : L + min(sc.T, (u - n_pre + 1) * KS_SUB); };
     // this wave's run among those that are not full: the ragged end of the prefix and the tree's (n_sub: none)
     auto last_own = [&]() {
         const int u = n_full + ((wave - n_full) & (NW - 1));
@@ -211,22 +213,22 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
         while (t < t_end) {
             int cum_b, cum_e;
             if (in_regs) {
-                b = __popcll(__ballot(p.Hkv * s_cum <= t));
+                b = __popcll(__ballot(sc.Hkv * s_cum <= t));
                 cum_e = __builtin_amdgcn_readlane(s_cum, b);
                 cum_b = cum_e - __builtin_amdgcn_readlane(s_units, b);
             } else {
                 if (b < 0)
-                    b = ta_find_request(p, cum, t);
-                else if ((int64_t)p.Hkv * cum[b + 1] <= t)
+                    b = ta_find_request(sc, cum, t);
+                else if ((int64_t)sc.Hkv * cum[b + 1] <= t)
                     ++b;
                 b = __builtin_amdgcn_readfirstlane(b);
                 cum_b = __builtin_amdgcn_readfirstlane(cum[b]);
                 cum_e = __builtin_amdgcn_readfirstlane(cum[b + 1]);
             }
             const int n_u = cum_e - cum_b;                          // schedule units of one list
-            g = (t - p.Hkv * cum_b) / n_u;
-            const int seg_start = p.Hkv * cum_b + g * n_u;
-            const int n_b = n_u - p.pad;
+            g = (t - sc.Hkv * cum_b) / n_u;
+            const int seg_start = sc.Hkv * cum_b + g * n_u;
+            const int n_b = n_u - sc.pad;
             const int j0 = t - seg_start;
             const int j1 = min(n_b, t_end - seg_start);
             if (j1 <= j0) {
@@ -234,17 +236,17 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
                 continue;
             }
             t = seg_start + (j1 == n_b ? n_u : j1);
-            slot = w + b * p.Hkv + g;
+            slot = w + b * sc.Hkv + g;
             whole = DIRECT && j0 == 0 && j1 == n_b;
             ta_note_owner(p, b, g, w, j0, j1, n_b, whole);
             if (in_regs) {
                 L = __builtin_amdgcn_readlane(s_len, b);
                 S = __builtin_amdgcn_readlane(s_start, b);
             } else {
-                L = __builtin_amdgcn_readfirstlane(p.B <= KS_LENS ? lens[b] : p.seq_lens[(int64_t)b * p.sl_s]);
-                S = __builtin_amdgcn_readfirstlane(p.B <= KS_LENS ? starts[b] : ta_kv_start(p, b));
+                L = __builtin_amdgcn_readfirstlane(sc.B <= KS_LENS ? lens[b] : sc.seq_lens[(int64_t)b * sc.sl_s]);
+                S = __builtin_amdgcn_readfirstlane(sc.B <= KS_LENS ? starts[b] : ta_kv_start(sc, b));
             }
-            bad = ta_request_ok(p, L, S) ? 0 : TA_STATUS_BAD_SEQLEN;
+            bad = ta_request_ok(sc, L, S) ? 0 : TA_STATUS_BAD_SEQLEN;
             const int tile0 = bad ? 0 : S / TA_TILE;
             has_tree = j1 == n_b;
             const int jp = has_tree ? n_b - 1 : j1;
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             hi = min((tile0 + jp) * TA_TILE, L);
             n_pre = !bad && hi > lo ? (hi - lo + KS_SUB - 1) / KS_SUB : 0;
             n_full = !bad && hi > lo ? (hi - lo) / KS_SUB : 0;
-            n_sub = bad ? 0 : n_pre + (has_tree ? (p.T + KS_SUB - 1) / KS_SUB : 0);
+            n_sub = bad ? 0 : n_pre + (has_tree ? (sc.T + KS_SUB - 1) / KS_SUB : 0);
             kgp = (const uint16_t *)p.k + (int64_t)g * p.k_sh;
             vgp = (const uint16_t *)p.v + (int64_t)g * p.v_sh;
             if (wave >= n_sub)
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
                 if (ul < n_sub)
                     pg_last = page_of(max(S, min(sub_pos(ul) + (l & 31), sub_end(ul) - 1)));
             }
-            if (ul < n_sub && ul >= n_pre && l < p.T) {
+            if (ul < n_sub && ul >= n_pre && l < sc.T) {
                 if (p.masks_in)
                     gmask = ta_given_mask(p, b, l);
                 else
@@ -423,11 +425,11 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TAPar
             bool wrong = false;
             if (p.masks_in) {
                 m = gmask;
-                wrong = l < p.T && !ta_given_mask_ok(m, l);
+                wrong = l < sc.T && !ta_given_mask_ok(m, l);
             } else {
-                int cur = l < p.T ? l : -1;
+                int cur = l < sc.T ? l : -1;
                 for (int steps = 0; __any(cur >= 0); ++steps) {
-                    wrong |= cur >= 0 && (cur >= p.T || steps >= p.T);
+                    wrong |= cur >= 0 && (cur >= sc.T || steps >= sc.T);
                     if (cur >= 0)
                         m |= 1ull << (cur & 63);
                     const int up = __shfl(parent, cur & 63, TA_WAVE);
@@ -703,7 +705,7 @@ static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
         attr_set[dev] = true;
     }
     hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC, DIRECT>), dim3(p.n_wg, (p.rows + 32 * RB - 1) / (32 * RB)), dim3(64 * NW), smem,
-                       stream, p);
+                       stream, TA_SCHED_ARGS(p), p);
     return hipGetLastError();
 }
 
