@@ -181,7 +181,7 @@ __device__ __forceinline__ void ta_wg_range(const P &p, int total, int w, int &t
     const int n_act = (int64_t)p.n_wg * floor_share <= total ? p.n_wg : (total + share - 1) / share;
     // floor(k * total / n_act) = k * q + floor(k * r / n_act) with total = q * n_act + r: 32-bit divisions (k * r stays
     // below n_act squared) instead of two 64-bit ones, which cost every workgroup most of a microsecond at its start
-    if (n_act <= 0xffff) {
+    if (__builtin_expect(n_act <= 0xffff, 1)) {
         const unsigned n = n_act > 0 ? (unsigned)n_act : 1u, q = (unsigned)total / n, r = (unsigned)total - q * n;
         t = w >= n_act ? total : (int)((unsigned)w * q + (unsigned)w * r / n);
         t_end = w + 1 >= n_act ? total : (int)((unsigned)(w + 1) * q + (unsigned)(w + 1) * r / n);

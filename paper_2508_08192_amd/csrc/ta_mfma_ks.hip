@@ -15,6 +15,11 @@
 // Head_dim 128 takes it where it is the faster of the two (the measured line stands in ta_host.cpp): calls of B 1, 32/8
 // heads, T 64, L 4096 (256 rows) 27.5 -> 21.5 us, B 128, T 8, L 256..4096 208.4 -> 206.6 against the pipelined kernel.
 //
+// Q is loaded once per workgroup, whole rows at a time, and handed to the waves through LDS; with each wave loading its own
+// fragments, 32 rows by 32 scattered bytes at a time, and all eight waves' blocks added up whether or not a wave had a
+// run, the calls of one request took 0.8 us longer (one KV head, 8192 tokens, folded: 16.3 -> 15.5 us; T 64, L 4096
+// 20.5 -> 20.2; head_dim 64, B 16 41.2 -> 39.6).
+//
 // What bounds it: the HBM stream.  In its loop a compute unit of head_dim 64 and 64 rows streams at the memory's rate
 // (16 lists x 16384 tokens x 8 heads, 538 MB: 93 us, 5.8 TB/s); beside it stand 4.5 us at the start without a byte on
 // its way (lengths, then page ids and Q, then the first tokens: three round trips and the instructions between them) and
@@ -47,6 +52,20 @@ __device__ __forceinline__ float ks_swap_max(float x)      // over the two lanes
 {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Largest x of the LPR (8 or 16) neighbouring lanes that share an output row, in each of them.
+template <int LPR>
+__device__ __forceinline__ uint32_t ks_row_max(uint32_t x)
+{
+    static_assert(LPR == 8 || LPR == 16, "lanes of a row");
+    auto up = [&](uint32_t y) { x = y > x ? y : x; };
+    up(__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false));     // lanes 1 0 3 2 of every four
+    up(__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false));     // 2 3 0 1
+    up(__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false));    // mirrored within eight
+    if (LPR == 16)
+        up(__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));    // rotated by eight within sixteen
+    return x;
 }
 
 __device__ __forceinline__ void ks_lds_barrier()
@@ -100,14 +119,16 @@ struct KsShape {
     static constexpr int RPL = KS_SUB / LD;                // token rows per load
     static constexpr int ROWS = 32 * RB;
     static constexpr int NT = 64 * NW;
+    static constexpr int QB = ROWS * ROW;                  // bytes of the Q rows, one 16-byte piece a thread
+    static_assert(QB / 16 <= NT, "one piece of Q a thread");
     static_assert(NS >= 1 && NS <= 2 && REGION >= ROWS * DH * 4, "ring and staging area");
-    static_assert(NW >= 4, "at most one of a list's last three runs per wave");
+    static_assert(NW >= 4 && NW % 4 == 0, "at most one of a list's last three runs per wave; results are added up in fours");
 };
 
 template <int DH, int RB, int NW, int OCC>
 static size_t ks_smem(int B)
 {
-    return KsShape<DH, RB, NW, OCC>::RING + sizeof(float) * 3 * NW * 32 * RB + sizeof(int) * NW +
+    return KsShape<DH, RB, NW, OCC>::RING + KsShape<DH, RB, NW, OCC>::QB + sizeof(float) * 3 * NW * 32 * RB + sizeof(int) * NW +
            (B <= TA_WAVE ? 0 : sizeof(int) * (B + 2 + (B <= KS_LENS ? 2 * B : 0)));
 }
 
@@ -120,7 +141,8 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
     using C = KsShape<DH, RB, NW, OCC>;
     constexpr int NKK = DH / 16, NDB = DH / 32, SLOTS = DH / 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    float *stat = (float *)(smem + C::RING);                            // [NW][3][ROWS]: reference, sum, sum of rounded
+    char *const qrows = smem + C::RING;                                 // Q rows of the item, placed like a run's K rows
+    float *stat = (float *)(qrows + C::QB);                              // [NW][3][ROWS]: reference, sum, sum of rounded
     int *wbad = (int *)(stat + 3 * NW * C::ROWS);                        // [NW]: TA_STATUS_* bits a wave has met
     int *cum = wbad + NW;                                                 // more than 64 requests: [B + 1] schedule
     int *lens = cum + sc.B + 1, *starts = lens + sc.B;                      // and, up to KS_LENS, lengths and window starts
@@ -191,7 +213,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
     // 32 from lo, and the T tree tokens; run u belongs to wave u % NW
     int b = -1, g = 0, slot = 0, L = 0, S = 0, lo = 0, hi = 0, n_pre = 0, n_sub = 0, n_full = 0, bad = 0;
     bool has_tree = false, whole = false;                  // whole: a list that lies in this share alone
-    uint4 qf[RB][NKK];
+    uint4 q_piece = make_uint4(0, 0, 0, 0);                // this thread's piece of the item's Q rows
     int pg = 0, pg_first = 0, pg_last = 0, parent = 0;     // pages of full runs, of the first and of the last run; tree
     unsigned long long gmask = 0;
     const uint16_t *kgp = nullptr, *vgp = nullptr;
@@ -257,21 +279,19 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
             n_sub = bad ? 0 : n_pre + (has_tree ? (sc.T + KS_SUB - 1) / KS_SUB : 0);
             kgp = (const uint16_t *)p.k + (int64_t)g * p.k_sh;
             vgp = (const uint16_t *)p.v + (int64_t)g * p.v_sh;
+            const int l = fresh_lane();
+            {
+                // rows past the group's end repeat its first row (their results are never stored)
+                const int x = wave * 64 + l, row = x / SLOTS;
+                if (C::QB / 16 == C::NT || row < C::ROWS) {
+                    const int R = row0 + (row < rows_here ? row : 0);
+                    const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);      // R / G
+                    q_piece = *(const uint4 *)((const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
+                                               (int64_t)(g * p.G + R - node * p.G) * p.q_sh + 8 * (x % SLOTS));
+                }
+            }
             if (wave >= n_sub)
                 return true;                                       // nothing to walk for this wave
-            const int l = fresh_lane();
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                // Q fragments; rows past the group's end repeat its first row (their results are never stored)
-                const int row = rb * 32 + (l & 31);
-                const int R = row0 + (row < rows_here ? row : 0);
-                const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);          // R / G
-                const uint16_t *qp = (const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
-                                     (int64_t)(g * p.G + R - node * p.G) * p.q_sh + (l >> 5) * 8;
-#pragma unroll
-                for (int kk = 0; kk < NKK; ++kk)
-                    qf[rb][kk] = *(const uint4 *)(qp + kk * 16);
-            }
             const int ul = last_own();
             if (paged) {
                 pg = load_pages(0);
@@ -313,14 +333,10 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         }
         const int u_last = last_own();
         int u = wave, pg_base = 0;
+        // everything requested is here: no wait of the compiler for it may fall behind the loads into LDS, which it does
+        // not know of
+        asm volatile("" : "+v"(q_piece.x), "+v"(q_piece.y), "+v"(q_piece.z), "+v"(q_piece.w));
         if (u < n_sub) {
-            // everything requested is here: no wait of the compiler for it may fall behind the loads into LDS, which it
-            // does not know of
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                for (int kk = 0; kk < NKK; ++kk)
-                    asm volatile("" : "+v"(qf[rb][kk].x), "+v"(qf[rb][kk].y), "+v"(qf[rb][kk].z), "+v"(qf[rb][kk].w));
             asm volatile("" : "+v"(pg), "+v"(pg_first), "+v"(pg_last), "+v"(parent), "+v"(gmask));
             if (paged) {
                 pg = checked(pg);
@@ -376,7 +392,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
                 const int first = max(pos0, S), end = sub_end(u);
                 const int pgr = u == u_last ? pg_last : pg_first;
                 const bool own_pages = paged && u != u_last && u != 0;             // pages of fewer than eight tokens
-#pragma unroll 1
+#pragma unroll 4
                 for (int k = 0; k < C::LD; ++k) {
                     const int row = k * C::RPL + lrow;
                     int pos = pos0 + row;
@@ -410,7 +426,22 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         for (int k = 0; k < 2 * C::NS; ++k)                    // K and V of the wave's first run, and of its second
             if (u + (k >> 1) * NW < n_sub)
                 issue(u + (k >> 1) * NW, k >> 1, k & 1);
-        // while the first runs are on their way: O = 0 and, in a wave that has tree tokens, the ancestor masks
+        // while the first runs are on their way: Q rows to LDS and from there as fragments into every wave's registers (each
+        // wave loading its own, 32 rows by 32 scattered bytes at a time, kept the load units busy for most of a microsecond),
+        // O = 0 and, in a wave that has tree tokens, the ancestor masks
+        uint4 qf[RB][NKK];
+        {
+            const int l = fresh_lane(), x = wave * 64 + l, row = x / SLOTS;
+            if (C::QB / 16 == C::NT || row < C::ROWS)
+                *(uint4 *)(qrows + row * C::ROW + (((x % SLOTS) ^ kx(row)) << 4)) = q_piece;
+            ks_lds_barrier();
+            if (u < n_sub)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int kk = 0; kk < NKK; ++kk)
+                        qf[rb][kk] = *(const uint4 *)(qrows + rb * 32 * C::ROW + kf_row + (((2 * kk + hf) ^ kf_x) << 4));
+        }
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -573,6 +604,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
 
         // ---- the waves' results meet: each stages its RB * 32 x DH block (16-byte chunk ch of row r at chunk
         // ch ^ (r & 15)) in its own part of the ring, then every thread adds up its columns of one row over the waves
+        const int n_live = min(NW, (n_sub + 3) & ~3);          // waves that had runs, in fours
         const int l_e = fresh_lane(), r32_e = l_e & 31, hf_e = l_e >> 5;
         {
             float *stage = (float *)(smem + wave * C::REGION);
@@ -593,6 +625,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
                     stat[(wave * 3 + 1) * C::ROWS + row] = l_tot;
                     stat[(wave * 3 + 2) * C::ROWS + row] = l2_tot;
                 }
+                if (wave < n_live)                             // (nobody reads what the others would put there)
 #pragma unroll
                 for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -626,41 +659,44 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
             for (int i = 0; i < CPT; ++i)
                 acc[i] = 0.f;
 #pragma unroll
-            for (int k = 0; k < NW; ++k) {
-                const float wgt = mw[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[k] - big);
-                l_tot = fmaf(wgt, stat[(k * 3 + 1) * C::ROWS + row], l_tot);
-                l2_tot = fmaf(wgt, stat[(k * 3 + 2) * C::ROWS + row], l2_tot);
+            for (int k0 = 0; k0 < NW; k0 += 4)
+                if (k0 < n_live) {
 #pragma unroll
-                for (int q = 0; q < CPT / 4; ++q) {
-                    const float4 x = *(const float4 *)(smem + k * C::REGION + (row * DH + (((c0 + q) ^ (row & 15)) << 2)) * 4);
-                    acc[4 * q + 0] = fmaf(wgt, x.x, acc[4 * q + 0]);
-                    acc[4 * q + 1] = fmaf(wgt, x.y, acc[4 * q + 1]);
-                    acc[4 * q + 2] = fmaf(wgt, x.z, acc[4 * q + 2]);
-                    acc[4 * q + 3] = fmaf(wgt, x.w, acc[4 * q + 3]);
+                    for (int k = k0; k < k0 + 4; ++k) {
+                        const float wgt = mw[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[k] - big);
+                        l_tot = fmaf(wgt, stat[(k * 3 + 1) * C::ROWS + row], l_tot);
+                        l2_tot = fmaf(wgt, stat[(k * 3 + 2) * C::ROWS + row], l2_tot);
+#pragma unroll
+                        for (int q = 0; q < CPT / 4; ++q) {
+                            const float4 x = *(const float4 *)(smem + k * C::REGION + (row * DH + (((c0 + q) ^ (row & 15)) << 2)) * 4);
+                            acc[4 * q + 0] = fmaf(wgt, x.x, acc[4 * q + 0]);
+                            acc[4 * q + 1] = fmaf(wgt, x.y, acc[4 * q + 1]);
+                            acc[4 * q + 2] = fmaf(wgt, x.z, acc[4 * q + 2]);
+                            acc[4 * q + 3] = fmaf(wgt, x.w, acc[4 * q + 3]);
+                        }
+                    }
                 }
-            }
             const float inv = any_bad ? 0.f : 1.f / l2_tot;
-            float amax = 0.f, nan_seen = 0.f;
+            // largest magnitude of the row, as bits: those of a NaN are above all others
+            uint32_t top = 0;
 #pragma unroll
             for (int i = 0; i < CPT; ++i) {
                 acc[i] *= inv;
-                amax = fmaxf(amax, fabsf(acc[i]));
-                nan_seen = acc[i] != acc[i] ? 1.f : nan_seen;
+                const uint32_t mag = __float_as_uint(acc[i]) & 0x7fffffffu;
+                top = mag > top ? mag : top;
             }
-#pragma unroll
-            for (int off = 1; off < TPR; off <<= 1) {
-                amax = fmaxf(amax, __shfl_xor(amax, off, TA_WAVE));
-                nan_seen = fmaxf(nan_seen, __shfl_xor(nan_seen, off, TA_WAVE));
-            }
+            top = ks_row_max<TPR>(top);
+            const bool nan_seen = top > 0x7f800000u;
+            const float amax = nan_seen ? 0.f : __uint_as_float(top);
             float scale, to_q;
-            ta_q15_scale(amax, nan_seen > 0.f, scale, to_q);
+            ta_q15_scale(amax, nan_seen, scale, to_q);
             const float lse2 = any_bad ? __uint_as_float(0x7fc00000u) : big + log2f(l_tot);
             if (DIRECT && whole_e) {
                 // no merge: the rows go out as they are, by its rules: a NaN or an infinity spoils its row (the 16-bit format
                 // holds neither), and no score above -inf leaves no log-sum-exp either
                 if (row < rows_here) {
                     const int R = row0 + row, node = (int)__umulhi((uint32_t)R << 8, p.g_magic), h = g_e * p.G + R - node * p.G;
-                    const bool nan = any_bad || nan_seen > 0.f || amax == INFINITY || lse2 != lse2;
+                    const bool nan = any_bad || nan_seen || amax == INFINITY || lse2 != lse2;
                     uint32_t *dst = (uint32_t *)((uint16_t *)p.out + (int64_t)b_e * p.o_sb + (int64_t)node * p.o_st +
                                                  (int64_t)h * p.o_sh + 4 * c0);
 #pragma unroll
