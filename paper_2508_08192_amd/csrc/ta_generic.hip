@@ -507,6 +507,8 @@ __device__ __forceinline__ float4 ta_part_f4(const ta_s4 &x)
 // DONE: some lists' outputs were written by the KV pass (p.direct).  Instances of their own: with the early way out in all of
 // them, and in the kernel below, other calls' merges took longer (one list of 512 rows, folded write-back, a workgroup per
 // row: 7.7 -> 8.4 us).
+constexpr int MR_FLIGHT = 4;                            // partials of a row in flight
+
 template <int D, bool NEW, bool HP, bool DONE>
 __global__ __launch_bounds__(256) void ta_merge_row_kernel(const int32_t *mg_parts, int mg_Hkv, TAParams p)
 {
@@ -566,6 +568,17 @@ __global__ __launch_bounds__(256) void ta_merge_row_kernel(const int32_t *mg_par
                 lk = p.ws_lse[(row0 + hl * pstride) * LS];
             }
         }
+        // The first partials' columns are requested with them, the next ones behind the sums over the former: one round
+        // trip less (B 8, 32/8 heads, T 16, L 300..2900, two to four partials per list).  (All rows of a wave belong to
+        // the same list, so n_parts and with it every branch here is uniform over the wave.)
+        typename ta_part_raw<HP>::type v[MR_FLIGHT];
+        auto fetch = [&](int k) {
+#pragma unroll
+            for (int u = 0; u < MR_FLIGHT; ++u)
+                if (k + u < n_parts)
+                    v[u] = ta_part_load4<HP>(o0 + (k + u) * ostride);
+        };
+        fetch(0);
         if constexpr (NEW)
             ta_scatter_locate(p, b, g, sc);
         const bool nan_seen = ta_part_max<LPR>(lk != lk ? 1.f : 0.f) > 0.f;
@@ -575,39 +588,20 @@ __global__ __launch_bounds__(256) void ta_merge_row_kernel(const int32_t *mg_par
         lse2 = nan_seen ? QNAN : mx + log2f(den);
         const float wk = nan_seen ? QNAN : ek / den * sk;
         const int src0 = lane - hl;
-        int k = 0;
-        for (; k + 4 <= n_parts; k += 4) {
-            typename ta_part_raw<HP>::type v[4];
+        for (int k = 0; k < n_parts; k += MR_FLIGHT) {
+            if (k > 0)
+                fetch(k);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                v[u] = ta_part_load4<HP>(o0 + (k + u) * ostride);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float wgt = __shfl(wk, src0 + k + u, TA_WAVE);
-                const float4 x = ta_part_f4(v[u]);
-                acc.x = fmaf(wgt, x.x, acc.x);
-                acc.y = fmaf(wgt, x.y, acc.y);
-                acc.z = fmaf(wgt, x.z, acc.z);
-                acc.w = fmaf(wgt, x.w, acc.w);
-            }
+            for (int u = 0; u < MR_FLIGHT; ++u)
+                if (k + u < n_parts) {
+                    const float wgt = __shfl(wk, src0 + k + u, TA_WAVE);
+                    const float4 x = ta_part_f4(v[u]);
+                    acc.x = fmaf(wgt, x.x, acc.x);
+                    acc.y = fmaf(wgt, x.y, acc.y);
+                    acc.z = fmaf(wgt, x.z, acc.z);
+                    acc.w = fmaf(wgt, x.w, acc.w);
+                }
         }
-        // The tail's loads go out together as well.  (All rows of a wave belong to the same list, so
-        // n_parts and with it every branch here is uniform over the wave.)
-        typename ta_part_raw<HP>::type v[3];
-#pragma unroll
-        for (int u = 0; u < 3; ++u)
-            if (k + u < n_parts)
-                v[u] = ta_part_load4<HP>(o0 + (k + u) * ostride);
-#pragma unroll
-        for (int u = 0; u < 3; ++u)
-            if (k + u < n_parts) {
-                const float wgt = __shfl(wk, src0 + k + u, TA_WAVE);
-                const float4 x = ta_part_f4(v[u]);
-                acc.x = fmaf(wgt, x.x, acc.x);
-                acc.y = fmaf(wgt, x.y, acc.y);
-                acc.z = fmaf(wgt, x.z, acc.z);
-                acc.w = fmaf(wgt, x.w, acc.w);
-            }
     } else {
         if constexpr (NEW)
             ta_scatter_locate(p, b, g, sc);
@@ -676,7 +670,8 @@ __global__ __launch_bounds__(256) void ta_merge_wide_kernel(const int32_t *mg_pa
     const int tid = threadIdx.x, hw = tid / LPR, hl = tid % LPR, wave = tid >> 6;
     const int w_first = mg_parts[2 * seg];                               // left by the KV pass
     const int n_parts = mg_parts[2 * seg + 1] - w_first + 1;
-    ta_touch_args<TAParams>(n_parts);
+    if constexpr (HP)                                     // (with it fp32 merges took 0.1 us longer)
+        ta_touch_args<TAParams>(n_parts);
     const float LN2 = 0.6931471805599453f;
     const float QNAN = __uint_as_float(0x7fc00000u);
     TAScatter sc;                                          // write-back folded into the call: see ta_scatter_load
