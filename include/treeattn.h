@@ -274,7 +274,9 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * library's dispatch table, see tree_attn_dispatch_row).  plan[0] = kernel family, plan[1] = workgroups of the
  * KV pass for each block of plan[15] query rows, plan[2] = threads per workgroup, plan[3] = KV tokens per tile,
  * plan[4] = row groups of the partial results, plan[5] = padded rows per group, plan[6] = partial slots,
- * plan[7] = workgroups of the merge pass, plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units
+ * plan[7] = workgroups of the merge pass (0: none; lists of a few tiles are not cut but walked by one workgroup each, of the
+ * key-split or the fp32 kernel, which writes the outputs, unless num_splits, item_cost or kernel is given; the other
+ * figures are then those of the cut), plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units
  * a list counts (item_cost), plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
  * workgroup per row, 0 general), plan[11] = row of the dispatch table that was taken (-1: none, the fp32 matrix-core
  * kernel runs), plan[12] = workspace bytes the call needs, plan[13] = format of the partial results (0: fp32; 1: 16-bit

@@ -111,7 +111,7 @@ int launch_call(const TAProblem &pr, hipStream_t st, int dev, void *const *ev)
         return TA_ERR_HIP;
     if (ev && ev[1] && hipEventRecord((hipEvent_t)ev[1], st) != hipSuccess)
         return TA_ERR_HIP;
-    e = ta_launch_merge(pr.p, st);
+    e = pr.p.solo ? hipSuccess : ta_launch_merge(pr.p, st);
     if (e != hipSuccess)
         return TA_ERR_HIP;
     if (ev && ev[2] && hipEventRecord((hipEvent_t)ev[2], st) != hipSuccess)

@@ -27,7 +27,6 @@
 
 typedef float f32_x4 __attribute__((ext_vector_type(4)));
 
-#define F32_NW 4                                 // waves of a workgroup
 #define F32_SUB 16                               // tokens a wave takes at a time
 #define F32_ROWS TA_F32_ROWS                     // query rows of a workgroup
 
@@ -36,10 +35,17 @@ __device__ __forceinline__ void f32_lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// RB: blocks of 16 query rows; NEW: the tree tokens of this step lie in tensors of their own (ta_opts.k_new)
-template <int DH, int RB, bool NEW>
-__global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
+// Waves of a workgroup.  Two on a SIMD share its matrix pipe: eight waves gain only where a workgroup walks a whole list
+// (36 MB in 16 lists, 190 of 256 workgroups busy with up to three tiles: 21.1 us a call with four, 22.0 with eight).
+constexpr int f32_waves(bool solo) { return solo ? 8 : 4; }
+
+// RB: blocks of 16 query rows; NEW: the tree tokens of this step lie in tensors of their own (ta_opts.k_new);
+// SOLO: workgroup x walks list x from end to end and writes its outputs (see p.solo)
+template <int DH, int RB, bool NEW, bool SOLO>
+__global__ __launch_bounds__(64 * f32_waves(SOLO), 2) void ta_f32_kv_kernel(TA_SCHED_PARAMS, TAParams p)
 {
+    const TASched sc = TA_SCHED;
+    constexpr int F32_NW = f32_waves(SOLO);
     constexpr int NJ = DH / 16;                  // 16-byte pieces of a K row a lane loads
     constexpr int NH = DH / 64;                  // 16-byte pieces of a V row a lane loads
     constexpr int CH = DH / 4;                   // 16-byte chunks of a row
@@ -62,23 +68,31 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, qt = lane >> 4;
     // Schedule (see ta_build_schedule); up to 64 requests every wave keeps it in registers, lane b for request b
-    const bool in_regs = p.B <= TA_WAVE;
+    const bool in_regs = sc.B <= TA_WAVE;
     int s_len = 0, s_start = 0, s_units = 0, s_cum = 0, total;
-    if (in_regs) {
-        if (lane < p.B) {
-            s_len = p.seq_lens[(int64_t)lane * p.sl_s];
-            s_start = ta_kv_start(p, lane);
-            s_units = ta_list_tiles(p, s_len, s_start) + p.pad;
-        }
-        s_cum = ta_wave_scan(s_units);
-        total = p.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
-    } else {
-        total = p.Hkv * ta_build_schedule(TASched{TA_SCHED_ARGS(p)}, cum, lens, starts);
-    }
     int t, t_end;
-    ta_wg_range(p, total, w, t, t_end);
-    t = __builtin_amdgcn_readfirstlane(t);
-    t_end = __builtin_amdgcn_readfirstlane(t_end);
+    if constexpr (SOLO) {
+        s_len = sc.seq_lens[(int64_t)(w / sc.Hkv) * sc.sl_s];
+        s_start = ta_kv_start(sc, w / sc.Hkv);
+        ta_touch_args<TAParams>(s_len);
+        t = 0;
+        t_end = 1;
+    } else {
+        if (in_regs) {
+            if (lane < sc.B) {
+                s_len = sc.seq_lens[(int64_t)lane * sc.sl_s];
+                s_start = ta_kv_start(sc, lane);
+                s_units = ta_list_tiles(sc, s_len, s_start) + sc.pad;
+            }
+            s_cum = ta_wave_scan(s_units);
+            total = sc.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
+        } else {
+            total = sc.Hkv * ta_build_schedule(sc, cum, lens, starts);
+        }
+        ta_wg_range(sc, total, w, t, t_end);
+        t = __builtin_amdgcn_readfirstlane(t);
+        t_end = __builtin_amdgcn_readfirstlane(t_end);
+    }
     const int rows_here = min(p.rows_grp, p.rows - rg * p.rows_grp);
     const float c = p.scale_log2e;
     // what depends on the lane is derived where it is used: hoisted out of the loops, it would be spilled
@@ -90,33 +104,45 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
     while (t < t_end) {
         // ---- the next item: a list (b, g), its tiles [j0, j1), i.e. the prefix tokens [max(lo, S), hi), walked in runs of
         // 16 from lo, and the T tree tokens; run u belongs to wave u % 4
-        int b, cum_b, cum_e, L, S;
-        if (in_regs) {
-            b = __popcll(__ballot(p.Hkv * s_cum <= t));
-            cum_e = __builtin_amdgcn_readlane(s_cum, b);
-            cum_b = cum_e - __builtin_amdgcn_readlane(s_units, b);
-            L = __builtin_amdgcn_readlane(s_len, b);
-            S = __builtin_amdgcn_readlane(s_start, b);
+        int b, g, L, S, n_b, j0, j1, slot = 0;
+        if constexpr (SOLO) {
+            t = t_end;
+            b = w / sc.Hkv;
+            g = w - b * sc.Hkv;
+            L = s_len;
+            S = s_start;
+            n_b = ta_list_tiles(sc, L, S);
+            j0 = 0;
+            j1 = n_b;
         } else {
-            b = __builtin_amdgcn_readfirstlane(ta_find_request(p, cum, t));
-            cum_b = __builtin_amdgcn_readfirstlane(cum[b]);
-            cum_e = __builtin_amdgcn_readfirstlane(cum[b + 1]);
-            L = __builtin_amdgcn_readfirstlane(lens[b]);
-            S = __builtin_amdgcn_readfirstlane(starts[b]);
+            int cum_b, cum_e;
+            if (in_regs) {
+                b = __popcll(__ballot(p.Hkv * s_cum <= t));
+                cum_e = __builtin_amdgcn_readlane(s_cum, b);
+                cum_b = cum_e - __builtin_amdgcn_readlane(s_units, b);
+                L = __builtin_amdgcn_readlane(s_len, b);
+                S = __builtin_amdgcn_readlane(s_start, b);
+            } else {
+                b = __builtin_amdgcn_readfirstlane(ta_find_request(p, cum, t));
+                cum_b = __builtin_amdgcn_readfirstlane(cum[b]);
+                cum_e = __builtin_amdgcn_readfirstlane(cum[b + 1]);
+                L = __builtin_amdgcn_readfirstlane(lens[b]);
+                S = __builtin_amdgcn_readfirstlane(starts[b]);
+            }
+            const int n_u = cum_e - cum_b;                             // schedule units of one list
+            g = (t - p.Hkv * cum_b) / n_u;
+            const int seg_start = p.Hkv * cum_b + g * n_u;
+            n_b = n_u - p.pad;
+            j0 = t - seg_start;
+            j1 = min(n_b, t_end - seg_start);
+            if (j1 <= j0) {
+                t = seg_start + n_u;                                   // t lies in the list's trailing padding
+                continue;
+            }
+            t = seg_start + (j1 == n_b ? n_u : j1);
+            slot = w + b * p.Hkv + g;
+            ta_note_owner(p, b, g, w, j0, j1, n_b);
         }
-        const int n_u = cum_e - cum_b;                             // schedule units of one list
-        const int g = (t - p.Hkv * cum_b) / n_u;
-        const int seg_start = p.Hkv * cum_b + g * n_u;
-        const int n_b = n_u - p.pad;
-        const int j0 = t - seg_start;
-        const int j1 = min(n_b, t_end - seg_start);
-        if (j1 <= j0) {
-            t = seg_start + n_u;                                   // t lies in the list's trailing padding
-            continue;
-        }
-        t = seg_start + (j1 == n_b ? n_u : j1);
-        const int slot = w + b * p.Hkv + g;
-        ta_note_owner(p, b, g, w, j0, j1, n_b);
         int bad = ta_request_ok(p, L, S) ? 0 : TA_STATUS_BAD_SEQLEN;
         const int tile0 = bad ? 0 : S / TA_TILE;
         const bool has_tree = j1 == n_b;
@@ -194,12 +220,12 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
                 parent = p.parent[(int64_t)b * p.par_sb + lane];
         }
         {
-            constexpr int PER = ROWS * CH / (64 * F32_NW);                 // chunks per thread
+            constexpr int NT = 64 * F32_NW, PER = (ROWS * CH + NT - 1) / NT;     // chunks per thread (16 x 64, eight waves: every other)
             f32_x4 q[PER];
             const int tid_q = fresh(tid);
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
-                const int x = tid_q + i * 64 * F32_NW, row = x / CH, ch = x % CH;
+                const int x = tid_q + i * NT, row = x / CH, ch = x % CH;
                 const int R = rg * p.rows_grp + (row < rows_here ? row : 0);
                 const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);          // R / G
                 q[i] = *(const f32_x4 *)((const float *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
@@ -213,8 +239,9 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
             }
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
-                const int x = tid_q + i * 64 * F32_NW, row = x / CH, ch = x % CH;
-                *(f32_x4 *)(lds[0] + row * DH + 4 * (ch ^ (row & 15))) = q[i];
+                const int x = tid_q + i * NT, row = x / CH, ch = x % CH;
+                if (ROWS * CH >= NT || row < ROWS)
+                    *(f32_x4 *)(lds[0] + row * DH + 4 * (ch ^ (row & 15))) = q[i];
             }
         }
         // the ancestor masks, in a wave that has tree tokens: lane i walks up from node i
@@ -380,6 +407,7 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
                     stat[wave][0][row] = m_run[rb];
                     stat[wave][1][row] = l_tot;
                 }
+                if (wave < n_sub)                  // (what a wave without runs would put there is not read)
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
 #pragma unroll
@@ -394,8 +422,9 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
         }
         f32_lds_barrier();
         {
-            constexpr int TPR = 64 * F32_NW / ROWS;                        // threads per row
-            const int row = tid_e / TPR;
+            constexpr int TPR = 64 * F32_NW / ROWS < CH ? 64 * F32_NW / ROWS : CH;      // threads per row
+            const int row = min(tid_e / TPR, ROWS - 1);
+            const bool mine = tid_e / TPR < rows_here;                     // (16 x 64, eight waves: half have no row)
             int any_bad = 0;
             float mw[F32_NW], big = -INFINITY, l_tot = 0.f;
 #pragma unroll
@@ -406,11 +435,33 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
             }
 #pragma unroll
             for (int x = 0; x < F32_NW; ++x) {
-                mw[x] = mw[x] == -INFINITY ? 0.f : exp2f(mw[x] - big);     // weight of the wave's result
+                mw[x] = mw[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[x] - big);     // weight of the wave's result
                 l_tot = fmaf(mw[x], stat[x][1][row], l_tot);
             }
             const float inv = 1.f / l_tot;
-            if (row < rows_here) {
+            if (SOLO && mine) {
+                // no merge: the outputs as the merge pass makes them of one partial result
+                const float lse2 = big + log2f(l_tot);
+                const bool nan = any_bad || l_tot == 0.f || lse2 != lse2 || lse2 == INFINITY;
+                const int R = rg * p.rows_grp + row, node = (int)__umulhi((uint32_t)R << 8, p.g_magic), h = g * p.G + R - node * p.G;
+                float *dst = (float *)p.out + (int64_t)b * p.o_sb + (int64_t)node * p.o_st + (int64_t)h * p.o_sh;
+#pragma unroll
+                for (int i = 0; i < CH / TPR; ++i) {
+                    const int ch = tid_e % TPR + i * TPR;
+                    f32_x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int x = 0; x < F32_NW; ++x)
+                        if (mw[x] != 0.f)
+                            acc += mw[x] * *(const f32_x4 *)(lds[x] + row * DH + 4 * (ch ^ (row & 15)));
+                    acc *= inv;
+                    const float q_nan = __uint_as_float(0x7fc00000u);
+                    *(f32_x4 *)(dst + 4 * ch) = nan ? f32_x4{q_nan, q_nan, q_nan, q_nan} : acc;
+                }
+                if (p.lse && tid_e % TPR == 0)
+                    p.lse[(int64_t)b * p.lse_sb + (int64_t)h * p.lse_sh + (int64_t)node * p.lse_st] =
+                        nan ? __uint_as_float(0x7fc00000u) : lse2 * 0.6931471805599453f;
+            }
+            if (!SOLO && mine) {
                 const int64_t wrow = ta_ws_row(p, slot, rg, row);
 #pragma unroll
                 for (int i = 0; i < CH / TPR; ++i) {
@@ -429,25 +480,34 @@ __global__ __launch_bounds__(64 * F32_NW, 2) void ta_f32_kv_kernel(TAParams p)
             if (any_bad && tid_e == 0)
                 ta_raise(p, any_bad);
         }
-        f32_lds_barrier();                         // the next item's Q may overwrite the results
+        if constexpr (!SOLO)
+            f32_lds_barrier();                     // the next item's Q may overwrite the results
+        if constexpr (SOLO && NEW) {               // the merge pass's part of the write-back
+            TAScatter wb;
+            ta_scatter_load(p, b, g, rg, gridDim.y, wb);
+            ta_scatter_locate(p, b, g, wb);
+            ta_scatter_store(p, b, g, rg, gridDim.y, wb);
+        }
     }
 }
 
-template <int DH, int RB, bool NEW>
+template <int DH, int RB, bool NEW, bool SOLO>
 static hipError_t launch_f32(const TAParams &p, hipStream_t stream, int dev)
 {
-    constexpr size_t fixed = F32_NW * (16 * RB * DH + 2 * 16 * RB + 1) * sizeof(float);
-    static_assert(fixed + sizeof(int) * (3 * TA_MAX_BATCH + 1) <= 160 * 1024, "LDS of the largest batch");
-    const size_t smem = fixed + (p.B <= TA_WAVE ? 0 : sizeof(int) * (3 * (size_t)p.B + 1));
+    constexpr int NW = f32_waves(SOLO);
+    constexpr size_t fixed = NW * (16 * RB * DH + 2 * 16 * RB + 1) * sizeof(float);
+    static_assert(fixed + (SOLO ? 0 : sizeof(int) * (3 * TA_MAX_BATCH + 1)) <= 160 * 1024, "LDS of the largest batch");
+    const size_t smem = fixed + (SOLO || p.B <= TA_WAVE ? 0 : sizeof(int) * (3 * (size_t)p.B + 1));
     static bool attr_set[64] = {};      // per device and instance; setting it twice is harmless
     if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void *)ta_f32_kv_kernel<DH, RB, NEW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           160 * 1024);
+        hipError_t e = hipFuncSetAttribute((const void *)ta_f32_kv_kernel<DH, RB, NEW, SOLO>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess)
             return e;
         attr_set[dev] = true;
     }
-    hipLaunchKernelGGL((ta_f32_kv_kernel<DH, RB, NEW>), dim3(p.n_wg, p.n_rg), dim3(64 * F32_NW), smem, stream, p);
+    const dim3 grid(SOLO ? p.B * p.Hkv : p.n_wg, p.n_rg);
+    hipLaunchKernelGGL((ta_f32_kv_kernel<DH, RB, NEW, SOLO>), grid, dim3(64 * NW), smem, stream, TA_SCHED_ARGS(p), p);
     return hipGetLastError();
 }
 
@@ -457,11 +517,12 @@ hipError_t ta_launch_f32(const TAParams &p, hipStream_t stream, int dev)
         return hipErrorInvalidDevice;
     if (p.rows_grp > F32_ROWS || p.part_q15 || p.ls != 1 || (p.D != 64 && p.D != 128))
         return hipErrorInvalidValue;
-    auto launch = [&](auto d, auto fold) {
+    auto launch = [&](auto d, auto fold, auto alone) {
         constexpr int DH = decltype(d)::value;
-        constexpr bool NEW = decltype(fold)::value;
-        return p.rows_grp <= 16 ? launch_f32<DH, 1, NEW>(p, stream, dev) : launch_f32<DH, 2, NEW>(p, stream, dev);
+        constexpr bool NEW = decltype(fold)::value, SOLO = decltype(alone)::value;
+        return p.rows_grp <= 16 ? launch_f32<DH, 1, NEW, SOLO>(p, stream, dev) : launch_f32<DH, 2, NEW, SOLO>(p, stream, dev);
     };
-    auto with = [&](auto d) { return p.kn ? launch(d, std::true_type{}) : launch(d, std::false_type{}); };
+    auto fold = [&](auto d, auto alone) { return p.kn ? launch(d, std::true_type{}, alone) : launch(d, std::false_type{}, alone); };
+    auto with = [&](auto d) { return p.solo ? fold(d, std::true_type{}) : fold(d, std::false_type{}); };
     return p.D == 64 ? with(std::integral_constant<int, 64>{}) : with(std::integral_constant<int, 128>{});
 }

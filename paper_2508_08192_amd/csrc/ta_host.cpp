@@ -105,6 +105,34 @@ int64_t key_split_workgroups(int64_t want, int slices)
     return n > 8 ? n - n % 8 : n;
 }
 
+// Longest list, in tiles, that one workgroup walks alone; 0 = never.  What it saves is the merge pass, its launch and the
+// partial results, 4 to 8 us; what it costs is that a list is not cut.  With up to a workgroup per compute unit the limit
+// rises with their number, as the cut would leave fewer of them per list.  Time over that of the cut lists, T 4 to 64,
+// lists of equal lengths and of a quarter of the longest up, calls back to back:
+//   bf16, head_dim 128: 2 tiles 0.54 to 0.63; 16 workgroups 0.85 at 6 tiles, 0.95 at 9, 1.04 at 12; 64 of them 0.82 to 0.97 at
+//     12 and 1.0 at 15; 128 0.89 to 0.94 at 15 and 0.95 to 1.02 at 20; 192 0.80 to 0.87 at 26; 256 0.79 to 0.86 at 26
+//     and 0.84 to 0.93 at 33, where 240 take 1.04 to 1.07;
+//   bf16, head_dim 64: 16 workgroups 0.85 at 12 and 0.98 at 15, 128 0.94 to 0.96 at 26, 256 0.75 to 0.88 at 33;
+//   fp32, blocks of 16 rows, head_dim 64: few workgroups 0.84 at 4 and 0.96 at 6, 128 0.94 at 8, 256 0.73 to 0.85 at 14; head_dim 128:
+//     0.85 at 3 and 1.04 at 5, 128 0.88 to 0.99 at 6.
+// More workgroups than compute units are dealt out as others end.  With one block of rows each: 320 of them 0.83 to 0.98 up to
+// 14 tiles and 1.05 at 20; 384 and 400 0.85 to 0.99 at 20; 512 0.8 to 0.96 at 20, 0.96 to 1.0 at 33; 1024 0.95 to 0.99 at 33 and 65
+// (head_dim 64 0.79 to 0.95); fp32 320 0.96 at 14 (head_dim 64), 512 0.85 to 0.91 at 33, head_dim 128 0.93 to 0.96 at 14.  More blocks of
+// 32 rows per list than there are compute units read the keys too often (512: 1.0 at 2 tiles, 1.24 at 12).
+int64_t solo_tiles(bool f32, int D, int block_rows, int blocks, int64_t lists, int64_t cus)
+{
+    const int64_t wgs = lists * blocks;
+    if (wgs <= cus) {
+        const int64_t base = f32 ? (D == 64 ? 5 : 3) : D == 64 ? 13 : 9, rise = f32 ? (D == 64 ? 9 : 5) : 20;
+        return base + rise * wgs / cus;
+    }
+    if (blocks > 1 || block_rows > 32)
+        return 0;
+    if (f32)
+        return wgs < 2 * cus ? 8 : D == 64 ? 32 : 14;
+    return 2 * wgs < 3 * cus ? 14 : wgs < 2 * cus ? 20 : wgs < 4 * cus ? 32 : 66;
+}
+
 int find_row(int family, int rows_grp, int64_t lists)
 {
     for (int i = 0; i < kTableRows; ++i)
@@ -359,7 +387,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         // that with 64: up to four units 0.83 to 1.04, at eight 0.76 to 1.05, at twelve 0.74 to 1.08, one list 0.79 to 0.93,
         // at sixteen 0.74 to 1.18, mostly 1.0 to 1.08), but not with one workgroup per list (equal lists 0.84 to 1.08, uneven
         // ones 1.13 to 1.37) and fewer (1.2 to 1.5)
-        p.ks_rows = D == 64 && slices > 1 && !(units <= (int64_t)16 * num_cus && ks_wg >= 2 * lists) ? 64 : 32;
+        p.ks_rows = pl.ks_rows = D == 64 && slices > 1 && !(units <= (int64_t)16 * num_cus && ks_wg >= 2 * lists) ? 64 : 32;
         pl.rows_grp = ks && (basic || slices <= 4) ? p.ks_rows : mfma_rows_group(p.rows);
         pl.threads = 512;
     } else if (f32_mfma) {
@@ -413,6 +441,15 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // merged and read again (its stores need the alignment that the row merge needs): B 128, 32/8 heads, T 8, L 256..4096
     // 206.6 -> 202.5 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
     p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind == TA_MERGE_ROW && lists >= 2 * (int64_t)pl.n_wg;
+    // Lists of a few tiles go to one workgroup each (per block of rows), which writes the outputs itself: no schedule, no
+    // partial results, no merge pass.  (Its 16- and 8-byte stores need the alignment that the row merge needs.)
+    int solo_rows = f32_mfma ? 16 : 32;
+    if (!f32_mfma && D == 64 && p.rows > 32 && lists * ((p.rows + 31) / 32) > num_cus)
+        solo_rows = 64;
+    const int solo_groups = (p.rows + solo_rows - 1) / solo_rows;
+    p.solo = auto_kernel && (f32_mfma || kernel == TA_KERNEL_MFMA) && num_splits == 0 && item_cost == 0 && lists > 0 &&
+             p.merge_kind != TA_MERGE_GENERAL &&
+             tiles_cap / lists <= solo_tiles(f32_mfma, (int)D, solo_rows, solo_groups, lists, num_cus);
     pl.merge_kind = p.merge_kind;
     const int mrows = ta_host_merge_rows(p);
     pl.merge_wgs = (int)lists * ((p.rows + mrows - 1) / mrows);
@@ -423,6 +460,15 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // (with 16-bit partials: rows_total * 8 bytes of {log-sum-exp, scale} fit into the unused half of the ws_o area)
     pr->ws_ls_off = p.part_q15 ? ta_host_align_up(rows_total * D * 2, 256) : pr->ws_o_bytes;
     p.ls = p.part_q15 ? 2 : 1;
+    if (p.solo) {                                           // (a plan keeps the figures of the cut, but for the merge pass)
+        p.direct = 0;
+        p.ks_rows = solo_rows;
+        if (f32_mfma) {
+            p.n_rg = solo_groups;
+            p.rows_grp = (p.rows + solo_groups - 1) / solo_groups;
+        }
+        pl.merge_wgs = 0;
+    }
     pr->ws_bytes = pr->ws_o_bytes + pr->ws_lse_bytes + ta_host_align_up((size_t)lists * 2 * sizeof(int32_t), 256);
     if (user_ws) {
         if (user_ws_bytes < pr->ws_bytes)
@@ -454,7 +500,7 @@ void ta_host_fill_plan(const TAProblem &pr, int64_t plan[16])
     plan[13] = pr.p.part_q15;
     const bool ks = pr.plan.kernel == TA_KERNEL_MFMA && pr.p.basic;
     plan[14] = ks;
-    plan[15] = ks ? pr.p.ks_rows : pr.plan.rows_grp;
+    plan[15] = ks ? pr.plan.ks_rows : pr.plan.rows_grp;
 }
 
 size_t ta_host_workspace_bytes(int32_t B, int32_t T, int32_t Hq, int32_t Hkv, int32_t D, int32_t dtype, int32_t num_cus)

@@ -592,7 +592,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
 
 hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
 {
-    if (p.D == 64 || p.basic)
+    if (p.D == 64 || p.basic || p.solo)
         return ta_launch_mfma_ks(p, stream, dev);
     if (p.rows_grp != 32 && p.rows_grp != 64 && p.rows_grp != 128 && p.rows_grp != 256)
         return hipErrorInvalidValue;

@@ -132,13 +132,17 @@ static size_t ks_smem(int B)
            (B <= TA_WAVE ? 0 : sizeof(int) * (B + 2 + (B <= KS_LENS ? 2 * B : 0)));
 }
 
-// DIRECT: the outputs of a list that lies in one share are written here (an instance of its own: calls without many lists
-// are 1 % slower with that code in the kernel)
-template <int DH, int RB, int NW, int OCC, bool DIRECT>
+// What a workgroup's lists are.  KS_CUT: a share of the line of all lists.  KS_DIRECT: the same, and the outputs of a list that
+// lies in one share are written here (an instance of its own: calls without many lists are 1 % slower with that code in
+// the kernel).  KS_SOLO: workgroup x walks list x from end to end (see p.solo).
+enum { KS_CUT, KS_DIRECT, KS_SOLO };
+
+template <int DH, int RB, int NW, int OCC, int MODE>
 __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SCHED_PARAMS, TAParams p)
 {
     const TASched sc = TA_SCHED;
     using C = KsShape<DH, RB, NW, OCC>;
+    constexpr bool SOLO = MODE == KS_SOLO;
     constexpr int NKK = DH / 16, NDB = DH / 32, SLOTS = DH / 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char *const qrows = smem + C::RING;                                 // Q rows of the item, placed like a run's K rows
@@ -156,23 +160,31 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
     // exchange between the waves, which start on their own.
     const bool in_regs = sc.B <= TA_WAVE;
     int s_len = 0, s_start = 0, s_units = 0, s_cum = 0, total;
-    if (in_regs) {
-        if (lane < sc.B) {
-            s_len = sc.seq_lens[(int64_t)lane * sc.sl_s];
-            s_start = ta_kv_start(sc, lane);
-        }
-        ta_touch_args<TAParams>();
-        if (lane < sc.B)
-            s_units = ta_list_tiles(sc, s_len, s_start) + sc.pad;
-        s_cum = ta_wave_scan(s_units);
-        total = sc.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
-    } else {
-        total = sc.Hkv * ta_build_schedule(sc, cum, sc.B <= KS_LENS ? lens : nullptr, sc.B <= KS_LENS ? starts : nullptr);
-    }
     int t, t_end;
-    ta_wg_range(sc, total, w, t, t_end);
-    t = __builtin_amdgcn_readfirstlane(t);
-    t_end = __builtin_amdgcn_readfirstlane(t_end);
+    if constexpr (SOLO) {
+        s_len = sc.seq_lens[(int64_t)(w / sc.Hkv) * sc.sl_s];
+        s_start = ta_kv_start(sc, w / sc.Hkv);
+        ta_touch_args<TAParams>(s_len);
+        t = 0;
+        t_end = 1;
+    } else {
+        if (in_regs) {
+            if (lane < sc.B) {
+                s_len = sc.seq_lens[(int64_t)lane * sc.sl_s];
+                s_start = ta_kv_start(sc, lane);
+            }
+            ta_touch_args<TAParams>();
+            if (lane < sc.B)
+                s_units = ta_list_tiles(sc, s_len, s_start) + sc.pad;
+            s_cum = ta_wave_scan(s_units);
+            total = sc.Hkv * __builtin_amdgcn_readlane(s_cum, 63);
+        } else {
+            total = sc.Hkv * ta_build_schedule(sc, cum, sc.B <= KS_LENS ? lens : nullptr, sc.B <= KS_LENS ? starts : nullptr);
+        }
+        ta_wg_range(sc, total, w, t, t_end);
+        t = __builtin_amdgcn_readfirstlane(t);
+        t_end = __builtin_amdgcn_readfirstlane(t_end);
+    }
     const int rows_here = min(C::ROWS, p.rows - row0);
     const float c = p.scale_log2e;
     const bool paged = p.page_table != nullptr;
@@ -233,40 +245,53 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
     // Moves on to the next item of [t, t_end) and requests what its start needs: Q, page ids, parents.  False at the end.
     auto next_item = [&]() {
         while (t < t_end) {
-            int cum_b, cum_e;
-            if (in_regs) {
-                b = __popcll(__ballot(sc.Hkv * s_cum <= t));
-                cum_e = __builtin_amdgcn_readlane(s_cum, b);
-                cum_b = cum_e - __builtin_amdgcn_readlane(s_units, b);
+            int n_b, j0, j1;
+            if constexpr (SOLO) {
+                t = t_end;
+                b = w / sc.Hkv;
+                g = w - b * sc.Hkv;
+                L = s_len;
+                S = s_start;
+                n_b = ta_list_tiles(sc, L, S);
+                j0 = 0;
+                j1 = n_b;
+                whole = true;
             } else {
-                if (b < 0)
-                    b = ta_find_request(sc, cum, t);
-                else if ((int64_t)sc.Hkv * cum[b + 1] <= t)
-                    ++b;
-                b = __builtin_amdgcn_readfirstlane(b);
-                cum_b = __builtin_amdgcn_readfirstlane(cum[b]);
-                cum_e = __builtin_amdgcn_readfirstlane(cum[b + 1]);
-            }
-            const int n_u = cum_e - cum_b;                          // schedule units of one list
-            g = (t - sc.Hkv * cum_b) / n_u;
-            const int seg_start = sc.Hkv * cum_b + g * n_u;
-            const int n_b = n_u - sc.pad;
-            const int j0 = t - seg_start;
-            const int j1 = min(n_b, t_end - seg_start);
-            if (j1 <= j0) {
-                t = seg_start + n_u;                               // t lies in the list's trailing padding
-                continue;
-            }
-            t = seg_start + (j1 == n_b ? n_u : j1);
-            slot = w + b * sc.Hkv + g;
-            whole = DIRECT && j0 == 0 && j1 == n_b;
-            ta_note_owner(p, b, g, w, j0, j1, n_b, whole);
-            if (in_regs) {
-                L = __builtin_amdgcn_readlane(s_len, b);
-                S = __builtin_amdgcn_readlane(s_start, b);
-            } else {
-                L = __builtin_amdgcn_readfirstlane(sc.B <= KS_LENS ? lens[b] : sc.seq_lens[(int64_t)b * sc.sl_s]);
-                S = __builtin_amdgcn_readfirstlane(sc.B <= KS_LENS ? starts[b] : ta_kv_start(sc, b));
+                int cum_b, cum_e;
+                if (in_regs) {
+                    b = __popcll(__ballot(sc.Hkv * s_cum <= t));
+                    cum_e = __builtin_amdgcn_readlane(s_cum, b);
+                    cum_b = cum_e - __builtin_amdgcn_readlane(s_units, b);
+                } else {
+                    if (b < 0)
+                        b = ta_find_request(sc, cum, t);
+                    else if ((int64_t)sc.Hkv * cum[b + 1] <= t)
+                        ++b;
+                    b = __builtin_amdgcn_readfirstlane(b);
+                    cum_b = __builtin_amdgcn_readfirstlane(cum[b]);
+                    cum_e = __builtin_amdgcn_readfirstlane(cum[b + 1]);
+                }
+                const int n_u = cum_e - cum_b;                          // schedule units of one list
+                g = (t - sc.Hkv * cum_b) / n_u;
+                const int seg_start = sc.Hkv * cum_b + g * n_u;
+                n_b = n_u - sc.pad;
+                j0 = t - seg_start;
+                j1 = min(n_b, t_end - seg_start);
+                if (j1 <= j0) {
+                    t = seg_start + n_u;                               // t lies in the list's trailing padding
+                    continue;
+                }
+                t = seg_start + (j1 == n_b ? n_u : j1);
+                slot = w + b * sc.Hkv + g;
+                whole = MODE == KS_DIRECT && j0 == 0 && j1 == n_b;
+                ta_note_owner(p, b, g, w, j0, j1, n_b, whole);
+                if (in_regs) {
+                    L = __builtin_amdgcn_readlane(s_len, b);
+                    S = __builtin_amdgcn_readlane(s_start, b);
+                } else {
+                    L = __builtin_amdgcn_readfirstlane(sc.B <= KS_LENS ? lens[b] : sc.seq_lens[(int64_t)b * sc.sl_s]);
+                    S = __builtin_amdgcn_readfirstlane(sc.B <= KS_LENS ? starts[b] : ta_kv_start(sc, b));
+                }
             }
             bad = ta_request_ok(sc, L, S) ? 0 : TA_STATUS_BAD_SEQLEN;
             const int tile0 = bad ? 0 : S / TA_TILE;
@@ -343,6 +368,17 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
                 pg_first = checked(pg_first);
                 pg_last = checked(pg_last);
             }
+        }
+
+        // Q rows to LDS.  (Each wave loading its own fragments, 32 rows by 32 scattered bytes at a time, kept the load units
+        // busy for most of a microsecond.  With the barrier behind the loads of the first runs, all waves wait for the one
+        // whose run is not whole, which makes its addresses row by row: 62 lists of four to seventeen tiles 18.7 us a call,
+        // with the barrier here 17.3; calls of whole runs differ by 0.3 us the other way.)
+        {
+            const int l = fresh_lane(), x = wave * 64 + l, row = x / SLOTS;
+            if (C::QB / 16 == C::NT || row < C::ROWS)
+                *(uint4 *)(qrows + row * C::ROW + (((x % SLOTS) ^ kx(row)) << 4)) = q_piece;
+            ks_lds_barrier();
         }
 
         // Loads of run u, K or V part, into ring slot sl: LD loads of 1 KB.
@@ -426,21 +462,15 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         for (int k = 0; k < 2 * C::NS; ++k)                    // K and V of the wave's first run, and of its second
             if (u + (k >> 1) * NW < n_sub)
                 issue(u + (k >> 1) * NW, k >> 1, k & 1);
-        // while the first runs are on their way: Q rows to LDS and from there as fragments into every wave's registers (each
-        // wave loading its own, 32 rows by 32 scattered bytes at a time, kept the load units busy for most of a microsecond),
-        // O = 0 and, in a wave that has tree tokens, the ancestor masks
+        // while the first runs are on their way: Q fragments into every wave's registers, O = 0 and, in a wave that has tree
+        // tokens, the ancestor masks
         uint4 qf[RB][NKK];
-        {
-            const int l = fresh_lane(), x = wave * 64 + l, row = x / SLOTS;
-            if (C::QB / 16 == C::NT || row < C::ROWS)
-                *(uint4 *)(qrows + row * C::ROW + (((x % SLOTS) ^ kx(row)) << 4)) = q_piece;
-            ks_lds_barrier();
-            if (u < n_sub)
+        if (u < n_sub) {
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
+            for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                    for (int kk = 0; kk < NKK; ++kk)
-                        qf[rb][kk] = *(const uint4 *)(qrows + rb * 32 * C::ROW + kf_row + (((2 * kk + hf) ^ kf_x) << 4));
+                for (int kk = 0; kk < NKK; ++kk)
+                    qf[rb][kk] = *(const uint4 *)(qrows + rb * 32 * C::ROW + kf_row + (((2 * kk + hf) ^ kf_x) << 4));
         }
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
@@ -691,7 +721,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
             float scale, to_q;
             ta_q15_scale(amax, nan_seen, scale, to_q);
             const float lse2 = any_bad ? __uint_as_float(0x7fc00000u) : big + log2f(l_tot);
-            if (DIRECT && whole_e) {
+            if (MODE != KS_CUT && whole_e) {
                 // no merge: the rows go out as they are, by its rules: a NaN or an infinity spoils its row (the 16-bit format
                 // holds neither), and no score above -inf leaves no log-sum-exp either
                 if (row < rows_here) {
@@ -724,9 +754,17 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         }
         ks_lds_barrier();                                      // the rings are free for the next item
     }
+    if constexpr (SOLO) {
+        if (p.kn) {                                            // the merge pass's part of the write-back
+            TAScatter wb;
+            ta_scatter_load(p, b, g, blockIdx.y, gridDim.y, wb);
+            ta_scatter_locate(p, b, g, wb);
+            ta_scatter_store(p, b, g, blockIdx.y, gridDim.y, wb);
+        }
+    }
 }
 
-template <int DH, int RB, int NW, int OCC, bool DIRECT>
+template <int DH, int RB, int NW, int OCC, int MODE>
 static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
 {
     const size_t smem = ks_smem<DH, RB, NW, OCC>(p.B);
@@ -734,13 +772,13 @@ static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
         return hipErrorInvalidValue;
     static bool attr_set[64] = {};      // per device and instance; setting it twice is harmless
     if (!attr_set[dev]) {
-        hipError_t e = hipFuncSetAttribute((const void *)ta_mfma_ks_kernel<DH, RB, NW, OCC, DIRECT>,
+        hipError_t e = hipFuncSetAttribute((const void *)ta_mfma_ks_kernel<DH, RB, NW, OCC, MODE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess)
             return e;
         attr_set[dev] = true;
     }
-    hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC, DIRECT>), dim3(p.n_wg, (p.rows + 32 * RB - 1) / (32 * RB)), dim3(64 * NW), smem,
+    hipLaunchKernelGGL((ta_mfma_ks_kernel<DH, RB, NW, OCC, MODE>), dim3(MODE == KS_SOLO ? p.B * p.Hkv : p.n_wg, (p.rows + 32 * RB - 1) / (32 * RB)), dim3(64 * NW), smem,
                        stream, TA_SCHED_ARGS(p), p);
     return hipGetLastError();
 }
@@ -749,11 +787,15 @@ hipError_t ta_launch_mfma_ks(const TAParams &p, hipStream_t stream, int dev)
 {
     if (dev < 0 || dev >= 64)
         return hipErrorInvalidDevice;
-    if ((p.ks_rows != 32 && p.ks_rows != 64) || p.rows_grp % p.ks_rows != 0 || !p.part_q15 || p.ls != 2)
+    if ((p.ks_rows != 32 && p.ks_rows != 64) || (!p.solo && p.rows_grp % p.ks_rows != 0) || !p.part_q15 || p.ls != 2)
         return hipErrorInvalidValue;
-    if (p.D == 128 && p.ks_rows == 32)
-        return p.direct ? launch_ks<128, 1, 8, 1, true>(p, stream, dev) : launch_ks<128, 1, 8, 1, false>(p, stream, dev);
-    if (p.D != 64 || p.direct)
+    if (p.solo && p.D == 128 && p.ks_rows == 32)
+        return launch_ks<128, 1, 8, 1, KS_SOLO>(p, stream, dev);
+    if (p.solo && p.D == 64)
+        return p.ks_rows == 32 ? launch_ks<64, 1, 8, 1, KS_SOLO>(p, stream, dev) : launch_ks<64, 2, 8, 1, KS_SOLO>(p, stream, dev);
+    if (p.D == 128 && p.ks_rows == 32 && !p.solo)
+        return p.direct ? launch_ks<128, 1, 8, 1, KS_DIRECT>(p, stream, dev) : launch_ks<128, 1, 8, 1, KS_CUT>(p, stream, dev);
+    if (p.D != 64 || p.direct || p.solo)
         return hipErrorInvalidValue;
-    return p.ks_rows == 32 ? launch_ks<64, 1, 8, 1, false>(p, stream, dev) : launch_ks<64, 2, 8, 1, false>(p, stream, dev);
+    return p.ks_rows == 32 ? launch_ks<64, 1, 8, 1, KS_CUT>(p, stream, dev) : launch_ks<64, 2, 8, 1, KS_CUT>(p, stream, dev);
 }

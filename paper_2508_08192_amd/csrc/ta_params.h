@@ -55,6 +55,7 @@ struct TAParams {
     int32_t basic;             // take the key-split matrix-core kernel, not the pipelined one
     int32_t ks_rows;           // rows one of its workgroups keeps: a row group, or an even part of one
     int32_t f32_mfma;          // fp32 inputs on the matrix cores (ta_f32.hip)
+    int32_t solo;              // one workgroup per list and block of rows walks it alone and writes the outputs: no merge pass
     int32_t direct;            // the key-split kernel writes the outputs of lists that lie in one share itself
     int32_t merge_kind;        // TA_MERGE_*: which merge kernel follows the KV pass
     int32_t part_q15;          // the partial outputs in ws_o are 16-bit fixed point with one scale per row
@@ -114,6 +115,7 @@ struct TAPlan {
     int32_t kernel;            // TA_KERNEL_GENERIC or TA_KERNEL_MFMA (basic is a flag of the parameters)
     int32_t n_wg, threads, n_rg, rows_grp, n_slots, min_q, merge_wgs;
     int32_t item_cost, merge_kind, table_row;
+    int32_t ks_rows;           // rows a workgroup of the key-split kernel keeps
 };
 
 struct TAProblem {
