@@ -105,32 +105,40 @@ int64_t key_split_workgroups(int64_t want, int slices)
     return n > 8 ? n - n % 8 : n;
 }
 
-// Longest list, in tiles, that one workgroup walks alone; 0 = never.  What it saves is the merge pass, its launch and the
-// partial results, 4 to 8 us; what it costs is that a list is not cut.  With up to a workgroup per compute unit the limit
-// rises with their number, as the cut would leave fewer of them per list.  Time over that of the cut lists, T 4 to 64,
-// lists of equal lengths and of a quarter of the longest up, calls back to back:
+// Do lists of up to `tiles` tiles go to one workgroup each?  0: no; TA_SOLO_WIDE: eight waves, a workgroup per compute unit;
+// TA_SOLO_PAIR: four waves, two workgroups.  What it saves is the merge pass, its launch and the partial results, 4 to 8 us;
+// what it costs is that a list is not cut.  With up to a workgroup per compute unit the limit rises with their number, as
+// the cut would leave fewer of them per list.  Time over that of the cut lists, T 4 to 64, lists of equal lengths and of a
+// quarter of the longest up, calls back to back:
 //   bf16, head_dim 128: 2 tiles 0.54 to 0.63; 16 workgroups 0.85 at 6 tiles, 0.95 at 9, 1.04 at 12; 64 of them 0.82 to 0.97 at
 //     12 and 1.0 at 15; 128 0.89 to 0.94 at 15 and 0.95 to 1.02 at 20; 192 0.80 to 0.87 at 26; 256 0.79 to 0.86 at 26
 //     and 0.84 to 0.93 at 33, where 240 take 1.04 to 1.07;
 //   bf16, head_dim 64: 16 workgroups 0.85 at 12 and 0.98 at 15, 128 0.94 to 0.96 at 26, 256 0.75 to 0.88 at 33;
 //   fp32, blocks of 16 rows, head_dim 64: few workgroups 0.84 at 4 and 0.96 at 6, 128 0.94 at 8, 256 0.73 to 0.85 at 14; head_dim 128:
 //     0.85 at 3 and 1.04 at 5, 128 0.88 to 0.99 at 6.
-// More workgroups than compute units are dealt out as others end.  With one block of rows each: 320 of them 0.83 to 0.98 up to
-// 14 tiles and 1.05 at 20; 384 and 400 0.85 to 0.99 at 20; 512 0.8 to 0.96 at 20, 0.96 to 1.0 at 33; 1024 0.95 to 0.99 at 33 and 65
-// (head_dim 64 0.79 to 0.95); fp32 320 0.96 at 14 (head_dim 64), 512 0.85 to 0.91 at 33, head_dim 128 0.93 to 0.96 at 14.  More blocks of
-// 32 rows per list than there are compute units read the keys too often (512: 1.0 at 2 tiles, 1.24 at 12).
-int64_t solo_tiles(bool f32, int D, int block_rows, int blocks, int64_t lists, int64_t cus)
+// More workgroups than compute units are dealt out as others end, so one's start should fall into another's stream: four waves
+// and half of the LDS each.  One block of rows, head_dim 128: 320 lists 0.43 at 2 tiles, 0.82 to 0.84 at 14 and 0.95 to 1.0
+// at 20; 384 0.89 to 0.94 at 20; 512 to 1024 0.44 to 0.66 at 5, 0.82 to 0.92 at 20 and 0.92 to 0.99 at 33 (head_dim 64 0.66 to 0.86),
+// from where uneven lists take up to 1.08; 1024 on eight waves 0.97 to 0.99 at 33 and 65, L 256..4096 202.9 -> 197.6 us.
+// Two to eight blocks, which read the keys from the L2 again: up to 512 workgroups 0.51 to 0.61 at 2 tiles, 0.65 to 0.89 at 9, 0.74 to 1.10 at
+// 14; two blocks and 1024 0.82 at 5 and 1.07 at 9 (head_dim 64 0.86).  fp32, eight waves: 320 lists 0.96 at 14 (head_dim 64), 512
+// 0.85 to 0.91 at 33, head_dim 128 0.93 to 0.96 at 14.
+int solo_kind(bool f32, int D, int block_rows, int blocks, int64_t lists, int64_t cus, int64_t tiles)
 {
     const int64_t wgs = lists * blocks;
     if (wgs <= cus) {
         const int64_t base = f32 ? (D == 64 ? 5 : 3) : D == 64 ? 13 : 9, rise = f32 ? (D == 64 ? 9 : 5) : 20;
-        return base + rise * wgs / cus;
+        return tiles <= base + rise * wgs / cus ? TA_SOLO_WIDE : 0;
     }
-    if (blocks > 1 || block_rows > 32)
-        return 0;
     if (f32)
-        return wgs < 2 * cus ? 8 : D == 64 ? 32 : 14;
-    return 2 * wgs < 3 * cus ? 14 : wgs < 2 * cus ? 20 : wgs < 4 * cus ? 32 : 66;
+        return blocks == 1 && tiles <= (wgs < 2 * cus ? 8 : D == 64 ? 32 : 14) ? TA_SOLO_WIDE : 0;
+    if (block_rows > 32)
+        return 0;
+    const int64_t one = 2 * wgs < 3 * cus ? 16 : wgs < 2 * cus ? 20 : 33;
+    const int64_t more = wgs <= 2 * cus && blocks <= 8 ? 10 : wgs <= 4 * cus && blocks == 2 ? 6 : 0;
+    if (tiles <= (blocks == 1 ? one : more))
+        return TA_SOLO_PAIR;
+    return blocks == 1 && wgs >= 4 * cus && tiles <= 66 ? TA_SOLO_WIDE : 0;
 }
 
 int find_row(int family, int rows_grp, int64_t lists)
@@ -444,12 +452,12 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // Lists of a few tiles go to one workgroup each (per block of rows), which writes the outputs itself: no schedule, no
     // partial results, no merge pass.  (Its 16- and 8-byte stores need the alignment that the row merge needs.)
     int solo_rows = f32_mfma ? 16 : 32;
-    if (!f32_mfma && D == 64 && p.rows > 32 && lists * ((p.rows + 31) / 32) > num_cus)
+    if (!f32_mfma && D == 64 && p.rows > 32 && lists * ((p.rows + 31) / 32) > num_cus && lists * ((p.rows + 63) / 64) <= num_cus)
         solo_rows = 64;
     const int solo_groups = (p.rows + solo_rows - 1) / solo_rows;
-    p.solo = auto_kernel && (f32_mfma || kernel == TA_KERNEL_MFMA) && num_splits == 0 && item_cost == 0 && lists > 0 &&
-             p.merge_kind != TA_MERGE_GENERAL &&
-             tiles_cap / lists <= solo_tiles(f32_mfma, (int)D, solo_rows, solo_groups, lists, num_cus);
+    if (auto_kernel && (f32_mfma || kernel == TA_KERNEL_MFMA) && num_splits == 0 && item_cost == 0 && lists > 0 &&
+        p.merge_kind != TA_MERGE_GENERAL)
+        p.solo = solo_kind(f32_mfma, (int)D, solo_rows, solo_groups, lists, num_cus, tiles_cap / lists);
     pl.merge_kind = p.merge_kind;
     const int mrows = ta_host_merge_rows(p);
     pl.merge_wgs = (int)lists * ((p.rows + mrows - 1) / mrows);

@@ -54,15 +54,16 @@ __device__ __forceinline__ float ks_swap_max(float x)      // over the two lanes
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// Largest x of the LPR (8 or 16) neighbouring lanes that share an output row, in each of them.
+// Largest x of the LPR (4, 8 or 16) neighbouring lanes that share an output row, in each of them.
 template <int LPR>
 __device__ __forceinline__ uint32_t ks_row_max(uint32_t x)
 {
-    static_assert(LPR == 8 || LPR == 16, "lanes of a row");
+    static_assert(LPR == 4 || LPR == 8 || LPR == 16, "lanes of a row");
     auto up = [&](uint32_t y) { x = y > x ? y : x; };
     up(__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false));     // lanes 1 0 3 2 of every four
     up(__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false));     // 2 3 0 1
-    up(__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false));    // mirrored within eight
+    if (LPR >= 8)
+        up(__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false));    // mirrored within eight
     if (LPR == 16)
         up(__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));    // rotated by eight within sixteen
     return x;
@@ -119,8 +120,8 @@ struct KsShape {
     static constexpr int RPL = KS_SUB / LD;                // token rows per load
     static constexpr int ROWS = 32 * RB;
     static constexpr int NT = 64 * NW;
-    static constexpr int QB = ROWS * ROW;                  // bytes of the Q rows, one 16-byte piece a thread
-    static_assert(QB / 16 <= NT, "one piece of Q a thread");
+    static constexpr int QB = ROWS * ROW;                  // bytes of the Q rows
+    static constexpr int QP = (QB / 16 + NT - 1) / NT;     // 16-byte pieces of them a thread loads
     static_assert(NS >= 1 && NS <= 2 && REGION >= ROWS * DH * 4, "ring and staging area");
     static_assert(NW >= 4 && NW % 4 == 0, "at most one of a list's last three runs per wave; results are added up in fours");
 };
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
     // 32 from lo, and the T tree tokens; run u belongs to wave u % NW
     int b = -1, g = 0, slot = 0, L = 0, S = 0, lo = 0, hi = 0, n_pre = 0, n_sub = 0, n_full = 0, bad = 0;
     bool has_tree = false, whole = false;                  // whole: a list that lies in this share alone
-    uint4 q_piece = make_uint4(0, 0, 0, 0);                // this thread's piece of the item's Q rows
+    uint4 q_piece[C::QP] = {};                             // this thread's pieces of the item's Q rows
     int pg = 0, pg_first = 0, pg_last = 0, parent = 0;     // pages of full runs, of the first and of the last run; tree
     unsigned long long gmask = 0;
     const uint16_t *kgp = nullptr, *vgp = nullptr;
@@ -305,13 +306,14 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
             kgp = (const uint16_t *)p.k + (int64_t)g * p.k_sh;
             vgp = (const uint16_t *)p.v + (int64_t)g * p.v_sh;
             const int l = fresh_lane();
-            {
+#pragma unroll
+            for (int i = 0; i < C::QP; ++i) {
                 // rows past the group's end repeat its first row (their results are never stored)
-                const int x = wave * 64 + l, row = x / SLOTS;
-                if (C::QB / 16 == C::NT || row < C::ROWS) {
+                const int x = i * C::NT + wave * 64 + l, row = x / SLOTS;
+                if (C::QB / 16 >= C::NT || row < C::ROWS) {
                     const int R = row0 + (row < rows_here ? row : 0);
                     const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);      // R / G
-                    q_piece = *(const uint4 *)((const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
+                    q_piece[i] = *(const uint4 *)((const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
                                                (int64_t)(g * p.G + R - node * p.G) * p.q_sh + 8 * (x % SLOTS));
                 }
             }
@@ -360,7 +362,9 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         int u = wave, pg_base = 0;
         // everything requested is here: no wait of the compiler for it may fall behind the loads into LDS, which it does
         // not know of
-        asm volatile("" : "+v"(q_piece.x), "+v"(q_piece.y), "+v"(q_piece.z), "+v"(q_piece.w));
+#pragma unroll
+        for (int i = 0; i < C::QP; ++i)
+            asm volatile("" : "+v"(q_piece[i].x), "+v"(q_piece[i].y), "+v"(q_piece[i].z), "+v"(q_piece[i].w));
         if (u < n_sub) {
             asm volatile("" : "+v"(pg), "+v"(pg_first), "+v"(pg_last), "+v"(parent), "+v"(gmask));
             if (paged) {
@@ -375,9 +379,13 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         // whose run is not whole, which makes its addresses row by row: 62 lists of four to seventeen tiles 18.7 us a call,
         // with the barrier here 17.3; calls of whole runs differ by 0.3 us the other way.)
         {
-            const int l = fresh_lane(), x = wave * 64 + l, row = x / SLOTS;
-            if (C::QB / 16 == C::NT || row < C::ROWS)
-                *(uint4 *)(qrows + row * C::ROW + (((x % SLOTS) ^ kx(row)) << 4)) = q_piece;
+            const int l = fresh_lane();
+#pragma unroll
+            for (int i = 0; i < C::QP; ++i) {
+                const int x = i * C::NT + wave * 64 + l, row = x / SLOTS;
+                if (C::QB / 16 >= C::NT || row < C::ROWS)
+                    *(uint4 *)(qrows + row * C::ROW + (((x % SLOTS) ^ kx(row)) << 4)) = q_piece[i];
+            }
             ks_lds_barrier();
         }
 
@@ -789,6 +797,8 @@ hipError_t ta_launch_mfma_ks(const TAParams &p, hipStream_t stream, int dev)
         return hipErrorInvalidDevice;
     if ((p.ks_rows != 32 && p.ks_rows != 64) || (!p.solo && p.rows_grp % p.ks_rows != 0) || !p.part_q15 || p.ls != 2)
         return hipErrorInvalidValue;
+    if (p.solo == TA_SOLO_PAIR && p.ks_rows == 32)
+        return p.D == 128 ? launch_ks<128, 1, 4, 2, KS_SOLO>(p, stream, dev) : launch_ks<64, 1, 4, 2, KS_SOLO>(p, stream, dev);
     if (p.solo && p.D == 128 && p.ks_rows == 32)
         return launch_ks<128, 1, 8, 1, KS_SOLO>(p, stream, dev);
     if (p.solo && p.D == 64)

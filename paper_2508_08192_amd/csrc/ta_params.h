@@ -55,7 +55,7 @@ struct TAParams {
     int32_t basic;             // take the key-split matrix-core kernel, not the pipelined one
     int32_t ks_rows;           // rows one of its workgroups keeps: a row group, or an even part of one
     int32_t f32_mfma;          // fp32 inputs on the matrix cores (ta_f32.hip)
-    int32_t solo;              // one workgroup per list and block of rows walks it alone and writes the outputs: no merge pass
+    int32_t solo;              // TA_SOLO_*: one workgroup per list and block of rows walks it alone and writes the outputs
     int32_t direct;            // the key-split kernel writes the outputs of lists that lie in one share itself
     int32_t merge_kind;        // TA_MERGE_*: which merge kernel follows the KV pass
     int32_t part_q15;          // the partial outputs in ws_o are 16-bit fixed point with one scale per row
@@ -87,6 +87,10 @@ struct TACompact {
     int32_t vec;                       // rows can be moved in 16-byte pieces
     int32_t *status;
 };
+
+// How lists that are not cut are walked (no merge pass follows); 0: lists are cut.
+#define TA_SOLO_WIDE 1        // eight waves, one workgroup per compute unit at a time
+#define TA_SOLO_PAIR 2        // four waves, two workgroups (key-split kernel, blocks of 32 rows)
 
 // Which merge kernel combines the partial results.
 #define TA_MERGE_GENERAL 0    // one wave per output row, any head_dim and alignment

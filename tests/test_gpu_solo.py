@@ -54,13 +54,38 @@ def test_where_it_ends(dtype, D, Hq, T, tiles):
 
 
 @pytest.mark.parametrize("dtype,D,B,Hkv,T,G", [("bf16", 128, 256, 1, 8, 4), ("bf16", 128, 65, 4, 8, 4), ("bf16", 64, 128, 2, 16, 4),
-                                               ("bf16", 64, 150, 2, 8, 4), ("f32", 64, 129, 2, 4, 2), ("f32", 128, 300, 2, 4, 4)])
+                                               ("bf16", 64, 150, 2, 8, 4), ("f32", 64, 129, 2, 4, 2), ("f32", 128, 300, 2, 4, 4),
+                                               ("bf16", 128, 300, 1, 5, 1), ("bf16", 128, 100, 4, 11, 3), ("bf16", 64, 70, 8, 3, 4),
+                                               ("bf16", 128, 60, 2, 27, 4), ("bf16", 128, 60, 1, 64, 4), ("bf16", 64, 200, 2, 16, 4)])
 def test_as_many_lists_as_compute_units_and_more(dtype, D, B, Hkv, T, G):
     rng = np.random.default_rng(B)
     w = W.make_workload("many", B=B, T=T, Hq=G * Hkv, Hkv=Hkv, D=D, seq_lens=rng.integers(0, 300, size=B), trees=W.chain_tree(T),
                         page_size=32, seed=B, dtype=dtype)
     w.kv_start = (w.seq_lens // 3).astype(np.int32)
     _check(w, "solo %s D=%d B=%d" % (dtype, D, B))
+
+
+def test_write_back_of_more_lists_than_compute_units():
+    """The four-wave kernel's part of the write-back, for one and for two blocks of rows."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    for T in (5, 12):
+        w = W.make_workload("pairs", B=100, T=T, Hq=12, Hkv=3, D=128, seq_lens=np.arange(100), trees=W.chain_tree(T), page_size=16, seed=T)
+        new = [torch.randn(100, T, 3, 128, generator=torch.Generator().manual_seed(s)).bfloat16().cuda() for s in (1, 2)]
+        res = []
+        for folded in (False, True):
+            d = to_device(w)
+            assert _solo(w, d)
+            args = (d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"], d["lse"])
+            if folded:
+                ta.tree_attn_fwd_ex(*args, k_new=new[0], v_new=new[1])
+            else:
+                ta.tree_attn_append(new[0], new[1], *args[1:5])
+                ta.tree_attn_fwd(*args)
+            torch.cuda.synchronize()
+            res.append([d[x] for x in ("out", "lse", "k_cache", "v_cache")])
+        for x, y in zip(*res):
+            assert torch.equal(x, y)
 
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
