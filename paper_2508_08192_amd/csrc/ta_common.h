@@ -25,14 +25,15 @@ __device__ __forceinline__ void ta_raise(const TAParams &p, int bits)
 struct TASched {
     const int32_t *seq_lens, *kv_start;
     int64_t sl_s;
-    int32_t B, T, capacity, pad, Hkv, n_wg, min_q;
+    int32_t B, T, capacity, pad, Hkv, n_wg, min_q, one_parts;
 };
 #define TA_SCHED_PARAMS                                                                                                  \
     const int32_t *sc_lens, const int32_t *sc_start, int64_t sc_sl_s, int sc_B, int sc_T, int sc_cap, int sc_pad, int sc_Hkv, \
-        int sc_n_wg, int sc_min_q
+        int sc_n_wg, int sc_min_q, int sc_one_parts
 #define TA_SCHED_ARGS(p) \
-    (p).seq_lens, (p).kv_start, (p).sl_s, (p).B, (p).T, (p).capacity, (p).pad, (p).Hkv, (p).n_wg, (p).min_q
-#define TA_SCHED TASched{sc_lens, sc_start, sc_sl_s, sc_B, sc_T, sc_cap, sc_pad, sc_Hkv, sc_n_wg, sc_min_q}
+    (p).seq_lens, (p).kv_start, (p).sl_s, (p).B, (p).T, (p).capacity, (p).pad, (p).Hkv, (p).n_wg, (p).min_q, \
+        (p).one_parts
+#define TA_SCHED TASched{sc_lens, sc_start, sc_sl_s, sc_B, sc_T, sc_cap, sc_pad, sc_Hkv, sc_n_wg, sc_min_q, sc_one_parts}
 
 // Reads the argument block's lines at once, and waits for them (and for `x`): called where the first loads are on their way.
 // (The compiler loads an argument where it is first used, so lines that are missing would be waited for one by one.)
@@ -161,10 +162,23 @@ __device__ __forceinline__ int ta_build_schedule(const TASched &p, int *cum, int
 template <typename P>
 __device__ __forceinline__ int ta_share(const P &p, int total)
 {
-    int share = (total + p.n_wg - 1) / p.n_wg;
+    int n = p.n_wg;
+    const bool one = total <= 8 * p.one_parts;
+    if (one && n > p.one_parts)
+        n = p.one_parts;
+    int share = (total + n - 1) / n;
+    if (one && share == 5)
+        share = 6;
     return share < p.min_q ? p.min_q : share;
 }
 
+// A single list of the key-split kernel is cut into no more partial results than its merge, a workgroup per row, takes in one
+// round (64; head_dim 64: 128), as long as that leaves shares of up to eight units, and six where it would be five (their
+// ten runs of 32 tokens are a round and a quarter of the eight waves: 16384 tokens 17.9 us with five, 15.4 with six).  8 and 5
+// heads on one KV head, T 4 to 16, us a call by graph replay, without and with: 8192 tokens 16.1 to 17.2 -> 14.9 to 15.9, 12500
+// 16.4 to 17.3 -> 15.3 to 16.5, 16384 16.5 to 18.6 -> 14.6 to 15.9, 20000 16.8 to 18.2 -> 14.8 to 16.1, 32000 17.5 to 19.1 -> 16.5 to 18.0; from 48000
+// on more workgroups are the faster (17.7 against 19.7).  Head_dim 64, one block of rows, 16384 14.1 -> 12.7.
+//
 // Units [t, t_end) of workgroup w.  The line is cut evenly, at floor(k * total / n_act), among the n_act workgroups
 // that have work: all of them when that gives each at least TA_EVEN_CUT_FROM units (and the smallest share), else
 // as many as whole shares of ceil(total / n_wg) units (at least min_q) fill, so that a small batch is not cut into
@@ -178,7 +192,7 @@ __device__ __forceinline__ void ta_wg_range(const P &p, int total, int w, int &t
 {
     const int share = ta_share(p, total);
     const int floor_share = p.min_q > TA_EVEN_CUT_FROM ? p.min_q : TA_EVEN_CUT_FROM;
-    const int n_act = (int64_t)p.n_wg * floor_share <= total ? p.n_wg : (total + share - 1) / share;
+    const int n_act = (int64_t)p.n_wg * floor_share <= total && total > 8 * p.one_parts ? p.n_wg : (total + share - 1) / share;
     // floor(k * total / n_act) = k * q + floor(k * r / n_act) with total = q * n_act + r: 32-bit divisions (k * r stays
     // below n_act squared) instead of two 64-bit ones, which cost every workgroup most of a microsecond at its start
     if (__builtin_expect(n_act <= 0xffff, 1)) {
