@@ -433,8 +433,12 @@ __global__ __launch_bounds__(64 * f32_waves(SOLO), 2) void ta_f32_kv_kernel(TA_S
                 mw[x] = stat[x][0][row];
                 big = fmaxf(big, mw[x]);
             }
+            // the waves that met a score above -inf; only they are added up, also where the weight of one vanishes: a zero times an
+            // infinity among its values is the NaN that column is due
+            uint32_t met = 0;
 #pragma unroll
             for (int x = 0; x < F32_NW; ++x) {
+                met |= (mw[x] != -INFINITY ? 1u : 0u) << x;
                 mw[x] = mw[x] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[x] - big);     // weight of the wave's result
                 l_tot = fmaf(mw[x], stat[x][1][row], l_tot);
             }
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(64 * f32_waves(SOLO), 2) void ta_f32_kv_kernel(TA_S
                     f32_x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int x = 0; x < F32_NW; ++x)
-                        if (mw[x] != 0.f)
+                        if ((met >> x) & 1u)
                             acc += mw[x] * *(const f32_x4 *)(lds[x] + row * DH + 4 * (ch ^ (row & 15)));
                     acc *= inv;
                     const float q_nan = __uint_as_float(0x7fc00000u);
@@ -469,7 +473,7 @@ __global__ __launch_bounds__(64 * f32_waves(SOLO), 2) void ta_f32_kv_kernel(TA_S
                     f32_x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int x = 0; x < F32_NW; ++x)
-                        if (mw[x] != 0.f)
+                        if ((met >> x) & 1u)
                             acc += mw[x] * *(const f32_x4 *)(lds[x] + row * DH + 4 * (ch ^ (row & 15)));
                     *(f32_x4 *)(p.ws_o + wrow * DH + 4 * ch) = any_bad ? f32_x4{0.f, 0.f, 0.f, 0.f} : acc * inv;
                 }

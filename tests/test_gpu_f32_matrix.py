@@ -112,6 +112,32 @@ def test_infinities_and_nans_come_out_as_from_the_scalar_kernel():
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("below", [120, 130, 140, 200])
+@pytest.mark.parametrize("splits", [0, 1])
+def test_an_infinite_value_counts_however_small_its_probability(D, below, splits):
+    """A run of 16 tokens whose scores lie 2^below under the others' (a wave of its own walks it), one value of it infinite:
+    that column is no number, the others are, and the log-sum-exp is that of the other tokens."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    w = W.make_workload("far", B=1, T=1, Hq=2, Hkv=1, D=D, seq_lens=[64], trees=W.chain_tree(1), page_size=128, seed=5,
+                        dtype="f32", paged=False)
+    d = to_device(w)
+    d["q"].zero_()
+    d["q"][..., 0] = 1.0
+    d["k_cache"][..., 0] = 0.0
+    d["k_cache"][0, 0, 16:32, 0] = -below * float(np.log(2) * np.sqrt(D))
+    d["v_cache"][0, 0, 20, 5] = float("inf")
+    print("f32 far below D=%d below=%d splits=%d" % (D, below, splits), flush=True)
+    out, lse = torch.zeros_like(d["q"]), torch.zeros((1, 2, 1), device="cuda")
+    ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], None, d["seq_lens"], d["tree_parent"], out, lse, num_splits=splits)
+    torch.cuda.synchronize()
+    finite = torch.isfinite(out)
+    assert not finite[..., 5].any()
+    finite[..., 5] = True
+    assert finite.all() and (lse - float(np.log(49))).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("folded", [False, True])
 def test_requests_with_mistakes_are_spoiled_and_reported(D, folded):
     check_requests_with_mistakes("f32", D, folded)
