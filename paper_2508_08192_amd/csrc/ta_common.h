@@ -174,10 +174,12 @@ __device__ __forceinline__ int ta_share(const P &p, int total)
 
 // A single list of the key-split kernel is cut into no more partial results than its merge, a workgroup per row, takes in one
 // round (64; head_dim 64: 128), as long as that leaves shares of up to eight units, and six where it would be five (their
-// ten runs of 32 tokens are a round and a quarter of the eight waves: 16384 tokens 17.9 us with five, 15.4 with six).  8 and 5
-// heads on one KV head, T 4 to 16, us a call by graph replay, without and with: 8192 tokens 16.1 to 17.2 -> 14.9 to 15.9, 12500
-// 16.4 to 17.3 -> 15.3 to 16.5, 16384 16.5 to 18.6 -> 14.6 to 15.9, 20000 16.8 to 18.2 -> 14.8 to 16.1, 32000 17.5 to 19.1 -> 16.5 to 18.0; from 48000
-// on more workgroups are the faster (17.7 against 19.7).  Head_dim 64, one block of rows, 16384 14.1 -> 12.7.
+// ten runs of 32 tokens are a round and a quarter of the eight waves).  Us a call by graph replay in a table as wide as the
+// list, without and with: 32 rows 25600 tokens 18.4 -> 17.3, 32384 19.0 -> 17.9; 60 and 64 rows 17280 17.8 -> 17.1, 25600 18.7 to 19.1 -> 17.5; 128
+// rows, which are cut into 64 at most anyway, 17280 20.9 -> 17.5 by the six; head_dim 64, 32 rows, 25600 14.4 -> 13.4.  From
+// 48000 tokens on more workgroups are the faster (17.7 against 19.7).  With fewer workgroups than that (or, head_dim 64, as
+// many), whose shares are longer, six units only leave some of them idle: 512 rows, 3900 tokens 22.4 us with six, 20.6 with five; 256
+// rows, 8000 tokens 19.4 and 17.5; head_dim 64, 128 rows, 17280 tokens 15.3 and 14.9.
 //
 // Units [t, t_end) of workgroup w.  The line is cut evenly, at floor(k * total / n_act), among the n_act workgroups
 // that have work: all of them when that gives each at least TA_EVEN_CUT_FROM units (and the smallest share), else

@@ -449,7 +449,10 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // merged and read again (its stores need the alignment that the row merge needs): B 128, 32/8 heads, T 8, L 256..4096
     // 206.6 -> 202.5 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
     p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind == TA_MERGE_ROW && lists >= 2 * (int64_t)pl.n_wg;
-    p.one_parts = ks && lists == 1 && num_splits == 0 && p.merge_kind == TA_MERGE_WIDE ? 8192 / (int)D : 0;
+    if (ks && lists == 1 && num_splits == 0 && p.merge_kind == TA_MERGE_WIDE) {
+        const int parts = 8192 / (int)D;                    // (fewer workgroups: see ta_share)
+        p.one_parts = pl.n_wg > parts || (D == 128 && pl.n_wg == parts) ? parts : 0;
+    }
     // Lists of a few tiles go to one workgroup each (per block of rows), which writes the outputs itself: no schedule, no
     // partial results, no merge pass.  (Its 16- and 8-byte stores need the alignment that the row merge needs.)
     int solo_rows = f32_mfma ? 16 : 32;

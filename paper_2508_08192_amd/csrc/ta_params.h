@@ -36,7 +36,7 @@ struct TAParams {
     int32_t n_rg;              // row groups
     int32_t n_wg;              // workgroups of the KV pass along x
     int32_t min_q;             // smallest share of tiles a workgroup takes
-    int32_t one_parts;         // key-split kernel, one list: partial results that its merge takes in one round, else 0
+    int32_t one_parts;         // key-split kernel, one list that it can cut into as many: partial results that its merge takes in one round, else 0
     int32_t pad;               // schedule units a list counts on top of its tiles (fixed cost per list)
     uint32_t g_magic;          // 2^24 / G + 1: R / G == mulhi(R << 8, g_magic) for R * G < 2^24 (matrix-core kernels)
     const int32_t *kv_start;   // [B] window starts, or null

@@ -1,8 +1,9 @@
 """The rules by which the KV pass cuts the batch's tile lists into workgroup shares, restated on the host and checked
 for the properties the kernels rely on: every tile belongs to exactly one workgroup, a list's owners are
 consecutive workgroups (the merge pass reads the partials of all workgroups from the owner of the list's first tile to
-the owner of its last one), no share is longer than ceil(total / n_wg) or the smallest share, and batches of equal
-lists that divide evenly among the workgroups are cut at the lists' edges.
+the owner of its last one), no share is longer than ceil(total / n_wg) or the smallest share (a single list that is cut by what its
+merge takes in one round: eight units), and batches of equal lists that divide evenly among the workgroups are cut at the
+lists' edges.
 
 The device code lives in paper_2508_08192_amd/csrc/ta_common.h (ta_build_schedule, ta_share, ta_wg_range) and at the
 top of the item loops of the KV kernels; the GPU parity tests exercise it directly.  This file pins the arithmetic
@@ -21,15 +22,26 @@ def _units(lens, Hkv, pad):
     return out, u
 
 
-def _cuts(total, n_wg, min_q):
-    share = max(min_q, -(-total // n_wg))
-    n_act = n_wg if n_wg * max(8, min_q) <= total else -(-total // share)
+def one_list_parts(D, n_wg):
+    """Partial results of a single list that its merge takes in one round, where the key-split kernel is cut by them; else 0."""
+    parts = 8192 // D
+    return parts if n_wg > parts or (D == 128 and n_wg == parts) else 0
+
+
+def _cuts(total, n_wg, min_q, one_parts=0):
+    one = total <= 8 * one_parts
+    share = -(-total // (min(n_wg, one_parts) if one else n_wg))
+    if one and share == 5:
+        share = 6
+    share = max(min_q, share)
+    n_act = n_wg if n_wg * max(8, min_q) <= total and not one else -(-total // share)
     return [total if k >= n_act else k * total // n_act for k in range(n_wg + 1)], share
 
 
-def _check(lens, Hkv, pad, n_wg, min_q):
+def _check(lens, Hkv, pad, n_wg, min_q, one_parts=0):
     lists, total = _units(lens, Hkv, pad)
-    cuts, share = _cuts(total, n_wg, min_q)
+    cuts, share = _cuts(total, n_wg, min_q, one_parts)
+    assert share <= max(-(-total // n_wg), min_q, 8 if total <= 8 * one_parts else 0)
     assert cuts[0] == 0 and cuts[-1] == total and all(0 <= b - a <= share for a, b in zip(cuts, cuts[1:]))
     owner_of_tile = {}
     for w in range(n_wg):
@@ -78,3 +90,18 @@ def test_shares_partition_the_tiles_and_the_merge_formula_finds_the_owners():
         n_wg = int(rng.choice([1, 2, 3, 7, 64, 256, 1024]))
         min_q = int(rng.choice([1, 4]))
         _check([int(x) for x in lens], Hkv, pad, n_wg, min_q)
+
+
+def test_one_list_is_cut_by_what_its_merge_takes_in_one_round():
+    for D in (64, 128):
+        for n_wg in (1, 8, 16, 32, 40, 64, 80, 128, 256, 304):
+            parts = one_list_parts(D, n_wg)
+            for tiles in range(1, 1200, 7):
+                for pad in (5, 7):
+                    _check([64 * (tiles - 1)], 1, pad, n_wg, 1, parts)
+                    cuts, share = _cuts(tiles + pad, n_wg, 1, parts)
+                    n_act = sum(b > a for a, b in zip(cuts, cuts[1:]))
+                    if parts and tiles + pad <= 8 * parts:
+                        assert n_act <= parts and share != 5
+                    else:
+                        assert (cuts, share) == _cuts(tiles + pad, n_wg, 1)
