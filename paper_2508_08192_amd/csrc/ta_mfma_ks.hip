@@ -375,9 +375,7 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
         }
 
         // Q rows to LDS.  (Each wave loading its own fragments, 32 rows by 32 scattered bytes at a time, kept the load units
-        // busy for most of a microsecond.  With the barrier behind the loads of the first runs, all waves wait for the one
-        // whose run is not whole, which makes its addresses row by row: 62 lists of four to seventeen tiles 18.7 us a call,
-        // with the barrier here 17.3; calls of whole runs differ by 0.3 us the other way.)
+        // busy for most of a microsecond.)
         {
             const int l = fresh_lane();
 #pragma unroll
@@ -386,7 +384,6 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
                 if (C::QB / 16 >= C::NT || row < C::ROWS)
                     *(uint4 *)(qrows + row * C::ROW + (((x % SLOTS) ^ kx(row)) << 4)) = q_piece[i];
             }
-            ks_lds_barrier();
         }
 
         // Loads of run u, K or V part, into ring slot sl: LD loads of 1 KB.
@@ -466,10 +463,23 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
             else
                 ks_vm_wait<0>();
         };
+        // The waves meet once for Q.  A wave whose first runs are whole requests them before it does; one that makes its
+        // addresses row by row, which takes longer, requests them behind, lest all wait for it (head_dim 128: 62 lists of four to
+        // seventeen tiles 18.7 us a call with the meeting behind all loads, 17.3 before all and so; one list of 64 rows and
+        // 64000 tokens 21.1 before all, 19.9 so).  Before all loads where that is the faster: head_dim 64, whose runs are half
+        // as long (one list of 25600 tokens 13.4 us, 13.8 with early loads), and short lists walked alone (two tiles 9.4 and 9.9).
+        const int u_2nd = u + (C::NS - 1) * NW;
+        // (a scalar: each wave meets the others exactly once, by a branch)
+        const int early = __builtin_amdgcn_readfirstlane(DH == 128 && !SOLO && fast_geom && u < n_full && lo + u * KS_SUB >= S &&
+                                                         (u_2nd < n_full || u_2nd >= n_sub));
+        if (!early)
+            ks_lds_barrier();
 #pragma unroll 1
         for (int k = 0; k < 2 * C::NS; ++k)                    // K and V of the wave's first run, and of its second
             if (u + (k >> 1) * NW < n_sub)
                 issue(u + (k >> 1) * NW, k >> 1, k & 1);
+        if (early)
+            ks_lds_barrier();
         // while the first runs are on their way: Q fragments into every wave's registers, O = 0 and, in a wave that has tree
         // tokens, the ancestor masks
         uint4 qf[RB][NKK];
