@@ -126,17 +126,19 @@ struct KsShape {
     static_assert(NW >= 4 && NW % 4 == 0, "at most one of a list's last three runs per wave; results are added up in fours");
 };
 
-template <int DH, int RB, int NW, int OCC>
-static size_t ks_smem(int B)
-{
-    return KsShape<DH, RB, NW, OCC>::RING + KsShape<DH, RB, NW, OCC>::QB + sizeof(float) * 3 * NW * 32 * RB + sizeof(int) * NW +
-           (B <= TA_WAVE ? 0 : sizeof(int) * (B + 2 + (B <= KS_LENS ? 2 * B : 0)));
-}
-
 // What a workgroup's lists are.  KS_CUT: a share of the line of all lists.  KS_DIRECT: the same, and the outputs of a list that
 // lies in one share are written here (an instance of its own: calls without many lists are 1 % slower with that code in
 // the kernel).  KS_SOLO: workgroup x walks list x from end to end (see p.solo).
 enum { KS_CUT, KS_DIRECT, KS_SOLO };
+
+// LDS of a workgroup.  (A workgroup that walks one list alone keeps no schedule.)
+template <int DH, int RB, int NW, int OCC, int MODE>
+static constexpr size_t ks_smem(int B)
+{
+    using C = KsShape<DH, RB, NW, OCC>;
+    return C::RING + C::QB + sizeof(float) * 3 * NW * C::ROWS + sizeof(int) * NW +
+           (MODE == KS_SOLO || B <= TA_WAVE ? 0 : sizeof(int) * (B + 2 + (B <= KS_LENS ? 2 * B : 0)));
+}
 
 template <int DH, int RB, int NW, int OCC, int MODE>
 __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SCHED_PARAMS, TAParams p)
@@ -787,7 +789,8 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
 template <int DH, int RB, int NW, int OCC, int MODE>
 static hipError_t launch_ks(const TAParams &p, hipStream_t stream, int dev)
 {
-    const size_t smem = ks_smem<DH, RB, NW, OCC>(p.B);
+    const size_t smem = ks_smem<DH, RB, NW, OCC, MODE>(p.B);
+    static_assert(OCC * ks_smem<DH, RB, NW, OCC, MODE>(TA_MAX_BATCH) <= 160 * 1024, "OCC workgroups per compute unit, whatever the batch");
     if (smem > 160 * 1024)
         return hipErrorInvalidValue;
     static bool attr_set[64] = {};      // per device and instance; setting it twice is harmless
