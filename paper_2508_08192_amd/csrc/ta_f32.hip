@@ -39,7 +39,7 @@ __device__ __forceinline__ void f32_lds_barrier()
 // (36 MB in 16 lists, 190 of 256 workgroups busy with up to three tiles: 21.1 us a call with four, 22.0 with eight).
 constexpr int f32_waves(bool solo) { return solo ? 8 : 4; }
 
-// RB: blocks of 16 query rows; NEW: the tree tokens of this step lie in tensors of their own (ta_opts.k_new);
+// RB: blocks of 16 query rows (SOLO: one); NEW: the tree tokens of this step lie in tensors of their own (ta_opts.k_new);
 // SOLO: workgroup x walks list x from end to end and writes its outputs (see p.solo)
 template <int DH, int RB, bool NEW, bool SOLO>
 __global__ __launch_bounds__(64 * f32_waves(SOLO), 2) void ta_f32_kv_kernel(TA_SCHED_PARAMS, TAParams p)
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(64 * f32_waves(SOLO), 2) void ta_f32_kv_kernel(TA_S
 
     while (t < t_end) {
         // ---- the next item: a list (b, g), its tiles [j0, j1), i.e. the prefix tokens [max(lo, S), hi), walked in runs of
-        // 16 from lo, and the T tree tokens; run u belongs to wave u % 4
+        // 16 from lo, and the T tree tokens; run u belongs to wave u % F32_NW
         int b, g, L, S, n_b, j0, j1, slot = 0;
         if constexpr (SOLO) {
             t = t_end;
@@ -524,7 +524,12 @@ hipError_t ta_launch_f32(const TAParams &p, hipStream_t stream, int dev)
     auto launch = [&](auto d, auto fold, auto alone) {
         constexpr int DH = decltype(d)::value;
         constexpr bool NEW = decltype(fold)::value, SOLO = decltype(alone)::value;
-        return p.rows_grp <= 16 ? launch_f32<DH, 1, NEW, SOLO>(p, stream, dev) : launch_f32<DH, 2, NEW, SOLO>(p, stream, dev);
+        if (p.rows_grp <= 16)
+            return launch_f32<DH, 1, NEW, SOLO>(p, stream, dev);
+        if constexpr (SOLO)
+            return hipErrorInvalidValue;                     // (a list walked alone is in blocks of up to 16 rows)
+        else
+            return launch_f32<DH, 2, NEW, false>(p, stream, dev);
     };
     auto fold = [&](auto d, auto alone) { return p.kn ? launch(d, std::true_type{}, alone) : launch(d, std::false_type{}, alone); };
     auto with = [&](auto d) { return p.solo ? fold(d, std::true_type{}) : fold(d, std::false_type{}); };
