@@ -118,8 +118,9 @@ int64_t key_split_workgroups(int64_t want, int slices)
 //     0.85 at 3 and 1.04 at 5, 128 0.88 to 0.99 at 6.
 // More workgroups than compute units are dealt out as others end, so one's start should fall into another's stream: four waves
 // and half of the LDS each.  One block of rows, head_dim 128: 320 lists 0.43 at 2 tiles, 0.82 to 0.84 at 14 and 0.95 to 1.0
-// at 20; 384 0.89 to 0.94 at 20; 512 to 1024 0.44 to 0.66 at 5, 0.82 to 0.92 at 20 and 0.92 to 0.99 at 33 (head_dim 64 0.66 to 0.86),
-// from where uneven lists take up to 1.08; 1024 on eight waves 0.97 to 0.99 at 33 and 65, L 256..4096 202.9 -> 197.6 us.
+// at 20; 384 0.89 to 0.94 at 20; 512 to 1024 0.44 to 0.66 at 5, 0.82 to 0.92 at 20 and 0.92 to 0.99 at 33 (head_dim 64 0.66 to 0.86).
+// Longer ones are cut: eight waves each take 0.96 to 1.01 at 40 to 80 tiles with 512 to 2048 lists of equal or evenly spread lengths,
+// but 1.04 to 1.68 where one list or an eighth of them is much longer than the rest (1024 lists, 66 tiles: 61.2 -> 79.4 us).
 // Two to eight blocks, which read the keys from the L2 again: up to 512 workgroups 0.51 to 0.61 at 2 tiles, 0.65 to 0.89 at 9, 0.74 to 1.10 at
 // 14; two blocks and 1024 0.82 at 5 and 1.07 at 9 (head_dim 64 0.86).  fp32, eight waves: 320 lists 0.96 at 14 (head_dim 64), 512
 // 0.85 to 0.91 at 33, head_dim 128 0.93 to 0.96 at 14.
@@ -136,9 +137,7 @@ int solo_kind(bool f32, int D, int block_rows, int blocks, int64_t lists, int64_
         return 0;
     const int64_t one = 2 * wgs < 3 * cus ? 16 : wgs < 2 * cus ? 20 : 33;
     const int64_t more = wgs <= 2 * cus && blocks <= 8 ? 10 : wgs <= 4 * cus && blocks == 2 ? 6 : 0;
-    if (tiles <= (blocks == 1 ? one : more))
-        return TA_SOLO_PAIR;
-    return blocks == 1 && wgs >= 4 * cus && tiles <= 66 ? TA_SOLO_WIDE : 0;
+    return tiles <= (blocks == 1 ? one : more) ? TA_SOLO_PAIR : 0;
 }
 
 int find_row(int family, int rows_grp, int64_t lists)

@@ -294,6 +294,15 @@ def test_which_matrix_core_kernel_takes_a_call(B, T, Hq, Hkv, max_pages, want):
     assert p["key_split"] == want, p
 
 
+@pytest.mark.parametrize("B", [64, 127, 128, 129, 512])
+@pytest.mark.parametrize("max_pages", [40, 65, 66, 130])
+def test_long_lists_are_cut_however_many_there_are(B, max_pages):
+    """One workgroup per list would leave the longest of an uneven batch to a single one."""
+    for D in (64, 128):
+        p = _plan(_good(B=B, T=8, Hq=32, Hkv=8, D=D, max_pages=max_pages, pages=B * max_pages), num_cus=256)
+        assert p["merge_workgroups"] > 0, p
+
+
 def test_head_dim_64_keeps_32_rows_only_with_two_workgroups_per_list():
     for B, rows in ((8, 32), (16, 64)):
         assert _plan(_good(B=B, T=16, Hq=32, Hkv=8, D=64, max_pages=5, pages=B * 5), num_cus=256)["rows_per_group"] == rows
