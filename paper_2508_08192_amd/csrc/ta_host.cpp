@@ -107,35 +107,52 @@ int64_t key_split_workgroups(int64_t want, int slices)
 
 // Do lists of up to `tiles` tiles go to one workgroup each?  0: no; TA_SOLO_WIDE: eight waves, a workgroup per compute unit;
 // TA_SOLO_PAIR: four waves, two workgroups.  What it saves is the merge pass, its launch and the partial results, 4 to 8 us;
-// what it costs is that a list is not cut.  With up to a workgroup per compute unit the limit rises with their number, as
-// the cut would leave fewer of them per list.  Time over that of the cut lists, T 4 to 64, lists of equal lengths and of a
-// quarter of the longest up, calls back to back:
-//   bf16, head_dim 128: 2 tiles 0.54 to 0.63; 16 workgroups 0.85 at 6 tiles, 0.95 at 9, 1.04 at 12; 64 of them 0.82 to 0.97 at
-//     12 and 1.0 at 15; 128 0.89 to 0.94 at 15 and 0.95 to 1.02 at 20; 192 0.80 to 0.87 at 26; 256 0.79 to 0.86 at 26
-//     and 0.84 to 0.93 at 33, where 240 take 1.04 to 1.07;
-//   bf16, head_dim 64: 16 workgroups 0.85 at 12 and 0.98 at 15, 128 0.94 to 0.96 at 26, 256 0.75 to 0.88 at 33;
-//   fp32, blocks of 16 rows, head_dim 64: few workgroups 0.84 at 4 and 0.96 at 6, 128 0.94 at 8, 256 0.73 to 0.85 at 14; head_dim 128:
-//     0.85 at 3 and 1.04 at 5, 128 0.88 to 0.99 at 6.
+// what it costs is that a list is not cut, and the host does not see how long each is.  So the lines lie where the cut is
+// no faster whatever the lengths: all equal, evenly spread, one or an eighth of them long and the rest a sixteenth (or one
+// token), the long ones anywhere or last.  Below: time over that of the cut, the worst of those, by graph replay; over random
+// shapes with T 1 to 64 and 1 to 8 heads per KV head at the line or one or two tiles below it, 516 calls by ten distributions,
+// the worst was 1.02 (head_dim 64, a tile above the line, 1.06).
+//
+// Up to a workgroup per compute unit, the more of them there are the fewer the cut would give each list:
+//   bf16, head_dim 128: 1 to 16 workgroups 0.88 to 0.91 at 9 tiles, 32 0.89 at 10 and 1.03 at 12, 64 0.87 at 10 and 1.0 at 12; 128 0.80 at
+//     10 and 0.88 at 14 (eight blocks 1.01 at 12), 1.06 at 16; 192 0.84 at 14, 0.95 at 18, 1.12 at 20; 256 0.89 at 20, 0.97 at 29 (four blocks 1.08);
+//   head_dim 64: 1 to 16 0.84 to 0.91 at 13, 64 0.87 to 0.95 at 16 and 1.01 at 18, 115 1.06 at 16 with five blocks, 128 0.95 at 18 and 1.04 at 20 (two blocks 1.16 at 23), 192 0.95 at
+//     20, 1.01 at 25 and 1.14 at 28, 256 0.92 at 22 and 1.03 at 26 with eight blocks, 0.91 at 33 with one; in blocks of 64 rows 0.76 to 0.96 at 14 and up to
+//     1.11 at 16 with 132 workgroups, 0.82 at 16 with 256;
+//   fp32, blocks of 16 rows, head_dim 64: one and two workgroups 1.0 at 4 and 1.03 at 5 (a launch less: 10.5 -> 8.8 us where the
+//     host sets the pace), 8 to 64 0.96 to 0.99 at 5, 1.12 at 6; 128 0.94 at 5, 1.0 at 6 and 1.07 at 7, 192 0.87 at 6 and 1.11 at 8, 256 0.89 at 8,
+//     1.0 at 10, 1.21 at 14;
+//   head_dim 128: 1.0 at 3 with one workgroup, 0.83 to 0.85 with more, 64 1.14 at 4; 128 0.95 at 4, 1.04 at 5; 192 0.95 at 5, 1.05 at 6; 256
+//     0.89 at 6, 0.99 at 7, 1.04 at 8.
 // More workgroups than compute units are dealt out as others end, so one's start should fall into another's stream: four waves
-// and half of the LDS each.  One block of rows, head_dim 128: 320 lists 0.43 at 2 tiles, 0.82 to 0.84 at 14 and 0.95 to 1.0
-// at 20; 384 0.89 to 0.94 at 20; 512 to 1024 0.44 to 0.66 at 5, 0.82 to 0.92 at 20 and 0.92 to 0.99 at 33 (head_dim 64 0.66 to 0.86).
-// Longer ones are cut: eight waves each take 0.96 to 1.01 at 40 to 80 tiles with 512 to 2048 lists of equal or evenly spread lengths,
-// but 1.04 to 1.68 where one list or an eighth of them is much longer than the rest (1024 lists, 66 tiles: 61.2 -> 79.4 us).
-// Two to eight blocks, which read the keys from the L2 again: up to 512 workgroups 0.51 to 0.61 at 2 tiles, 0.65 to 0.89 at 9, 0.74 to 1.10 at
-// 14; two blocks and 1024 0.82 at 5 and 1.07 at 9 (head_dim 64 0.86).  fp32, eight waves: 320 lists 0.96 at 14 (head_dim 64), 512
-// 0.85 to 0.91 at 33, head_dim 128 0.93 to 0.96 at 14.
+// and half of the LDS each.  One block of rows, head_dim 128: 264 lists 0.90 at 12 tiles, 0.98 at 14, 1.02 at 16; 384 0.97 at 16, 1.04 at 18; 512
+// 0.88 at 19, 1.0 at 26 and 1.21 at 33; 1024 0.85 at 19 and 0.99 at 33, but 1080, whose last ones run with most of the chip idle, 1.07 at 22;
+// head_dim 64 0.65 to 0.93 there.  Two to eight blocks, which read the keys from the L2 again: up to 512 workgroups 0.64 to 0.80 at
+// 5, 0.76 to 0.99 at 10; two blocks and 1024 0.72 at 3, 0.83 at 6.  fp32, eight waves, head_dim 64: 272 lists 0.92 at 7, 384 1.03 at 8; 512 0.91 at 8, 1.07 at 10, 1.77
+// at 32; 1024 0.85 at 14 and 1.02 at 20; head_dim 128: 272 0.99 at 3 and 1.09 at 4, 384 0.97 at 5 and 1.06 at 6, 512 0.98 at 5 and 1.10 at 6, 1024 0.93 at
+// 7, 1.03 at 8 and 1.18 at 12.
+// Not taken: eight waves for longer lists, four and more per compute unit.  0.96 to 1.01 at 40 to 80 tiles with 512 to 2048 lists of
+// equal or evenly spread lengths, but 1.04 to 1.68 where one list or an eighth of them is much longer than the rest (1024 lists, 66 tiles:
+// 61.2 -> 79.4 us).
 int solo_kind(bool f32, int D, int block_rows, int blocks, int64_t lists, int64_t cus, int64_t tiles)
 {
     const int64_t wgs = lists * blocks;
+    auto line = [&](int64_t least, int64_t base, int64_t rise) {
+        const int64_t l = base + rise * wgs / cus;
+        return l > least ? l : least;
+    };
     if (wgs <= cus) {
-        const int64_t base = f32 ? (D == 64 ? 5 : 3) : D == 64 ? 13 : 9, rise = f32 ? (D == 64 ? 9 : 5) : 20;
-        return tiles <= base + rise * wgs / cus ? TA_SOLO_WIDE : 0;
+        const int64_t limit = f32 ? (D == 64 ? line(5, 1, 7) : line(3, 2, 4))
+                              : D == 128 ? line(9, 1, 18) : block_rows > 32 ? 14 : line(13, 12, 8);
+        return tiles <= limit ? TA_SOLO_WIDE : 0;
     }
-    if (f32)
-        return blocks == 1 && tiles <= (wgs < 2 * cus ? 8 : D == 64 ? 32 : 14) ? TA_SOLO_WIDE : 0;
+    if (f32) {
+        const int64_t limit = D == 64 ? (wgs < 2 * cus ? 7 : wgs < 4 * cus ? 8 : 14) : 2 * wgs < 3 * cus ? 3 : wgs < 4 * cus ? 5 : 7;
+        return blocks == 1 && tiles <= limit ? TA_SOLO_WIDE : 0;
+    }
     if (block_rows > 32)
         return 0;
-    const int64_t one = 2 * wgs < 3 * cus ? 16 : wgs < 2 * cus ? 20 : 33;
+    const int64_t one = 2 * wgs < 3 * cus ? 14 : wgs < 2 * cus ? 16 : 18;
     const int64_t more = wgs <= 2 * cus && blocks <= 8 ? 10 : wgs <= 4 * cus && blocks == 2 ? 6 : 0;
     return tiles <= (blocks == 1 ? one : more) ? TA_SOLO_PAIR : 0;
 }

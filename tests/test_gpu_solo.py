@@ -54,7 +54,7 @@ def test_where_it_ends(dtype, D, Hq, T, tiles):
 
 
 @pytest.mark.parametrize("dtype,D,B,Hkv,T,G", [("bf16", 128, 256, 1, 8, 4), ("bf16", 128, 65, 4, 8, 4), ("bf16", 64, 128, 2, 16, 4),
-                                               ("bf16", 64, 150, 2, 8, 4), ("f32", 64, 129, 2, 4, 2), ("f32", 128, 300, 2, 4, 4),
+                                               ("bf16", 64, 150, 2, 8, 4), ("f32", 64, 129, 2, 4, 2), ("f32", 128, 520, 2, 4, 4),
                                                ("bf16", 128, 300, 1, 5, 1), ("bf16", 128, 100, 4, 11, 3), ("bf16", 64, 70, 8, 3, 4),
                                                ("bf16", 128, 60, 2, 27, 4), ("bf16", 128, 60, 1, 64, 4), ("bf16", 64, 200, 2, 16, 4)])
 def test_as_many_lists_as_compute_units_and_more(dtype, D, B, Hkv, T, G):

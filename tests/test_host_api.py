@@ -294,6 +294,27 @@ def test_which_matrix_core_kernel_takes_a_call(B, T, Hq, Hkv, max_pages, want):
     assert p["key_split"] == want, p
 
 
+@pytest.mark.parametrize("dtype,D,T,Hq,B,Hkv,tiles", [
+    # bf16 up to a workgroup per compute unit: one block of rows, several, head_dim 64 and its blocks of 64 rows
+    (ta.TA_BF16, 128, 8, 4, 1, 1, 9), (ta.TA_BF16, 128, 8, 32, 16, 8, 10), (ta.TA_BF16, 128, 8, 32, 24, 8, 14),
+    (ta.TA_BF16, 128, 8, 32, 32, 8, 19), (ta.TA_BF16, 128, 64, 32, 4, 8, 19), (ta.TA_BF16, 128, 16, 32, 8, 8, 10),
+    (ta.TA_BF16, 64, 8, 4, 1, 1, 13), (ta.TA_BF16, 64, 8, 32, 16, 8, 16), (ta.TA_BF16, 64, 8, 32, 32, 8, 20),
+    (ta.TA_BF16, 64, 16, 32, 20, 8, 14), (ta.TA_BF16, 64, 64, 32, 8, 8, 14),
+    # more workgroups
+    (ta.TA_BF16, 128, 8, 32, 33, 8, 14), (ta.TA_BF16, 64, 8, 32, 48, 8, 16), (ta.TA_BF16, 128, 8, 32, 64, 8, 18),
+    (ta.TA_BF16, 64, 8, 32, 256, 8, 18), (ta.TA_BF16, 128, 16, 32, 32, 8, 10), (ta.TA_BF16, 128, 16, 32, 64, 8, 6),
+    # fp32
+    (ta.TA_F32, 64, 4, 4, 1, 1, 5), (ta.TA_F32, 64, 4, 32, 24, 8, 6), (ta.TA_F32, 64, 4, 32, 32, 8, 8),
+    (ta.TA_F32, 64, 4, 32, 40, 8, 7), (ta.TA_F32, 64, 4, 32, 64, 8, 8), (ta.TA_F32, 64, 4, 32, 128, 8, 14),
+    (ta.TA_F32, 128, 4, 4, 1, 1, 3), (ta.TA_F32, 128, 4, 32, 16, 8, 4), (ta.TA_F32, 128, 4, 32, 32, 8, 6),
+    (ta.TA_F32, 128, 4, 32, 40, 8, 3), (ta.TA_F32, 128, 4, 32, 64, 8, 5), (ta.TA_F32, 128, 4, 32, 128, 8, 7)])
+def test_lists_are_walked_alone_only_where_the_cut_is_no_faster_whatever_their_lengths(dtype, D, T, Hq, B, Hkv, tiles):
+    for n, alone in ((tiles, True), (tiles + 1, False)):
+        pages = n - 1 if T < 64 else n                   # (the tree's own tokens do not count as prefix)
+        p = _plan(_good(B=B, T=T, Hq=Hq, Hkv=Hkv, D=D, dtype=dtype, max_pages=pages, pages=B * pages), num_cus=256)
+        assert (p["merge_workgroups"] == 0) == alone, (n, p)
+
+
 @pytest.mark.parametrize("B", [64, 127, 128, 129, 512])
 @pytest.mark.parametrize("max_pages", [40, 65, 66, 130])
 def test_long_lists_are_cut_however_many_there_are(B, max_pages):
