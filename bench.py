@@ -298,6 +298,14 @@ def measure(ctx, steps, warmup, log, num_splits=0, kernel=0, check=False, item_c
                 in_region=in_region, region=region, kernel_pass=kp, settle_steps=settle_steps, settle_s=settle_s)
 
 
+def kv_kernel(plan):
+    """Name of the kernel that runs a plan's KV pass.  (Lists walked alone, no merge pass: the key-split or the fp32 kernel,
+    whatever the plan's other figures, those of the cut, say.)"""
+    if plan["kernel"] == 2:
+        return "ta_mfma_ks_kernel" if plan["key_split"] or plan["merge_workgroups"] == 0 else "ta_mfma_sp_kernel"
+    return "ta_f32_kv_kernel" if plan["table_row"] < 0 else "ta_generic_kv_kernel"
+
+
 def dispatch_check(ctx, log, base):
     """The library's own pick (one row of its dispatch table) against forced alternatives (ta_opts.num_splits,
     ta_opts.item_cost) on one prepared workload: events from before the KV pass to after the merge pass, median over
@@ -405,8 +413,7 @@ def main():
                 "unit": "TFLOP/s", "frac": m["mfma_frac"], "traffic": traffic}
     src = m["region"] if m["in_region"] else m["kernel_pass"]
     med_us = src["kv_pass_us"]["median"]
-    roof.update({"kernel": ("ta_mfma_ks_kernel" if plan["key_split"] else "ta_mfma_sp_kernel") if plan["kernel"] == 2
-                 else "ta_f32_kv_kernel" if plan["table_row"] < 0 else "ta_generic_kv_kernel",
+    roof.update({"kernel": kv_kernel(plan),
                  "avg_launch_us": kv_us, "median_launch_us": med_us, "min_launch_us": src["kv_pass_us"]["min"],
                  "launches_timed": src["kv_pass_us"]["n"],
                  "timed": "HIP events on the launch stream, every step of the timed region" if m["in_region"] else

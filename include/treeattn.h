@@ -120,7 +120,7 @@ typedef struct {
                                  known when the choice is made: AUTO takes a batch for as large as its page table
                                  (max_pages * page_size) allows.  A caller whose tables are many times wider than its
                                  requests are long, and whose batches are small, can name the kernel instead: with more
-                                 than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 21.5 us
+                                 than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 20.2 us
                                  a call and 27.5), with 32 rows and a few requests of some hundred tokens the pipelined
                                  kernel a tenth. */
 
@@ -274,10 +274,10 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * library's dispatch table, see tree_attn_dispatch_row).  plan[0] = kernel family, plan[1] = workgroups of the
  * KV pass for each block of plan[15] query rows, plan[2] = threads per workgroup, plan[3] = KV tokens per tile,
  * plan[4] = row groups of the partial results, plan[5] = padded rows per group, plan[6] = partial slots,
- * plan[7] = workgroups of the merge pass (0: none; lists of a few tiles are not cut but walked by one workgroup each, of the
- * key-split or the fp32 kernel, which writes the outputs, unless num_splits, item_cost or kernel is given; the other
- * figures are then those of the cut), plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units
- * a list counts (item_cost), plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
+ * plan[7] = workgroups of the merge pass (0: none.  Lists of a few tiles are not cut, unless num_splits, item_cost or
+ * kernel is given: a workgroup of the key-split kernel (bf16) or of the fp32 matrix-core kernel takes each whole, per block
+ * of its rows, and writes the outputs.  The other figures, plan[14] among them, are then still those of the cut),
+ * plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units a list counts (item_cost), plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
  * workgroup per row, 0 general), plan[11] = row of the dispatch table that was taken (-1: none, the fp32 matrix-core
  * kernel runs), plan[12] = workspace bytes the call needs, plan[13] = format of the partial results (0: fp32; 1: 16-bit
  * fixed point with one fp32 scale per row), plan[14] = 1 if the key-split matrix-core kernel runs, plan[15] = query rows

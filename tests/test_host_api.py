@@ -324,6 +324,18 @@ def test_long_lists_are_cut_however_many_there_are(B, max_pages):
         assert p["merge_workgroups"] > 0, p
 
 
+@pytest.mark.parametrize("kw,name", [
+    (dict(B=16, T=16, max_pages=9), "ta_mfma_ks_kernel"), (dict(B=16, T=16, max_pages=100), "ta_mfma_sp_kernel"),
+    (dict(B=16, T=4, max_pages=100), "ta_mfma_ks_kernel"), (dict(B=16, T=16, D=64, max_pages=9), "ta_mfma_ks_kernel"),
+    (dict(B=16, T=4, max_pages=2, dtype=ta.TA_F32), "ta_f32_kv_kernel"), (dict(B=16, T=4, max_pages=40, dtype=ta.TA_F32), "ta_f32_kv_kernel"),
+    (dict(B=16, T=4, D=96, max_pages=2), "ta_generic_kv_kernel")])
+def test_the_benchmark_names_the_kernel_that_runs(kw, name):
+    """Also where the lists are walked alone and the plan's figures are those of the cut, which another kernel would walk."""
+    import bench
+    p = _plan(_good(Hq=32, Hkv=8, pages=kw["B"] * kw["max_pages"], **kw), num_cus=256)
+    assert bench.kv_kernel(p) == name, p
+
+
 def test_head_dim_64_keeps_32_rows_only_with_two_workgroups_per_list():
     for B, rows in ((8, 32), (16, 64)):
         assert _plan(_good(B=B, T=16, Hq=32, Hkv=8, D=64, max_pages=5, pages=B * 5), num_cus=256)["rows_per_group"] == rows
