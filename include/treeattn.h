@@ -277,7 +277,8 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * plan[7] = workgroups of the merge pass (0: none.  Lists of a few tiles are not cut, unless num_splits, item_cost or
  * kernel is given: a workgroup of the key-split kernel (bf16) or of the fp32 matrix-core kernel takes each whole, per block
  * of its rows, and writes the outputs.  The other figures, plan[14] among them, are then still those of the cut),
- * plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units a list counts (item_cost), plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
+ * plan[8] = smallest share of tiles per workgroup, plan[9] = schedule units a list counts (item_cost),
+ * plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
  * workgroup per row, 0 general), plan[11] = row of the dispatch table that was taken (-1: none, the fp32 matrix-core
  * kernel runs), plan[12] = workspace bytes the call needs, plan[13] = format of the partial results (0: fp32; 1: 16-bit
  * fixed point with one fp32 scale per row), plan[14] = 1 if the key-split matrix-core kernel runs, plan[15] = query rows

@@ -111,14 +111,16 @@ def with_decoy_pages(dev):
     return dev
 
 
-def check_requests_with_mistakes(dtype, D, folded, kernel=0):
+def check_requests_with_mistakes(dtype, D, folded, kernel=0, lens=(300, 90, 61, 40, 128, 33), copies=1, alone=None):
     """A page id outside the cache in a prefix and under the tree tokens (also where their rows come from k_new and the page
     only receives them), a bad length, a cyclic tree given as parents and as masks: NaN rows, the status bit, nothing written
-    for the tokens whose page does not exist, and every other request as it was."""
+    for the tokens whose page does not exist, and every other request as it was.  The mistakes are in the first six requests of
+    `copies` times six; `alone`: whether the lists of the plain call are walked alone (None: not asked)."""
     import torch
     from paper_2508_08192_amd import treeattn as ta
-    B, T, Hq, Hkv, ps = 6, 19, 4, 2, 16
-    lens = [300, 90, 61, 40, 128, 33]
+    B, T, Hq, Hkv, ps = 6 * copies, 19, 4, 2, 16
+    lens = list(lens) * copies
+    assert lens[0] > 112 and lens[1] % ps != 0 and (lens[2] + T - 1) // ps > lens[2] // ps and lens[4] % ps == 0
     trees = np.stack([W.bfs_tree(T, [3], 5)] * B)
     w = W.make_workload("mistakes", B=B, T=T, Hq=Hq, Hkv=Hkv, D=D, seq_lens=lens, trees=trees, page_size=ps, seed=91, dtype=dtype)
     n_pages = w.k_cache.shape[0]
@@ -140,12 +142,17 @@ def check_requests_with_mistakes(dtype, D, folded, kernel=0):
         assert bits == int(own.item())
         return out, lse, d["k_cache"], d["v_cache"], bits
 
+    if alone is not None:
+        d = to_device(w)
+        plan = ta.tree_attn_plan(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"],
+                                 d["lse"], kernel=kernel)
+        assert (plan["merge_workgroups"] == 0) == alone, plan
     good = call(w.page_table, w.seq_lens, trees)
     assert good[4] == 0 and torch.isfinite(good[0]).all()
     tree_page = w.page_table.copy()
-    tree_page[1, 90 // ps] = n_pages                            # holds the last prefix tokens and the first of the tree
-    tree_page[2, (61 + T - 1) // ps] = n_pages + 3              # holds the last tokens of the tree alone
-    tree_page[4, 128 // ps] = -1                                # the prefix ends on a page: the tree's alone
+    tree_page[1, lens[1] // ps] = n_pages                       # holds the last prefix tokens and the first of the tree
+    tree_page[2, (lens[2] + T - 1) // ps] = n_pages + 3         # holds the last tokens of the tree alone
+    tree_page[4, lens[4] // ps] = -1                            # the prefix ends on a page: the tree's alone
     prefix = w.page_table.copy()
     prefix[0, 7] = n_pages
     bad_len = w.seq_lens.copy()
@@ -165,12 +172,11 @@ def check_requests_with_mistakes(dtype, D, folded, kernel=0):
             print("mistakes %s D=%d folded=%s kernel=%d splits=%d: %s" % (dtype, D, folded, kernel, splits, what), flush=True)
             out, lse, k, v, bits = call(table, seq, tree, num_splits=splits, **kw)
             assert bits == bit, (what, bits)
-            for b in range(B):
-                if b in hit:
-                    assert torch.isnan(out[b]).all() and torch.isnan(lse[b]).all(), (what, b)
-                else:
-                    assert (out[b].float() - good[0][b].float()).abs().max() <= tol, (what, b)
-                    assert (lse[b] - good[1][b]).abs().max() <= lse_tol, (what, b)
+            for b in hit:
+                assert torch.isnan(out[b]).all() and torch.isnan(lse[b]).all(), (what, b)
+            rest = [b for b in range(B) if b not in hit]
+            assert (out[rest].float() - good[0][rest].float()).abs().max() <= tol, what
+            assert (lse[rest] - good[1][rest]).abs().max() <= lse_tol, what
             if what == "page of the tree" and folded:
                 rows = (k != to_device(w)["k_cache"]).any(dim=3).any(dim=1).sum().item()
                 # (6 of request 1's tokens lie on its bad page, 16 of request 2's, 16 of request 4's)

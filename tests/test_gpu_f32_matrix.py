@@ -42,6 +42,22 @@ def test_schedule_in_registers_and_in_lds_with_windows(B):
     _check(w, "B=%d" % B)
 
 
+@pytest.mark.parametrize("B,D,Hq,T", [(64, 64, 4, 4), (65, 64, 4, 4), (65, 128, 4, 9), (257, 64, 4, 4), (257, 128, 8, 12)])
+@pytest.mark.parametrize("cost", [1, 2])
+def test_schedule_of_cut_lists_in_registers_and_in_lds(B, D, Hq, T, cost):
+    """The same batches with a list cost named, which keeps lists of a few tiles on the cut path; blocks of 16 and of 32 rows."""
+    from paper_2508_08192_amd import treeattn as ta
+    rng = np.random.default_rng(B)
+    w = W.make_workload("sched", B=B, T=T, Hq=Hq, Hkv=2, D=D, seq_lens=rng.integers(0, 200, size=B), trees=W.chain_tree(T),
+                        page_size=32, seed=B, dtype="f32")
+    w.kv_start = (w.seq_lens // 3).astype(np.int32)
+    d = to_device(w)
+    plan = ta.tree_attn_plan(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"], d["lse"],
+                             item_cost=cost)
+    assert plan["table_row"] == -1 and plan["merge_workgroups"] > 0, plan
+    _check(w, "cut B=%d D=%d T=%d cost=%d" % (B, D, T, cost), item_cost=cost)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_options_agree_with_the_scalar_kernel(D):
     """Masks encoded before the call, a subset of the nodes asking, the write-back folded in, rows whose start is no multiple

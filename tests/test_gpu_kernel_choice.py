@@ -78,9 +78,11 @@ def test_parts_of_a_row_group_with_every_option():
 
 
 @pytest.mark.parametrize("T,Hq,Hkv,ps", [(8, 12, 3, 16), (23, 4, 4, 0), (50, 4, 4, 32)])
-def test_many_lists_are_finished_without_a_merge(T, Hq, Hkv, ps):
+@pytest.mark.parametrize("cost", [0, 9])
+def test_many_lists_are_finished_without_a_merge(T, Hq, Hkv, ps, cost):
     """At least two lists per workgroup: the ones that lie whole in a share are written by the KV pass, the others merged,
-    with the write-back folded in, a strided output, bad requests among them and no log-sum-exp asked for."""
+    with the write-back folded in, a strided output, bad requests among them and no log-sum-exp asked for.  A list cost that
+    is named keeps them cut; without one the shorter of these batches are walked alone."""
     import torch
     from paper_2508_08192_amd import treeattn as ta
     B = 200
@@ -94,17 +96,22 @@ def test_many_lists_are_finished_without_a_merge(T, Hq, Hkv, ps):
     ref, ref_lse = run_oracle(w)
     d["out"] = torch.zeros((B, T, Hq, 132), dtype=d["q"].dtype, device="cuda")[..., 4:132] if T == 8 else d["out"]
     print("kernel choice: many lists T=%d" % T, flush=True)
-    got, lse = run_hip(w, d)
+    if cost:
+        plan = ta.tree_attn_plan(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"],
+                                 d["lse"], item_cost=cost)
+        assert plan["merge_workgroups"] > 0 and plan["key_split"] == (T < 50) and B * Hkv >= 2 * plan["kv_workgroups"], plan
+    got, lse = run_hip(w, d, item_cost=cost)
     assert_parity(got, lse, ref, ref_lse, "bf16", "many lists T=%d" % T)
     for _ in range(3):                                  # repeated calls leave the same
-        again, lse2 = run_hip(w, d)
+        again, lse2 = run_hip(w, d, item_cost=cost)
         assert np.array_equal(again, got) and np.array_equal(lse2, lse)
-    ta.tree_attn_fwd(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"], None)
+    ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"], None,
+                        item_cost=cost)
     torch.cuda.synchronize()
     assert np.array_equal(d["out"].float().cpu().numpy().astype(np.float64), got)
     d["seq_lens"][7] = -1
     ta.tree_attn_last_status()
-    bad, bad_lse = run_hip(w, d)
+    bad, bad_lse = run_hip(w, d, item_cost=cost)
     assert ta.tree_attn_last_status() == ta.TA_STATUS_BAD_SEQLEN
     assert np.isnan(bad[7]).all() and np.isnan(bad_lse[7]).all()
     keep = [b for b in range(B) if b != 7]
@@ -115,10 +122,10 @@ def test_many_lists_are_finished_without_a_merge(T, Hq, Hkv, ps):
     args = (d["page_table"], d["seq_lens"], d["tree_parent"])
     k1, v1 = d["k_cache"].clone(), d["v_cache"].clone()
     o1, l1 = torch.zeros_like(d["q"]), torch.zeros_like(d["lse"])
-    ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], *args, o1, l1, k_new=k_new, v_new=v_new)
+    ta.tree_attn_fwd_ex(d["q"], d["k_cache"], d["v_cache"], *args, o1, l1, k_new=k_new, v_new=v_new, item_cost=cost)
     ta.tree_attn_append(k_new, v_new, k1, v1, d["page_table"], d["seq_lens"])
     o2, l2 = torch.zeros_like(o1), torch.zeros_like(l1)
-    ta.tree_attn_fwd(d["q"], k1, v1, *args, o2, l2)
+    ta.tree_attn_fwd_ex(d["q"], k1, v1, *args, o2, l2, item_cost=cost)
     torch.cuda.synchronize()
     assert torch.equal(k1, d["k_cache"]) and torch.equal(v1, d["v_cache"]) and torch.equal(o1, o2) and torch.equal(l1, l2)
 

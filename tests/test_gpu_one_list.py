@@ -9,18 +9,24 @@ from tests.helpers import assert_parity, run_hip, run_oracle, to_device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,T,Hq", [(128, 8, 8), (128, 4, 5), (64, 4, 8)])
-@pytest.mark.parametrize("tiles", [59, 60, 122, 123, 187, 251, 252, 314, 506, 507, 1018, 1019])
+EDGES = (59, 60, 122, 123, 187, 251, 252, 314, 506, 507)
+
+
+@pytest.mark.parametrize("D,T,Hq,tiles", [(128, T, Hq, t) for T, Hq in ((8, 8), (7, 5)) for t in EDGES] +
+                         [(128, 4, 5, t) for t in (314, 506, 507)] +           # (one block of rows: from 257 tiles on)
+                         [(64, 4, 8, t) for t in EDGES + (1018, 1019)])
 def test_shares_of_one_list(D, T, Hq, tiles):
-    if tiles > 600 and D == 128:
-        return                                 # (beyond the rule there)
+    from paper_2508_08192_amd import treeattn as ta
     for wide in (False, True):
         L = 64 * (tiles - 1) - 7
         w = W.make_workload("one", B=1, T=T, Hq=Hq, Hkv=1, D=D, seq_lens=[L], trees=W.chain_tree(T), page_size=64, seed=tiles)
         if wide:
             w.page_table = np.ascontiguousarray(np.concatenate([w.page_table, w.page_table], axis=1))
+        d = to_device(w)
+        plan = ta.tree_attn_plan(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"], d["lse"])
+        assert plan["key_split"] == 1 and plan["merge_kernel"] == ta.TA_MERGE_D128_WIDE and plan["merge_workgroups"] > 0, plan
         print("one list D=%d T=%d tiles=%d wide=%s" % (D, T, tiles, wide), flush=True)
-        got, lse = run_hip(w, to_device(w))
+        got, lse = run_hip(w, d)
         ref, ref_lse = run_oracle(w)
         assert_parity(got, lse, ref, ref_lse, "bf16", "D=%d T=%d tiles=%d wide=%s" % (D, T, tiles, wide))
 

@@ -88,14 +88,13 @@ def test_write_back_of_more_lists_than_compute_units():
             assert torch.equal(x, y)
 
 
-@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
-@pytest.mark.parametrize("T,skew", [(7, 0), (33, 0), (7, 1)])
+@pytest.mark.parametrize("dtype,D,T,skew", [(dtype, D, T, skew) for dtype in ("bf16", "f32") for D in (64, 128)
+                                            for T, skew in ((7, 0), (33, 0), (7, 1)) if dtype == "f32" or not skew])
 def test_write_back_folded_in(dtype, D, T, skew):
-    """The same outputs and caches as write-back and call in turn, bit for bit; fp32 rows of k_new that begin anywhere too."""
+    """The same outputs and caches as write-back and call in turn, bit for bit; fp32 rows of k_new that begin anywhere too
+    (such rows of bf16 take the scalar kernel)."""
     import torch
     from paper_2508_08192_amd import treeattn as ta
-    if skew and dtype == "bf16":
-        return                                 # (such rows take the scalar kernel)
     lens = [0, 5, 64, 100]
     w = W.make_workload("fold", B=4, T=T, Hq=6, Hkv=2, D=D, seq_lens=lens, trees=W.chain_tree(T), page_size=16, seed=T, dtype=dtype)
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -121,8 +120,12 @@ def test_write_back_folded_in(dtype, D, T, skew):
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
 @pytest.mark.parametrize("folded", [False, True])
-def test_requests_with_mistakes(dtype, D, folded):
-    check_requests_with_mistakes(dtype, D, folded, 0)
+@pytest.mark.parametrize("copies", [1, 22])
+def test_requests_with_mistakes(dtype, D, folded, copies):
+    """Up to three tiles a list; 22 times six requests: more workgroups than the device has compute units (bf16: the four-wave
+    kernel; fp32, whose 38 rows are three blocks, cuts those)."""
+    check_requests_with_mistakes(dtype, D, folded, 0, lens=(125, 90, 61, 40, 112, 33), copies=copies,
+                                 alone=copies == 1 or dtype == "bf16")
 
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
