@@ -145,3 +145,81 @@ def test_values_that_are_not_finite(dtype, D):
     a, b = run_hip(w, d), run_hip(w, d, num_splits=1)
     for x, y in zip(a, b):
         assert np.array_equal(np.isfinite(x), np.isfinite(y))
+
+
+@pytest.mark.parametrize("seed", range(48))
+def test_forms_against_the_scalar_kernel(seed):
+    """Orders and strides of every tensor, page sizes, windows, masks, a subset of the nodes asking, the write-back folded in, no
+    log-sum-exp: random combinations on lists walked alone, by either number of waves.  Both kernels take the same inputs in
+    fp32 sums; bf16 probabilities and outputs are 2^-9 each off, 1e-2 of the largest as elsewhere, fp32 1e-5."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    rng = np.random.default_rng(seed)
+    bf16, D = bool(seed % 2), 64 if seed % 4 < 2 else 128
+    dt = torch.bfloat16 if bf16 else torch.float32
+    Hkv, G, T = int(rng.choice([1, 2, 3, 8])), int(rng.choice([1, 2, 4, 5])), int(rng.choice([1, 3, 8, 17, 33, 64]))
+    Hq = Hkv * G
+    B = int(rng.choice([1, 2, 5])) if seed % 3 else -(-280 // Hkv)     # every third: more lists than compute units, small trees
+    T = T if seed % 3 else min(T, 8 if bf16 else 3)
+    ps = int(rng.choice([0, 1, 8, 32, 128]))
+    most = 64 if D == 128 and not bf16 else 128
+    lens = rng.integers(0, most + 1, size=B)
+    gen = torch.Generator().manual_seed(seed)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=gen).to(dt)
+
+    def laid_out(t, order, pad):
+        """The same values with the dimensions in memory in this order and `pad` more elements per row."""
+        inv = [order.index(i) for i in range(t.dim())]
+        full = torch.zeros([t.shape[i] for i in order[:-1]] + [t.shape[-1] + pad], dtype=t.dtype)
+        full[..., :t.shape[-1]] = t.permute(order)
+        return full.cuda()[..., :t.shape[-1]].permute(inv)
+
+    if ps:
+        width = int((lens.max() + T - 1) // ps + 1)
+        ids = rng.permutation(B * width).astype(np.int32).reshape(B, width)
+        table = torch.from_numpy(np.concatenate([ids, ids[:, :1]], axis=1)).cuda()[:, :width]
+        shape = (B * width, Hkv, ps, D)
+    else:
+        table, shape = None, (B, Hkv, int(lens.max()) + T, D)
+    tok, node = rng.choice([0, 16], size=2)
+    kv = [laid_out(normal(*shape), [0, 1, 2, 3] if rng.random() < 0.5 else [0, 2, 1, 3], int(tok)) for _ in range(2)]
+    Tq = int(rng.integers(1, T + 1))
+    q = laid_out(normal(B, Tq, Hq, D), [0, 1, 2, 3] if rng.random() < 0.5 else [0, 2, 1, 3], int(node))
+    seq = torch.zeros(2 * B, dtype=torch.int32, device="cuda")
+    seq[::2] = torch.from_numpy(lens.astype(np.int32)).cuda()
+    trees = np.stack([W.random_tree(T, min(T, 6), rng) for _ in range(B)]) if rng.random() < 0.5 else W.random_tree(T, min(T, 6), rng)
+    parent = torch.from_numpy(np.ascontiguousarray(trees)).cuda()
+    opts = {"q_node_offset": T - Tq}
+    if rng.random() < 0.5:
+        opts["kv_start"] = torch.from_numpy((lens * rng.random(B)).astype(np.int32)).cuda()
+    if rng.random() < 0.5:
+        opts["tree_masks"] = torch.empty(tuple(parent.shape), dtype=torch.int64, device="cuda")
+        ta.tree_attn_encode(parent, opts["tree_masks"])
+    if rng.random() < 0.5:
+        opts["k_new"], opts["v_new"] = (laid_out(normal(B, T, Hkv, D), [0, 2, 1, 3] if rng.random() < 0.5 else [0, 1, 2, 3], 8)
+                                        for _ in range(2))
+    out_order = [0, 1, 2, 3] if rng.random() < 0.5 else [0, 2, 1, 3]
+    with_lse = rng.random() < 0.8
+    res = []
+    for kernel in (0, 1):
+        k, v = (x.clone(memory_format=torch.preserve_format) for x in kv)
+        out = laid_out(torch.zeros(B, Tq, Hq, D, dtype=dt), out_order, 8)
+        lse = torch.zeros(B, Tq, Hq, device="cuda").permute(0, 2, 1) if with_lse else None
+        if kernel == 0:
+            plan = ta.tree_attn_plan(q, k, v, table, seq[::2], parent, out, lse)
+            assert plan["merge_workgroups"] == 0, plan
+        print("solo forms seed=%d kernel=%d %s D=%d B=%d %d/%d T=%d/%d ps=%d %s" %
+              (seed, kernel, dt, D, B, Hq, Hkv, Tq, T, ps, sorted(opts)), flush=True)
+        ta.tree_attn_last_status()
+        ta.tree_attn_fwd_ex(q, k, v, table, seq[::2], parent, out, lse, kernel=kernel, **opts)
+        assert ta.tree_attn_last_status() == 0
+        res.append((out.float(), lse, k, v))
+    (o0, l0, k0, v0), (o1, l1, k1, v1) = res
+    assert torch.isfinite(o0).all()
+    tol = 1e-2 if bf16 else 1e-5
+    assert (o0 - o1).abs().max() <= tol * o1.abs().max()
+    if with_lse:
+        assert (l0 - l1).abs().max() <= (1e-3 if bf16 else 1e-5 * max(1.0, float(l1.abs().max())))
+    assert torch.equal(k0, k1) and torch.equal(v0, v1)
