@@ -466,9 +466,10 @@ __device__ __forceinline__ uint16_t ta_f32_to_bf16(float f)
 }
 
 // The write-back of ta_opts.k_new / v_new for one (request, KV head) list: its T rows go to logical positions
-// L_b .. L_b+T-1 of the caches.  Every workgroup of the merge pass takes part (workgroup `part` of the `parts` that
-// serve the list moves the tokens part, part + parts, ...); nothing in the same call reads those cache positions (the
-// KV pass takes the tree tokens from the dense tensors).  The work comes in three steps so that a merge kernel can
+// L_b .. L_b+T-1 of the caches.  Every workgroup of the merge pass takes part, or, where lists are walked alone and there is
+// none, every workgroup of the KV pass when its list is done (workgroup `part` of the `parts` that serve the list moves the
+// tokens part, part + parts, ...).  Others may still read the caches then, but nothing in the same call reads those positions:
+// the tree tokens come from the dense tensors, and loads past a prefix's end repeat an attended token.  The work comes in three steps so that a merge kernel can
 // hide it behind its own loads: ta_scatter_load issues the loads that depend on nothing (the request's length and
 // this thread's first 16-byte piece), ta_scatter_locate looks the destination up in the page table once the length
 // is there, ta_scatter_store writes -- and moves what the first piece per thread does not cover (more pieces than

@@ -1,8 +1,9 @@
 // Matrix-core KV pass of libtreeattn for gfx950, fp32 inputs: head_dim 64 or 128, fp32 products and sums throughout
 // (v_mfma_f32_16x16x4_f32, a chain of fp32 multiply-adds per element, rounded as the vector ALU rounds them).
 //
-// A workgroup keeps up to 32 query rows of one (request, KV head); its four waves (eight where it walks a whole list alone, with
-// 16 rows) split the KEYS of its share, each takes every fourth run of 16 tokens with its own running softmax, and their results meet in LDS when the item ends, like in
+// A workgroup keeps up to 32 query rows of one (request, KV head); its four waves (eight where it walks a whole list alone,
+// with up to 16 rows) split the KEYS of its share, each takes every fourth (eighth) run of 16 tokens with its own running
+// softmax, and their results meet in LDS when the item ends, like in
 // ta_mfma_ks.hip.  Per run (transposed products, a lane owns one query row of each block of 16 throughout):
 //     S^T[token, row] = K . Q^T        A = K (registers), B = Q (LDS)
 //     O^T[d, row]    += V^T . P^T      A = V^T (registers), B = P (registers)

@@ -463,7 +463,7 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     p.part_q15 = kernel == TA_KERNEL_MFMA ? 1 : 0;
     // With at least two lists per workgroup most lie whole in a share, and their partial results need not be written,
     // merged and read again (its stores need the alignment that the row merge needs): B 128, 32/8 heads, T 8, L 256..4096
-    // 206.6 -> 202.5 us a call, L 75..300 64.7 -> 60.6.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
+    // 206.6 -> 202.5 us a call.  With 16 rows and fewer there is nothing to gain (59.6 and 60.0).
     p.direct = ks && D == 128 && p.rows > 16 && p.merge_kind == TA_MERGE_ROW && lists >= 2 * (int64_t)pl.n_wg;
     if (ks && lists == 1 && num_splits == 0 && p.merge_kind == TA_MERGE_WIDE) {
         const int parts = 8192 / (int)D;                    // (fewer workgroups: see ta_share)

@@ -13,7 +13,7 @@
 //
 // More rows are served by workgroups side by side, which share the stream through the L2 (see key_split_workgroups).
 // Head_dim 128 takes it where it is the faster of the two (the measured line stands in ta_host.cpp): calls of B 1, 32/8
-// heads, T 64, L 4096 (256 rows) 27.5 -> 21.5 us, B 128, T 8, L 256..4096 208.4 -> 206.6 against the pipelined kernel.
+// heads, T 64, L 4096 (256 rows) 27.5 -> 20.2 us, B 128, T 8, L 256..4096 208.4 -> 199 against the pipelined kernel.
 //
 // Q is loaded once per workgroup, whole rows at a time, and handed to the waves through LDS; with each wave loading its own
 // fragments, 32 rows by 32 scattered bytes at a time, and all eight waves' blocks added up whether or not a wave had a
@@ -28,7 +28,9 @@
 // through registers for all waves between barriers and computed with two waves of eight, took 115 us.
 // Why eight waves: 64 KB in flight per compute unit are too few (four waves: 130 us on the 538 MB).  Two workgroups of
 // four waves per unit share its bandwidth unevenly, the older one takes more (ends at 156 and 185 us of one launch),
-// and cut the work into twice as many partial results.
+// and cut the work into twice as many partial results.  They run where lists are short, uncut and more than the compute
+// units (TA_SOLO_PAIR, the lines stand in ta_host.cpp): no partial results there, and one's start falls into the other's
+// stream (1024 lists of 19 tiles 0.85 of the cut's time).
 #include <initializer_list>
 
 #include "ta_common.h"
