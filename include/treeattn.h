@@ -120,7 +120,7 @@ typedef struct {
                                  known when the choice is made: AUTO takes a batch for as large as its page table
                                  (max_pages * page_size) allows.  A caller whose tables are many times wider than its
                                  requests are long, and whose batches are small, can name the kernel instead: with more
-                                 than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 20.2 us
+                                 than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 19.8 us
                                  a call and 27.5), with 32 rows and a few requests of some hundred tokens the pipelined
                                  kernel a tenth. */
 

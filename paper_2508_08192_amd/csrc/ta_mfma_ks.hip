@@ -13,7 +13,7 @@
 //
 // More rows are served by workgroups side by side, which share the stream through the L2 (see key_split_workgroups).
 // Head_dim 128 takes it where it is the faster of the two (the measured line stands in ta_host.cpp): calls of B 1, 32/8
-// heads, T 64, L 4096 (256 rows) 27.5 -> 20.2 us, B 128, T 8, L 256..4096 208.4 -> 199 against the pipelined kernel.
+// heads, T 64, L 4096 (256 rows) 27.5 -> 19.8 us, B 128, T 8, L 256..4096 208.4 -> 199 against the pipelined kernel.
 //
 // Q is loaded once per workgroup, whole rows at a time, and handed to the waves through LDS; with each wave loading its own
 // fragments, 32 rows by 32 scattered bytes at a time, and all eight waves' blocks added up whether or not a wave had a
@@ -24,7 +24,7 @@
 // (16 lists x 16384 tokens x 8 heads, 538 MB: 93 us, 5.8 TB/s); beside it stand 4.5 us at the start without a byte on
 // its way (lengths, then page ids and Q, then the first tokens: three round trips and the instructions between them) and
 // the end of an item, where the waves wait for the slowest (a run of 32 tokens takes a wave 3 us when all stream).
-// Head_dim 64, B 16, 32/8 heads, T 16, L 2048..8192: KV pass 40.6 us; the kernel it replaced, which staged 64-token tiles
+// Head_dim 64, B 16, 32/8 heads, T 16, L 2048..8192: KV pass 37.6 us; the kernel it replaced, which staged 64-token tiles
 // through registers for all waves between barriers and computed with two waves of eight, took 115 us.
 // Why eight waves: 64 KB in flight per compute unit are too few (four waves: 130 us on the 538 MB).  Two workgroups of
 // four waves per unit share its bandwidth unevenly, the older one takes more (ends at 156 and 185 us of one launch),
