@@ -446,6 +446,15 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         pl.n_wg = (int)(tiles_cap > 0 ? tiles_cap : 1);
     pl.n_slots = pl.n_wg + (int)lists;
     p.rows_grp = pl.rows_grp; p.n_rg = pl.n_rg; p.n_wg = pl.n_wg; p.min_q = pl.min_q;
+    // The pipelined kernel's wide blocks (16x16x32 products) draw less power and take more instructions.  Where all waves
+    // have rows and stay in their loops the clock is what the power allows, so they are the faster ones there; short shares
+    // run at the highest clock, and with 64 rows and fewer the waves wait for the memory.  32 lists of equal length, 8 heads on
+    // one KV head, time over that of the narrow blocks by tiles per workgroup: 256 rows 4 1.05, 8 1.04, 16 0.98, 32 0.98, 64 0.96
+    // (4 lists of 131072 tokens, 8 KV heads: 0.95); 128 rows 4 and 8 1.02, 32 0.98 to 1.02 from one card to the next, 64 0.96,
+    // 128 0.97; 64 rows 1.02 to 1.03.  Tiles are counted from what the page table can hold, of which a batch fills half in the
+    // mean; what a window leaves of it the host does not know.
+    p.wide = kernel == TA_KERNEL_MFMA && !ks && !p.kv_start && pl.rows_grp > 64 &&
+             tiles_cap >= (int64_t)(pl.rows_grp > 128 ? 24 : 64) * pl.n_wg;
 
     // merge kernel: partials per list the schedule produces on average = the KV pass's workgroups spread over the
     // lists, plus the one boundary each list shares with its neighbour

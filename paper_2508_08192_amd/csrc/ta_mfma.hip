@@ -12,12 +12,14 @@
 // ta_mfma_ks.hip splits the keys of a share over the waves and serves head_dim 64.)
 //
 // Each wave owns a block of 32 rows.  Both contractions are issued in transposed form so that
-// a lane owns one query row per block throughout (row statistics never leave the lane):
+// a lane holds one or two query rows of it throughout (row statistics need a lane swap or two, and only where they change):
 //     S^T[token, row] = K[token, :] . Q[row, :]      A = K fragment (LDS),  B = Q fragment (registers)
 //     O^T[d, row]    += V^T[d, token] . P^T[token, row]   A = V^T fragment (LDS), B = P (registers)
-// with v_mfma_f32_32x32x16_bf16.  The accumulator layout of S^T (lane = row, registers = tokens) is,
-// up to a fixed permutation of the 16 contraction slots, the B-operand layout the second product
+// with v_mfma_f32_32x32x16_bf16 or, WIDE, 16x16x32.  The accumulator layout of S^T (lane = row, registers = tokens) is,
+// up to a fixed permutation of the contraction slots, the B-operand layout the second product
 // needs; the V fragments come out of the row-major tile with the same slot permutation.
+#include <type_traits>
+
 #include "ta_common.h"
 
 #define MF_D 128
@@ -50,8 +52,8 @@ __device__ __forceinline__ void vm_wait()
 // ---------------------------------------------------------------------------------------------
 // 256-row variant, software-pipelined inside every wave: 8 waves of 32 rows, two per SIMD.
 //
-// Block i of a wave is one instruction stream that interleaves the 16 MFMAs of O^T += V^T(i-1).P^T(i-1), the
-// 16 MFMAs of S^T(i+1) = K(i+1).Q^T and the running softmax of S^T(i) (see gen_sp_block.py), so the wave feeds the
+// Block i of a wave is one instruction stream that interleaves the MFMAs of O^T += V^T(i-1).P^T(i-1), the
+// MFMAs of S^T(i+1) = K(i+1).Q^T and the running softmax of S^T(i) (see gen_sp_block.py), so the wave feeds the
 // matrix pipe and the vector ALU at once and needs no phase skew; one workgroup barrier per tile remains.
 // K and V tiles travel global -> LDS without touching registers (global_load_lds_dwordx4), three blocks
 // ahead of their first use, into a ring of 3 K tiles and a ring of 5 V tiles.  Both lie there as in the cache, one
@@ -74,6 +76,16 @@ typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 
 #include "ta_sp_block.inc"
 
+// Which of a wave's 32 rows a lane serves, and with which tokens and head-dim columns: four (a quad) of every eight or sixteen.
+template <bool WIDE>
+struct SpLane {
+    static __device__ __forceinline__ int row(int lane, int rb) { return WIDE ? (lane & 15) + 16 * rb : lane & 31; }
+    static __device__ __forceinline__ int part(int lane) { return lane >> (WIDE ? 4 : 5); }      // the lane's quad
+    // the row whose sums, reference and scale the lane holds when an item ends, and whether it is the lane that stores them
+    static __device__ __forceinline__ int own(int lane) { return WIDE ? (lane & 15) + 16 * (lane >> 5) : lane & 31; }
+    static __device__ __forceinline__ bool writes(int lane) { return (lane & (WIDE ? 16 : 32)) == 0; }
+};
+
 // every lane moves 16 bytes from base + off to LDS offset lds_wave_base + 16*lane (base is wave-uniform)
 __device__ __forceinline__ void dma16s(const void *base, uint32_t off, uint32_t lds_wave_base)
 {
@@ -90,9 +102,12 @@ struct SpTag {
 // amdgpu_num_vgpr(16): the register allocator stays in v0..v31; v32..v255 belong to the asm blocks (see gen_sp_block.py)
 // NEW: the tree tokens' K/V come from the dense tensors of ta_opts.k_new / v_new (an instance of its own, so that the
 // ordinary call carries none of that addressing).
-template <bool NEW>
+// WIDE: the blocks built on 16x16x32 products (SpWide in gen_sp_block.py); the rule for it stands in ta_host.cpp.
+template <bool NEW, bool WIDE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_mfma_sp_kernel(TA_SCHED_PARAMS, TAParams p)
 {
+    using X = std::conditional_t<WIDE, SpWide, SpNarrow>;
+    using Lane = SpLane<WIDE>;
     const TASched sc = TA_SCHED;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     unsigned long long *masks = (unsigned long long *)(smem + SP_AUX_OFF);
@@ -111,7 +126,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r32 = lane & 31, hf = lane >> 5;
     int t, t_end;
     {
         int t0, t1;
@@ -124,14 +138,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
     const bool paged = p.page_table != nullptr;
     const uint32_t ksp = (uint32_t)p.k_sp, kss = (uint32_t)p.k_ss, vsp = (uint32_t)p.v_sp, vss = (uint32_t)p.v_ss;
     // Lane constants of the blocks (LDS byte offsets), kept in their fixed registers:
-    //   K fragment of step kk: row r32, 16-byte slot (2kk + hf) ^ (r32 & 15), i.e. base ^ 32kk inside the tile
-    //   V fragment of head-dim block db (transposing read, groups of 16 lanes): the lane names the 8-byte piece
-    //   p = lane & 3 of 32-byte block (2db + h16) ^ tk of token row tk = 4hf + k', with h16 = (lane >> 4) & 1 the
-    //   half of the head-dim block the group serves and k' = (lane >> 2) & 3; i.e. (base ^ 64db) + 4096kb (+ 2048)
+    //   K fragment: the lane's token row and 16-byte slot of step 0, XOR-placed by row & 15; step kk is base ^ 32 kk
+    //   (WIDE: 64 kk) inside the tile
+    //   V fragment (transposing read, groups of 16 lanes): the lane names the 8-byte piece lane & 3 of a 32-byte block of
+    //   token row tk, at block ^ (tk & 7).  Block 2 db + h16 and tk = 4 (lane >> 5) + k', with h16 = (lane >> 4) & 1 the
+    //   half of the head-dim block the group serves and k' = (lane >> 2) & 3; WIDE: block db, tk = 4 (lane >> 4) + k'.
+    //   Head-dim block db is base ^ 64 db (WIDE: 32 db).
     {
-        const int h16 = (lane >> 4) & 1, tk = 4 * hf + ((lane >> 2) & 3), pc = lane & 3;
-        sp_set_bases(lds0 + SP_V_OFF + (uint32_t)(tk * 256 + ((h16 ^ tk) << 5) + pc * 8),
-                     lds0 + (uint32_t)(r32 * 256 + ((hf ^ (r32 & 15)) << 4)));
+        const int h16 = WIDE ? 0 : (lane >> 4) & 1, tk = 4 * (lane >> (WIDE ? 4 : 5)) + ((lane >> 2) & 3), pc = lane & 3;
+        const int row = Lane::row(lane, 0);
+        X::set_bases(lds0 + SP_V_OFF + (uint32_t)(tk * 256 + ((h16 ^ (tk & 7)) << 5) + pc * 8),
+                     lds0 + (uint32_t)(row * 256 + ((Lane::part(lane) ^ (row & 15)) << 4)));
     }
     // Cache-load role of a lane: tile rows drow and drow+4, 16-byte slot dslot; the source chunk is the slot
     // XOR-ed with the row's placement (K: row & 15; V: 2 * (row & 7)).
@@ -223,28 +240,40 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
         }
 
         if (active) {
-            // Q of this lane's row goes straight into its fixed registers; it is first read after the wait for the
+            // Q of this lane's rows goes straight into its fixed registers; it is first read after the wait for the
             // first tile, which these loads precede.  Rows past the group's end read the group's first row (their
             // results are never stored).
             const int xl = fresh_tid();
-            const int row = (xl >> 6) * 32 + (xl & 31), hfl = (xl >> 5) & 1;
-            const int R = rg * p.rows_grp + (row < rows_here ? row : 0);
-            const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);                 // R / G
-            sp_load_q((const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
-                      (int64_t)(g * p.G + R - node * p.G) * p.q_sh + hfl * 8);
+            auto q_row = [&](int rb) {
+                const int row = (xl >> 6) * 32 + Lane::row(xl & 63, rb);
+                const int R = rg * p.rows_grp + (row < rows_here ? row : 0);
+                const int node = (int)__umulhi((uint32_t)R << 8, p.g_magic);             // R / G
+                return (const uint16_t *)p.q + (int64_t)b * p.q_sb + (int64_t)node * p.q_st +
+                       (int64_t)(g * p.G + R - node * p.G) * p.q_sh + Lane::part(xl & 63) * 8;
+            };
+            const uint16_t *q0 = q_row(0);
+            X::load_q(q0, WIDE ? q_row(1) : q0);
         }
         const uint16_t *kgp = (const uint16_t *)p.k + (int64_t)g * p.k_sh;
         const uint16_t *vgp = (const uint16_t *)p.v + (int64_t)g * p.v_sh;
 
-        // bits of the tokens tile ti really holds for this lane's half, or all ones when nothing is to mask
-        auto tile_mask = [&](int ti) -> unsigned long long {
+        // bits of the tokens tile ti really holds for the lane's row rb, from the lane's first token on, or all ones when
+        // nothing is to mask
+        auto tile_mask = [&](int ti, int rb) -> unsigned long long {
             const int x = fresh_tid();
-            const int rw = (x >> 6) * 32 + (x & 31), h = (x >> 5) & 1;
+            const int rw = (x >> 6) * 32 + Lane::row(x & 63, rb), at = 4 * Lane::part(x & 63);
             const int j = j0 + ti;
             if (j == n_b - 1)
                 return (rw < rows_here ? masks[p.q_off + __umulhi((uint32_t)(rg * p.rows_grp + rw) << 8, p.g_magic)]
-                                       : ~0ull) >> (4 * h);
-            return ta_prefix_tile_mask((tile0 + j) * TA_TILE, L, S) >> (4 * h);
+                                       : ~0ull) >> at;
+            return ta_prefix_tile_mask((tile0 + j) * TA_TILE, L, S) >> at;
+        };
+        auto mask_scores = [&](int ti, auto buffer_a) {
+            const unsigned long long m0 = tile_mask(ti, 0), m1 = WIDE ? tile_mask(ti, 1) : m0;
+            if constexpr (decltype(buffer_a)::value)
+                X::mask_A((uint32_t)m0, (uint32_t)(m0 >> 32), (uint32_t)m1, (uint32_t)(m1 >> 32));
+            else
+                X::mask_B((uint32_t)m0, (uint32_t)(m0 >> 32), (uint32_t)m1, (uint32_t)(m1 >> 32));
         };
         // tiles that need a mask: the tree tile, a last prefix tile that is not full, a first one that begins before S
         auto tile_ragged = [&](int ti) {
@@ -359,7 +388,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
         };
 
         int bad = 0;                                       // TA_STATUS_* bits this item has to report
-        float m_run = -INFINITY, l_run = 0.f, l2_run = 0.f;   // l2: sum of the bf16-rounded probabilities
+        // sums of the probabilities (l) and of their bf16 roundings (w) of the lane's two rows, over the lane's tokens
+        float l0 = 0.f, l1 = 0.f, w0 = 0.f, w1 = 0.f;
 
         for (int s0 = 0; s0 < n; s0 += span_tiles) {
             const int ns = min(span_tiles, n - s0);            // tiles s0 .. s0+ns-1 of the item; i is span-local
@@ -416,7 +446,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
             }
             if (s0 == 0) {
                 // while the first tiles are on their way: O = 0 and the ancestor masks
-                sp_zero_o();
+                X::zero_o();
                 if (has_tree_tile && !p.masks_in && !ta_encode_tree_lds(fresh_tid(), p.T, masks, flag, par_s)) {
                     bad = TA_STATUS_BAD_PARENT;
                     vm_wait<0>();                              // nothing may still land in the rings after this item
@@ -429,11 +459,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
                 wait_loads(issued - 1);
             lds_barrier();
             if (active)
-                sp_s_first(0u);
-            if (active && tile_ragged(s0)) {
-                const unsigned long long vm = tile_mask(s0);
-                sp_mask_A((uint32_t)vm, (uint32_t)(vm >> 32));
-            }
+                X::s_first(0u);
+            if (active && tile_ragged(s0))
+                mask_scores(s0, SpTag<true>{});
             if (ns > 1 && own_first)
                 wait_first(issued - 2);                        // tile 1 has landed
             else if (ns > 1)
@@ -450,34 +478,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
                 }
                 const bool has_next = i + 1 < ns;
                 const uint32_t ska = kn * MF_TILE_BYTES, sva = vp * MF_TILE_BYTES;
-                float alpha = 1.f;
+                uint32_t moved = 0;                        // a softmax reference has moved in this tile
                 if (!active) {
                 } else if constexpr (A) {
                     if (i == 0) {
                         if (has_next)
-                            sp_head_A(m_run, l_run, l2_run, alpha, c, ska);
+                            X::head_A(l0, l1, w0, w1, moved, c, ska);
                         else
-                            sp_only_A(m_run, l_run, l2_run, alpha, c);
+                            X::only_A(l0, l1, w0, w1, moved, c);
                     } else if (has_next) {
-                        sp_full_A(sva, m_run, l_run, l2_run, alpha, c, ska);
+                        X::full_A(sva, l0, l1, w0, w1, moved, c, ska);
                     } else {
-                        sp_last_A(sva, m_run, l_run, l2_run, alpha, c);
+                        X::last_A(sva, l0, l1, w0, w1, moved, c);
                     }
                 } else {
                     if (has_next)
-                        sp_full_B(sva, m_run, l_run, l2_run, alpha, c, ska);
+                        X::full_B(sva, l0, l1, w0, w1, moved, c, ska);
                     else
-                        sp_last_B(sva, m_run, l_run, l2_run, alpha, c);
+                        X::last_B(sva, l0, l1, w0, w1, moved, c);
                 }
-                if (__any(alpha != 1.0f))
-                    sp_scale_o(alpha);             // O still holds sums relative to the old reference
-                if (active && has_next && tile_ragged(s0 + i + 1)) {
-                    const unsigned long long vm = tile_mask(s0 + i + 1);
-                    if constexpr (A)
-                        sp_mask_B((uint32_t)vm, (uint32_t)(vm >> 32));
-                    else
-                        sp_mask_A((uint32_t)vm, (uint32_t)(vm >> 32));
-                }
+                if (moved)
+                    X::scale_o();                  // O still holds sums relative to the old reference
+                if (active && has_next && tile_ragged(s0 + i + 1))
+                    mask_scores(s0 + i + 1, SpTag<!A>{});
                 if (i + 2 < ns)
                     wait_loads(i + 3 < ns ? 1 : 0);            // this wave's part of tile i+2 has landed
                 lds_barrier();
@@ -508,7 +531,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
                     uint32_t koff0, koff1, voff0, voff1;
                     lane_offsets(koff0, koff1, voff0, voff1, wave);
                     if (active)
-                        sp_fast_loop(m_run, l_run, l2_run, ik_o, iv_o, kn_o, vp_o, pos, cnt, c_kg, c_vg, c_sp, c_ss, c_pp, c_pc, c_dst,
+                        X::fast_loop(l0, l1, w0, w1, ik_o, iv_o, kn_o, vp_o, pos, cnt, c_kg, c_vg, c_sp, c_ss, c_pp, c_pc, c_dst,
                                      koff0, koff1, voff0, voff1);
                     else
                         sp_fast_loop_helper(ik_o, iv_o, kn_o, vp_o, pos, cnt, c_kg, c_vg, c_sp, c_ss, c_pp, c_pc, c_dst, koff0,
@@ -527,7 +550,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
                 }
             }
             if (active)
-                sp_pv(vp * MF_TILE_BYTES);
+                X::pv(vp * MF_TILE_BYTES);
             lds_barrier();                                     // the rings are free for the next span or item
         }
         if (bad != 0) {
@@ -549,19 +572,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
             // order in its part of the (now idle) K/V rings and then stores whole rows.
             const int x = fresh_tid();
             const int ln = x & 63, wv = x >> 6;
-            const int r32_ = ln & 31, h = ln >> 5;
-            const float l_tot = l_run + __shfl_xor(l_run, 32, TA_WAVE);
-            const float l2_tot = l2_run + __shfl_xor(l2_run, 32, TA_WAVE);
             // The wave that stores the staged rows of active wave w: w itself, or -- row groups of up to 128 rows --
             // the helper wave that also loads w's rows, so that w goes on to the next item meanwhile.
             const int stores_for = shift_loads ? takeover : (active ? wv : -1);
             if (active) {
-                // 16-byte chunk c of row r sits at chunk c ^ (r & 15); the lane's eight bytes of it at 8 h
-                float scale;
-                sp_put_q15(1.f / l2_tot, lds0 + (uint32_t)(wv * 16384 + r32_ * 256 + ((r32_ & 15) << 4) + 8 * h), scale);
-                if (h == 0 && wv * 32 + r32_ < rows_here) {
-                    const int64_t wrow = ta_ws_row(p, slot, rg, wv * 32 + r32_);
-                    *(float2 *)&p.ws_lse[2 * wrow] = make_float2(m_run + log2f(l_tot), scale);
+                // 16-byte chunk c of row r sits at chunk c ^ (r & 15); of the lane's first four values, eight bytes, the
+                // chunk is part / 2 and the half of it part & 1
+                float scale, m_run;
+                const int row = Lane::row(ln, 0), part = Lane::part(ln);
+                X::row_totals(l0, l1, w0, w1, m_run);
+                X::put_q15(1.f / w0, lds0 + (uint32_t)(wv * 16384 + row * 256 + (((part >> 1) ^ (row & 15)) << 4) + 8 * (part & 1)),
+                           scale);
+                const int own = wv * 32 + Lane::own(ln);
+                if (Lane::writes(ln) && own < rows_here) {
+                    const int64_t wrow = ta_ws_row(p, slot, rg, own);
+                    *(float2 *)&p.ws_lse[2 * wrow] = make_float2(m_run + log2f(l0), scale);
                 }
             }
             if (shift_loads)
@@ -607,7 +632,8 @@ hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
     if (dev < 0 || dev >= 64)
         return hipErrorInvalidDevice;
     if (!attr_set[dev]) {
-        for (const void *fn : {(const void *)ta_mfma_sp_kernel<false>, (const void *)ta_mfma_sp_kernel<true>}) {
+        for (const void *fn : {(const void *)ta_mfma_sp_kernel<false, false>, (const void *)ta_mfma_sp_kernel<true, false>,
+                               (const void *)ta_mfma_sp_kernel<false, true>, (const void *)ta_mfma_sp_kernel<true, true>}) {
             hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512);
             if (e != hipSuccess)
                 return e;
@@ -615,9 +641,10 @@ hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
         attr_set[dev] = true;
     }
     const dim3 grid(p.n_wg, p.n_rg);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(512), smem, stream, TA_SCHED_ARGS(p), p); };
     if (p.kn)
-        hipLaunchKernelGGL((ta_mfma_sp_kernel<true>), grid, dim3(512), smem, stream, TA_SCHED_ARGS(p), p);
+        p.wide ? launch(ta_mfma_sp_kernel<true, true>) : launch(ta_mfma_sp_kernel<true, false>);
     else
-        hipLaunchKernelGGL((ta_mfma_sp_kernel<false>), grid, dim3(512), smem, stream, TA_SCHED_ARGS(p), p);
+        p.wide ? launch(ta_mfma_sp_kernel<false, true>) : launch(ta_mfma_sp_kernel<false, false>);
     return hipGetLastError();
 }

@@ -56,6 +56,7 @@ struct TAParams {
     int32_t basic;             // take the key-split matrix-core kernel, not the pipelined one
     int32_t ks_rows;           // rows one of its workgroups keeps: a row group, or an even part of one
     int32_t f32_mfma;          // fp32 inputs on the matrix cores (ta_f32.hip)
+    int32_t wide;              // pipelined kernel: the blocks built on 16x16x32 products
     int32_t solo;              // TA_SOLO_*: one workgroup per list and block of rows walks it alone and writes the outputs
     int32_t direct;            // the key-split kernel writes the outputs of lists that lie in one share itself
     int32_t merge_kind;        // TA_MERGE_*: which merge kernel follows the KV pass
