@@ -617,6 +617,32 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
                         for (int i = 0; i < 16; ++i)
                             o[rb][db][i] *= alpha;
                 }
+            }
+            // ---- V fragments.  Parts younger than this run's V: with two runs in the ring K and V of the next one
+            // and the K just requested, with one the K just requested
+            if (C::NS > 1)
+                wait_parts(ahead ? 3 : next ? 2 : 0);
+            else
+                wait_parts(ahead ? 1 : 0);
+            const char *vt = vring + sl * C::SUBB + vf_row;
+            // All of them are requested here and arrive under the exponentials: left to the compiler, each was requested when
+            // the one before had been used (head_dim 64, B 16 39.05 us a call, now 38.75; one list of 8192 tokens 14.63, now
+            // 14.54).
+            typedef __attribute__((address_space(3))) ks_s4 *lds_s4;
+            typedef short s8 __attribute__((ext_vector_type(8)));
+            s8 vf[2][NDB];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) {
+                    const char *a = vt + kb * 16 * C::ROW + (((2 * db + vh16) ^ vf_x) << 5);
+                    const ks_s4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)a);
+                    const ks_s4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(a + 8 * C::ROW));
+                    vf[kb][db] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
                 // (a row that has not seen a token yet keeps -inf: its probabilities are exp2(-inf) = 0)
                 const float neg_m = m_run[rb] == -INFINITY ? 0.f : -m_run[rb];
                 float e[16], sum[2] = {0.f, 0.f}, sum2[2] = {0.f, 0.f};
@@ -635,29 +661,16 @@ __global__ __launch_bounds__(64 * NW, OCC * NW / 4) void ta_mfma_ks_kernel(TA_SC
                 pb[rb][0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
                 pb[rb][1] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
             }
-            // ---- O^T += V^T . P^T.  Parts younger than this run's V: with two runs in the ring K and V of the next one
-            // and the K just requested, with one the K just requested
-            if (C::NS > 1)
-                wait_parts(ahead ? 3 : next ? 2 : 0);
-            else
-                wait_parts(ahead ? 1 : 0);
-            const char *vt = vring + sl * C::SUBB + vf_row;
+            // ---- O^T += V^T . P^T
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int db = 0; db < NDB; ++db) {
-                    typedef __attribute__((address_space(3))) ks_s4 *lds_s4;
-                    typedef short s8 __attribute__((ext_vector_type(8)));
-                    const char *a = vt + kb * 16 * C::ROW + (((2 * db + vh16) ^ vf_x) << 5);
-                    const ks_s4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)a);
-                    const ks_s4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(a + 8 * C::ROW));
-                    const s8 vf = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+                for (int db = 0; db < NDB; ++db)
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb)
-                        o[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(ks_bf16x8, vf),
+                        o[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(ks_bf16x8, vf[kb][db]),
                                                                             __builtin_bit_cast(ks_bf16x8, pb[rb][kb]),
                                                                             o[rb][db], 0, 0, 0);
-                }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // the V rows are in registers
             if (ahead)
                 issue(un, sl, true);
