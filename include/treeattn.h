@@ -281,8 +281,9 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
  * workgroup per row, 0 general), plan[11] = row of the dispatch table that was taken (-1: none, the fp32 matrix-core
  * kernel runs), plan[12] = workspace bytes the call needs, plan[13] = format of the partial results (0: fp32; 1: 16-bit
- * fixed point with one fp32 scale per row), plan[14] = 1 if the key-split matrix-core kernel runs, plan[15] = query rows
- * a workgroup of the KV pass keeps.
+ * fixed point with one fp32 scale per row), plan[14]: bit 0 is 1 if the key-split matrix-core kernel runs, the bits above are
+ * what the pipelined one is built on (0: 32x32x16 products, paced; 1: the same, not paced; 2: 16x16x32 products),
+ * plan[15] = query rows a workgroup of the KV pass keeps.
  * HOST pointers.
  */
 int tree_attn_plan(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,

@@ -86,12 +86,7 @@ def frag(r):
 class Narrow:
     """v_mfma_f32_32x32x16_bf16: a lane holds one query row, lane & 31, with 4 * (lane >> 5) + {0..3} of every eight tokens
     or head-dim columns."""
-    name, rows = "SpNarrow", 1                            # rows of a lane
-    # Steady-state tiles: so many s_nop 7 early in the block.  Waves with few rows wait for the memory, and a block as short as
-    # it can be makes them ask in step: B 16, 32/8 heads, T 16, L 16384 170.8 us a call with none, 170.1 with two, 168.4 with four
-    # and 168.2 with eight (169.5 before the blocks got shorter); 32 such lists of 512 to 8192 tokens 108.9, 108.2, 108.0, 108.1.
-    pace = 4
-
+    name, rows, pace = "SpNarrow", 1, 0                   # rows of a lane, waits in its steady-state tiles
     # four scores of one row at a time: (row, score registers, P registers, last PV fragment multiplied with these)
     quads = [(0, [4 * g + k for k in range(4)], [2 * g, 2 * g + 1], 4 * (g // 2) + 3) for g in range(8)]
     # the row of O's register quads (head-dim columns in ascending order per row), and where one goes in the staging block:
@@ -140,6 +135,16 @@ class Narrow:
             dst = vr(sn + 16 * tb, 16)
             out.append((rd, [mfma % (dst, vr(f, 4), vr(Q + 4 * kk, 4), "0" if kk == 0 else dst)]))
         return out
+
+
+class Paced(Narrow):
+    """The narrow blocks with a wait of four s_nop 7 early in every steady-state tile, for row groups of up to 128 rows, where at
+    least half of the waves only move tiles.  128 rows without it: 0.97 to 1.0 of the time back to back, and single calls after
+    a copy, which run at a higher clock, 0.97 to 1.01 on four cards, but 1.07 to 1.28 on a fifth (16 lists of 49152 tokens 88.5 us
+    with it, 105.1 without).  32 and 64 rows: both within 1 %.  With more rows the waves wait for the products and it only costs:
+    time with it over that without, back to back and single, 136 to 192 rows 1.0 to 1.02 and 1.0 to 1.04, 224 to 512 rows 1.0 to
+    1.01 and 1.0 to 1.02."""
+    name, pace = "SpPaced", 4
 
 
 class Wide:
@@ -670,6 +675,7 @@ def generate():
         body.append(fast_loop(sh, "fast_loop"))
         body += helpers(sh)
         out.append("struct %s {\n%s\n};" % (sh.name, "\n\n".join(body)))
+    out.append("struct %s : %s {\n%s\n};" % (Paced.name, Narrow.name, fast_loop(Paced, "fast_loop")))
     out.append(fast_loop(Narrow, "sp_fast_loop_helper", helper=True))
     return "\n\n".join(out) + "\n"
 

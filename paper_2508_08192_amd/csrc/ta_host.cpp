@@ -453,8 +453,10 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // (4 lists of 131072 tokens, 8 KV heads: 0.95); 128 rows 4 and 8 1.02, 32 0.98 to 1.02 from one card to the next, 64 0.96,
     // 128 0.97; 64 rows 1.02 to 1.03.  Tiles are counted from what the page table can hold, of which a batch fills half in the
     // mean; what a window leaves of it the host does not know.
-    p.wide = kernel == TA_KERNEL_MFMA && !ks && !p.kv_start && pl.rows_grp > 64 &&
-             tiles_cap >= (int64_t)(pl.rows_grp > 128 ? 24 : 64) * pl.n_wg;
+    const bool wide = !p.kv_start && pl.rows_grp > 64 && tiles_cap >= (int64_t)(pl.rows_grp > 128 ? 24 : 64) * pl.n_wg;
+    // Otherwise the narrow ones, in row groups of up to 128 rows with a wait in every tile (figures beside Paced in gen_sp_block.py).
+    if (kernel == TA_KERNEL_MFMA && !ks)
+        p.blocks = wide ? TA_BLOCKS_WIDE : pl.rows_grp > 128 ? TA_BLOCKS_NARROW : TA_BLOCKS_PACED;
 
     // merge kernel: partials per list the schedule produces on average = the KV pass's workgroups spread over the
     // lists, plus the one boundary each list shares with its neighbour
@@ -536,7 +538,7 @@ void ta_host_fill_plan(const TAProblem &pr, int64_t plan[16])
     plan[12] = (int64_t)pr.ws_bytes;
     plan[13] = pr.p.part_q15;
     const bool ks = pr.plan.kernel == TA_KERNEL_MFMA && pr.p.basic;
-    plan[14] = ks;
+    plan[14] = ks ? 1 : pr.p.blocks << 1;
     plan[15] = ks ? pr.plan.ks_rows : pr.plan.rows_grp;
 }
 

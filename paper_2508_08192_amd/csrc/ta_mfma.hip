@@ -102,11 +102,11 @@ struct SpTag {
 // amdgpu_num_vgpr(16): the register allocator stays in v0..v31; v32..v255 belong to the asm blocks (see gen_sp_block.py)
 // NEW: the tree tokens' K/V come from the dense tensors of ta_opts.k_new / v_new (an instance of its own, so that the
 // ordinary call carries none of that addressing).
-// WIDE: the blocks built on 16x16x32 products (SpWide in gen_sp_block.py); the rule for it stands in ta_host.cpp.
-template <bool NEW, bool WIDE>
+// X: the blocks it is built on, SpPaced, SpNarrow or (16x16x32 products) SpWide of gen_sp_block.py; the rule stands in ta_host.cpp.
+template <bool NEW, class X>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_mfma_sp_kernel(TA_SCHED_PARAMS, TAParams p)
 {
-    using X = std::conditional_t<WIDE, SpWide, SpNarrow>;
+    constexpr bool WIDE = std::is_same_v<X, SpWide>;
     using Lane = SpLane<WIDE>;
     const TASched sc = TA_SCHED;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -632,8 +632,9 @@ hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
     if (dev < 0 || dev >= 64)
         return hipErrorInvalidDevice;
     if (!attr_set[dev]) {
-        for (const void *fn : {(const void *)ta_mfma_sp_kernel<false, false>, (const void *)ta_mfma_sp_kernel<true, false>,
-                               (const void *)ta_mfma_sp_kernel<false, true>, (const void *)ta_mfma_sp_kernel<true, true>}) {
+        for (const void *fn : {(const void *)ta_mfma_sp_kernel<false, SpPaced>, (const void *)ta_mfma_sp_kernel<true, SpPaced>,
+                               (const void *)ta_mfma_sp_kernel<false, SpNarrow>, (const void *)ta_mfma_sp_kernel<true, SpNarrow>,
+                               (const void *)ta_mfma_sp_kernel<false, SpWide>, (const void *)ta_mfma_sp_kernel<true, SpWide>}) {
             hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512);
             if (e != hipSuccess)
                 return e;
@@ -642,9 +643,15 @@ hipError_t ta_launch_mfma(const TAParams &p, hipStream_t stream, int dev)
     }
     const dim3 grid(p.n_wg, p.n_rg);
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(512), smem, stream, TA_SCHED_ARGS(p), p); };
-    if (p.kn)
-        p.wide ? launch(ta_mfma_sp_kernel<true, true>) : launch(ta_mfma_sp_kernel<true, false>);
+    auto launch_on = [&](auto blocks) {
+        using X = decltype(blocks);
+        p.kn ? launch(ta_mfma_sp_kernel<true, X>) : launch(ta_mfma_sp_kernel<false, X>);
+    };
+    if (p.blocks == TA_BLOCKS_WIDE)
+        launch_on(SpWide{});
+    else if (p.blocks == TA_BLOCKS_NARROW)
+        launch_on(SpNarrow{});
     else
-        p.wide ? launch(ta_mfma_sp_kernel<false, true>) : launch(ta_mfma_sp_kernel<false, false>);
+        launch_on(SpPaced{});
     return hipGetLastError();
 }

@@ -56,7 +56,7 @@ struct TAParams {
     int32_t basic;             // take the key-split matrix-core kernel, not the pipelined one
     int32_t ks_rows;           // rows one of its workgroups keeps: a row group, or an even part of one
     int32_t f32_mfma;          // fp32 inputs on the matrix cores (ta_f32.hip)
-    int32_t wide;              // pipelined kernel: the blocks built on 16x16x32 products
+    int32_t blocks;            // TA_BLOCKS_*: what the pipelined kernel is built on
     int32_t solo;              // TA_SOLO_*: one workgroup per list and block of rows walks it alone and writes the outputs
     int32_t direct;            // the key-split kernel writes the outputs of lists that lie in one share itself
     int32_t merge_kind;        // TA_MERGE_*: which merge kernel follows the KV pass
@@ -89,6 +89,11 @@ struct TACompact {
     int32_t vec;                       // rows can be moved in 16-byte pieces
     int32_t *status;
 };
+
+// Blocks of the pipelined kernel (gen_sp_block.py).
+#define TA_BLOCKS_PACED 0     // 32x32x16 products, a wait in every steady-state tile
+#define TA_BLOCKS_NARROW 1    // the same without the wait
+#define TA_BLOCKS_WIDE 2      // 16x16x32 products
 
 // How lists that are not cut are walked (no merge pass follows); 0: lists are cut.
 #define TA_SOLO_WIDE 1        // eight waves, one workgroup per compute unit at a time

@@ -422,4 +422,7 @@ def tree_attn_plan(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, 
     keys = ("kernel", "kv_workgroups", "threads", "tile", "row_groups", "rows_per_group", "partial_slots",
             "merge_workgroups", "min_share", "item_cost", "merge_kernel", "table_row", "workspace_bytes",
             "partials_q15", "key_split", "workgroup_rows")
-    return dict(zip(keys, [int(x) for x in plan]))
+    d = dict(zip(keys, [int(x) for x in plan]))
+    d["blocks"] = d["key_split"] >> 1              # the pipelined kernel's: TA_BLOCKS_* of csrc/ta_params.h
+    d["key_split"] &= 1
+    return d

@@ -1,0 +1,54 @@
+"""Which blocks the pipelined kernel is built on (no GPU needed): the plan says so, and the generator writes what the plan means."""
+import importlib.util
+import os
+import re
+
+import pytest
+
+from paper_2508_08192_amd import treeattn as ta
+from paper_2508_08192_amd.treeattn import Desc
+
+PACED, NARROW, WIDE = 0, 1, 2
+MFMA = 2
+
+
+def _plan(rows, lists, tiles, kernel=MFMA, **kw):
+    """A call of `lists` requests with one KV head and `rows` query rows, in a table of `tiles` tiles and the tree's."""
+    T = next(t for t in range(min(rows, 64), 0, -1) if rows % t == 0)
+    G, table = rows // T, tiles - 1 + -(-T // 64)
+    return ta.tree_attn_plan(
+        Desc((lists, T, G, 128), ta.TA_BF16), Desc((lists * table, 1, 64, 128), ta.TA_BF16),
+        Desc((lists * table, 1, 64, 128), ta.TA_BF16), Desc((lists, table), ta.TA_I32), Desc((lists,), ta.TA_I32),
+        Desc((T,), ta.TA_I32), Desc((lists, T, G, 128), ta.TA_BF16), Desc((lists, G, T), ta.TA_F32), kernel=kernel, **kw)
+
+
+@pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 72, 96, 128, 129, 136, 160, 192, 224, 256, 320, 512])
+@pytest.mark.parametrize("lists,tiles", [(32, 20), (400, 5)])
+def test_only_row_groups_of_up_to_128_rows_are_paced(rows, lists, tiles):
+    """The wait in a paced tile costs calls of 129 rows and more 1 to 2 %."""
+    p = _plan(rows, lists, tiles)
+    assert p["key_split"] == 0 and p["merge_workgroups"] > 0
+    assert p["blocks"] == (PACED if rows <= 128 else NARROW), p
+
+
+def test_the_key_split_kernel_has_no_blocks():
+    assert _plan(32, 32, 20, kernel=3)["key_split"] == 1 and _plan(32, 32, 20, kernel=3)["blocks"] == 0
+
+
+def _steady_loop(text, struct):
+    """The lines of a struct's steady-state loop, without the ones behind its branch back."""
+    body = text[re.search(r"^struct %s\b" % struct, text, re.M).start():]
+    lines = re.findall(r'"([^"\\]*)\\n\\t"', body[body.index(" fast_loop("):body.index("}", body.index(" fast_loop("))])
+    return lines[:lines.index("s_cbranch_scc1 1b") + 1]
+
+
+def test_only_paced_blocks_wait_in_the_steady_state():
+    path = os.path.join(os.path.dirname(ta.__file__), "csrc", "gen_sp_block.py")
+    spec = importlib.util.spec_from_file_location("gen_sp_block", path)
+    gen = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(gen)
+    text = gen.generate()
+    paced, narrow, wide = (_steady_loop(text, s) for s in ("SpPaced", "SpNarrow", "SpWide"))
+    assert "s_nop 7" not in narrow and "s_nop 7" not in wide
+    assert paced.count("s_nop 7") == 8 and len(narrow) > 400              # two tiles; else they are the same work:
+    assert sorted(x for x in paced if x[0] == "v" or x[:2] == "ds") == sorted(x for x in narrow if x[0] == "v" or x[:2] == "ds")
