@@ -122,7 +122,10 @@ typedef struct {
                                  requests are long, and whose batches are small, can name the kernel instead: with more
                                  than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 19.8 us
                                  a call and 27.5), with 32 rows and a few requests of some hundred tokens the pipelined
-                                 kernel a tenth. */
+                                 kernel a tenth.  The pipelined kernel's form for long shares (plan[14]) is chosen from the
+                                 table too: with 97 to 128 rows, 225 to 256 or as many in the last of several groups of
+                                 256, a table four times as wide as the requests can cost up to a twentieth where they
+                                 leave a workgroup or a list some 12 to 24 tiles of 64 tokens. */
 
 typedef struct {
     float scale;              /* softmax scale; <= 0 or NaN selects 1/sqrt(head_dim) */

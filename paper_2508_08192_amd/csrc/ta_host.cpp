@@ -446,14 +446,23 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
         pl.n_wg = (int)(tiles_cap > 0 ? tiles_cap : 1);
     pl.n_slots = pl.n_wg + (int)lists;
     p.rows_grp = pl.rows_grp; p.n_rg = pl.n_rg; p.n_wg = pl.n_wg; p.min_q = pl.min_q;
-    // The pipelined kernel's wide blocks (16x16x32 products) draw less power and take more instructions.  Where all waves
-    // have rows and stay in their loops the clock is what the power allows, so they are the faster ones there; short shares
-    // run at the highest clock, and with 64 rows and fewer the waves wait for the memory.  32 lists of equal length, 8 heads on
-    // one KV head, time over that of the narrow blocks by tiles per workgroup: 256 rows 4 1.05, 8 1.04, 16 0.98, 32 0.98, 64 0.96
-    // (4 lists of 131072 tokens, 8 KV heads: 0.95); 128 rows 4 and 8 1.02, 32 0.98 to 1.02 from one card to the next, 64 0.96,
-    // 128 0.97; 64 rows 1.02 to 1.03.  Tiles are counted from what the page table can hold, of which a batch fills half in the
-    // mean; what a window leaves of it the host does not know.
-    const bool wide = !p.kv_start && pl.rows_grp > 64 && tiles_cap >= (int64_t)(pl.rows_grp > 128 ? 24 : 64) * pl.n_wg;
+    // The pipelined kernel's wide blocks (16x16x32 products) draw less power and take more instructions.  They are for calls whose
+    // clock is what the power allows: all waves of every row group that computes have rows (four of groups of 128, eight of 256),
+    // and stay in their steady-state loops, which a run of one list's tiles in one share is for.  Time over that of the narrow blocks,
+    // over 4 to 400 lists of equal and evenly spread lengths, by tiles per share or list, whichever are fewer: back to back; with
+    // matrix products of a layer's size before each call; single calls after a copy, which run at a higher clock.
+    //   256, 240 and 512 rows: 12 tiles 1.0 to 1.05, 0.98 to 1.05, 1.0 to 1.04; 24 0.97 to 1.01, 0.91 to 1.04, 1.0 to 1.05; 48
+    //     0.97 to 0.99, 0.92 to 1.01, 0.98 to 1.01; 100 and more 0.96 to 0.99, 0.96 to 1.0, 0.96 to 1.0;
+    //   128 and 100 rows: 24 0.98 to 1.02, 0.99 to 1.04, 0.99 to 1.03; 48 0.96 to 0.99, 0.95 to 1.01, 0.98 to 1.01; 100 and more
+    //     0.95 to 0.98, 0.91 to 1.0, 0.99 to 1.01;
+    //   some waves without rows: 136 to 192 rows 0.98 to 1.07 and single 1.01 to 1.08 at any length, 224 single up to 1.06, 320
+    //     single 1.0 to 1.05, 96 0.97 to 1.03 and single 0.99 to 1.04; 64 rows 1.02 to 1.03.
+    // So 48 tiles are the line.  Tiles are counted from what the page table can hold: twice that many with 256 rows, for
+    // lengths spread evenly or a table twice as wide as its requests; four times with 128, where less is gained.  What a window
+    // leaves of the tiles the host does not know.
+    const bool waves_full = (p.rows - 1) % pl.rows_grp >= pl.rows_grp - 32;
+    const bool wide = !p.kv_start && pl.rows_grp > 64 && waves_full &&
+                      tiles_cap >= (pl.rows_grp > 128 ? 96 : 192) * (lists > pl.n_wg ? lists : (int64_t)pl.n_wg);
     // Otherwise the narrow ones, in row groups of up to 128 rows with a wait in every tile (figures beside Paced in gen_sp_block.py).
     if (kernel == TA_KERNEL_MFMA && !ks)
         p.blocks = wide ? TA_BLOCKS_WIDE : pl.rows_grp > 128 ? TA_BLOCKS_NARROW : TA_BLOCKS_PACED;

@@ -1,44 +1,64 @@
-"""The pipelined kernel's wide blocks (16x16x32 products; calls with more than 64 rows per KV head and long shares): shares of
+"""The pipelined kernel's wide blocks (16x16x32 products; long shares of row groups of which all waves have rows): shares of
 every number of tiles around those that the steady-state loop takes, rows at the edges of the two sixteens a lane holds,
 trees of every length and pages of several sizes, a softmax reference that moves in mid-walk, values that are no numbers;
-against the fp64 oracle."""
+against the fp64 oracle.  The same shapes with other blocks where some waves have none.  (tests/test_pipelined_blocks.py holds the
+rule itself.)"""
 import numpy as np
 import pytest
 
 from paper_2508_08192_amd import workloads as W
-from tests.helpers import assert_parity, run_hip, run_oracle
+from tests.helpers import assert_parity, run_hip, run_oracle, to_device
 
 pytestmark = pytest.mark.gpu
 MFMA = 2
-TILES_128, TILES_256 = 64, 24                  # a workgroup, from where calls of up to 128 and 256 rows take them
+PACED, NARROW, WIDE = 0, 1, 2
+LONG = 200 * 64                                # tokens a table has to hold for the wide blocks to be chosen
 
 
-def _workload(T, Hq, Hkv, lens, ps, seed):
+def _workload(T, Hq, Hkv, lens, ps, seed, long=True):
     rng = np.random.default_rng(seed)
     trees = np.stack([W.random_tree(T, min(T, 7), rng) for _ in lens])
     # values of half the size: a node that sees two tokens has outputs as large as they are, and bf16 rounds one of 4 and more by
     # up to 1.6e-2, which alone is more than the parity bar of 1e-2 (of less than 4: 7.8e-3)
-    return W.make_workload("wide", B=len(lens), T=T, Hq=Hq, Hkv=Hkv, D=128, seq_lens=lens, trees=trees, page_size=ps, seed=seed,
-                           paged=ps > 0, kv_std=0.5)
+    w = W.make_workload("wide", B=len(lens), T=T, Hq=Hq, Hkv=Hkv, D=128, seq_lens=lens, trees=trees, page_size=ps, seed=seed,
+                        paged=ps > 0, kv_std=0.5)
+    if long and ps:
+        w.page_table = np.pad(w.page_table, ((0, 0), (0, max(0, LONG // ps - w.page_table.shape[1]))))
+    elif long:
+        room = ((0, 0), (0, 0), (0, max(0, LONG - w.k_cache.shape[2])), (0, 0))
+        w.k_cache, w.v_cache = np.pad(w.k_cache, room), np.pad(w.v_cache, room)
+    return w
 
 
-def _check(w, what, splits):
-    tiles = w.B * w.Hkv * ((int(w.seq_lens.max()) + 63) // 64 + 1)
-    rows = w.T * w.Hq // w.Hkv
-    assert rows > 64 and tiles >= splits * (TILES_128 if rows <= 128 else TILES_256), what
+def _blocks(T, Hq, Hkv):
+    rows = T * Hq // Hkv
+    return WIDE if rows > 64 and (rows - 1) % (128 if rows <= 128 else 256) >= (96 if rows <= 128 else 224) else \
+        PACED if rows <= 128 else NARROW
+
+
+def _plan(d, splits, kernel=MFMA):
+    from paper_2508_08192_amd import treeattn as ta
+    return ta.tree_attn_plan(d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"], d["out"],
+                             d["lse"], kernel=kernel, num_splits=splits)
+
+
+def _check(w, what, splits, blocks):
+    d = to_device(w)
+    assert _plan(d, splits)["blocks"] == blocks, what
     print(what, flush=True)
-    got, lse = run_hip(w, kernel=MFMA, num_splits=splits)
+    got, lse = run_hip(w, d, kernel=MFMA, num_splits=splits)
     ref, ref_lse = run_oracle(w)
     assert_parity(got, lse, ref, ref_lse, "bf16", what)
 
 
-@pytest.mark.parametrize("T,Hq,Hkv", [(64, 2, 1), (13, 5, 1), (17, 4, 1), (33, 5, 1), (32, 8, 1), (51, 5, 1), (64, 16, 2)])
+@pytest.mark.parametrize("T,Hq,Hkv", [(64, 2, 1), (1, 97, 1), (49, 2, 1), (45, 5, 1), (37, 13, 1), (32, 8, 1), (51, 5, 1),
+                                      (64, 16, 2), (13, 5, 1), (17, 4, 1), (33, 5, 1)])
 @pytest.mark.parametrize("ps", [0, 4, 16, 64])
 def test_tiles_rows_and_tree_ends(T, Hq, Hkv, ps):
     lens = [0, 1, 15, 16, 17, 47, 48, 63, 64, 65, 128, 129, 192, 255, 256, 257, 320, 383, 384, 449, 512, 577, 640, 700]
     w = _workload(T, Hq, Hkv, lens, ps, 7 + T)
     for splits in (1, 2):
-        _check(w, "wide T=%d %d/%d ps=%d splits=%d" % (T, Hq, Hkv, ps, splits), splits)
+        _check(w, "wide T=%d %d/%d ps=%d splits=%d" % (T, Hq, Hkv, ps, splits), splits, _blocks(T, Hq, Hkv))
 
 
 @pytest.mark.parametrize("T,Hq", [(16, 8), (32, 8)])
@@ -54,7 +74,7 @@ def test_reference_moves_in_mid_walk(T, Hq):
         row = (k[page, 0, pos % 64].astype(np.uint32) << 16).view(np.float32) * np.float32(2.0 + 8.0 * rng.random())
         k[page, 0, pos % 64] = (row.view(np.uint32) >> 16).astype(np.uint16)
     w.k_cache = k
-    _check(w, "moving reference T=%d" % T, 1)
+    _check(w, "moving reference T=%d" % T, 1, WIDE)
 
 
 @pytest.mark.parametrize("T,Hq", [(16, 8), (32, 8)])
@@ -63,7 +83,9 @@ def test_a_value_that_is_no_number_spoils_its_rows(T, Hq):
     v = w.v_cache.copy()
     v[int(w.page_table[0, 20]), 0, 13, 77] = 0x7fc0
     w.v_cache = v
-    got, lse = run_hip(w, kernel=MFMA, num_splits=1)
+    d = to_device(w)
+    assert _plan(d, 1)["blocks"] == WIDE
+    got, lse = run_hip(w, d, kernel=MFMA, num_splits=1)
     ref, ref_lse = run_oracle(w)
     assert np.isnan(got[0]).all() and np.isfinite(lse[0]).all()
     assert_parity(got[1:], lse[1:], ref[1:], ref_lse[1:], "bf16", "no number T=%d" % T)

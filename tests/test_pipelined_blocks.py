@@ -31,6 +31,27 @@ def test_only_row_groups_of_up_to_128_rows_are_paced(rows, lists, tiles):
     assert p["blocks"] == (PACED if rows <= 128 else NARROW), p
 
 
+@pytest.mark.parametrize("rows", [65, 72, 96, 97, 128, 129, 136, 160, 192, 224, 225, 256, 320, 480, 512])
+def test_wide_blocks_only_where_all_waves_have_rows(rows):
+    """Otherwise they take up to 1.08 times as long, whatever the length."""
+    full = 96 < rows <= 128 or 224 < rows <= 256 or rows == 512
+    for lists, tiles in ((16, 4000), (100, 1500), (600, 900)):
+        assert _plan(rows, lists, tiles)["blocks"] == (WIDE if full else PACED if rows <= 128 else NARROW), (lists, tiles)
+
+
+@pytest.mark.parametrize("rows,line,form", [(256, 96, NARROW), (512, 96, NARROW), (128, 192, PACED)])
+def test_wide_blocks_only_for_long_shares_of_long_lists(rows, line, form):
+    """Tiles per workgroup and per list, both: many short lists in a share leave no steady state."""
+    wgs = 256 // -(-rows // 256)
+    for lists in (1, 8, 64, 256, 400):
+        runs = max(lists, wgs)
+        for tiles, want in (((line * runs - 1) // lists, form), (-(-line * runs // lists), WIDE)):
+            p = _plan(rows, lists, tiles)
+            assert p["kv_workgroups"] == wgs and p["blocks"] == want, (lists, tiles, p)
+    assert _plan(rows, 400, line // 2)["blocks"] == form           # (line tiles and more a workgroup)
+    assert _plan(rows, 1, 2 * line, num_splits=2)["blocks"] == WIDE and _plan(rows, 1, line, num_splits=2)["blocks"] == form
+
+
 def test_the_key_split_kernel_has_no_blocks():
     assert _plan(32, 32, 20, kernel=3)["key_split"] == 1 and _plan(32, 32, 20, kernel=3)["blocks"] == 0
 
