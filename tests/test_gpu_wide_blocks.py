@@ -89,3 +89,77 @@ def test_a_value_that_is_no_number_spoils_its_rows(T, Hq):
     ref, ref_lse = run_oracle(w)
     assert np.isnan(got[0]).all() and np.isfinite(lse[0]).all()
     assert_parity(got[1:], lse[1:], ref[1:], ref_lse[1:], "bf16", "no number T=%d" % T)
+
+
+@pytest.mark.parametrize("T,Hq,Hkv,offset", [(40, 8, 2, 8), (64, 4, 1, 4), (64, 8, 1, 0), (28, 8, 2, 0)])
+@pytest.mark.parametrize("splits", [1, 2])
+def test_every_option_on_wide_blocks(T, Hq, Hkv, offset, splits):
+    """64 to 512 query rows a KV head: a subset of the nodes, given masks, the write-back folded in (its own instance of the
+    kernel), a bad page and a bad length each spoiling its own request only; against append and the scalar kernel."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    w = _workload(T, Hq, Hkv, [700, 70, 385, 40], 32, 3 + T)
+    B, Tq = 4, T - offset
+    d = to_device(w)
+    masks = torch.empty((B, T), dtype=torch.int64, device="cuda")
+    ta.tree_attn_encode(d["tree_parent"], masks)
+    k_new, v_new = (torch.randn(B, T, Hkv, 128, generator=torch.Generator().manual_seed(s)).mul_(0.5).bfloat16().cuda() for s in (1, 2))
+    d["q"] = d["q"][:, offset:].contiguous()
+    d["page_table"][1, 1] = 1 << 30
+    d["seq_lens"][3] = -5
+    rest = (d["page_table"], d["seq_lens"], d["tree_parent"])
+
+    def call(kernel, folded, **kw):
+        k, v = d["k_cache"].clone(), d["v_cache"].clone()
+        out, lse = torch.zeros_like(d["q"]), torch.zeros((B, Hq, Tq), device="cuda")
+        if folded:
+            kw = dict(kw, k_new=k_new, v_new=v_new)
+        else:
+            ta.tree_attn_append(k_new, v_new, k, v, d["page_table"], d["seq_lens"])
+        ta.tree_attn_last_status()
+        print("wide, every option, T=%d rows=%d kernel=%d folded=%s" % (T, Tq * Hq // Hkv, kernel, folded), flush=True)
+        ta.tree_attn_fwd_ex(d["q"], k, v, *rest, out, lse, kernel=kernel, q_node_offset=offset, **kw)
+        assert ta.tree_attn_last_status() == ta.TA_STATUS_BAD_PAGE | ta.TA_STATUS_BAD_SEQLEN
+        for b in (1, 3):
+            assert torch.isnan(out[b]).all() and torch.isnan(lse[b]).all()
+        return out[[0, 2]].float(), lse[[0, 2]], k, v
+
+    d["out"], d["lse"] = torch.empty_like(d["q"]), torch.empty((B, Hq, Tq), device="cuda")
+    assert _plan(d, splits)["blocks"] == WIDE
+    ref = call(1, False)
+    plain = call(MFMA, False, num_splits=splits)
+    for given in ({}, {"tree_masks": masks}):
+        got = call(MFMA, True, num_splits=splits, **given)
+        assert all(torch.equal(x, y) for x, y in zip(got, plain))         # append followed by the plain call, bit for bit
+    # probabilities as bf16 (2^-9 each) and the result rounded to bf16 (2^-9): 1e-2 as elsewhere
+    assert (plain[0] - ref[0]).abs().max() <= 1e-2 * ref[0].abs().max() and (plain[1] - ref[1]).abs().max() <= 1e-3
+
+
+@pytest.mark.parametrize("T,Hq", [(16, 8), (32, 8)])
+def test_a_captured_call_replays(T, Hq):
+    """A captured call on wide blocks leaves what an eager one does, replay after replay, also for lengths set in between."""
+    import torch
+    from paper_2508_08192_amd import treeattn as ta
+    w = _workload(T, Hq, 1, [64 * 66 + 3, 1500], 64, 5)
+    d = to_device(w)
+    args = (d["q"], d["k_cache"], d["v_cache"], d["page_table"], d["seq_lens"], d["tree_parent"])
+    assert _plan(d, 1)["blocks"] == WIDE
+    call = lambda out, lse: ta.tree_attn_fwd_ex(*args, out, lse, kernel=MFMA, num_splits=1)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        call(d["out"], d["lse"])
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            call(d["out"], d["lse"])
+    for lens in ([64 * 66 + 3, 1500], [640, 64 * 20], [4000, 0]):
+        d["seq_lens"].copy_(torch.tensor(lens, dtype=torch.int32))
+        out, lse = torch.zeros_like(d["out"]), torch.zeros_like(d["lse"])
+        call(out, lse)
+        d["out"].zero_()
+        d["lse"].zero_()
+        torch.cuda.synchronize()
+        print("wide, replay T=%d %s" % (T, lens), flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, d["out"]) and torch.equal(lse, d["lse"])
