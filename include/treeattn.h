@@ -122,7 +122,7 @@ typedef struct {
                                  requests are long, and whose batches are small, can name the kernel instead: with more
                                  than 128 rows key-split saves up to a quarter (256 rows, 8 lists of 4096 tokens: 19.8 us
                                  a call and 27.5), with 32 rows and a few requests of some hundred tokens the pipelined
-                                 kernel a tenth.  The pipelined kernel's form for long shares (plan[14]) is chosen from the
+                                 kernel a tenth.  The pipelined kernel's form for long shares (tree_attn_plan_blocks) is chosen from the
                                  table too: with 97 to 128 rows, 225 to 256 or as many in the last of several groups of
                                  256, a table four times as wide as the requests can cost up to a twentieth where they
                                  leave a workgroup or a list some 12 to 24 tiles of 64 tokens. */
@@ -284,15 +284,22 @@ int tree_attn_last_status(int32_t *host_status, void *stream);
  * plan[10] = merge kernel (1 head_dim 128 or 64 and aligned outputs, 2 the same with one
  * workgroup per row, 0 general), plan[11] = row of the dispatch table that was taken (-1: none, the fp32 matrix-core
  * kernel runs), plan[12] = workspace bytes the call needs, plan[13] = format of the partial results (0: fp32; 1: 16-bit
- * fixed point with one fp32 scale per row), plan[14]: bit 0 is 1 if the key-split matrix-core kernel runs, the bits above are
- * what the pipelined one is built on (0: 32x32x16 products, paced; 1: the same, not paced; 2: 16x16x32 products),
- * plan[15] = query rows a workgroup of the KV pass keeps.
+ * fixed point with one fp32 scale per row), plan[14] = 1 if the key-split matrix-core kernel runs, plan[15] = query rows
+ * a workgroup of the KV pass keeps.
  * HOST pointers.
  */
 int tree_attn_plan(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,
                    const ta_tensor *page_table, const ta_tensor *seq_lens, const ta_tensor *tree_parent,
                    const ta_tensor *out, const ta_tensor *lse, const ta_opts *opts, int32_t num_cus,
                    int64_t plan[16]);
+
+/*
+ * What the pipelined matrix-core kernel of such a call is built on (host-only; 0 also where another kernel runs):
+ * 0 32x32x16 products with a wait per tile, 1 the same without the wait, 2 16x16x32 products; negative: a status.
+ */
+int tree_attn_plan_blocks(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,
+                          const ta_tensor *page_table, const ta_tensor *seq_lens, const ta_tensor *tree_parent,
+                          const ta_tensor *out, const ta_tensor *lse, const ta_opts *opts, int32_t num_cus);
 
 /*
  * Row `index` of the dispatch table (host-only; returns TA_ERR_OPTS past the last row): row[0] = kernel family,

@@ -547,7 +547,7 @@ void ta_host_fill_plan(const TAProblem &pr, int64_t plan[16])
     plan[12] = (int64_t)pr.ws_bytes;
     plan[13] = pr.p.part_q15;
     const bool ks = pr.plan.kernel == TA_KERNEL_MFMA && pr.p.basic;
-    plan[14] = ks ? 1 : pr.p.blocks << 1;
+    plan[14] = ks;
     plan[15] = ks ? pr.plan.ks_rows : pr.plan.rows_grp;
 }
 
@@ -743,6 +743,20 @@ const char *tree_attn_strerror(int status)
     }
 }
 
+static int plan_problem(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache, const ta_tensor *page_table,
+                        const ta_tensor *seq_lens, const ta_tensor *tree_parent, const ta_tensor *out, const ta_tensor *lse,
+                        const ta_opts *opts, int32_t num_cus, TAProblem *pr)
+{
+    ta_opts o;
+    if (opts) {
+        o = *opts;
+        o.workspace = nullptr;      // planning never needs the scratch itself
+        o.workspace_bytes = 0;
+    }
+    return ta_host_build_problem(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse, opts ? &o : nullptr,
+                                 num_cus > 0 ? num_cus : 256, pr);
+}
+
 int tree_attn_plan(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,
                    const ta_tensor *page_table, const ta_tensor *seq_lens, const ta_tensor *tree_parent,
                    const ta_tensor *out, const ta_tensor *lse, const ta_opts *opts, int32_t num_cus,
@@ -751,18 +765,20 @@ int tree_attn_plan(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor
     if (!plan)
         return TA_ERR_NULL;
     TAProblem pr;
-    ta_opts o;
-    if (opts) {
-        o = *opts;
-        o.workspace = nullptr;      // planning never needs the scratch itself
-        o.workspace_bytes = 0;
-    }
-    int rc = ta_host_build_problem(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse,
-                                   opts ? &o : nullptr, num_cus > 0 ? num_cus : 256, &pr);
+    int rc = plan_problem(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse, opts, num_cus, &pr);
     if (rc != TA_OK)
         return rc;
     ta_host_fill_plan(pr, plan);
     return TA_OK;
+}
+
+int tree_attn_plan_blocks(const ta_tensor *q, const ta_tensor *k_cache, const ta_tensor *v_cache,
+                          const ta_tensor *page_table, const ta_tensor *seq_lens, const ta_tensor *tree_parent,
+                          const ta_tensor *out, const ta_tensor *lse, const ta_opts *opts, int32_t num_cus)
+{
+    TAProblem pr;
+    int rc = plan_problem(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse, opts, num_cus, &pr);
+    return rc != TA_OK ? rc : pr.p.blocks;
 }
 
 int tree_attn_dispatch_row(int32_t index, int64_t row[8])

@@ -27,6 +27,7 @@ TA_ERR_BATCH, TA_ERR_OPTS = -12, -13
 EXPORTS = (
     "tree_attn_fwd", "tree_attn_fwd_ex", "tree_attn_workspace_bytes", "tree_attn_reserve", "tree_attn_release",
     "tree_attn_encode", "tree_attn_append", "tree_attn_compact", "tree_attn_last_status", "tree_attn_plan",
+    "tree_attn_plan_blocks",
     "tree_attn_dispatch_row", "tree_attn_stream_read", "tree_attn_mfma_probe", "tree_attn_fwd_static", "tree_attn_strerror", "tree_attn_version",
 )
 
@@ -134,6 +135,8 @@ def load_library():
         lib.tree_attn_plan.restype = ctypes.c_int
         lib.tree_attn_plan.argtypes = [T, T, T, T, T, T, T, T, ctypes.POINTER(ta_opts), ctypes.c_int32,
                                        ctypes.POINTER(ctypes.c_int64)]
+        lib.tree_attn_plan_blocks.restype = ctypes.c_int
+        lib.tree_attn_plan_blocks.argtypes = [T, T, T, T, T, T, T, T, ctypes.POINTER(ta_opts), ctypes.c_int32]
         lib.tree_attn_strerror.restype = ctypes.c_char_p
         lib.tree_attn_strerror.argtypes = [ctypes.c_int]
         lib.tree_attn_version.restype = ctypes.c_int
@@ -414,7 +417,8 @@ def tree_attn_plan(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, 
     ds = [_desc(x) for x in (q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, lse)]
     o = _opts(scale, num_splits, kernel, None, None, item_cost, status=status)
     plan = (ctypes.c_int64 * 16)()
-    rc = load_library().tree_attn_plan(*[_ref(d) for d in ds], ctypes.byref(o), num_cus, plan)
+    call = [_ref(d) for d in ds] + [ctypes.byref(o), num_cus]
+    rc = load_library().tree_attn_plan(*call, plan)
     if rc != TA_OK:
         if check:
             raise TreeAttnError(rc, "tree_attn_plan")
@@ -423,6 +427,5 @@ def tree_attn_plan(q, k_cache, v_cache, page_table, seq_lens, tree_parent, out, 
             "merge_workgroups", "min_share", "item_cost", "merge_kernel", "table_row", "workspace_bytes",
             "partials_q15", "key_split", "workgroup_rows")
     d = dict(zip(keys, [int(x) for x in plan]))
-    d["blocks"] = d["key_split"] >> 1              # the pipelined kernel's: TA_BLOCKS_* of csrc/ta_params.h
-    d["key_split"] &= 1
+    d["blocks"] = int(load_library().tree_attn_plan_blocks(*call))   # the pipelined kernel's: TA_BLOCKS_* of csrc/ta_params.h
     return d

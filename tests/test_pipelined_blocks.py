@@ -1,4 +1,5 @@
 """Which blocks the pipelined kernel is built on (no GPU needed): the plan says so, and the generator writes what the plan means."""
+import ctypes
 import importlib.util
 import os
 import re
@@ -12,14 +13,17 @@ PACED, NARROW, WIDE = 0, 1, 2
 MFMA = 2
 
 
-def _plan(rows, lists, tiles, kernel=MFMA, **kw):
+def _call(rows, lists, tiles):
     """A call of `lists` requests with one KV head and `rows` query rows, in a table of `tiles` tiles and the tree's."""
     T = next(t for t in range(min(rows, 64), 0, -1) if rows % t == 0)
     G, table = rows // T, tiles - 1 + -(-T // 64)
-    return ta.tree_attn_plan(
-        Desc((lists, T, G, 128), ta.TA_BF16), Desc((lists * table, 1, 64, 128), ta.TA_BF16),
-        Desc((lists * table, 1, 64, 128), ta.TA_BF16), Desc((lists, table), ta.TA_I32), Desc((lists,), ta.TA_I32),
-        Desc((T,), ta.TA_I32), Desc((lists, T, G, 128), ta.TA_BF16), Desc((lists, G, T), ta.TA_F32), kernel=kernel, **kw)
+    return (Desc((lists, T, G, 128), ta.TA_BF16), Desc((lists * table, 1, 64, 128), ta.TA_BF16),
+            Desc((lists * table, 1, 64, 128), ta.TA_BF16), Desc((lists, table), ta.TA_I32), Desc((lists,), ta.TA_I32),
+            Desc((T,), ta.TA_I32), Desc((lists, T, G, 128), ta.TA_BF16), Desc((lists, G, T), ta.TA_F32))
+
+
+def _plan(rows, lists, tiles, kernel=MFMA, **kw):
+    return ta.tree_attn_plan(*_call(rows, lists, tiles), kernel=kernel, **kw)
 
 
 @pytest.mark.parametrize("rows", [1, 32, 33, 64, 65, 72, 96, 128, 129, 136, 160, 192, 224, 256, 320, 512])
@@ -54,6 +58,20 @@ def test_wide_blocks_only_for_long_shares_of_long_lists(rows, line, form):
 
 def test_the_key_split_kernel_has_no_blocks():
     assert _plan(32, 32, 20, kernel=3)["key_split"] == 1 and _plan(32, 32, 20, kernel=3)["blocks"] == 0
+
+
+def test_key_split_is_zero_or_one_whatever_the_blocks():
+    """plan[14] as a caller of the C function reads it: `if (plan[14])`."""
+    for rows, lists, tiles, kernel, blocks in ((64, 32, 20, MFMA, PACED), (256, 32, 20, MFMA, NARROW), (256, 16, 4000, MFMA, WIDE),
+                                               (32, 32, 20, 3, 0), (256, 16, 4000, 1, 0)):
+        descs = [ta._desc(x) for x in _call(rows, lists, tiles)]
+        plan, opts = (ctypes.c_int64 * 16)(), ta._opts(None, 0, kernel, None, None, 0)
+        args = [ctypes.byref(d) for d in descs] + [ctypes.byref(opts), 256]
+        assert ta.load_library().tree_attn_plan(*args, plan) == ta.TA_OK
+        assert plan[14] == (1 if kernel == 3 else 0), list(plan)
+        assert ta.load_library().tree_attn_plan_blocks(*args) == blocks
+    args[-2] = ctypes.byref(ta._opts(None, 0, 9, None, None, 0))
+    assert ta.load_library().tree_attn_plan_blocks(*args) == ta.TA_ERR_OPTS
 
 
 def _steady_loop(text, struct):
