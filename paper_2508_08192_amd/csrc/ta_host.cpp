@@ -453,16 +453,15 @@ int ta_host_build_problem(const ta_tensor *q, const ta_tensor *k, const ta_tenso
     // matrix products of a layer's size before each call; single calls after a copy, which run at a higher clock.
     //   256, 240 and 512 rows: 12 tiles 1.0 to 1.05, 0.98 to 1.05, 1.0 to 1.04; 24 0.97 to 1.01, 0.91 to 1.04, 1.0 to 1.05; 48
     //     0.97 to 0.99, 0.92 to 1.01, 0.98 to 1.01; 100 and more 0.96 to 0.99, 0.96 to 1.0, 0.96 to 1.0;
-    //   128 and 100 rows: 24 0.98 to 1.02, 0.99 to 1.04, 0.99 to 1.03; 48 0.96 to 0.99, 0.95 to 1.01, 0.98 to 1.01; 100 and more
-    //     0.95 to 0.98, 0.91 to 1.0, 0.99 to 1.01;
+    //   128 and 100 rows: 24 0.98 to 1.02, 0.99 to 1.04, 0.99 to 1.03; 32 0.97 to 0.99, 1.0 to 1.02, 0.99 to 1.0; 48 0.96 to 0.99,
+    //     0.95 to 1.02, 0.98 to 1.01; 100 and more 0.95 to 0.98, 0.91 to 1.0, 0.98 to 1.01;
     //   some waves without rows: 136 to 192 rows 0.98 to 1.07 and single 1.01 to 1.08 at any length, 224 single up to 1.06, 320
     //     single 1.0 to 1.05, 96 0.97 to 1.03 and single 0.99 to 1.04; 64 rows 1.02 to 1.03.
-    // So 48 tiles are the line.  Tiles are counted from what the page table can hold: twice that many with 256 rows, for
-    // lengths spread evenly or a table twice as wide as its requests; four times with 128, where less is gained.  What a window
-    // leaves of the tiles the host does not know.
+    // So 48 tiles are the line.  Tiles are counted from what the page table can hold: twice that many, for lengths spread evenly
+    // or a table twice as wide as its requests.  What a window leaves of the tiles the host does not know.
     const bool waves_full = (p.rows - 1) % pl.rows_grp >= pl.rows_grp - 32;
     const bool wide = !p.kv_start && pl.rows_grp > 64 && waves_full &&
-                      tiles_cap >= (pl.rows_grp > 128 ? 96 : 192) * (lists > pl.n_wg ? lists : (int64_t)pl.n_wg);
+                      tiles_cap >= 96 * (lists > pl.n_wg ? lists : (int64_t)pl.n_wg);
     // Otherwise the narrow ones, in row groups of up to 128 rows with a wait in every tile (figures beside Paced in gen_sp_block.py).
     if (kernel == TA_KERNEL_MFMA && !ks)
         p.blocks = wide ? TA_BLOCKS_WIDE : pl.rows_grp > 128 ? TA_BLOCKS_NARROW : TA_BLOCKS_PACED;
