@@ -11,13 +11,14 @@ the matrix pipe and the vector ALU busy at the same time:
   S    S^T(i+1) = K(i+1) . Q^T           16 A fragments from the swizzled K tile
   SM   running softmax of S^T(i) -> P(i) about 155 vector instructions
 
-The blocks exist in two forms.  Narrow: v_mfma_f32_32x32x16_bf16, one per fragment.  Wide: v_mfma_f32_16x16x32_bf16, two
-per fragment.  Their 32-deep products move 8 accumulator values per lane in and out of the register file where the narrow one moves
-16, and draw less power for it: in a loop of nothing but products of normal values this card sustains 1.99 PFLOP/s with them and 1.75
-with the narrow ones, 1.77 and 1.57 with the fragments' LDS reads beside them.  But a wave issues 32 instructions more per tile
-(3940 clocks a tile where the narrow blocks take 3870).  So they are for calls whose clock is what the power allows (the rule
-stands in ta_host.cpp): 4 lists x 8 KV heads of 131072 tokens, 256 rows 593 -> 563 us a call, 64 lists of 2048 to 32768 tokens
-173 -> 167.  Narrow and Wide below say how rows, tokens and head-dim columns lie in the lanes.
+The blocks exist in two forms.  Narrow: v_mfma_f32_32x32x16_bf16, one per fragment (Paced: the same with a wait in every
+steady-state tile).  Wide: v_mfma_f32_16x16x32_bf16, two per fragment.  Their 32-deep products move 8 accumulator values per lane
+in and out of the register file where the narrow one moves 16, and draw less power for it: in a loop of nothing but products of normal
+values this card sustains 1.99 PFLOP/s with them and 1.75 with the narrow ones, 1.77 and 1.57 with the fragments' LDS reads beside them.  But a wave issues 32 instructions more per tile:
+4 lists x 8 KV heads of 131072 tokens, 256 rows, busy cycles of a compute unit per tile 3513 narrow and 3740 wide, of a launch
+back to back 0.90 M at 1.55 GHz and 0.96 M at 1.67 GHz.  So they are for calls whose clock is what the power allows (the rule
+stands in ta_host.cpp): those lists 591 -> 574 us a call, 64 lists of 2048 to 32768 tokens 174.0 -> 169.6, either as a single
+call 535 -> 522 and 177.5 -> 178.0.  Narrow and Wide below say how rows, tokens and head-dim columns lie in the lanes.
 
 The large operands live in fixed physical VGPRs that the compiler never sees: the kernel is compiled with
 amdgpu_num_vgpr(16), which confines the register allocator to v0..v31 (the attribute counts in units of two on
@@ -38,7 +39,8 @@ elements E_j[0..3]) and lane i receives E_{4k + i/4}[i % 4] for k = 0..3.  With 
 A operand of the second product (rows = head-dim columns, contraction = tokens) without any re-layout.  The token
 sets (narrow: 16kb + 4hf + {0..3}, then + 8, for the lane's half hf of the wave; wide: 32kb + 4g + {0..3}, then + 16, for its
 group g) follow the contraction slots the probabilities occupy after the first product.  Four groups on one block of sixteen
-token rows, or two on two neighbouring blocks of eight: the placement spreads either half of the wave over all banks.
+token rows (wide) meet no bank conflict; two on two neighbouring blocks of eight (narrow) lose a third of the LDS cycles to them
+(LDS busy 28 % of the cycles instead of 44 %).
 
 Small helpers move values between the two worlds: zero_o, load_q, set_bases, scale_o, row_totals, mask_A/B, put_q15.
 
@@ -495,8 +497,10 @@ def fast_step_items(sh, cur, label, helper=False):
     aux += sm[:12] + [dict(t="s_nop 7")] * (0 if helper else sh.pace)
     aux += page_b
     rest = sm[12:]
-    # Loads of tile i+3: late in the block, one every 10 softmax instructions from the 90th on (they are not needed
-    # before the end of the next block; issued early they cost the 256-row shapes 1.4 %, spread evenly 1 %).
+    # Loads of tile i+3: one every 10 softmax instructions from the 92nd on (80 behind the first 12); they are not needed
+    # before the end of the next block.  Time of a call with them from the 16th, 52nd or 102nd on over that: 64 rows and fewer
+    # 0.998 to 1.003; 256 rows (wide), 64 lists of 2048 to 32768 tokens and 4 x 8 of 131072, 0.992, 0.993 to 0.996, 0.995;
+    # 448 rows (not paced), 30 lists x 4 heads of 16191 tokens 0.986, 0.990, 0.994.
     di, dma_end = 0, 0
     if helper:
         for x in dma:

@@ -508,7 +508,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
                 vp = vp == SP_RV - 1 ? 0 : vp + 1;
             };
             // Steady state: every tile involved is a full prefix tile inside one page (or the contiguous cache), so
-            // whole pairs of tiles run inside sp_fast_loop, which does its own loads and bookkeeping.
+            // whole pairs of tiles run inside X::fast_loop, which does its own loads and bookkeeping.
             const int n_plain = max(0, min(ns, L / TA_TILE - (tile0 + j0 + s0)));     // leading full prefix tiles of the span
             int i = 0;
 #pragma unroll 1
@@ -567,8 +567,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(16))) void ta_m
 
         {
             // Partial result of this (workgroup, list) overlap, as 16-bit fixed point with one scale per row (see
-            // ta_part_row).  A lane holds four-value pieces of one row, eight values apart; written like that,
-            // every store would touch 64 cache lines.  So each wave first turns its 32 x 128 block into row-major
+            // ta_part_row).  A lane holds four-value pieces of one row, eight values apart (WIDE: of two rows, sixteen apart);
+            // written like that, every store would touch 64 cache lines.  So each wave first turns its 32 x 128 block into row-major
             // order in its part of the (now idle) K/V rings and then stores whole rows.
             const int x = fresh_tid();
             const int ln = x & 63, wv = x >> 6;
